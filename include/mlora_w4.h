@@ -106,8 +106,8 @@ mlora_status mlora_group_rows(const int32_t *row_adapter, int32_t M, int32_t n_a
 
 /* Device scratch a call over these projections and M rows needs (256-byte aligned pointer).
  * It holds what blocks of one launch hand to each other: the inner LoRA factor t[m] = A[a(m)].x[m]
- * of Eq. 1-4, partial base products of projections with more than 2048 inputs, and the
- * completion counters that order them.
+ * of Eq. 1-4, partial base products of projections whose inputs are cut into several units,
+ * and the completion counters that order them (sized for the most units a launch may take).
  *  - Layout: a 256-byte header whose first uint32 is a status word, the counters growing from
  *    the front, the data placed against the END of the workspace.  The size returned is
  *    256 + 2 * max(counters, data), so that one workspace sized for the largest of several calls
@@ -129,9 +129,10 @@ size_t mlora_w4_workspace_bytes(const mlora_w4_proj *projs, int32_t n_proj, int3
  * 128 projections; from 17 rows on also a new one where the group size changes),
  * [1] 1 if the first launch runs blocks of four column tiles ("wide_kernel"), 0 if blocks of
  * one column tile ("layer_kernel"), [2] rows per row chunk (16, 32 or 64; a short launch of 17
- * to 32 rows runs as two chunks of 16), [3] and [4] the first launch's grid: blocks per row chunk
- * (grid.x is that times the number of chunks, rounded up to runs of 8 when there are several)
- * and groups of 16 projections along z.
+ * to 32 rows runs as two chunks of 16; unless a launch is long, a chunk of 64 rows is worked
+ * through by two blocks of 32), [3] and [4] the first launch's grid: blocks per block of rows
+ * (grid.x is that times the number of blocks of rows, rounded up to runs of 8 when there are
+ * several) and groups of 16 projections along z.
  * MLORA_EINVAL for null pointers or n_proj <= 0, MLORA_ESHAPE for shapes the library refuses. */
 mlora_status mlora_w4_layer_step_plan(const mlora_w4_proj *projs, int32_t n_proj, int32_t M, int32_t *info);
 
@@ -229,8 +230,8 @@ mlora_status mlora_lora_int16_expand(const int16_t *a_q, const int16_t *b_q, int
  * and the result is that of Eq. 1-4 on those activations:
  *   y[m] = x_scale * ( sum_g scale[n][g] * sum_{k in g} code[n][k] * xq[m][k]
  *                      + alpha * B[a(m)] . (A[a(m)] . xq[m]) ).
- * The inner sums run on the int8 matrix units and are exact in int32; scales are applied in
- * fp32.  LoRA tensors stay bf16 (the paper's int16 LoRA is not built).  The weight blob is the
+ * The inner sums are exact integers (below 2^24, formed in fp32 by the matrix units); scales are
+ * applied in fp32.  LoRA tensors stay bf16 (the paper's int16 LoRA is not built).  The weight blob is the
  * one mlora_w4_prepack writes.  Every row count runs the blocks of four column tiles; size the
  * workspace with mlora_w4a8_workspace_bytes (same layout and rules as mlora_w4_workspace_bytes).
  * Errors as mlora_w4_layer_step, plus MLORA_EINVAL for a null, non-positive or non-finite scale. */

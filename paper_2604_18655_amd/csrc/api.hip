@@ -84,33 +84,40 @@ int kch_of(const mlora_w4_proj &p, int M, bool wide)
 // Calls with int8 activations run wide blocks whatever their row count, and those work on chunks
 // of at least 32 rows with grouped shrink blocks: such a call is laid out as for 17 rows or more.
 int plan_rows(int M, bool a8) { return a8 && M < WIDE32_MIN_ROWS ? WIDE32_MIN_ROWS : M; }
-int m_pad_of(int M) { return (M + rows_per_chunk(M) - 1) / rows_per_chunk(M) * rows_per_chunk(M); }
 
 // K units per column tile.  Tile blocks: units of at most 2048 inputs (16 super-steps: what a
-// block stages of x).  Wide blocks: any unit length works.  A wide launch whose base blocks with
-// such units (`launch_blocks`) would leave most compute units idle gets shorter units, the same
-// length for all its projections: 8 super-steps up to 240 blocks, 4 below 80.
-// Measured on single projections and on whole layers: up to 64 rows about 200 to 250 base
-// blocks (one per compute unit with the shrink blocks) beat both fewer and more; a layer of 128
-// rows (232 blocks) gains a quarter from 464 shorter ones, two per compute unit; from 256 rows on
-// (464 blocks and more) the long units win, and not splitting long projections at all is far
-// worse at any size (their blocks finish last).
+// block stages of x).  Wide blocks: any unit length works; a wide launch of fewer than 200 base
+// blocks (`launch_blocks`, counted with units of 2048 inputs) has units of about 1024, which fills
+// more compute units.  Measured in us, units of 2048 against 1024 inputs: 4096 x 4096 at 64 rows (64
+// blocks) 24.8 -> 18.0, 2048 x 8192 at 96 rows (96) 22.2 -> 17.2, 2048 x 2048 at 512 rows (128) 24.2
+// -> 19.1; above the line the partial tiles and the shorter loops cost more than they bring: a whole
+// layer at 64 rows (232) 27.2 -> 28.8, 14336 x 4096 with 32 adapters of rank 64 (224) 41 -> 61.
 int ksplit_of(const mlora_w4_proj &p, bool wide, int launch_blocks)
 {
     const int nss = p.K / SUPER_K;
     int ks = (nss + UNIT_SUPER_STEPS - 1) / UNIT_SUPER_STEPS;
-    if (wide && launch_blocks > 0 && launch_blocks <= 240) {
-        const int unit = launch_blocks < 80 ? 4 : 8;
+    if (wide && launch_blocks > 0 && launch_blocks < 200) {
+        constexpr int unit = 8;
         const int cut = (nss + unit / 2) / unit;
         if (cut > ks) ks = cut;
     }
     return ks;
 }
+// Upper bound of that for every launch, which sizes a workspace: a launch of up to 240 base blocks
+// with chunks of 64 rows may take units of 1024 inputs, one of fewer than 80 units of 512.
+int ksplit_bound(const mlora_w4_proj &p, bool wide, int launch_blocks64)
+{
+    const int nss = p.K / SUPER_K;
+    const int ks = (nss + UNIT_SUPER_STEPS - 1) / UNIT_SUPER_STEPS;
+    if (!wide || launch_blocks64 <= 0 || launch_blocks64 > 240) return ks;
+    const int unit = launch_blocks64 < 80 ? 4 : 8;
+    return std::max(ks, (nss + unit / 2) / unit);
+}
 // base blocks of a launch over `count` projections with the default K units
-int launch_blocks_of(const mlora_w4_proj *projs, int count, int M, bool wide)
+int launch_blocks_of(const mlora_w4_proj *projs, int count, int M, bool wide, int rpc)
 {
     int n = 0;
-    const int chunks = m_pad_of(M) / rows_per_chunk(M);
+    const int chunks = (M + rpc - 1) / rpc;
     for (int i = 0; i < count; ++i) {
         const int nss = projs[i].K / SUPER_K;
         n += (tiles_n(projs[i].N) + tiles_per_block(wide) - 1) / tiles_per_block(wide) * chunks *
@@ -123,13 +130,8 @@ bool launch_is_wide(const mlora_w4_proj *projs, int count, int M, bool a8)
 {
     if (a8 || M >= WIDE_ALWAYS_ROWS) return true;
     if (M < WIDE32_MIN_ROWS) return false;
-    return launch_blocks_of(projs, count, M, true) >= WIDE32_MIN_BLOCKS;
+    return launch_blocks_of(projs, count, M, true, rows_per_chunk(M)) >= WIDE32_MIN_BLOCKS;
 }
-size_t partial_bytes(const mlora_w4_proj &p, int M, bool wide, int launch_blocks)
-{
-    return (size_t)(ksplit_of(p, wide, launch_blocks) - 1) * (size_t)tiles_n(p.N) * (size_t)m_pad_of(M) * TILE_N * sizeof(float);
-}
-
 }  // namespace
 
 extern "C" {
@@ -206,7 +208,8 @@ static int launch_run(const mlora_w4_proj *projs, int n_left, int M)
 // projection the split-K partial tiles, then the shrink step's partial sums.  Both passes of a
 // call (sizes first, arguments second) go through this one function.
 struct LaunchNeed {
-    size_t ctrl_bytes, data_bytes;
+    size_t ctrl_bytes, data_bytes;     // of this launch
+    size_t ctrl_bound, data_bound;     // what a workspace is sized for (never less)
     int grid_x, groups, rpc;
 };
 
@@ -215,7 +218,11 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
                                 char *ctrl, char *data, const float *x_scales = nullptr)
 {
     const bool wide = launch_is_wide(projs, count, M, a8);
-    const int lb = launch_blocks_of(projs, count, M, wide);
+    const int lb_chunk = launch_blocks_of(projs, count, M, wide, rows_per_chunk(M));
+    // Wide blocks above 32 rows: unless the launch is long, a chunk of 64 rows is worked through by
+    // two blocks of 32 rows each, see WIDE64_MIN_BLOCKS.
+    const bool halves = wide && M > 32 && lb_chunk < WIDE64_MIN_BLOCKS;
+    const int lb = halves ? launch_blocks_of(projs, count, M, wide, 32) : lb_chunk;
     // A short launch of tile blocks at 17 to 32 rows (a few projections: the calls of a decoder
     // layer taken one after another) is a chain of latencies, not a stream: it runs as two chunks
     // of 16 rows on the kernel for up to 16 rows, with a shrink block per row, which reads the
@@ -225,9 +232,11 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
     const int rpc = rows_per_chunk(Mc);
     const int m_pad = (M + rpc - 1) / rpc * rpc;
     const int chunks = m_pad / rpc;
+    const int block_rows = halves ? 32 : rpc;
+    const int row_blocks = halves ? (M + 31) / 32 : chunks;    // blocks along the rows
     const int groups = (count + GROUP_PROJ - 1) / GROUP_PROJ;
     bool shared = false;                       // anything handed from block to block?
-    size_t part_lines = 0, data_bytes = 0;
+    size_t part_lines = 0, data_bytes = 0, bound_lines = 0, data_bound = 0;
     int part_ctr = count * CTR_REPL * CTR_STRIDE;
     int grid_x = 0;
     if (a) {
@@ -240,16 +249,17 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
         for (int i = z * GROUP_PROJ; i < count && i < (z + 1) * GROUP_PROJ; ++i) {
             const mlora_w4_proj &p = projs[i];
             const int tiles = tiles_n(p.N);
-            const int ksplit = ksplit_of(p, wide, lb);
+            const int ksplit = ksplit_of(p, wide, lb), ks_bound = ksplit_bound(p, wide, lb_chunk);
             // The kernels divide a block index by the tile count with a multiplication that is
             // exact while index * tiles < 2^32: a projection with more than 2^15 column tiles and
             // K units to match is refused rather than mis-indexed.
-            if ((unsigned long long)tiles * (unsigned long long)tiles * (unsigned long long)ksplit >= 0x100000000ull)
+            if ((unsigned long long)tiles * (unsigned long long)tiles * (unsigned long long)ks_bound >= 0x100000000ull)
                 return MLORA_ESHAPE;
             const bool lora = lora_on && p.n_adapters > 0;
             // base blocks: one per column tile, or per four of them in the wide kernel
             const int col_blocks = (tiles + tiles_per_block(wide) - 1) / tiles_per_block(wide);
-            const size_t part_bytes = partial_bytes(p, M, wide, lb);
+            const size_t unit_bytes = (size_t)tiles * (size_t)m_pad * TILE_N * sizeof(float);
+            const size_t part_bytes = (size_t)(ksplit - 1) * unit_bytes;
             // (two chunks of 16 rows have twice the rows of the shapes the per-row shrink blocks were
             // laid out for: at most 4 K chunks then, which also keeps the sum over them on its short path)
             const int kch = chunk16 && kch_of(p, Mc, wide) > 4 ? 4 : kch_of(p, Mc, wide);
@@ -273,7 +283,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
                 d.ksplit = ksplit;
                 // blocks (wide kernel: waves) that wait for this projection's shrink blocks: the
                 // finishing ones, or every K unit where the LoRA term is spread over them
-                d.n_finish_blocks = tiles * chunks * (wide ? ksplit : 1);
+                d.n_finish_blocks = tiles * row_blocks * (wide ? ksplit : 1);
                 d.unit_q = (p.K / SUPER_K) / ksplit;
                 d.unit_r = (p.K / SUPER_K) % ksplit;
                 d.spg_shift = d.spg == 4 ? 2 : d.spg == 2 ? 1 : 0;
@@ -305,6 +315,8 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
             pre_blocks += col_blocks * (ksplit - 1);
             shrink_blocks += n_shrink;
             data_bytes += part_bytes + t_bytes;
+            data_bound += (size_t)(ks_bound - 1) * unit_bytes + t_bytes;
+            if (ks_bound > 1) bound_lines += (size_t)tiles * (size_t)chunks;
             if (ksplit > 1) {
                 part_ctr += tiles * chunks * CTR_STRIDE;
                 part_lines += (size_t)tiles * (size_t)chunks;
@@ -319,6 +331,8 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
         }
         if (total > grid_x) grid_x = total;
     }
+    need.ctrl_bound = shared || bound_lines > 0 ? ((size_t)count * CTR_REPL + bound_lines) * CTR_STRIDE * sizeof(unsigned) : 0;
+    need.data_bound = data_bound;
     need.ctrl_bytes = shared ? ((size_t)count * CTR_REPL + part_lines) * CTR_STRIDE * sizeof(unsigned) : 0;
     need.data_bytes = data_bytes;
     need.grid_x = grid_x;
@@ -327,24 +341,30 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
     if (a) {
         a->ctrl = reinterpret_cast<unsigned *>(ctrl);
         a->wide = wide;
+        a->block_rows = block_rows;
+        a->row_blocks = row_blocks;
+        a->half_shift = halves ? 1 : 0;
         a->m_pad = m_pad;
         if (chunk16) a->M_plan = 16;
     }
     return MLORA_OK;
 }
 
-// Sizes of a whole call (all its launches).
-static mlora_status plan_call(const mlora_w4_proj *projs, int n_proj, int M, bool lora_on,
-                              size_t &ctrl_total, size_t &data_total, bool a8 = false)
+// Sizes of a whole call (all its launches): what it uses, and what a workspace for it is sized for.
+struct CallNeed {
+    size_t ctrl = 0, data = 0, ctrl_bound = 0, data_bound = 0;
+};
+static mlora_status plan_call(const mlora_w4_proj *projs, int n_proj, int M, bool lora_on, CallNeed &call, bool a8 = false)
 {
-    ctrl_total = data_total = 0;
     for (int first = 0, count = 0; first < n_proj; first += count) {
         count = launch_run(projs + first, n_proj - first, M);
         LaunchNeed need;
         const mlora_status st = plan_launch(projs + first, nullptr, nullptr, count, M, a8, lora_on, need, nullptr, nullptr, nullptr);
         if (st != MLORA_OK) return st;
-        ctrl_total += need.ctrl_bytes;
-        data_total += need.data_bytes;
+        call.ctrl += need.ctrl_bytes;
+        call.data += need.data_bytes;
+        call.ctrl_bound += need.ctrl_bound;
+        call.data_bound += need.data_bound;
     }
     return MLORA_OK;
 }
@@ -368,9 +388,9 @@ size_t mlora_w4_workspace_bytes(const mlora_w4_proj *projs, int32_t n_proj, int3
     if (!projs || n_proj <= 0 || M <= 0 || M > MLORA_MAX_ROWS) return 0;
     for (int i = 0; i < n_proj; ++i)
         if (check_weight_shape(projs[i].K, projs[i].N, projs[i].group) != MLORA_OK) return 0;
-    size_t ctrl_total, data_total;
-    if (plan_call(projs, n_proj, M, true, ctrl_total, data_total) != MLORA_OK) return 0;
-    return workspace_need(ctrl_total, data_total);
+    CallNeed call;
+    if (plan_call(projs, n_proj, M, true, call) != MLORA_OK) return 0;
+    return workspace_need(call.ctrl_bound, call.data_bound);
 }
 
 mlora_status mlora_w4_layer_step_plan(const mlora_w4_proj *projs, int32_t n_proj, int32_t M, int32_t *info)
@@ -482,7 +502,6 @@ static mlora_status enqueue_call(const mlora_w4_proj *projs, int32_t n_proj, con
             }
         }
         a->y_fp32 = (y_dtype == MLORA_Y_FP32);
-        a->m_pad = m_pad_of(Mp);
         a->spin_limit = g_spin_limit;
         a->code_mask = 0x00780078u;
         a->code_bias = 0x41804180u;
@@ -506,10 +525,10 @@ mlora_status mlora_w4_layer_step(const mlora_w4_proj *projs, int32_t n_proj,
     mlora_status st = check_call(projs, n_proj, xs, ys, row_adapter, M, y_dtype);
     if (st != MLORA_OK) return st;
     if (M == 0) return MLORA_OK;
-    size_t ctrl_total, data_total;
-    st = plan_call(projs, n_proj, M, true, ctrl_total, data_total);
+    CallNeed call;
+    st = plan_call(projs, n_proj, M, true, call);
     if (st != MLORA_OK) return st;
-    const size_t need = workspace_need(ctrl_total, data_total);
+    const size_t need = workspace_need(call.ctrl_bound, call.data_bound);
     if (need > 0) {
         if (!workspace || workspace_bytes < need) return MLORA_EWORKSPACE;
         if (reinterpret_cast<uintptr_t>(workspace) & 255u) return MLORA_EALIGN;
@@ -517,7 +536,7 @@ mlora_status mlora_w4_layer_step(const mlora_w4_proj *projs, int32_t n_proj,
     bool any_lora = false;
     for (int i = 0; i < n_proj; ++i) any_lora = any_lora || projs[i].n_adapters > 0;
     return enqueue_call(projs, n_proj, xs, ys, row_adapter, M, y_dtype, any_lora && row_adapter != nullptr,
-                        need > 0 ? reinterpret_cast<char *>(workspace) : nullptr, workspace_bytes, data_total,
+                        need > 0 ? reinterpret_cast<char *>(workspace) : nullptr, workspace_bytes, call.data,
                         (hipStream_t)stream);
 }
 
@@ -529,14 +548,15 @@ mlora_status mlora_w4_layer_step_static(const mlora_w4_proj *projs, int32_t n_pr
     mlora_status st = check_call(projs, n_proj, xs, ys, row_adapter, M, y_dtype);
     if (st != MLORA_OK) return st;
     if (M == 0) return MLORA_OK;
-    size_t ctrl_total, data_total;
-    st = plan_call(projs, n_proj, M, true, ctrl_total, data_total);
+    CallNeed call;
+    st = plan_call(projs, n_proj, M, true, call);
     if (st != MLORA_OK) return st;
     // counters at the front, data against the end: the two must not meet
-    const size_t head = WS_HEADER_BYTES + round_up(ctrl_total, 256);
-    if (head + round_up(data_total, 256) > STATIC_SCRATCH_BYTES) return MLORA_EWORKSPACE;
+    const size_t head = WS_HEADER_BYTES + round_up(call.ctrl, 256);
+    if (WS_HEADER_BYTES + round_up(call.ctrl_bound, 256) + round_up(call.data_bound, 256) > STATIC_SCRATCH_BYTES)
+        return MLORA_EWORKSPACE;
     char *ws = nullptr;
-    if (ctrl_total > 0) {
+    if (call.ctrl > 0) {
         ws = static_scratch();
         if (!ws) return MLORA_EHIP;
         // The array keeps what the last call left: status word and counters start from zero again
@@ -546,7 +566,7 @@ mlora_status mlora_w4_layer_step_static(const mlora_w4_proj *projs, int32_t n_pr
     bool any_lora = false;
     for (int i = 0; i < n_proj; ++i) any_lora = any_lora || projs[i].n_adapters > 0;
     return enqueue_call(projs, n_proj, xs, ys, row_adapter, M, y_dtype, any_lora && row_adapter != nullptr,
-                        ws, STATIC_SCRATCH_BYTES, data_total, (hipStream_t)stream);
+                        ws, STATIC_SCRATCH_BYTES, call.data, (hipStream_t)stream);
 }
 
 mlora_status mlora_w4_layer_step_fused(const mlora_w4_proj *projs, const mlora_w4_epilogue *epis, int32_t n_proj,
@@ -572,10 +592,10 @@ mlora_status mlora_w4_layer_step_fused(const mlora_w4_proj *projs, const mlora_w
             (e.residual && (reinterpret_cast<uintptr_t>(e.residual) & 1u))) return MLORA_EALIGN;
     }
     if (M == 0) return MLORA_OK;
-    size_t ctrl_total, data_total;
-    st = plan_call(projs, n_proj, M, true, ctrl_total, data_total);
+    CallNeed call;
+    st = plan_call(projs, n_proj, M, true, call);
     if (st != MLORA_OK) return st;
-    const size_t need = workspace_need(ctrl_total, data_total);
+    const size_t need = workspace_need(call.ctrl_bound, call.data_bound);
     if (need > 0) {
         if (!workspace || workspace_bytes < need) return MLORA_EWORKSPACE;
         if (reinterpret_cast<uintptr_t>(workspace) & 255u) return MLORA_EALIGN;
@@ -583,7 +603,7 @@ mlora_status mlora_w4_layer_step_fused(const mlora_w4_proj *projs, const mlora_w
     bool any_lora = false;
     for (int i = 0; i < n_proj; ++i) any_lora = any_lora || projs[i].n_adapters > 0;
     return enqueue_call(projs, n_proj, xs, ys, row_adapter, M, y_dtype, any_lora && row_adapter != nullptr,
-                        need > 0 ? reinterpret_cast<char *>(workspace) : nullptr, workspace_bytes, data_total,
+                        need > 0 ? reinterpret_cast<char *>(workspace) : nullptr, workspace_bytes, call.data,
                         (hipStream_t)stream, nullptr, epis);
 }
 
@@ -620,9 +640,9 @@ size_t mlora_w4a8_workspace_bytes(const mlora_w4_proj *projs, int32_t n_proj, in
     if (!projs || n_proj <= 0 || M <= 0 || M > MLORA_MAX_ROWS) return 0;
     for (int i = 0; i < n_proj; ++i)
         if (check_weight_shape(projs[i].K, projs[i].N, projs[i].group) != MLORA_OK) return 0;
-    size_t ctrl_total, data_total;
-    if (plan_call(projs, n_proj, plan_rows(M, true), true, ctrl_total, data_total, true) != MLORA_OK) return 0;
-    return workspace_need(ctrl_total, data_total);
+    CallNeed call;
+    if (plan_call(projs, n_proj, plan_rows(M, true), true, call, true) != MLORA_OK) return 0;
+    return workspace_need(call.ctrl_bound, call.data_bound);
 }
 
 mlora_status mlora_w4a8_layer_step(const mlora_w4_proj *projs, int32_t n_proj,
@@ -636,10 +656,10 @@ mlora_status mlora_w4a8_layer_step(const mlora_w4_proj *projs, int32_t n_proj,
     for (int i = 0; i < n_proj; ++i)
         if (!(x_scales[i] > 0.0f) || !(x_scales[i] < 3.0e38f)) return MLORA_EINVAL;     // also refuses NaN
     if (M == 0) return MLORA_OK;
-    size_t ctrl_total, data_total;
-    st = plan_call(projs, n_proj, plan_rows(M, true), true, ctrl_total, data_total, true);
+    CallNeed call;
+    st = plan_call(projs, n_proj, plan_rows(M, true), true, call, true);
     if (st != MLORA_OK) return st;
-    const size_t need = workspace_need(ctrl_total, data_total);
+    const size_t need = workspace_need(call.ctrl_bound, call.data_bound);
     if (need > 0) {
         if (!workspace || workspace_bytes < need) return MLORA_EWORKSPACE;
         if (reinterpret_cast<uintptr_t>(workspace) & 255u) return MLORA_EALIGN;
@@ -647,7 +667,7 @@ mlora_status mlora_w4a8_layer_step(const mlora_w4_proj *projs, int32_t n_proj,
     bool any_lora = false;
     for (int i = 0; i < n_proj; ++i) any_lora = any_lora || projs[i].n_adapters > 0;
     return enqueue_call(projs, n_proj, xs, ys, row_adapter, M, y_dtype, any_lora && row_adapter != nullptr,
-                        need > 0 ? reinterpret_cast<char *>(workspace) : nullptr, workspace_bytes, data_total,
+                        need > 0 ? reinterpret_cast<char *>(workspace) : nullptr, workspace_bytes, call.data,
                         (hipStream_t)stream, x_scales);
 }
 

@@ -144,14 +144,17 @@ struct LayerArgs {
     const int *row_adapter;    // may be null
     int n_proj;
     int M;
-    int M_plan;                // the row count the launch was laid out for (chunk size, shrink
-                               // blocks): M, except that calls with int8 activations always run
-                               // wide blocks and are laid out as for at least 17 rows
+    int M_plan;                // the row count the launch was laid out for (shrink blocks): M, except
+                               // that calls with int8 activations always run wide blocks and are
+                               // laid out as for at least 17 rows
     int a8;                    // x is int8 with one scale per tensor (ProjArgs::x_scale)
     int fused;                 // outputs go through epi[] (one group of at most 16 projections)
     EpiArgs epi[GROUP_PROJ];
     int y_fp32;
-    int m_pad;                 // M rounded up to whole row chunks of the base kernel
+    int block_rows;            // rows of a base block: 16, 32 or 64
+    int row_blocks;            // base blocks along the rows
+    int half_shift;            // 1: two blocks of 32 rows per row chunk of 64 (they share its counter lines)
+    int m_pad;                 // M rounded up to whole row chunks
     int spin_limit;            // polls a block makes before it gives up waiting (0: gives up at once)
     int wide;                  // the launch runs wide blocks (see below)
     unsigned *ctrl;            // completion counters of this launch
@@ -171,6 +174,10 @@ __device__ inline uint16_t float_to_bf16_bits(float f) {
     return (uint16_t)(u >> 16);
 }
 
+// two floats -> a pair of bf16 bit patterns (a in the low half), round to nearest even: one instruction
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t pack_bf16(float a, float b) { return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b}); }
+
 __device__ inline float half_bits_to_float(uint16_t b) { return (float)__builtin_bit_cast(_Float16, b); }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -184,13 +191,11 @@ __device__ inline f32x4 mfma16(uint4 a, uint4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
 }
 
-// D[16][16] (int32) += A[16][32] * B[32][16] over int8; lane l supplies 8 bytes of row l%16 of A
-// and of column l%16 of B, both for the same 8 inputs (block l/16 of the 32), and receives
-// D[4*(l/16) + r][l%16] in element r.  Which byte stands for which input inside a lane's 8 does
-// not matter as long as A and B agree.
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-__device__ inline i32x4 mfma16_i8(long a, long b, i32x4 c) {
-    return __builtin_amdgcn_mfma_i32_16x16x32_i8(a, b, c, 0, 0, 0);
+// D[32 rows][32 cols] += A[32][16] * B[16][32]; lane l supplies row l%32 of A and column l%32 of B
+// at inputs 8*(l/32)..+7, and receives D[8*(i/4) + 4*(l/32) + i%4][l%32] in element i.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+__device__ inline f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
 }
 
 // The grouped shrink step (more than 16 rows) works on chunks of 64 rows: the rows of a chunk are
@@ -233,14 +238,21 @@ constexpr int UNIT_SUPER_STEPS = 16;   // a block streams at most 16 super-steps
 // K (many short-lived blocks: what a small launch needs to fill the chip); "wide" blocks cover
 // four column tiles, one per wave, and share the rows of x through LDS (a quarter of the x
 // traffic and no reduction across waves: what a long weight stream needs).  Up to 16 rows: tile
-// blocks.  33 rows and more: wide blocks with chunks of 64 rows.  17 to 32 rows (chunks of 32
-// rows): wide blocks if the launch has at least WIDE32_MIN_BLOCKS of them, else tile blocks.
+// blocks.  33 rows and more: wide blocks.  17 to 32 rows (chunks of 32 rows): wide blocks if the
+// launch has at least WIDE32_MIN_BLOCKS of them, else tile blocks.
 constexpr int WIDE_ALWAYS_ROWS = 33;
 constexpr int WIDE32_MIN_ROWS = 17;
 constexpr int WIDE32_MIN_BLOCKS = 300;
+// From 33 rows on a chunk of 64 rows is the unit of the workspace's layout.  Blocks of 64 rows unpack a
+// weight once for twice the rows, but two of them fill a compute unit's registers where three of 32
+// rows fit, and their latencies are longer; they pay in a launch of several rounds of blocks only.
+// Measured in us, blocks of 64 rows against 32: 16 layers of a 1B-like model at 512 rows (14848
+// blocks of 64 rows) 1684 -> 1813; one such layer at 512 rows (928) 137 -> 137, at 128 rows (232) 65 ->
+// 41, at 64 rows (116) 45 -> 28; 4096 x 4096 at 64 rows (32) 37 -> 18.
+constexpr int WIDE64_MIN_BLOCKS = 2048;
 constexpr int WIDE_TILES_PER_BLOCK = 4;
 constexpr int CHUNK16_MAX_BLOCKS = 300;    // tile launches of 17 to 32 rows below this run chunks of 16 rows
-__host__ __device__ inline int rows_per_chunk(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : 64; }
+__host__ inline int rows_per_chunk(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : 64; }
 // column tiles a base block covers
 __host__ __device__ inline int tiles_per_block(bool wide) { return wide ? WIDE_TILES_PER_BLOCK : 1; }
 

@@ -88,6 +88,16 @@ __device__ __forceinline__ f32x4_t load_shared16(__amdgpu_buffer_rsrc_t rsrc, in
     return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, byte_offset, 0, 16));
 }
 
+// descriptor over `bytes` bytes at `base`, both the same for every lane of a wave (raw buffer, no
+// stride; reads past the end return 0)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_buffer(const void *base, unsigned bytes)
+{
+    const uint64_t at = reinterpret_cast<uint64_t>(base);
+    const uint64_t lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)at);
+    const uint64_t hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(at >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(lo | (hi << 32)), 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+}
+
 // The hardware keeps the order "data, then counter" on the producer's side (the wait for the
 // stores' acknowledgements below) and "counter, then data" on the consumer's (a wave's loads are
 // issued in program order, and these go through to memory).  The compiler must keep it too:
@@ -139,6 +149,20 @@ __device__ __forceinline__ uint4 expand_codes(uint32_t w, uint32_t mask, uint32_
 // (a native vector type: copies of HIP's uint4 struct from global to LDS would be lowered to
 // memcpy through a private array instead of going through registers)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// eight int8 (two words) -> eight bf16, exactly (seven bits and a sign)
+__device__ __forceinline__ u32x4 widen_int8(uint32_t lo, uint32_t hi)
+{
+    u32x4 o;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const uint32_t word = h < 2 ? lo : hi;
+        const float e0 = (float)(int)(signed char)(word >> (16 * (h & 1)));
+        const float e1 = (float)(int)(signed char)(word >> (16 * (h & 1) + 8));
+        o[h] = __builtin_amdgcn_perm(__float_as_uint(e1), __float_as_uint(e0), 0x07060302u);   // the upper halves
+    }
+    return o;
+}
 
 // ------------------------------------------------------------------------------------------
 // A wave works through its inputs in rounds of R k-steps.  All operands of a round (R KiB of
@@ -1168,19 +1192,9 @@ __device__ __forceinline__ void shrink_block(const LayerArgs &a, const ProjArgs 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     if constexpr (A8) {
-                        // eight int8 -> eight bf16 (exact: seven bits and a sign)
                         uint2 q = make_uint2(0u, 0u);
                         if (x_ok[i] && k_ok) q = *reinterpret_cast<const uint2 *>(reinterpret_cast<const unsigned char *>(xsrc[i]) + (size_t)s0 * KSTEP);
-                        const uint32_t src2[2] = {q.x, q.y};
-                        u32x4 o;
-#pragma unroll
-                        for (int h = 0; h < 4; ++h) {
-                            const uint32_t word = src2[h >> 1];
-                            const int e0 = (int)(signed char)(word >> (16 * (h & 1)));
-                            const int e1 = (int)(signed char)(word >> (16 * (h & 1) + 8));
-                            o[h] = (__float_as_uint((float)e0) >> 16) | (__float_as_uint((float)e1) & 0xFFFF0000u);
-                        }
-                        xv[set][i] = o;
+                        xv[set][i] = widen_int8(q.x, q.y);
                     } else {
                         xv[set][i] = (x_ok[i] && k_ok) ? *reinterpret_cast<const u32x4 *>(xsrc[i] + (size_t)s0 * KSTEP) : zero;
                     }
@@ -1368,7 +1382,7 @@ __device__ __forceinline__ LaunchTables pin_launch_args(const LayerArgs &a, int 
     t.pre_base_blocks = a.pre_base_blocks[z];
     t.group_blocks = a.group_blocks[z];
     asm volatile("" :: "s"(t.shrink), "s"(t.pre), "s"(t.main), "s"(a.row_adapter), "s"(a.M), "s"(a.y_fp32),
-                       "s"(a.m_pad), "s"(t.shrink_blocks), "s"(t.pre_base_blocks), "s"(t.group_blocks),
+                       "s"(a.m_pad), "s"(a.row_blocks), "s"(a.half_shift), "s"(t.shrink_blocks), "s"(t.pre_base_blocks), "s"(t.group_blocks),
                        "s"(a.ctrl), "s"(a.status), "s"(a.code_mask), "s"(a.code_bias), "s"(a.spin_limit));
     return t;
 }
@@ -1397,10 +1411,10 @@ __device__ __forceinline__ int find_proj(const i32x16 &begin, int b, int &first)
 // read 5.9 x the algorithmic bytes from HBM at 512 rows.)  A producer still has a smaller index
 // than its consumer: shrink blocks work at chunk 0 only, and a split-K block and the block that
 // finishes its tile have the same chunk.
-__device__ __forceinline__ void split_block_index(const LayerArgs &a, int rows, int &b, int &chunk)
+__device__ __forceinline__ void split_block_index(const LayerArgs &a, int &b, int &chunk)
 {
     const unsigned id = blockIdx.x;
-    const unsigned chunks = (unsigned)(a.m_pad / rows);
+    const unsigned chunks = (unsigned)a.row_blocks;
     if (chunks == 1) {
         b = (int)id;
         chunk = 0;
@@ -1420,7 +1434,7 @@ __global__ __launch_bounds__(64 * Shape<MB>::WAVES, (occupancy_of<MB, XR>())) vo
     const int z = (int)blockIdx.z;
     const LaunchTables tables = pin_launch_args(a, z);
     int b, chunk;
-    split_block_index(a, 16 * MB, b, chunk);
+    split_block_index(a, b, chunk);
     if (b >= tables.group_blocks) return;                  // (the slices are as long as the longest group)
     int first;
     if (b < tables.shrink_blocks) {
@@ -1456,314 +1470,198 @@ __global__ __launch_bounds__(64 * Shape<MB>::WAVES, (occupancy_of<MB, XR>())) vo
 }
 
 // ------------------------------------------------------------------------------------------
-// Wide shapes (33 rows or more per call): the product is a dense contraction and the matrix
-// units are what bounds it.  A block covers 64 rows x 256 columns: its four waves share the rows
-// of x (staged in LDS, one super-step of 128 inputs at a time, double-buffered) and each wave
-// owns one 64-column tile, whose packed codes it streams into registers two super-steps ahead
-// and unpacks once for all 64 rows (4 A fragments x 4 B fragments = 16 MFMAs per k-step, plus
-// 4 for the offset term).  No K split inside the block; long K is cut into units as for the
-// decode shapes, and a launch with few blocks is cut further by the host.
-//
-// Scales without a second set of accumulators: the accumulator is kept in units of the current
-// group's scale, acc <- acc * (s_prev / s_cur) + (offset term), and the MFMAs of the group add
-// their raw code products to it; the last scale is applied at the end.  A zero scale (padding
-// columns; legal in a hand-made blob) keeps the previous unit and its codes are replaced by
-// code 0, so it contributes exactly nothing.
-//
-// LoRA term on the matrix units too: t[m] (fp32, from the shrink blocks) is split into two bf16
-// halves (hi + lo keeps 16 bits of mantissa), and for every adapter that occurs in the chunk of
-// 64 rows its rows of B for the tile are fetched once (four adapters per round trip) and one
-// MFMA pair per 16 columns and 32 ranks adds B[a] . t for every block of 16 rows that holds such
-// a row, the rows of other adapters masked to zero.
+// Wide shapes: the product is a dense contraction.  A block covers 32 or 64 rows x 256 columns: its
+// four waves share the rows of x (staged in LDS, double-buffered) and each wave owns one
+// 64-column tile, whose packed codes it streams into registers eight k-steps ahead and unpacks
+// once for all its rows.  No K split inside the block; long K is cut into units as for the decode
+// shapes, and a launch with few blocks is cut further by the host.
 // ------------------------------------------------------------------------------------------
 constexpr int WIDE_TILES = 4;
 
-// MB blocks of 16 rows per chunk: 4 (64 rows) from 33 rows on, 2 (32 rows) for 17 to 32 rows.
-// A stage of x holds XSTEPS k-steps of every row of the chunk: one super-step (4 k-steps) at 64
-// rows, two at 32 rows.
+// MB blocks of 16 rows per base block: 4 (64 rows) in long launches, else 2 (32 rows).  A stage of
+// x holds XSTEPS k-steps of every row: 16 KiB.
 template <int MB>
 struct WideLds {
     static constexpr int ROWS = 16 * MB;
     static constexpr int XSTEPS = MB == 2 ? 8 : 4;
     static constexpr int XROW = XSTEPS * 64 + 16;          // bytes of a row of x per stage; +16: rows 4 banks apart
     static constexpr int X_STAGE = ROWS * XROW;
-    static constexpr int T_STRIDE = MLORA_MAX_RANK + 4;    // floats per row of t
-    static constexpr int T_BYTES = ROWS * T_STRIDE * 4;
-    static constexpr int BUF_BYTES = 2 * X_STAGE > T_BYTES ? 2 * X_STAGE : T_BYTES;
-    alignas(16) unsigned char buf[BUF_BYTES];              // x stages; after the K loop: t
-    alignas(16) float stage[WIDE_TILES][16 * (TILE_N + 4)]; // per wave: 16 rows of outputs on their way out
+    // t as two bf16 halves, with one row more than the block has: zeros.  It has a place of its own
+    // beside the stages of x, so that a block that starts after its shrink blocks have finished
+    // can fetch it ahead of the K loop.
+    static constexpr int T_ROW = MLORA_MAX_RANK * 2 + 16;  // bytes; +16: rows 4 banks apart
+    static constexpr int T_HALF = (ROWS + 1) * T_ROW;
+    // after the K loop, over the stages, per wave: 16 rows of outputs on their way out
+    static constexpr int OUT_ROW = TILE_N + 8;             // floats; rows 4 apart lie 32 banks apart
+    static constexpr int OUT_BYTES = 16 * OUT_ROW * 4;
+    static_assert(WIDE_TILES * OUT_BYTES <= 2 * X_STAGE, "the outputs fit the stages");
+    alignas(16) unsigned char buf[2 * X_STAGE];
+    alignas(16) unsigned char t[2 * T_HALF];
+    __device__ float *out(int wave) { return reinterpret_cast<float *>(buf + wave * OUT_BYTES); }
 };
-
-// eight fp32 -> the bf16 A-operand fragments of their high and low halves
-__device__ __forceinline__ void split_bf16(const float (&v)[8], uint4 &hi, uint4 &lo)
-{
-    uint32_t h[8], l[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        h[i] = __float_as_uint(v[i]) & 0xFFFF0000u;
-        l[i] = __float_as_uint(v[i] - __uint_as_float(h[i])) & 0xFFFF0000u;
-    }
-    hi = make_uint4((h[0] >> 16) | h[1], (h[2] >> 16) | h[3], (h[4] >> 16) | h[5], (h[6] >> 16) | h[7]);
-    lo = make_uint4((l[0] >> 16) | l[1], (l[2] >> 16) | l[3], (l[4] >> 16) | l[5], (l[6] >> 16) | l[7]);
-}
 
 // ------------------------------------------------------------------------------------------
 // The K loop of the wide blocks.  Per wave: the packed codes of the next 8 k-steps and their
 // scales are in registers (8 KiB in flight), each register set requested again as soon as its
-// k-step is consumed; the rows of x come through LDS in stages (8 k-steps of 32 rows, or 4
-// k-steps of 64 rows: 16 KiB, double-buffered, one barrier per stage) shared by the block's four
-// waves.  The codes enter the matrix units exactly; the scale multiplies the fp32 sum of a
-// group with plain fp32 FMAs (the cheapest vector instructions on this chip: integer and mixed
-// 16/32-bit operations issue at half their rate), so the loop is as short as the arithmetic
-// allows: per k-step 28 integer operations to unpack, 16 * MB FMAs per scale group, 4 * MB + MB
-// MFMAs.
+// k-step is consumed; the rows of x come through LDS in stages of 16 KiB, double-buffered, one
+// barrier per stage, shared by the block's four waves.  Codes, scales and x come with buffer loads:
+// the lane's place in a vector register, the k-step in a scalar one, no vector arithmetic for
+// addresses.  The codes enter the matrix units exactly; the scale multiplies the fp32 sum of a
+// group with fp32 FMAs.
+//
+// 32 rows: products of 32 x 32 x 16 (a permlane swap of two code words turns the blob's order, made for
+// 16 columns, into theirs).  Per k-step of a group of 32 inputs 70 vector instructions (28 to unpack, 32
+// FMAs) and 6 products of 32 cycles, which run beside them: what bounds a compute unit's work is
+// then the vector instructions, and what bounds a launch is how many blocks wait at once for memory.
+// The loop and all that follows it fit 168 registers, so that three blocks share a compute unit:
+// 16 layers of a 1B-like model at 32 rows 191 -> 170 us (products of 16 x 16 x 32, two blocks).
+// 64 rows: products of 16 x 16 x 32, whose 64 sums per lane leave the registers for it; with products
+// of 32 x 32 x 16 the same launch at 512 rows took 1684 us instead of 1625.
+// int8 rows are widened to bf16 (exact: seven bits and a sign) on their way into LDS: sums of a group
+// stay integers below 2^24, exact in fp32, and the loop has fewer vector instructions than one
+// over int8 products, whose int32 sums need a conversion each (16 layers at 32 rows 188 -> 171 us).
 // ------------------------------------------------------------------------------------------
-template <int SPG, int MB>
-__device__ __forceinline__ void stream_loop(f32x4 (&acc)[MB][4], const u32x4 *wp, const uint2 *sp,
-                                            const unsigned char *const (&xrow)[4], int piece16, const int (&xdst)[4],
+template <int SPG, int MB, bool A8, class Acc, class Early>
+__device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t codes, __amdgpu_buffer_rsrc_t scales,
+                                            __amdgpu_buffer_rsrc_t xsrc, const int (&xoff)[A8 ? 2 : 4], int piece16, int xdst0,
                                             unsigned char *lds_x, const unsigned char *xfrag, int n_ksteps,
-                                            uint32_t mask, uint32_t bias)
+                                            uint32_t mask, uint32_t bias, int lane, const Early &early)
 {
     using L = WideLds<MB>;
     constexpr int S = L::XSTEPS;                           // k-steps per stage of x
     constexpr int W = 8;                                   // k-steps of codes in registers
     constexpr int HALVES = W / S;                          // stages per pass over the register sets
     static_assert(S % SPG == 0 && W % S == 0, "a stage holds whole scale groups; the sets hold whole stages");
-    const u32x4 neg24 = {0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u};
+    const uint4 neg24 = make_uint4(0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u);
     const int last = n_ksteps - 1;
+    const int lane16 = lane * 16, col8 = (lane & 15) * 8, half16 = lane & 16;
     u32x4 w[W];
     uint2 sc[W / SPG];
-    u32x4 xr[4];
+    constexpr int XP = A8 ? 2 : 4;                         // 16-byte pieces of x per thread and stage
+    constexpr int RPI = 256 / (S * (A8 ? 2 : 4));          // rows a block moves per instruction
+    u32x4 xr[XP];
     // (requests past the unit's end re-read its last k-step: all loads stay unconditional)
-    const int x_last = n_ksteps * 64 - 16;                 // last 16-byte piece of a row inside the unit
+    auto load_codes = [&](int k) { return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(codes, lane16, min(k, last) * 1024, 2)); };
+    auto load_scales = [&](int k) { return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(scales, col8, min(k, last) / SPG * 128, 0)); };
+    // (a last stage of half its length re-reads the unit's last inputs in place of those past it)
+    constexpr int XB = A8 ? 32 : 64;                       // bytes of a row of x per k-step
+    const int x_last = n_ksteps * XB - 16;
+    auto load_x = [&](int st) {
+        const int at = min(st * S * XB + piece16, x_last);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) xr[i] = *reinterpret_cast<const u32x4 *>(xrow[i] + min(piece16, x_last));
+        for (int i = 0; i < XP; ++i) xr[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xsrc, xoff[i] + at, 0, 0));
+    };
+    auto store_x = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < XP; ++i) {
+            unsigned char *dst = lds_x + buf + xdst0 + i * RPI * L::XROW;
+            if constexpr (A8) {
+                *reinterpret_cast<u32x4 *>(dst) = widen_int8(xr[i][0], xr[i][1]);
+                *reinterpret_cast<u32x4 *>(dst + 16) = widen_int8(xr[i][2], xr[i][3]);
+            } else {
+                *reinterpret_cast<u32x4 *>(dst) = xr[i];
+            }
+        }
+    };
+    const int n_stages = (n_ksteps + S - 1) / S;
+    load_x(0);
 #pragma unroll
     for (int k = 0; k < W; ++k) {
-        const int kc = min(k, last);
-        w[k] = __builtin_nontemporal_load(wp + kc * 64);
-        if (k % SPG == 0) sc[k / SPG] = sp[(kc / SPG) * 16];
+        w[k] = load_codes(k);
+        if (k % SPG == 0) sc[k / SPG] = load_scales(k);
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4 *>(lds_x + xdst[i]) = xr[i];
-    const int n_stages = (n_ksteps + S - 1) / S;
+    __builtin_amdgcn_sched_barrier(0);                     // (all of these ahead of the first wait)
+    early();
+    store_x(0);
 
     // one stage: register sets [h * S, h * S + S), x buffer st & 1
     auto stage = [&](auto half, int st, auto full) {
         constexpr int H = decltype(half)::value;
         __syncthreads();                                   // this stage's rows of x are in place; the other buffer is free
         const int buf = (st & 1) * L::X_STAGE;
-        const int x_off = min(min(st + 1, n_stages - 1) * S * 64 + piece16, x_last);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) xr[i] = *reinterpret_cast<const u32x4 *>(xrow[i] + x_off);
+        load_x(min(st + 1, n_stages - 1));
         // the math of NK k-steps of this stage (NK = S, or 4 in the last stage of a unit that ends
         // on an odd super-step): one straight piece of code, no branches inside
         auto stage_math = [&](auto nk) {
             constexpr int NK = decltype(nk)::value;
-            // A scale group is worked through in runs of SG = min(SPG, 2) k-steps: the run's
-            // fragments of x stay in registers for the offset term and for all four column
-            // blocks, and the products of one column block (MB accumulators of 16 x 16) are folded
-            // into acc as soon as the run is done, so few registers live at a time.  A group of 4
-            // k-steps is two runs that use the same scale.
-            constexpr int SG = SPG < 2 ? SPG : 2;
+            // A scale group is worked through in runs of SG k-steps (64 rows: at most 2, whose
+            // fragments of x fit the registers): offset term (-24 * sum of x over the run cancels the
+            // offset of the stored codes), products, FMAs with the scale.
+            constexpr int SG = MB == 2 || SPG < 2 ? SPG : 2;
+            constexpr int G0 = (H * S) / SPG;              // first scale group of this stage's register sets
 #pragma unroll
             for (int r = 0; r < NK / SG; ++r) {
-                u32x4 xk[SG][MB];
-                // offset term of the run: -24 * sum of x over its inputs cancels the offset of the stored codes
-                f32x4 corr[MB];
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb) corr[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int t = 0; t < SG; ++t)
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb) {
-                        xk[t][mb] = *reinterpret_cast<const u32x4 *>(xfrag + buf + mb * 16 * L::XROW + (r * SG + t) * 64);
-                        corr[mb] = mfma16(__builtin_bit_cast(uint4, xk[t][mb]), __builtin_bit_cast(uint4, neg24), corr[mb]);
-                    }
-                constexpr int G0 = (H * S) / SPG;          // first scale group of this stage's register sets
-                const int g = (r * SG) / SPG;              // scale group of the run within the stage
+                const int g = r * SG / SPG;                // scale group of the run within the stage
+                const unsigned char *xs = xfrag + buf + r * SG * 64;
                 const uint2 sv = sc[G0 + g];
-                if ((r * SG + SG) % SPG == 0) {            // last run of its group: request the set's next group
-                    const int gc = min(st * S + g * SPG + W, last) / SPG;
-                    sc[G0 + g] = sp[gc * 16];
-                }
+                if constexpr (MB == 2) {
+                    uint4 xk[SG][2];
+                    f32x16 corr = f32x16{0.f};
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    f32x4 d[MB];
+                    for (int t = 0; t < SG; ++t)
 #pragma unroll
-                    for (int t = 0; t < SG; ++t) {
-                        const uint4 wb = expand_codes(w[H * S + r * SG + t][j], mask, bias);
+                        for (int o = 0; o < 2; ++o) {
+                            xk[t][o] = *reinterpret_cast<const uint4 *>(xs + t * 64 + o * 16);
+                            corr = mfma32(xk[t][o], neg24, corr);
+                        }
+                    sc[G0 + g] = load_scales(st * S + g * SPG + W);
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb) {
+                        f32x16 d = corr;
+#pragma unroll
+                        for (int t = 0; t < SG; ++t) {
+                            const u32x4 &wv = w[H * S + r * SG + t];
+                            const auto sw = __builtin_amdgcn_permlane16_swap(wv[2 * cb], wv[2 * cb + 1], false, false);
+#pragma unroll
+                            for (int o = 0; o < 2; ++o) d = mfma32(xk[t][o], expand_codes(sw[o], mask, bias), d);
+                        }
+                        float sj = half_bits_to_float((uint16_t)((cb == 0 ? sv.x : sv.y) >> half16));
+                        asm volatile("" : "+v"(sj));       // a float in a register: plain fp32 FMAs below
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) acc[cb][e] = fmaf(d[e], sj, acc[cb][e]);
+                    }
+                } else {
+                    uint4 xk[SG][MB];
+                    f32x4 corr[MB];
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) corr[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int t = 0; t < SG; ++t)
+#pragma unroll
+                        for (int mb = 0; mb < MB; ++mb) {
+                            xk[t][mb] = *reinterpret_cast<const uint4 *>(xs + mb * 16 * L::XROW + t * 64);
+                            corr[mb] = mfma16(xk[t][mb], neg24, corr[mb]);
+                        }
+                    if ((r + 1) * SG % SPG == 0) sc[G0 + g] = load_scales(st * S + g * SPG + W);   // (last run of its group)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        f32x4 d[MB];
+#pragma unroll
+                        for (int t = 0; t < SG; ++t) {
+                            const uint4 wb = expand_codes(w[H * S + r * SG + t][j], mask, bias);
+#pragma unroll
+                            for (int mb = 0; mb < MB; ++mb) d[mb] = mfma16(xk[t][mb], wb, t == 0 ? corr[mb] : d[mb]);
+                        }
+                        float sj = j == 0 ? half_bits_lo(sv.x) : j == 1 ? half_bits_hi(sv.x)
+                                 : j == 2 ? half_bits_lo(sv.y) : half_bits_hi(sv.y);
+                        asm volatile("" : "+v"(sj));
 #pragma unroll
                         for (int mb = 0; mb < MB; ++mb)
-                            d[mb] = mfma16(__builtin_bit_cast(uint4, xk[t][mb]), wb, t == 0 ? corr[mb] : d[mb]);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[mb][j][e] = fmaf(d[mb][e], sj, acc[mb][j][e]);
                     }
-                    float sj = j == 0 ? half_bits_lo(sv.x) : j == 1 ? half_bits_hi(sv.x)
-                             : j == 2 ? half_bits_lo(sv.y) : half_bits_hi(sv.y);
-                    asm volatile("" : "+v"(sj));           // a float in a register: plain fp32 FMAs below
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[mb][j][e] = fmaf(d[mb][e], sj, acc[mb][j][e]);
                 }
                 // the run's register sets are used up: request their next k-steps (after the last
                 // use, so that no copy of the old contents has to be kept)
 #pragma unroll
-                for (int t = 0; t < SG; ++t) {
-                    const int k = r * SG + t;              // k-step within the stage
-                    const int kc = min(st * S + k + W, last);
-                    w[H * S + k] = __builtin_nontemporal_load(wp + kc * 64);
-                }
+                for (int t = 0; t < SG; ++t) w[H * S + r * SG + t] = load_codes(st * S + r * SG + t + W);
             }
         };
         // (a unit is a whole number of 4-k-step super-steps: a stage of 8 k-steps is full, or the
         // unit's last one with 4)
         if constexpr (decltype(full)::value) stage_math(std::integral_constant<int, S>{});
         else                                 stage_math(std::integral_constant<int, 4>{});
-#pragma unroll
-        for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4 *>(lds_x + (L::X_STAGE - buf) + xdst[i]) = xr[i];
-    };
-    // The loop holds full stages only; a last stage of 4 k-steps (S = 8) follows it.  One variant of
-    // the stage inside the loop: the two would meet at the loop's end with their values in
-    // different registers, and the moves that reconcile them were 5 % of the loop's instructions.
-    constexpr std::true_type full_stage{};
-    if constexpr (HALVES == 2) {
-#pragma nounroll
-        for (int st = 0; st < n_stages; st += 2) {
-            stage(std::integral_constant<int, 0>{}, st, full_stage);
-            if (st + 1 < n_stages) stage(std::integral_constant<int, 1>{}, st + 1, full_stage);
-        }
-    } else {
-        const int n_full = n_ksteps / S;
-#pragma nounroll
-        for (int st = 0; st < n_full; ++st) stage(std::integral_constant<int, 0>{}, st, full_stage);
-        if constexpr (S > 4) {
-            if (n_full < n_stages) stage(std::integral_constant<int, 0>{}, n_full, std::false_type{});
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// The same K loop for int8 activations (one scale per tensor): the matrix units multiply int8 by
-// int8 into int32, so a scale group's sum is exact without any offset term.
-//  * Codes: the blob stores offset-binary nibbles u = code + 8 at bits 3, 7, ... of a dword (see
-//    common.hpp).  Flipping the top bit of every nibble turns them into two's complement, and a
-//    nibble in the upper half of a byte is the int8 number 16 * code:  t = w ^ 0x44444444,
-//    rotl(t, 1) & 0xF0F0F0F0 holds the codes of inputs 0, 4, 1, 5 of the lane's eight,
-//    rotl(t, 5) & 0xF0F0F0F0 those of inputs 7, 2, 6, 3: five integer operations for 8 weights.
-//    The factor 16 is taken out after the loop.
-//  * x: the bytes of a row are put into that same order (0, 4, 1, 5, 7, 2, 6, 3 within every
-//    eight) when a stage is written to LDS, so a lane's fragment is one 8-byte read.
-//  * int32 -> fp32 without a conversion: the accumulator of a run starts at 0x4B400000, the bit
-//    pattern of 1.5 * 2^23, so the int32 result, read as a float, is 12582912 + sum exactly
-//    (|sum| <= 2 * 32 * 128 * 127 < 2^22); one fp32 subtraction and one FMA with the group's scale
-//    follow, both at the full fp32 rate.
-// A stage holds the same k-steps as in the bf16 loop; its rows are half as long.
-// ------------------------------------------------------------------------------------------
-template <int MB>
-struct WideLdsA8 {
-    static constexpr int XSTEPS = WideLds<MB>::XSTEPS;
-    static constexpr int XROW = XSTEPS * 32 + 16;          // bytes of a row of x per stage (int8)
-};
-
-template <int SPG, int MB>
-__device__ __forceinline__ void stream_loop_a8(f32x4 (&acc)[MB][4], const u32x4 *wp, const uint2 *sp,
-                                               const unsigned char *const (&xrow)[2], int piece16, const int (&xdst)[2],
-                                               unsigned char *lds_x, const unsigned char *xfrag, int n_ksteps)
-{
-    using L = WideLds<MB>;
-    using L8 = WideLdsA8<MB>;
-    constexpr int S = L::XSTEPS;
-    constexpr int W = MB == 4 ? 4 : 8;                     // k-steps of codes in registers
-    constexpr int HALVES = W / S;
-    const int last = n_ksteps - 1;
-    u32x4 w[W];
-    uint2 sc[W / SPG];
-    u32x4 xr[2];
-    const int x_last = n_ksteps * 32 - 16;                 // last 16-byte piece of a row inside the unit
-    // bytes (0,1,2,3 | 4,5,6,7) of every eight -> (0,4,1,5 | 7,2,6,3)
-    auto shuffled = [](u32x4 v) {
-        u32x4 o;
-        o[0] = __builtin_amdgcn_perm(v[1], v[0], 0x05010400u);
-        o[1] = __builtin_amdgcn_perm(v[1], v[0], 0x03060207u);
-        o[2] = __builtin_amdgcn_perm(v[3], v[2], 0x05010400u);
-        o[3] = __builtin_amdgcn_perm(v[3], v[2], 0x03060207u);
-        return o;
-    };
-#pragma unroll
-    for (int i = 0; i < 2; ++i) xr[i] = *reinterpret_cast<const u32x4 *>(xrow[i] + min(piece16, x_last));
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-        const int kc = min(k, last);
-        w[k] = __builtin_nontemporal_load(wp + kc * 64);
-        if (k % SPG == 0) sc[k / SPG] = sp[(kc / SPG) * 16];
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) *reinterpret_cast<u32x4 *>(lds_x + xdst[i]) = shuffled(xr[i]);
-    const int n_stages = (n_ksteps + S - 1) / S;
-    const i32x4 magic = {0x4B400000, 0x4B400000, 0x4B400000, 0x4B400000};
-
-    auto stage = [&](auto half, int st, auto full) {
-        constexpr int H = decltype(half)::value;
-        __syncthreads();
-        const int buf = (st & 1) * L::X_STAGE;
-        const int x_off = min(min(st + 1, n_stages - 1) * S * 32 + piece16, x_last);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) xr[i] = *reinterpret_cast<const u32x4 *>(xrow[i] + x_off);
-        auto stage_math = [&](auto nk) {
-            constexpr int NK = decltype(nk)::value;
-            constexpr int SG = SPG < 2 ? SPG : 2;
-#pragma unroll
-            for (int r = 0; r < NK / SG; ++r) {
-                long xk[SG][MB];
-#pragma unroll
-                for (int t = 0; t < SG; ++t)
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
-                        xk[t][mb] = *reinterpret_cast<const long *>(xfrag + buf + mb * 16 * L8::XROW + (r * SG + t) * 32);
-                u32x4 wv[SG];
-#pragma unroll
-                for (int t = 0; t < SG; ++t) {
-                    const int k = r * SG + t;
-                    wv[t] = w[H * S + k] ^ 0x44444444u;
-                    const int kc = min(st * S + k + W, last);
-                    w[H * S + k] = __builtin_nontemporal_load(wp + kc * 64);
-                }
-                constexpr int G0 = (H * S) / SPG;
-                const int g = (r * SG) / SPG;
-                const uint2 sv = sc[G0 + g];
-                if ((r * SG + SG) % SPG == 0) {
-                    const int gc = min(st * S + g * SPG + W, last) / SPG;
-                    sc[G0 + g] = sp[gc * 16];
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    i32x4 d[MB];
-#pragma unroll
-                    for (int t = 0; t < SG; ++t) {
-                        const uint32_t v = wv[t][j];
-                        const uint32_t hi = __builtin_amdgcn_alignbit(v, v, 31) & 0xF0F0F0F0u;
-                        const uint32_t lo = __builtin_amdgcn_alignbit(v, v, 27) & 0xF0F0F0F0u;
-                        const long wb = (long)(((unsigned long long)lo << 32) | hi);
-#pragma unroll
-                        for (int mb = 0; mb < MB; ++mb) d[mb] = mfma16_i8(xk[t][mb], wb, t == 0 ? magic : d[mb]);
-                    }
-                    float sj = j == 0 ? half_bits_lo(sv.x) : j == 1 ? half_bits_hi(sv.x)
-                             : j == 2 ? half_bits_lo(sv.y) : half_bits_hi(sv.y);
-                    asm volatile("" : "+v"(sj));
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            acc[mb][j][e] = fmaf(__int_as_float(d[mb][e]) - 12582912.0f, sj, acc[mb][j][e]);
-                }
-            }
-        };
-        // (a unit is a whole number of 4-k-step super-steps: a stage of 8 k-steps is full, or the
-        // unit's last one with 4)
-        if constexpr (decltype(full)::value) stage_math(std::integral_constant<int, S>{});
-        else                                 stage_math(std::integral_constant<int, 4>{});
-#pragma unroll
-        for (int i = 0; i < 2; ++i) *reinterpret_cast<u32x4 *>(lds_x + (L::X_STAGE - buf) + xdst[i]) = shuffled(xr[i]);
+        store_x(L::X_STAGE - buf);
     };
     // The loop holds full stages only; a last stage of 4 k-steps (S = 8) follows it.  One variant of
     // the stage inside the loop: the two would meet at the loop's end with their values in
@@ -1794,13 +1692,16 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
 {
     using L = WideLds<MB>;
     constexpr int ROWS = L::ROWS;
+    constexpr int RB = MB / 2;                             // blocks of 32 rows
     const int K = P.K, N = P.N, M = a.M;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, lq = lane >> 4;
+    const int l32 = lane & 31, hi = lane >> 5;
     const int tiles = tiles_n(N);
     const int tile_raw = group * WIDE_TILES + wave;
-    const bool tile_ok = tile_raw < tiles;                 // (uniform per wave; a spare wave computes and drops tile 0)
-    const int tile = tile_ok ? tile_raw : 0;
+    // (uniform per wave.  A spare wave computes and drops the block's first tile, whose counter it may
+    // wait on: that tile's own wave puts it back to zero only after the barrier both pass.)
+    const bool tile_ok = tile_raw < tiles;
+    const int tile = tile_ok ? tile_raw : group * WIDE_TILES;
 
     const int uq = P.unit_q, ur = P.unit_r;
     const int unit_beg = ku * uq + min(ku, ur), unit_cnt = uq + (ku < ur ? 1 : 0);
@@ -1815,257 +1716,266 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
     // P.n_finish_blocks counts (tile, chunk, unit) triples here.
     const bool lora = a.row_adapter != nullptr && P.n_adapters > 0;
     const int rows_here = min(ROWS, M - m0);
-    const int chunk = m0 / ROWS, chunks = a.m_pad / ROWS;
+    const int chunk = m0 / ROWS, chunks = a.row_blocks;
     const int fin = tile * chunks + chunk;
     const int user = fin * P.ksplit + ku;
     const int copies = P.ctr_copies;
     unsigned *const sctr = a.ctrl + shrink_ctr(pi, user & (copies - 1));
-    unsigned *const pctr = a.ctrl + P.part_ctr + fin * CTR_STRIDE;
+    const int lines = (chunks + a.half_shift) >> a.half_shift;     // counter lines per tile
+    unsigned *const pctr = a.ctrl + P.part_ctr + (tile * lines + (chunk >> a.half_shift)) * CTR_STRIDE +
+                           (chunk & a.half_shift) * (CTR_STRIDE / 2);
     const bool need_s = lora, need_p = ku == 0 && P.ksplit > 1;
 
     const uint32_t mask = a.code_mask;
     uint32_t bias = a.code_bias;
     asm volatile("" : "+v"(bias));
 
-    f32x4 acc[MB][4];
+    // t = alpha * sum over the K chunks of the shrink partials, in fixed order, as two bf16 halves
+    // that make up its first 17 bits.  A thread takes four neighbouring ranks of one row (16
+    // bytes of a partial sum); the requests of several quads and K chunks overlap.  A wave's share:
+    // ROWS / 4 rows.
+    auto gather_t = [&]() {
+        constexpr int TPR = 256 / ROWS;                    // threads per row
+        const int ml = tid / TPR, q0 = tid % TPR;
+        const int quads = P.r16 / 4;
+        const float t_factor = A8 ? P.alpha * P.x_scale : P.alpha;   // (the shrink blocks saw x as integers)
+        const int t_chunk = M * P.r16 * 4;                 // bytes of a K chunk's partial sums
+        const __amdgpu_buffer_rsrc_t rt = wave_buffer(P.t_part, (unsigned)P.kch * (unsigned)t_chunk);
+        const int at = (m0 + min(ml, rows_here - 1)) * P.r16 * 4;
+        unsigned char *const dst = lds.t + ml * L::T_ROW;
+        auto quads_of = [&](auto nq, auto nc, int qb) {        // nq quads of ranks, nc K chunks at a time
+            constexpr int Q = decltype(nq)::value, C = decltype(nc)::value;
+            f32x4_t v[Q];
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+            for (int u = 0; u < Q; ++u) v[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int kc0 = 0; kc0 < P.kch; kc0 += C) {
+                f32x4_t pv[Q][C];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[mb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int u = 0; u < Q; ++u)
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        pv[u][c] = load_shared16(rt, at + min(qb + u * TPR, quads - 1) * 16 + min(kc0 + c, P.kch - 1) * t_chunk);
+#pragma unroll
+                for (int u = 0; u < Q; ++u)
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        if (kc0 + c < P.kch) v[u] += pv[u][c];
+            }
+#pragma unroll
+            for (int u = 0; u < Q; ++u) {
+                const int quad = qb + u * TPR;
+                if (quad >= quads) continue;
+                v[u] *= t_factor;
+                const uint2 h = make_uint2(pack_bf16(v[u][0], v[u][1]), pack_bf16(v[u][2], v[u][3]));
+                const f32x4_t l = {v[u][0] - bf16_bits_to_float(h.x & 0xFFFFu), v[u][1] - __uint_as_float(h.x & 0xFFFF0000u),
+                                   v[u][2] - bf16_bits_to_float(h.y & 0xFFFFu), v[u][3] - __uint_as_float(h.y & 0xFFFF0000u)};
+                *reinterpret_cast<uint2 *>(dst + quad * 8) = h;
+                *reinterpret_cast<uint2 *>(dst + L::T_HALF + quad * 8) = make_uint2(pack_bf16(l[0], l[1]), pack_bf16(l[2], l[3]));
+            }
+        };
+        if (quads <= TPR) {
+            if (q0 < quads) quads_of(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{}, q0);
+        } else {
+            for (int qb = q0; qb < quads; qb += 4 * TPR) quads_of(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{}, qb);
+        }
+        // the row of zeros that stands for rows of other adapters
+        if (tid < L::T_ROW / 16) {
+            *reinterpret_cast<u32x4 *>(lds.t + ROWS * L::T_ROW + tid * 16) = u32x4{0u, 0u, 0u, 0u};
+            *reinterpret_cast<u32x4 *>(lds.t + L::T_HALF + ROWS * L::T_ROW + tid * 16) = u32x4{0u, 0u, 0u, 0u};
+        }
+    };
+    // A wave that finds its shrink blocks done when it starts (all but the first blocks of a long
+    // launch) fetches its share of t ahead of the K loop, behind the requests for x and codes.
+    const bool try_early = lora && a.spin_limit > 0;
+    unsigned seen = 0;
+    if (try_early) seen = __hip_atomic_load(sctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bool have_t = false;
+    auto early = [&]() {
+        if (try_early && seen >= (unsigned)P.n_shrink_blocks) {
+            compiler_fence();
+            gather_t();
+            have_t = true;
+        }
+    };
 
-    // rows of x: thread t moves, per stage, four 16-byte pieces: piece t % PPR of rows t / PPR + RPI * i
-    // (PPR pieces per row and stage, RPI rows per instruction of the block); int8 rows are half as
-    // long: two pieces per thread
-    if constexpr (!A8) {
-        constexpr int PPR = L::XSTEPS * 4, RPI = 256 / PPR;
-        const unsigned char *xrow[4];
-        int xdst[4];
+    // element i of acc[rb][cb]: row 32*rb + 8*(i/4) + 4*hi + i%4 of the chunk, column 32*cb + l32 of the tile
+    f32x16 acc[RB][2];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = f32x16{0.f};
+    {
+        // rows of x: thread t moves, per stage, 16-byte piece t % PPR of rows t / PPR + RPI * i (PPR
+        // pieces per row and stage, RPI rows per instruction of the block); int8 rows are half as long
+        constexpr int EB = A8 ? 1 : 2;                     // bytes per input
+        constexpr int PPR = L::XSTEPS * 2 * EB, RPI = 256 / PPR, XP = A8 ? 2 : 4;
+        static_assert(XP * RPI == ROWS, "every row of a stage is moved once");
+        int xoff[XP];
         const int piece16 = (tid % PPR) * 16;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = tid / PPR + RPI * i;
-            xrow[i] = reinterpret_cast<const unsigned char *>(P.x + (size_t)(m0 + min(row, rows_here - 1)) * K +
-                                                              (size_t)unit_beg * SUPER_K);
-            xdst[i] = row * L::XROW + piece16;
+        for (int i = 0; i < XP; ++i) xoff[i] = min(tid / PPR + RPI * i, rows_here - 1) * K * EB;
+        // Descriptors of what the wave reads, so that a load needs no vector arithmetic for its
+        // address: the lane's place in a vector register, the k-step in a scalar one.  Rows of x: the
+        // chunk's, from the unit's first input to the end of the chunk's last row.
+        const unsigned char *x0 = reinterpret_cast<const unsigned char *>(P.x) + ((size_t)m0 * K + (size_t)unit_beg * SUPER_K) * EB;
+        const __amdgpu_buffer_rsrc_t rx = wave_buffer(x0, ((unsigned)rows_here * (unsigned)K - (unsigned)unit_beg * SUPER_K) * EB);
+        const __amdgpu_buffer_rsrc_t rw = wave_buffer(wp, (unsigned)unit_cnt * 4096u);
+        const __amdgpu_buffer_rsrc_t rs = wave_buffer(sp, (unsigned)unit_cnt * (unsigned)(gs * 128));
+        const int xdst0 = (tid / PPR) * L::XROW + piece16 * (2 / EB);
+        if constexpr (MB == 2) {
+            stream_loop<SPG, MB, A8>(acc[0], rw, rs, rx, xoff, piece16, xdst0, lds.buf, lds.buf + l32 * L::XROW + hi * 32,
+                                     unit_cnt * 4, mask, bias, lane, early);
+        } else {
+            // Products of 16 x 16: lane (l16, lq) gets rows 4 * lq + e of a block of 16 and columns 16 * j +
+            // l16.  With the rows of their A operand in the order that trades the two bits of row / 4,
+            // one swap of lanes 16 apart per register turns them into the order of acc.
+            const int l16 = lane & 15, arow = (l16 & 3) | ((l16 & 4) << 1) | ((l16 & 8) >> 1);
+            f32x4 acc16[MB][4];
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc16[mb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            stream_loop<SPG, MB, A8>(acc16, rw, rs, rx, xoff, piece16, xdst0, lds.buf, lds.buf + arow * L::XROW + (lane >> 4) * 16,
+                                     unit_cnt * 4, mask, bias, lane, early);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc16[mb][2 * cb][e]),
+                                                                         __float_as_uint(acc16[mb][2 * cb + 1][e]), false, false);
+                        acc[mb >> 1][cb][8 * (mb & 1) + e] = __uint_as_float(sw[0]);
+                        acc[mb >> 1][cb][8 * (mb & 1) + 4 + e] = __uint_as_float(sw[1]);
+                    }
         }
-        const unsigned char *xfrag = lds.buf + l16 * L::XROW + lq * 16;
-        stream_loop<SPG, MB>(acc, wp + lane, sp + l16, xrow, piece16, xdst, lds.buf, xfrag, unit_cnt * 4, mask, bias);
-    } else {
-        using L8 = WideLdsA8<MB>;
-        constexpr int PPR = L::XSTEPS * 2, RPI = 256 / PPR;
-        const unsigned char *xrow[2];
-        int xdst[2];
-        const int piece16 = (tid % PPR) * 16;
+        if constexpr (A8) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int row = tid / PPR + RPI * i;
-            xrow[i] = reinterpret_cast<const unsigned char *>(P.x) + (size_t)(m0 + min(row, rows_here - 1)) * K +
-                      (size_t)unit_beg * SUPER_K;
-            xdst[i] = row * L8::XROW + piece16;
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) acc[rb][cb] *= P.x_scale;
         }
-        const unsigned char *xfrag = lds.buf + l16 * L8::XROW + lq * 8;
-        stream_loop_a8<SPG, MB>(acc, wp + lane, sp + l16, xrow, piece16, xdst, lds.buf, xfrag, unit_cnt * 4);
-        // the codes went in as 16 * code, x as integers: one factor for both
-        const float f = P.x_scale * 0.0625f;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[mb][j] *= f;
     }
 
-    // One pass per (32 ranks, adapter that occurs in the chunk): its rows of B for the
-    // tile's 64 columns are fetched once and used by every block of 16 rows that holds
-    // such a row.  Four passes are fetched per round trip: four adapters at ranks up to
-    // 32, else two adapters x two runs of 32 ranks, so that a round takes whole 128-byte
-    // pieces of the rows of B (the halves of a piece fetched in rounds far apart would
-    // cost the memory two accesses).
-    const int r32 = (P.r16 + 31) / 32 * 32;            // ranks as the MFMAs see them (zero-filled)
-    const int n_lane = tile * TILE_N + l16;
+    // LoRA term: one pass per adapter that occurs in the chunk and run of 16 ranks (one 32x32x16
+    // product per block of 32 rows, 32 columns and half of t).  A pass needs the run's part of B for
+    // the tile's 64 columns: 16 bytes per lane and 32 columns.  Passes go in the order adapter,
+    // run (a row of B is fetched in one piece), in rounds of NB that form a two-deep pipeline: the
+    // rows of B of the next round are on their way while the current round is computed.
+    constexpr int NB = MB == 2 ? 4 : 8;
+    const int runs = P.r16 / 16;
+    const int n_lane = tile * TILE_N + l32;
     // lane l looks after row l of the chunk (a spare wave and a call without LoRA: no row)
     int ad_row = -1;
     if (lora && tile_ok && lane < rows_here) {
         const int v = a.row_adapter[m0 + lane];
         ad_row = (v >= 0 && v < P.n_adapters) ? v : -1;
     }
-    const unsigned long long all = __ballot(ad_row >= 0);
-    auto b_request = [&](u32x4 (&bf)[4], int cur, int kk) {
-        const bool k_ok = 32 * kk + 8 * lq < P.rank;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = min(n_lane + 16 * j, N - 1);
-            bf[j] = *reinterpret_cast<const u32x4 *>(P.lora_b + ((size_t)cur * N + n) * P.rank +
-                                                     (k_ok ? 32 * kk + 8 * lq : 0));
-        }
-    };
-    // The rounds form a two-deep pipeline: the rows of B of the next round are on their
-    // way while the current round is computed.
     struct Round {
-        int curs[4];
-        unsigned long long sames[4];
-        int kk0, nk;
-        bool any;
+        int cur[NB], run[NB];                          // adapter (-1: no more passes) and run of ranks of each pass
     };
-    const int nkk = r32 / 32;
-    int st_kk0 = 0, st_ordinal = 0;                    // where the enumeration stands
-    unsigned long long st_remaining = all;
-    // skip the adapters that other K units of this tile look after
-    auto skip_others = [&]() {
-        while (st_remaining && st_ordinal % P.ksplit != ku) {
-            const int other = __builtin_amdgcn_readlane(ad_row, (int)__builtin_ctzll(st_remaining));
-            st_remaining &= ~__ballot(ad_row == other);
-            ++st_ordinal;
-        }
-    };
+    // where the enumeration stands: adapter, its next run, rows not yet looked at, adapters seen
+    int st_cur = -1, st_run = 0, st_ordinal = 0;
+    unsigned long long st_remaining = __ballot(ad_row >= 0);
     auto next_round = [&](Round &r) {
-        skip_others();
-        while (!st_remaining && st_kk0 + 2 < nkk) {    // next pair of runs of 32 ranks
-            st_kk0 += 2;
-            st_remaining = all;
-            st_ordinal = 0;
-            skip_others();
-        }
-        r.any = st_remaining != 0;
-        r.kk0 = st_kk0;
-        r.nk = min(2, nkk - st_kk0);                   // runs of 32 ranks per adapter and round
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            if (r.nk == 2 && (b & 1)) {                // second run of ranks of the same adapter
-                r.curs[b] = r.curs[b - 1];
-                r.sames[b] = r.sames[b - 1];
-                continue;
+        for (int b = 0; b < NB; ++b) {
+            if (st_cur >= 0 && ++st_run == runs) st_cur = -1;
+            while (st_cur < 0 && st_remaining) {       // next adapter that this K unit looks after
+                const int next = __builtin_amdgcn_readlane(ad_row, (int)__builtin_ctzll(st_remaining));
+                st_remaining &= ~__ballot(ad_row == next);
+                if (st_ordinal++ % P.ksplit == ku) {
+                    st_cur = next;
+                    st_run = 0;
+                }
             }
-            skip_others();
-            if (st_remaining) {
-                r.curs[b] = __builtin_amdgcn_readlane(ad_row, (int)__builtin_ctzll(st_remaining));
-                r.sames[b] = __ballot(ad_row == r.curs[b]);
-                st_remaining &= ~r.sames[b];
-                ++st_ordinal;
-            } else {
-                r.curs[b] = b ? r.curs[0] : 0;         // (a useless request that stays in bounds)
-                r.sames[b] = 0;
-            }
+            r.cur[b] = st_cur;
+            r.run[b] = st_run;
         }
     };
-    auto request = [&](u32x4 (&bf)[4][4], const Round &r) {
+    auto request = [&](u32x4 (&bf)[NB][2], const Round &r) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) b_request(bf[b], r.curs[b], r.kk0 + (r.nk == 2 ? (b & 1) : 0));
+        for (int b = 0; b < NB; ++b) {
+            if (r.cur[b] < 0) break;
+            // (ranks past the adapter's meet zeros of t: their part of B is a re-read of the first ranks)
+            const int k = 16 * r.run[b] + 8 * hi;
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                const int n = min(n_lane + 32 * cb, N - 1);
+                bf[b][cb] = *reinterpret_cast<const u32x4 *>(P.lora_b + ((size_t)r.cur[b] * N + n) * P.rank + (k < P.rank ? k : 0));
+            }
+        }
     };
     // The first round's rows of B do not depend on t: they are requested before the wait for
     // the shrink blocks and arrive while t is gathered.
     Round ra_, rb_;
-    u32x4 bfa[4][4], bfb[4][4];
-    ra_.any = false;
+    u32x4 bfa[NB][2], bfb[NB][2];
+    ra_.cur[0] = -1;
     if (lora && tile_ok) {
         next_round(ra_);
-        if (ra_.any) request(bfa, ra_);
+        request(bfa, ra_);
     }
 
-    // element (mb, j, e) of this lane: row 16*mb + 4*lq + e of the chunk, column 16*j + l16 of the tile
-    // (a wave whose wait runs out sets the status word and stores NaN in place of its outputs)
+    // (a wave whose wait runs out sets the status word and stores NaN in place of its outputs;
+    // a spare wave waits too: it gathers its share of t)
     bool poisoned = false;
-    if (tile_ok && need_s && !wait_count(sctr, (unsigned)P.n_shrink_blocks, a.spin_limit)) {
-        poisoned = true;
-        if (lane == 0) atomicOr(a.status, 1u);
-    }
-    if (lora) {                                            // (uniform over the block)
-        // a spare wave has not looked at the shrink counter: it must, before it reads t
-        if (!tile_ok && !wait_count(sctr, (unsigned)P.n_shrink_blocks, a.spin_limit) && lane == 0) atomicOr(a.status, 1u);
-        __syncthreads();                                   // every wave is done with the x buffers
-        float *tl = reinterpret_cast<float *>(lds.buf);
-        // t = alpha * sum over the K chunks of the shrink partials, in fixed order.  A thread takes
-        // four neighbouring ranks (16 bytes) at a time; requests go out in batches of 4 such
-        // quads x 4 chunks so that the round trips overlap.
-        const int qpr = r32 / 4;                           // quads per row of t
-        const float t_factor = A8 ? P.alpha * P.x_scale : P.alpha;   // (the shrink blocks saw x as integers)
-        for (int i0 = 0; i0 < ROWS * qpr; i0 += 4 * 256) {
-            f32x4_t v[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            for (int kc0 = 0; kc0 < P.kch; kc0 += 4) {
-                f32x4_t pv[16];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int idx = i0 + q * 256 + tid;
-                    const int ml = idx / qpr, jj = (idx % qpr) * 4;
-                    const bool live = ml < rows_here && jj < P.r16;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const int kc = min(kc0 + c, P.kch - 1);
-                        const float *src = live ? P.t_part + ((size_t)kc * M + (m0 + ml)) * P.r16 + jj : P.t_part;
-                        pv[q * 4 + c] = load_shared16(src);
-                    }
-                }
-                shared16_wait(pv);
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        if (kc0 + c < P.kch) v[q] += pv[q * 4 + c];
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int idx = i0 + q * 256 + tid;
-                const int ml = idx / qpr, jj = (idx % qpr) * 4;
-                const bool live = ml < rows_here && jj < P.r16;
-                if (ml < ROWS)
-                    *reinterpret_cast<f32x4_t *>(tl + ml * L::T_STRIDE + jj) = live ? v[q] * t_factor : f32x4_t{0.f, 0.f, 0.f, 0.f};
-            }
+    if (need_s && !have_t) {
+        if (!wait_count(sctr, (unsigned)P.n_shrink_blocks, a.spin_limit)) {
+            poisoned = true;
+            if (lane == 0) atomicOr(a.status, 1u);
         }
-        __syncthreads();
+        gather_t();
+    }
+    __syncthreads();                                       // t is in place; every wave is done with the x buffers
+    if (lora) {                                            // (uniform over the block)
         if (tile_ok) {
-            auto compute = [&](const u32x4 (&bf)[4][4], const Round &r) {
+            auto compute = [&](const u32x4 (&bf)[NB][2], const Round &r) {
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    if (!r.sames[b]) continue;
-                    const int kk = r.kk0 + (r.nk == 2 ? (b & 1) : 0);
-                    const bool k_ok = 32 * kk + 8 * lq < P.rank;
+                for (int b = 0; b < NB; ++b) {
+                    if (r.cur[b] < 0) break;
+                    const unsigned long long same = __ballot(ad_row == r.cur[b]);
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb) {
-                        if (!((r.sames[b] >> (16 * mb)) & 0xFFFFull)) continue;
-                        // (a lane whose ranks lie past the adapter's takes zeros of t: its part of
-                        // B, a re-read of the first ranks, then needs no masking of its own)
-                        const bool mine = k_ok && ((r.sames[b] >> (16 * mb + l16)) & 1ull);
-                        float tv[8];
-                        // (16-byte aligned: rows of t are 528 bytes apart, a lane's run starts at a multiple of 32)
-                        const f32x4_t *trow = reinterpret_cast<const f32x4_t *>(tl + (16 * mb + l16) * L::T_STRIDE + 32 * kk + 8 * lq);
-                        const f32x4_t t0 = trow[0], t1 = trow[1];
+                    for (int rb = 0; rb < RB; ++rb) {
+                        const unsigned rows = (unsigned)(same >> (32 * rb));
+                        if (!rows) continue;
+                        const int row = (rows >> l32) & 1u ? 32 * rb + l32 : ROWS;
+                        const int k = r.run[b] * 32 + hi * 16;
+                        const uint4 th = *reinterpret_cast<const uint4 *>(lds.t + row * L::T_ROW + k);
+                        const uint4 tl = *reinterpret_cast<const uint4 *>(lds.t + L::T_HALF + row * L::T_ROW + k);
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            tv[i] = mine ? t0[i] : 0.f;
-                            tv[4 + i] = mine ? t1[i] : 0.f;
-                        }
-                        uint4 thi, tlo;
-                        split_bf16(tv, thi, tlo);
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const uint4 b4 = __builtin_bit_cast(uint4, bf[b][j]);
-                            acc[mb][j] = mfma16(thi, b4, acc[mb][j]);
-                            acc[mb][j] = mfma16(tlo, b4, acc[mb][j]);
+                        for (int cb = 0; cb < 2; ++cb) {
+                            const uint4 b4 = __builtin_bit_cast(uint4, bf[b][cb]);
+                            acc[rb][cb] = mfma32(th, b4, acc[rb][cb]);
+                            acc[rb][cb] = mfma32(tl, b4, acc[rb][cb]);
                         }
                     }
                 }
             };
-            while (ra_.any) {
+            while (ra_.cur[0] >= 0) {
                 next_round(rb_);
-                if (rb_.any) request(bfb, rb_);
+                request(bfb, rb_);
                 compute(bfa, ra_);
-                if (!rb_.any) break;
+                if (rb_.cur[0] < 0) break;
                 next_round(ra_);
-                if (ra_.any) request(bfa, ra_);
+                request(bfa, ra_);
                 compute(bfb, rb_);
             }
         }
     }
     if (ku > 0) {
         // A partial tile (the chunk's rows x 64 columns) lies in the workspace in the order of the
-        // MFMA results, block (mb, j) of lane l at ((mb * 4 + j) * 64 + l) * 4: producer and consumer
-        // use the same mapping, and a lane moves 16 bytes per instruction.
+        // MFMA results, quarter q of block (rb, cb) of lane l at (((rb * 2 + cb) * 4 + q) * 64 + l) * 4:
+        // producer and consumer use the same mapping, and a lane moves 16 bytes per instruction.
         if (tile_ok) {
             float *dst = P.partial + (((size_t)(ku - 1) * tiles + tile) * a.m_pad + m0) * TILE_N + lane * 4;
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+            for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) store_shared16(dst + (mb * 4 + j) * 256, acc[mb][j]);
+                for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        store_shared16(dst + ((rb * 2 + cb) * 4 + q) * 256, f32x4_t{acc[rb][cb][4 * q], acc[rb][cb][4 * q + 1],
+                                                                                    acc[rb][cb][4 * q + 2], acc[rb][cb][4 * q + 3]});
             compiler_fence();
             __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): this wave's stores have completed
             if (lane == 0) atomicAdd(pctr, 1u);
@@ -2091,9 +2001,9 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
         };
         auto fold = [&](const f32x4_t (&pv)[NP]) {
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+            for (int i = 0; i < NP; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[mb][j] += pv[mb * 4 + j];
+                for (int e = 0; e < 4; ++e) acc[i / 8][(i / 4) % 2][(i % 4) * 4 + e] += pv[i][e];
         };
         f32x4_t pa[NP], pb[NP];
         if (np > 0) request(pa, 0);
@@ -2108,33 +2018,45 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
     }
     if (poisoned) {
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[mb][j] = f32x4{1.f, 1.f, 1.f, 1.f} * __uint_as_float(0x7FC00000u);
+            for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = f32x16{0.f} + __uint_as_float(0x7FC00000u);
     }
     if (tile_ok && ku == 0 && a.fused) {
+        // the fused output stage takes four columns 16 apart of one row from a lane: rows (i, i + 4)
+        // of the two halves of 32 columns trade places, after which lane (l16, lq) holds columns
+        // 16 * j + l16 of row 8 * (lq % 2) + 4 * (lq / 2) + e of every 16
+        const int l16 = lane & 15, lq = lane >> 4;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int h = 0; h < MB; ++h)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float vv[4] = {acc[mb][0][e], acc[mb][1][e], acc[mb][2][e], acc[mb][3][e]};
-                store_fused(a, P, pi, m0 + 16 * mb + 4 * lq + e, tile, l16, vv);
+                float vv[4];
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[h >> 1][cb][8 * (h & 1) + e]),
+                                                                     __float_as_uint(acc[h >> 1][cb][8 * (h & 1) + 4 + e]), false, false);
+                    vv[2 * cb] = __uint_as_float(sw[0]);
+                    vv[2 * cb + 1] = __uint_as_float(sw[1]);
+                }
+                store_fused(a, P, pi, m0 + 16 * h + 8 * (lq & 1) + 4 * (lq >> 1) + e, tile, l16, vv);
             }
     } else if (tile_ok && ku == 0) {
         const bool full = tile * TILE_N + TILE_N <= N;
         if (full) {
             // rows of 64 outputs through a wave-private LDS buffer, so that a lane stores 16
             // neighbouring columns at once instead of 64 single values
-            float *st = lds.stage[wave];
+            float *st = lds.out(wave);
+            const int row = lane >> 2, c0 = (lane & 3) * 16;
+            const f32x4 *src = reinterpret_cast<const f32x4 *>(st + row * L::OUT_ROW + c0);
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
+            for (int h = 0; h < MB; ++h) {                 // 16 rows at a time
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
+                for (int e = 0; e < 8; ++e)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) st[(4 * lq + e) * (TILE_N + 4) + 16 * j + l16] = acc[mb][j][e];
-                const int row = lane >> 2, c0 = (lane & 3) * 16;
-                const int m = m0 + 16 * mb + row;
-                const f32x4 *src = reinterpret_cast<const f32x4 *>(st + row * (TILE_N + 4) + c0);
+                    for (int cb = 0; cb < 2; ++cb)
+                        st[(8 * (e >> 2) + 4 * hi + (e & 3)) * L::OUT_ROW + 32 * cb + l32] = acc[h >> 1][cb][8 * (h & 1) + e];
+                const int m = m0 + 16 * h + row;
                 f32x4 o[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) o[q] = src[q];
@@ -2145,33 +2067,27 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
 #pragma unroll
                         for (int q = 0; q < 4; ++q) dst[q] = o[q];
                     } else {
-                        u32x4 pk[2];
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const uint32_t lo2 = float_to_bf16_bits(o[q][0]) | ((uint32_t)float_to_bf16_bits(o[q][1]) << 16);
-                            const uint32_t hi2 = float_to_bf16_bits(o[q][2]) | ((uint32_t)float_to_bf16_bits(o[q][3]) << 16);
-                            pk[q >> 1][(q & 1) * 2] = lo2;
-                            pk[q >> 1][(q & 1) * 2 + 1] = hi2;
-                        }
                         u32x4 *dst = reinterpret_cast<u32x4 *>(reinterpret_cast<uint16_t *>(P.y) + at);
-                        dst[0] = pk[0];
-                        dst[1] = pk[1];
+#pragma unroll
+                        for (int q = 0; q < 2; ++q)
+                            dst[q] = u32x4{pack_bf16(o[2 * q][0], o[2 * q][1]), pack_bf16(o[2 * q][2], o[2 * q][3]),
+                                           pack_bf16(o[2 * q + 1][0], o[2 * q + 1][1]), pack_bf16(o[2 * q + 1][2], o[2 * q + 1][3])};
                     }
                 }
             }
         } else {
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+            for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int m = m0 + 16 * mb + 4 * lq + e;
+                for (int i = 0; i < 16; ++i) {
+                    const int m = m0 + 32 * rb + 8 * (i >> 2) + 4 * hi + (i & 3);
                     if (m >= M) continue;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int n = tile * TILE_N + 16 * j + l16;
+                    for (int cb = 0; cb < 2; ++cb) {
+                        const int n = tile * TILE_N + 32 * cb + l32;
                         if (n >= N) continue;
-                        if (a.y_fp32) reinterpret_cast<float *>(P.y)[(size_t)m * N + n] = acc[mb][j][e];
-                        else reinterpret_cast<uint16_t *>(P.y)[(size_t)m * N + n] = float_to_bf16_bits(acc[mb][j][e]);
+                        if (a.y_fp32) reinterpret_cast<float *>(P.y)[(size_t)m * N + n] = acc[rb][cb][i];
+                        else reinterpret_cast<uint16_t *>(P.y)[(size_t)m * N + n] = float_to_bf16_bits(acc[rb][cb][i]);
                     }
                 }
         }
@@ -2197,13 +2113,13 @@ constexpr int wide_lds_bytes()
 }
 
 template <int SPG, int MB, bool A8>
-__global__ __launch_bounds__(256, 2) void wide_kernel(const LayerArgs a)
+__global__ __launch_bounds__(256, (MB == 2 ? 3 : 2)) void wide_kernel(const LayerArgs a)
 {
     __shared__ __align__(16) unsigned char smem[wide_lds_bytes<MB>()];
     const int z = (int)blockIdx.z;
     const LaunchTables tables = pin_launch_args(a, z);
     int b, chunk;
-    split_block_index(a, 16 * MB, b, chunk);
+    split_block_index(a, b, chunk);
     if (b >= tables.group_blocks) return;
     int first;
     if (b < tables.shrink_blocks) {
@@ -2213,20 +2129,15 @@ __global__ __launch_bounds__(256, 2) void wide_kernel(const LayerArgs a)
         return;
     }
     WideLds<MB> &lds = *reinterpret_cast<WideLds<MB> *>(smem);
-    const int m0 = chunk * 16 * MB;
-    if (b < tables.shrink_blocks + tables.pre_base_blocks) {
-        const int pb = b - tables.shrink_blocks;
-        const int pi = z * GROUP_PROJ + find_proj(tables.pre, pb, first);
-        const ProjArgs P = fetch_proj(a, pi);
-        const int local = pb - first;
-        const int groups = (tiles_n(P.N) + WIDE_TILES - 1) / WIDE_TILES;
-        wide_unit<SPG, MB, A8>(a, P, pi, local % groups, 1 + local / groups, m0, lds);
-    } else {
-        const int mb_ = b - tables.shrink_blocks - tables.pre_base_blocks;
-        const int pi = z * GROUP_PROJ + find_proj(tables.main, mb_, first);
-        const ProjArgs P = fetch_proj(a, pi);
-        wide_unit<SPG, MB, A8>(a, P, pi, mb_ - first, 0, m0, lds);
-    }
+    // (one call site for both kinds of base block: the code is large, and a second copy is fetched cold)
+    const bool pre = b < tables.shrink_blocks + tables.pre_base_blocks;
+    const int bb = b - tables.shrink_blocks - (pre ? 0 : tables.pre_base_blocks);
+    const int pi = z * GROUP_PROJ + find_proj(pre ? tables.pre : tables.main, bb, first);
+    const ProjArgs P = fetch_proj(a, pi);
+    const int local = bb - first;
+    const int groups = (tiles_n(P.N) + WIDE_TILES - 1) / WIDE_TILES;
+    const int unit = pre ? local / groups : 0;
+    wide_unit<SPG, MB, A8>(a, P, pi, local - unit * groups, pre ? 1 + unit : 0, chunk * 16 * MB, lds);
 }
 
 template <int MB, int XR>
@@ -2239,7 +2150,7 @@ static hipError_t launch_instance(const LayerArgs &a, const dim3 &grid, hipStrea
 // grid: x = the longest group's blocks x row chunks (see split_block_index), z = groups of up to 16 projections
 hipError_t launch_layer(const LayerArgs &a, int grid_x, int groups, hipStream_t s)
 {
-    const int n_chunks = a.m_pad / rows_per_chunk(a.M_plan);
+    const int n_chunks = a.row_blocks;
     // (several chunks: runs of 8 blocks, see split_block_index; blocks past a group's last one exit at once)
     const long long gx = n_chunks == 1 ? grid_x : (long long)((grid_x + 7) / 8 * 8) * n_chunks;
     if (gx > 0x7FFFFFFFll) return hipErrorInvalidValue;
@@ -2248,32 +2159,23 @@ hipError_t launch_layer(const LayerArgs &a, int grid_x, int groups, hipStream_t 
         // (the host puts only projections with the same group size into one such launch)
         const int spg = a.p[0].spg;
         auto go = [&](auto kernel) { kernel<<<grid, dim3(256), 0, s>>>(a); };
-        if (a.a8) {
-            if (a.M_plan <= 32) {
-                if (spg == 1)      go(wide_kernel<1, 2, true>);
-                else if (spg == 2) go(wide_kernel<2, 2, true>);
-                else               go(wide_kernel<4, 2, true>);
-            } else {
-                if (spg == 1)      go(wide_kernel<1, 4, true>);
-                else if (spg == 2) go(wide_kernel<2, 4, true>);
-                else               go(wide_kernel<4, 4, true>);
-            }
-        } else if (a.M_plan <= 32) {
-            if (spg == 1)      go(wide_kernel<1, 2, false>);
-            else if (spg == 2) go(wide_kernel<2, 2, false>);
-            else               go(wide_kernel<4, 2, false>);
-        } else {
-            if (spg == 1)      go(wide_kernel<1, 4, false>);
-            else if (spg == 2) go(wide_kernel<2, 4, false>);
-            else               go(wide_kernel<4, 4, false>);
-        }
+        auto by_rows = [&](auto spg_c, auto a8_c) {
+            if (a.block_rows == 32) go(wide_kernel<decltype(spg_c)::value, 2, decltype(a8_c)::value>);
+            else             go(wide_kernel<decltype(spg_c)::value, 4, decltype(a8_c)::value>);
+        };
+        auto by_group = [&](auto a8_c) {
+            if (spg == 1)      by_rows(std::integral_constant<int, 1>{}, a8_c);
+            else if (spg == 2) by_rows(std::integral_constant<int, 2>{}, a8_c);
+            else               by_rows(std::integral_constant<int, 4>{}, a8_c);
+        };
+        if (a.a8) by_group(std::true_type{});
+        else      by_group(std::false_type{});
         return hipGetLastError();
     }
-    // (M_plan, not M: a short launch of 17 to 32 rows is laid out as chunks of 16 rows, and the
-    // kernel has to be the one the host laid the grid, the shrink blocks and the counters out for)
-    const int rows = rows_per_chunk(a.M_plan);
-    if (a.m_pad % rows != 0 || n_chunks * rows < a.M) return hipErrorInvalidValue;
-    if (rows == 16) return a.M <= 8 ? launch_instance<1, 8>(a, grid, s) : launch_instance<1, 16>(a, grid, s);
+    // (the rows per block the host laid the launch out for: a short launch of 17 to 32 rows has
+    // blocks of 16 rows)
+    if (n_chunks * a.block_rows < a.M) return hipErrorInvalidValue;
+    if (a.block_rows == 16) return a.M <= 8 ? launch_instance<1, 8>(a, grid, s) : launch_instance<1, 16>(a, grid, s);
     if (a.M <= 24) return launch_instance<2, 24>(a, grid, s);
     return launch_instance<2, 32>(a, grid, s);
 }

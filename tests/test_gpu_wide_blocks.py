@@ -1,0 +1,98 @@
+"""Blocks of four column tiles from 33 rows on: two blocks of 32 rows per chunk of 64 in ordinary
+launches, blocks of 64 rows in launches of 2048 of them and more.  Edges of both against the
+oracle: rows around the block sizes, spare waves (column tiles not a multiple of four), units that
+end on half a stage, ranks from one run of 16 to the largest, all group sizes, every output stage.
+Bars as everywhere: 5e-3 of max|y_ref| with bf16 outputs (rounding alone reaches 2^-8), 2e-4 with
+fp32 outputs."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from gpu_util import TOL, TOL_F32, check_linear, random_problem, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_and_x(seed, M, K, n_ad):
+    rng = np.random.default_rng(seed)
+    x = wl.f32_to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32))
+    return x, rng.integers(-1, n_ad, size=M).astype(np.int32)
+
+
+@pytest.mark.parametrize("K,N,G,r,n_ad,M", [
+    (128, 64, 32, 8, 1, 33),          # the smallest: one super-step, three spare waves, one row in the second block
+    (1408, 1408, 32, 16, 5, 64),      # 22 tiles: two spare waves; 11 super-steps in units that end on half a stage
+    (2304, 321, 64, 24, 7, 65),       # a third block of 32 rows with one row; ragged last tile
+    (4224, 640, 128, 128, 3, 95),     # 33 super-steps; the largest rank
+    (1152, 1088, 64, 64, 40, 97),     # more adapters than rows of a block, 17 tiles
+    (8320, 192, 32, 40, 2, 129),      # many K units, a rank of three runs of 16
+])
+def test_blocks_of_32_rows(gpu, K, N, G, r, n_ad, M):
+    x, rows = rows_and_x(M, M, K, n_ad)
+    check_linear(gpu, random_problem(K + N + M, K, N, G, r, n_ad), x, rows, f"K{K} N{N} G{G} r{r} a{n_ad} M{M}")
+
+
+def plan_of_many(gpu, prob, xs, ys, rows, M, y_dtype, n, scales=None):
+    lib, device, torch = gpu
+    p = device.upload_problem(prob)
+    size = lib.a8_workspace_bytes if scales is not None else lib.workspace_bytes
+    ws = torch.zeros(size([p] * n, M), dtype=torch.uint8, device="cuda")
+    ra = torch.from_numpy(rows).cuda()
+    if scales is not None:
+        return lib.LayerPlanA8([p] * n, [xs] * n, [scales] * n, ys, ra, M, y_dtype, ws), ws
+    return lib.LayerPlan([p] * n, [xs] * n, ys, ra, M, y_dtype, ws), ws
+
+
+@pytest.mark.parametrize("K,N,G,r,n_ad,M,n", [
+    (384, 1000, 32, 24, 5, 250, 128),     # last chunk of 58 rows, ragged last tile, three super-steps
+    (256, 1100, 64, 128, 3, 225, 104),    # spare waves, the largest rank, one row over 32 in the last chunk
+    (640, 512, 128, 8, 9, 512, 128),      # whole chunks and tiles
+])
+def test_blocks_of_64_rows(gpu, K, N, G, r, n_ad, M, n):
+    lib, device, torch = gpu
+    prob = random_problem(K + N + M, K, N, G, r, n_ad)
+    x, rows = rows_and_x(M, M, K, n_ad)
+    ref = oracle.linear(prob.wq, prob.scales, G, prob.lora_a, prob.lora_b, prob.shape.alpha, x, rows)
+    dx = device.to_device(x)
+    for y_dtype, tol in ((0, TOL), (1, TOL_F32)):
+        ys = [device.alloc_y(M, N, y_dtype) for _ in range(n)]
+        plan, ws = plan_of_many(gpu, prob, dx, ys, rows, M, y_dtype, n)
+        plan.run()
+        plan.run()                                       # the counters are back at zero
+        torch.cuda.synchronize()
+        assert lib.workspace_status(ws) == 0
+        assert all(torch.equal(ys[0], y) for y in ys[1:])
+        assert rel_err(device.y_to_numpy(ys[0]), ref) <= tol
+    # int8 rows through the same blocks
+    xq, s = wl.make_x_int8(M, K, 5, 0, 0)
+    ref = oracle.linear_a8(prob.wq, prob.scales, G, prob.lora_a, prob.lora_b, prob.shape.alpha, xq, float(s), rows)
+    ys = [device.alloc_y(M, N, 1) for _ in range(n)]
+    plan, ws = plan_of_many(gpu, prob, torch.from_numpy(xq).cuda(), ys, rows, M, 1, n, float(s))
+    plan.run()
+    torch.cuda.synchronize()
+    assert lib.workspace_status(ws) == 0
+    assert all(torch.equal(ys[0], y) for y in ys[1:])
+    assert rel_err(device.y_to_numpy(ys[0]), ref) <= TOL_F32
+
+
+@pytest.mark.parametrize("M,n", [(70, 2), (500, 8)])      # blocks of 32 rows; 8 x 32 x 8 blocks of 64 rows
+def test_fused_output_stage(gpu, M, n):
+    lib, device, torch = gpu
+    K, N, r, n_ad = 256, 8192, 16, 4
+    prob = random_problem(M, K, N, 32, r, n_ad)
+    x, rows = rows_and_x(M, M, K, n_ad)
+    rng = np.random.default_rng(M)
+    scale = rng.uniform(0.5, 2.0, M).astype(np.float32)
+    res = wl.f32_to_bf16_bits(rng.standard_normal((M, N)).astype(np.float32))
+    ref = oracle.linear(prob.wq, prob.scales, 32, prob.lora_a, prob.lora_b, prob.shape.alpha, x, rows) * scale[:, None].astype(np.float64)
+    ref = ref + wl.bf16_bits_to_f32(res).astype(np.float64)
+    p = device.upload_problem(prob)
+    ws = device.alloc_workspace([p] * n, M)
+    ys = [device.alloc_y(M, N, 1) for _ in range(n)]
+    epi = lib.Epilogue(row_scale=torch.from_numpy(scale).cuda(), residual=device.to_device(res))
+    lib.LayerPlanFused([p] * n, [epi] * n, [device.to_device(x)] * n, ys, torch.from_numpy(rows).cuda(), M, 1, ws).run()
+    torch.cuda.synchronize()
+    assert lib.workspace_status(ws) == 0
+    assert all(torch.equal(ys[0], y) for y in ys[1:])
+    assert rel_err(device.y_to_numpy(ys[0]), ref) <= TOL_F32

@@ -1,8 +1,8 @@
 // DS2D step on the device (Section 3.5 and Appendix A.2 of the paper): from the logits of all
 // rows of a step, verify the draft tree greedily and draft the next one.  Two kernels:
 //
-//   ds2d_best_partial  grid (slices of the vocabulary, rows): the k best logits of one row inside
-//                      one slice, k = 1 for token rows (only the arg-max is needed), b'_j for
+//   ds2d_best_partial  a wavefront per (slice of 4096 logits, row): the k best logits of the row inside
+//                      the slice, k = 1 for token rows (only the arg-max is needed), b'_j for
 //                      forecast embedding j, as sortable 64-bit keys.  Reads every logit once:
 //                      this is the kernel that is bound by HBM.
 //   ds2d_verify_draft  one block per stream: arg-max of every token row from the partial keys,
@@ -11,9 +11,8 @@
 //
 // A candidate is a 64-bit key: the logit mapped to an unsigned number that orders like the
 // stated rule (larger logit first, +0 = -0, NaN last) in the high half, the complement of the
-// token id in the low half (lower id first among equals).  Keys of different tokens differ, so
-// "the best key below the one found in the round before" enumerates candidates in order without
-// any bookkeeping; 0 marks an empty slot.
+// token id in the low half (lower id first among equals).  Keys of different tokens differ; 0 marks
+// an empty slot.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -27,8 +26,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int DS_THREADS = 256;
-constexpr int DS_ELEMS = 16;                           // logits per thread
-constexpr int DS_SLICE = DS_THREADS * DS_ELEMS;        // logits per block
+constexpr int DS_SLICE = 4096;                         // logits per wavefront
 constexpr int DS_KMAX = MLORA_DS2D_MAX_BRANCH;
 
 struct Ds2dArgs {
@@ -55,6 +53,26 @@ __device__ inline unsigned long long key_of(float v, unsigned token)
 }
 __device__ inline float bf16_value(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
 
+// how many candidates a row needs: 1 for a token row, b'_j for forecast embedding j
+__device__ inline int wanted(const Ds2dArgs &a, int r)
+{
+    if (r < a.T) return 1;
+    const int j = (r - a.T) % a.m;                     // 0-based number of the embedding
+    return j < a.next_depth ? a.next_branch[j] : 0;
+}
+
+// the largest value over a wavefront (rows of 16 lanes by DPP rotations, then the four rows)
+template <int N>
+__device__ __forceinline__ int ror_i32(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x120 + N, 0xF, 0xF, false); }
+__device__ __forceinline__ int wave_max_i32(int v)
+{
+    v = max(v, ror_i32<8>(v));
+    v = max(v, ror_i32<4>(v));
+    v = max(v, ror_i32<2>(v));
+    v = max(v, ror_i32<1>(v));
+    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
 __device__ inline unsigned long long wave_max(unsigned long long v)
 {
 #pragma unroll
@@ -64,259 +82,308 @@ __device__ inline unsigned long long wave_max(unsigned long long v)
     }
     return v;
 }
-// the largest value over the block; `slot` is 2 x 4 words of LDS, alternated by `phase`
-__device__ inline unsigned long long block_max(unsigned long long v, unsigned long long *slot, int phase)
-{
-    v = wave_max(v);
-    unsigned long long *s = slot + (phase & 1) * 4;
-    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
-    __syncthreads();
-    unsigned long long r = s[0];
-#pragma unroll
-    for (int w = 1; w < DS_THREADS / 64; ++w) r = s[w] > r ? s[w] : r;
-    return r;
-}
 
-// how many candidates a row needs: 1 for a token row, b'_j for forecast embedding j
-__device__ inline int wanted(const Ds2dArgs &a, int r)
-{
-    if (r < a.T) return 1;
-    const int j = (r - a.T) % a.m;                     // 0-based number of the embedding
-    return j < a.next_depth ? a.next_branch[j] : 0;
-}
-
-// 32-bit keys for bf16 logits: a bf16 value orders by 16 bits, which leaves room for the position
-// inside the block's slice (4096 logits): (sortable value << 16) | (0xFFFF - position).  Lower
-// positions are lower token ids, so these keys order a slice exactly like the 64-bit ones; they
-// are widened when the winners are stored.
-__device__ inline unsigned key16_of(unsigned h, unsigned pos)
-{
-    unsigned hi;
-    if ((h & 0x7FFFu) > 0x7F80u) hi = 0u;                              // NaN
-    else {
-        if (h == 0x8000u) h = 0u;                                      // -0 counts as +0
-        hi = (h & 0x8000u) ? (~h & 0xFFFFu) : (h | 0x8000u);
-    }
-    return (hi << 16) | (0xFFFFu - pos);
-}
-template <int N>
-__device__ __forceinline__ unsigned ror_u32(unsigned v)
-{
-    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + N, 0xF, 0xF, false);
-}
-// the largest value over the block: rows of 16 lanes by DPP rotations, the 16 rows through LDS
-// (`slot` is 2 x 16 words, alternated by `phase`)
-__device__ inline unsigned block_max(unsigned v, unsigned *slot, int phase)
-{
-    unsigned o;
-    o = ror_u32<8>(v); v = o > v ? o : v;
-    o = ror_u32<4>(v); v = o > v ? o : v;
-    o = ror_u32<2>(v); v = o > v ? o : v;
-    o = ror_u32<1>(v); v = o > v ? o : v;
-    unsigned *s = slot + (phase & 1) * 16;
-    if ((threadIdx.x & 15) == 0) s[threadIdx.x >> 4] = v;
-    __syncthreads();
-    const uint4 *q = reinterpret_cast<const uint4 *>(s);
-    unsigned r = 0u;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint4 t = q[i];
-        const unsigned m0 = t.x > t.y ? t.x : t.y, m1 = t.z > t.w ? t.z : t.w;
-        const unsigned m = m0 > m1 ? m0 : m1;
-        r = m > r ? m : r;
-    }
-    return r;
-}
-
+// element j of a 16-byte vector of logits: the bit pattern as a signed number.  Among positive numbers
+// it orders like the logit, and it is negative where the logit is.
 template <bool FP32>
-__global__ __launch_bounds__(DS_THREADS) void ds2d_best_partial(const Ds2dArgs a)
+__device__ __forceinline__ int element(const u32x4 &q, int j)
 {
-    using Key = typename std::conditional<FP32, unsigned long long, unsigned>::type;
-    __shared__ __align__(16) Key slot[32];
+    if constexpr (FP32) return (int)q[j];
+    else return (j & 1) ? (int)q[j >> 1] >> 16 : (int)(short)(q[j >> 1] & 0xFFFFu);
+}
+template <bool FP32>
+__device__ __forceinline__ int vector_max(const u32x4 &q)
+{
+    if constexpr (FP32) {
+        return max(max((int)q[0], (int)q[1]), max((int)q[2], (int)q[3]));
+    } else {
+        // two 16-bit maxima per instruction
+        // (the words as plain numbers first: a bit cast of a vector's element takes the vector's start)
+        typedef short s16x2 __attribute__((ext_vector_type(2)));
+        const unsigned w0 = q[0], w1 = q[1], w2 = q[2], w3 = q[3];
+        const s16x2 a = __builtin_elementwise_max(__builtin_bit_cast(s16x2, w0), __builtin_bit_cast(s16x2, w1));
+        const s16x2 b = __builtin_elementwise_max(__builtin_bit_cast(s16x2, w2), __builtin_bit_cast(s16x2, w3));
+        const s16x2 c = __builtin_elementwise_max(a, b);
+        return max((int)c[0], (int)c[1]);
+    }
+}
+
+// Slices whose winners are not all above zero (and finite or infinite numbers): all elements by their
+// keys, the best one below the last winner's per round.
+// (Reads the slice again every round: what matters here is that the common path keeps its registers.)
+template <bool FP32>
+__device__ __forceinline__ void slice_by_keys(const Ds2dArgs &a, long long slice_first, int pos_lo, int pos_hi, unsigned token_lo, int k,
+                                              unsigned long long *out, int lane)
+{
+    unsigned long long below = ~0ull;
+    for (int round = 0; round < k; ++round) {
+        unsigned long long best = 0ull;
+#pragma unroll 4
+        for (int pos = pos_lo + lane; pos < pos_hi; pos += 64) {
+            const long long e = slice_first + pos;
+            const float v = FP32 ? reinterpret_cast<const float *>(a.logits)[e] : bf16_value(reinterpret_cast<const unsigned short *>(a.logits)[e]);
+            unsigned long long key = key_of(v, (unsigned)(pos - pos_lo) + token_lo);
+            key = key < below ? key : 0ull;
+            best = key > best ? key : best;
+        }
+        best = wave_max(best);
+        if (lane == 0) out[round] = best;
+        below = best;                            // (0: the slice holds fewer than k logits, the rest are empty slots)
+    }
+}
+
+// What bounds it: reading the logits once.  A wavefront owns a slice and needs no barrier: 16-byte
+// loads, eight (bf16) in flight per lane, a packed maximum per vector, and only one vector per lane and
+// round is looked at element by element.  That works on bit patterns as signed numbers, so it holds
+// for winners above zero; a slice whose next best logit is zero, negative, NaN or missing goes to
+// slice_by_keys.  240 rows of 128256 bf16 logits (61.6 MB): a block per slice with keys for all
+// elements 25.3 us, this 15.3 us (4.0 TB/s).  Four wavefronts per SIMD: the registers for eight spill
+// (35 us).
+template <bool FP32>
+__global__ __launch_bounds__(DS_THREADS, 4) void ds2d_best_partial(const Ds2dArgs a)
+{
     const int row = blockIdx.y;
     const int k = wanted(a, row % a.R);
-    if (k == 0) return;
+    const int lane = threadIdx.x & 63;
+    const int slice = (int)blockIdx.x * (DS_THREADS / 64) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (k == 0 || slice >= a.slices) return;
     // The row's logits are elements [row * V, row * V + V) of the whole array.  They are read
     // with aligned 16-byte loads counted from the start of the array (rows need no alignment of
-    // their own); elements of a vector that belong to a neighbouring row are ignored, and the
-    // last, partial vector of the array is read element by element.
+    // their own); elements of a vector that belong to a neighbouring row are ignored.
     constexpr int EPV = FP32 ? 4 : 8;                                   // elements per vector
-    constexpr int VPT = DS_ELEMS / EPV;                                 // vectors per thread
+    constexpr int VPT = DS_SLICE / EPV / 64;                            // vectors per lane
     const long long first = (long long)row * a.V, last = first + a.V;
-    const long long vec0 = first / EPV + (long long)blockIdx.x * (DS_THREADS * VPT);
+    const long long vec0 = first / EPV + (long long)slice * (64 * VPT);
     const long long full_vectors = a.total / EPV;
     const long long slice_first = vec0 * EPV;                           // element at position 0
-    // the row's part of this slice, as positions 0 .. DS_SLICE, and the token id at pos_lo
+    // the row's part of this slice, as positions pos_lo .. pos_hi, and the token id at pos_lo
     const int pos_lo = first > slice_first ? (int)(first - slice_first) : 0;
     const int pos_hi = last - slice_first < DS_SLICE ? (last > slice_first ? (int)(last - slice_first) : 0) : DS_SLICE;
     const unsigned token_lo = (unsigned)(slice_first + pos_lo - first);
-    Key key[DS_ELEMS];
+    unsigned long long *out = a.partial + ((size_t)row * a.slices + slice) * DS_KMAX;
+    if (pos_hi <= pos_lo) {
+        if (lane < k) out[lane] = 0ull;
+        return;
+    }
+    // (a slice with the last, partial vector of the array: element by element)
+    if (pos_hi > (full_vectors - vec0) * EPV) {
+        slice_by_keys<FP32>(a, slice_first, pos_lo, pos_hi, token_lo, k, out, lane);
+        return;
+    }
+    u32x4 q[VPT];
 #pragma unroll
     for (int u = 0; u < VPT; ++u) {
-        const long long vi = vec0 + (long long)u * DS_THREADS + threadIdx.x;
-        const long long e0 = vi * EPV;
-        const unsigned pos0 = (unsigned)(u * DS_THREADS + threadIdx.x) * EPV;
-        unsigned bits[EPV];                     // fp32 patterns, or bf16 patterns in the low half
-        if (e0 >= last) {
-#pragma unroll
-            for (int j = 0; j < EPV; ++j) bits[j] = 0u;
-        } else if (vi < full_vectors) {
-            const u32x4 q = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.logits) + vi);
-            if constexpr (FP32) {
-                bits[0] = q.x; bits[1] = q.y; bits[2] = q.z; bits[3] = q.w;
-            } else {
-                bits[0] = q.x & 0xFFFFu; bits[1] = q.x >> 16; bits[2] = q.y & 0xFFFFu; bits[3] = q.y >> 16;
-                bits[4] = q.z & 0xFFFFu; bits[5] = q.z >> 16; bits[6] = q.w & 0xFFFFu; bits[7] = q.w >> 16;
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < EPV; ++j) {
-                bits[j] = 0u;
-                if (e0 + j < a.total) {
-                    if constexpr (FP32) bits[j] = reinterpret_cast<const unsigned *>(a.logits)[e0 + j];
-                    else bits[j] = reinterpret_cast<const unsigned short *>(a.logits)[e0 + j];
-                }
-            }
-        }
+        // (vectors past the array: re-reads of its last one, outside the row)
+        const long long vi = min(vec0 + u * 64 + lane, full_vectors - 1);
+        q[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.logits) + vi);
+    }
+    constexpr int LOWEST = FP32 ? (int)0x80000000 : -32768;             // below every positive number; never a winner
+    // the largest element of a vector (its first position: base) that lies in the row and comes after (top,
+    // winner) in the order of candidates
+    auto rest_max = [&](const u32x4 &v, int base, int top, int winner) {
+        int m = LOWEST;
 #pragma unroll
         for (int j = 0; j < EPV; ++j) {
-            const int pos = (int)pos0 + j;                  // inside the row iff pos_lo <= pos < pos_hi
-            const bool inside = pos >= pos_lo && pos < pos_hi;
-            if constexpr (FP32) key[u * EPV + j] = inside ? key_of(__uint_as_float(bits[j]), (unsigned)(pos - pos_lo) + token_lo) : 0ull;
-            else key[u * EPV + j] = inside ? key16_of(bits[j], (unsigned)pos) : 0u;
+            const int e = element<FP32>(v, j), pos = base + j;
+            if (pos >= pos_lo && pos < pos_hi && (e < top || (e == top && pos > winner))) m = max(m, e);
         }
-    }
-    unsigned long long *out = a.partial + ((size_t)row * a.slices + blockIdx.x) * DS_KMAX;
-    Key below = ~(Key)0;
-    for (int round = 0; round < k; ++round) {
-        Key best = 0;
+        return m;
+    };
+    int vm[VPT], best = LOWEST;
+    const bool whole = pos_lo == 0 && pos_hi == DS_SLICE;
 #pragma unroll
-        for (int u = 0; u < DS_ELEMS; ++u) {
-            const Key c = key[u] < below ? key[u] : (Key)0;
-            best = c > best ? c : best;
+    for (int u = 0; u < VPT; ++u) {
+        vm[u] = whole ? vector_max<FP32>(q[u]) : rest_max(q[u], (u * 64 + lane) * EPV, 0x7FFFFFFF, DS_SLICE);
+        best = max(best, vm[u]);
+    }
+    int last_top = 0x7FFFFFFF, last_winner = -1;
+    for (int round = 0; round < k; ++round) {
+        const int top = wave_max_i32(best);
+        if (top <= 0 || top > (FP32 ? 0x7F800000 : 0x7F80)) {           // (uniform)
+            slice_by_keys<FP32>(a, slice_first, pos_lo, pos_hi, token_lo, k, out, lane);
+            return;
         }
-        best = block_max(best, slot, round);
-        if (threadIdx.x == 0) {
-            if constexpr (FP32) out[round] = best;
-            else {
-                // widen: the value's 16 bits on top, the complement of the token id below
-                const unsigned token = (unsigned)(slice_first + (long long)(0xFFFFu - (best & 0xFFFFu)) - first);
-                out[round] = best == 0u ? 0ull : ((unsigned long long)(best >> 16) << 48) | (unsigned long long)(~token);
+        // lowest position that holds it: the first vector of a lane that does (a lane's vectors are in the
+        // order of positions), then the first element that has not been a winner before
+        // (every lane does it, with its own first vector that reaches its maximum: branches would cost more)
+        int pos = DS_SLICE, at = 0;
+        u32x4 v = q[0];
+#pragma unroll
+        for (int u = VPT - 1; u >= 1; --u) at = vm[u] == best ? u : at;
+        at = vm[0] == best ? 0 : at;
+#pragma unroll
+        for (int u = 1; u < VPT; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = at == u ? q[u][e] : v[e];
+        const int base = (at * 64 + lane) * EPV, from = top == last_top ? max(pos_lo, last_winner + 1) : pos_lo;
+#pragma unroll
+        for (int j = EPV - 1; j >= 0; --j)
+            if (element<FP32>(v, j) == top && base + j >= from && base + j < pos_hi) pos = base + j;
+        const int winner = -wave_max_i32(-pos);
+        if (lane == 0) {
+            const unsigned bits = FP32 ? (unsigned)top : (unsigned)top << 16;
+            out[round] = key_of(__uint_as_float(bits), (unsigned)(winner - pos_lo) + token_lo);
+        }
+        if (round + 1 < k) {                                            // the winner's lane: its next best
+            const int rest = rest_max(v, base, top, winner);
+            const bool mine = pos == winner;
+            best = LOWEST;
+#pragma unroll
+            for (int u = 0; u < VPT; ++u) {
+                vm[u] = mine && at == u ? rest : vm[u];
+                best = max(best, vm[u]);
             }
         }
-        below = best;
-        if (best == 0) {                         // the slice holds fewer than k logits
-            for (int r2 = round + 1 + (int)threadIdx.x; r2 < k; r2 += DS_THREADS) out[r2] = 0ull;
-            break;
-        }
+        last_top = top;
+        last_winner = winner;
     }
 }
 
+// One block per stream: a chain of latencies, kept short.  Sixteen lanes reduce a token row's slices
+// without atomics; the walk is a ballot per level; the best candidates of a level are ranked by
+// counting, without rounds.  8 streams of 30 rows over 128256 logits: 7.6 -> 6.8 us, of which about half
+// are the launch and two dependent trips to memory.
+constexpr int DS_POOL = 2048;                          // candidate keys held in LDS
+__device__ __forceinline__ unsigned long long row16_max(unsigned long long v)
+{
+    auto step = [&](auto n) {
+        constexpr int N = decltype(n)::value;
+        const unsigned long long o = ((unsigned long long)(unsigned)ror_i32<N>((int)(v >> 32)) << 32) | (unsigned)ror_i32<N>((int)v);
+        v = o > v ? o : v;
+    };
+    step(std::integral_constant<int, 8>{});
+    step(std::integral_constant<int, 4>{});
+    step(std::integral_constant<int, 2>{});
+    step(std::integral_constant<int, 1>{});
+    return v;
+}
 __global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a)
 {
-    __shared__ unsigned long long slot[8];
     __shared__ unsigned long long best_key[MLORA_DS2D_MAX_ROWS];
-    __shared__ int tok[MLORA_DS2D_MAX_ROWS];
+    __shared__ unsigned long long pool[DS_POOL];
     __shared__ int walk_end, walk_token;
     __shared__ int cand[MLORA_DS2D_MAX_FORECAST][DS_KMAX];
     const int s = blockIdx.x, tid = threadIdx.x;
-
-    // arg-max of every token row: the best of the first keys of its slices.  All (row, slice)
-    // pairs are spread over the block, so the loads are independent of each other.
-    if (tid < a.T) {
-        best_key[tid] = 0ull;
-        tok[tid] = a.tokens[(size_t)s * a.T + tid];
-    }
-    __syncthreads();
     const unsigned long long *base = a.partial + (size_t)s * a.R * a.slices * DS_KMAX;
-    // (loads are issued in batches of eight before any of them is used: a loop that stores each
-    // value as it arrives would wait for memory once per element)
-    constexpr int BATCH = 8;
-    for (int i0 = 0; i0 < a.T * a.slices; i0 += BATCH * DS_THREADS) {
-        unsigned long long v[BATCH];
+
+    const int my_tok = tid < a.T ? a.tokens[(size_t)s * a.T + tid] : 0;
+    const int my_parent = tid < a.T ? a.parent[tid] : -1;
+    // arg-max of every token row: the best of the first keys of its slices, four loads in flight per lane
+    for (int r = tid >> 4; r < a.T; r += DS_THREADS / 16) {
+        const unsigned long long *p = base + (size_t)r * a.slices * DS_KMAX;
+        unsigned long long best = 0ull;
+        for (int c0 = tid & 15; c0 < a.slices; c0 += 64) {
+            unsigned long long v[4];
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const int i = i0 + u * DS_THREADS + tid;                          // row * slices + slice
-            v[u] = i < a.T * a.slices ? base[(size_t)i * DS_KMAX] : 0ull;
-        }
+            for (int u = 0; u < 4; ++u) v[u] = p[(size_t)min(c0 + 16 * u, a.slices - 1) * DS_KMAX];
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const int i = i0 + u * DS_THREADS + tid;
-            if (i < a.T * a.slices) atomicMax(&best_key[i / a.slices], v[u]);
+            for (int u = 0; u < 4; ++u) best = v[u] > best ? v[u] : best;
         }
+        best = row16_max(best);
+        if ((tid & 15) == 0) best_key[r] = best;
     }
     __syncthreads();
 
-    // the walk (one thread; the tree has at most 64 tokens and 8 levels; everything is in LDS)
-    if (tid == 0) {
+    // the walk, by the first wavefront: lane c looks after token row c (at most 32 of them)
+    if (tid < 64) {
         int32_t *rows = a.accepted_rows + (size_t)s * (a.m + 1);
         int32_t *out = a.emitted + (size_t)s * (a.m + 1);
-        int cur = 0, n = 0;
-        rows[0] = 0;
+        const int target = tid < a.T ? (int)(~(unsigned)(best_key[tid] & 0xFFFFFFFFull)) : 0;
+        int cur = 0, n = 0, my_row = tid == 0 ? 0 : -1, my_out = -1;          // lane i holds entry i of both lists
         while (true) {
-            const int target = (int)(~(unsigned)(best_key[cur] & 0xFFFFFFFFull));
-            int next = -1;
-            if (n < a.depth)
-                for (int c = cur + 1; c < a.T; ++c)
-                    if (a.parent[c] == cur && tok[c] == target) { next = c; break; }
-            if (next < 0) {
-                out[n] = target;
-                walk_token = target;
+            const int want = __builtin_amdgcn_readlane(target, cur);
+            if (tid == n) my_out = want;
+            const unsigned long long kids = n < a.depth ? __ballot(my_parent == cur && tid < a.T && my_tok == want) : 0ull;
+            if (!kids) {
+                if (tid == 0) walk_token = want;
                 break;
             }
-            out[n] = tok[next];
-            cur = next;
-            rows[++n] = cur;
+            cur = (int)__builtin_ctzll(kids);
+            ++n;
+            if (tid == n) my_row = cur;
         }
-        for (int i = n + 1; i <= a.m; ++i) rows[i] = out[i] = -1;
-        a.n_accepted[s] = n;
-        walk_end = cur;
+        if (tid <= a.m) {
+            rows[tid] = my_row;
+            out[tid] = my_out;
+        }
+        if (tid == 0) {
+            a.n_accepted[s] = n;
+            walk_end = cur;
+        }
     }
     __syncthreads();
     const int cur = walk_end;
     int32_t *nt = a.next_tokens + (size_t)s * a.T_next;
     if (tid == 0) nt[0] = walk_token;
 
-    // Level i of the next tree: the b'_i best of forecast embedding i of the node `cur`.  A
-    // thread keeps its share of a level's candidates in registers (two each: up to 512
-    // candidates, e.g. 32 slices x 16; what lies beyond is read again every round), and the loads
-    // of all levels are issued before the first round.
-    constexpr int OWN = 2;
-    unsigned long long own[MLORA_DS2D_MAX_FORECAST][OWN];
-#pragma unroll
-    for (int i = 0; i < MLORA_DS2D_MAX_FORECAST; ++i) {
-        if (i >= a.next_depth) break;
-        const int b = a.next_branch[i];
-        const unsigned long long *p = base + (size_t)(a.T + cur * a.m + i) * a.slices * DS_KMAX;
-#pragma unroll
-        for (int u = 0; u < OWN; ++u) {
-            const int c = tid + u * DS_THREADS;
-            own[i][u] = c < a.slices * b ? p[(size_t)(c / b) * DS_KMAX + (c % b)] : 0ull;
+    // Level i of the next tree: the b'_i best of forecast embedding i of the node `cur`, by rank: a
+    // candidate with r better ones is number r (keys differ).  Thread t looks at candidate t % 16 of
+    // slices t / 16, t / 16 + 16, ...  Common case: the candidates of all levels fit the pool and are
+    // requested at once.
+    const unsigned long long *rows_of_cur = base + (size_t)(a.T + cur * a.m) * a.slices * DS_KMAX;
+    const int r16 = tid & 15, s16 = tid >> 4;
+    int total = 0;
+    for (int i = 0; i < a.next_depth; ++i) total += a.slices * a.next_branch[i];
+    if (total <= DS_POOL) {
+        int at = 0;
+        for (int i = 0; i < a.next_depth; ++i) {
+            const int b = a.next_branch[i];
+            const unsigned long long *p = rows_of_cur + (size_t)i * a.slices * DS_KMAX;
+            if (r16 < b)
+                for (int c = s16; c < a.slices; c += 16) pool[at + c * b + r16] = p[(size_t)c * DS_KMAX + r16];
+            at += a.slices * b;
         }
-    }
-    int phase = 0;
-#pragma unroll
-    for (int i = 0; i < MLORA_DS2D_MAX_FORECAST; ++i) {
-        if (i >= a.next_depth) break;
-        const int b = a.next_branch[i];
-        const unsigned long long *p = base + (size_t)(a.T + cur * a.m + i) * a.slices * DS_KMAX;
-        const int n_cand = a.slices * b;
-        unsigned long long below = ~0ull;
-        for (int round = 0; round < b; ++round) {
-            unsigned long long v = 0ull;
-#pragma unroll
-            for (int u = 0; u < OWN; ++u) {
-                const unsigned long long q = own[i][u] < below ? own[i][u] : 0ull;
-                v = q > v ? q : v;
+        __syncthreads();
+        at = 0;
+        for (int i = 0; i < a.next_depth; ++i) {
+            const int b = a.next_branch[i], n_cand = a.slices * b;
+            const unsigned long long *list = pool + at;
+            for (int c = tid; c < n_cand; c += DS_THREADS) {
+                const unsigned long long key = list[c];
+                int better = 0;
+#pragma unroll 8
+                for (int o = 0; o < n_cand; ++o) better += list[o] > key ? 1 : 0;
+                if (key && better < b) cand[i][better] = (int)(~(unsigned)(key & 0xFFFFFFFFull));
             }
-            for (int c = tid + OWN * DS_THREADS; c < n_cand; c += DS_THREADS) {
-                unsigned long long q = p[(size_t)(c / b) * DS_KMAX + (c % b)];
-                q = q < below ? q : 0ull;
-                v = q > v ? q : v;
+            at += n_cand;
+        }
+    } else {
+        // a level's candidates in pieces of whole slices, the best so far at the front of the pool
+        for (int i = 0; i < a.next_depth; ++i) {
+            const int b = a.next_branch[i];
+            const unsigned long long *p = rows_of_cur + (size_t)i * a.slices * DS_KMAX;
+            int kept = 0;
+            for (int c0 = 0; c0 < a.slices;) {
+                const int n_slices = min(a.slices - c0, (DS_POOL - kept) / b), n = kept + n_slices * b;
+                __syncthreads();
+                if (r16 < b)
+                    for (int c = s16; c < n_slices; c += 16) pool[kept + c * b + r16] = p[(size_t)(c0 + c) * DS_KMAX + r16];
+                __syncthreads();
+                constexpr int OWN = DS_POOL / DS_THREADS;
+                unsigned long long own[OWN];
+                int rank[OWN];
+#pragma unroll
+                for (int u = 0; u < OWN; ++u) {
+                    const int c = u * DS_THREADS + tid;
+                    own[u] = c < n ? pool[c] : 0ull;
+                    rank[u] = 0;
+                }
+                for (int o = 0; o < n; ++o) {
+                    const unsigned long long other = pool[o];
+#pragma unroll
+                    for (int u = 0; u < OWN; ++u) rank[u] += other > own[u] ? 1 : 0;
+                }
+                __syncthreads();
+                if (tid < b) pool[tid] = 0ull;
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < OWN; ++u)
+                    if (own[u] && rank[u] < b) pool[rank[u]] = own[u];
+                kept = b;
+                c0 += n_slices;
             }
-            v = block_max(v, slot, phase++);
-            if (tid == 0) cand[i][round] = (int)(~(unsigned)(v & 0xFFFFFFFFull));
-            below = v;
+            __syncthreads();
+            if (tid < b) cand[i][tid] = (int)(~(unsigned)(pool[tid] & 0xFFFFFFFFull));
         }
     }
     __syncthreads();
@@ -469,8 +536,8 @@ mlora_status mlora_ds2d_step(const mlora_ds2d *d, const void *logits, const int3
     for (int r = 0; r < MLORA_DS2D_MAX_ROWS; ++r) a.parent[r] = r < T ? (signed char)par[r] : (signed char)-1;
 
     hipStream_t s = (hipStream_t)stream;
-    if (a.fp32) hipLaunchKernelGGL(ds2d_best_partial<true>, dim3(a.slices, d->n_streams * R), dim3(DS_THREADS), 0, s, a);
-    else hipLaunchKernelGGL(ds2d_best_partial<false>, dim3(a.slices, d->n_streams * R), dim3(DS_THREADS), 0, s, a);
+    if (a.fp32) hipLaunchKernelGGL(ds2d_best_partial<true>, dim3((a.slices + 3) / 4, d->n_streams * R), dim3(DS_THREADS), 0, s, a);
+    else hipLaunchKernelGGL(ds2d_best_partial<false>, dim3((a.slices + 3) / 4, d->n_streams * R), dim3(DS_THREADS), 0, s, a);
     hipLaunchKernelGGL(ds2d_verify_draft, dim3(d->n_streams), dim3(DS_THREADS), 0, s, a);
     return hipGetLastError() == hipSuccess ? MLORA_OK : MLORA_EHIP;
 }

@@ -44,35 +44,13 @@ __device__ __forceinline__ float load_shared(const float *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The same for 16 bytes at a time (the wide kernel's partial tiles: 64 KiB per block and unit).
-// There is no 128-bit atomic type, so these are the plain 128-bit instructions with the cache
-// policy of the 32-bit ones above (sc1), written out.  The compiler does not know that the load
-// is in flight: shared16_wait (vmcnt(0)) must stand between a batch of loads and the first use.
+// The same for 16 bytes at a time (the wide kernel's partial tiles).  There is no 128-bit atomic type,
+// so this is the plain 128-bit instruction with the cache policy of the 32-bit one above (sc1),
+// written out.
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store_shared16(float *p, f32x4_t v)
 {
     asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
-}
-__device__ __forceinline__ f32x4_t load_shared16(const float *p)
-{
-    f32x4_t v;
-    asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=&v"(v) : "v"(p) : "memory");
-    return v;
-}
-__device__ __forceinline__ void shared16_wait(f32x4_t (&v)[8])
-{
-    asm volatile("s_waitcnt vmcnt(0)"
-                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])
-                 :
-                 : "memory");
-}
-__device__ __forceinline__ void shared16_wait(f32x4_t (&v)[16])
-{
-    asm volatile("s_waitcnt vmcnt(0)"
-                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]),
-                   "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15])
-                 :
-                 : "memory");
 }
 // 16-byte loads of such data that the compiler can see (and so schedule, and wait for, by
 // itself): buffer loads with the same cache policy (sc1, bit 4 of the policy argument) through a

@@ -1491,8 +1491,10 @@ struct WideLds {
 // 16 columns, into theirs).  Per k-step of a group of 32 inputs 70 vector instructions (28 to unpack, 32
 // FMAs) and 6 products of 32 cycles, which run beside them: what bounds a compute unit's work is
 // then the vector instructions, and what bounds a launch is how many blocks wait at once for memory.
-// The loop and all that follows it fit 168 registers, so that three blocks share a compute unit:
-// 16 layers of a 1B-like model at 32 rows 191 -> 170 us (products of 16 x 16 x 32, two blocks).
+// The loop and all that follows it fit 168 registers without spills for every group size, so that three
+// blocks share a compute unit: 16 layers of a 1B-like model at 32 rows 191 -> 170 us (products of 16 x 16
+// x 32, two blocks).  A group of 128 inputs is two runs of two k-steps: in one run its fragments of x do
+// not fit (10 registers spilled inside the loop, the same launch in groups of 128 163 us against 146).
 // 64 rows: products of 16 x 16 x 32, whose 64 sums per lane leave the registers for it; with products
 // of 32 x 32 x 16 the same launch at 512 rows took 1684 us instead of 1625.
 // int8 rows are widened to bf16 (exact: seven bits and a sign) on their way into LDS: sums of a group
@@ -1562,10 +1564,10 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
         // on an odd super-step): one straight piece of code, no branches inside
         auto stage_math = [&](auto nk) {
             constexpr int NK = decltype(nk)::value;
-            // A scale group is worked through in runs of SG k-steps (64 rows: at most 2, whose
-            // fragments of x fit the registers): offset term (-24 * sum of x over the run cancels the
+            // A scale group is worked through in runs of SG k-steps (at most 2, whose fragments of x
+            // fit the registers): offset term (-24 * sum of x over the run cancels the
             // offset of the stored codes), products, FMAs with the scale.
-            constexpr int SG = MB == 2 || SPG < 2 ? SPG : 2;
+            constexpr int SG = SPG < 2 ? SPG : 2;
             constexpr int G0 = (H * S) / SPG;              // first scale group of this stage's register sets
 #pragma unroll
             for (int r = 0; r < NK / SG; ++r) {
@@ -1582,7 +1584,7 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
                             xk[t][o] = *reinterpret_cast<const uint4 *>(xs + t * 64 + o * 16);
                             corr = mfma32(xk[t][o], neg24, corr);
                         }
-                    sc[G0 + g] = load_scales(st * S + g * SPG + W);
+                    if ((r + 1) * SG % SPG == 0) sc[G0 + g] = load_scales(st * S + g * SPG + W);   // (last run of its group)
 #pragma unroll
                     for (int cb = 0; cb < 2; ++cb) {
                         f32x16 d = corr;
@@ -1663,7 +1665,7 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
 
 // group = index of the block's four tiles among the projection's; ku as in base_unit.  SPG =
 // k-steps per scale group, the same for every projection of the launch; MB = blocks of 16 rows
-// per chunk (2: calls of 17 to 32 rows, 4: 33 rows and more).
+// per base block (4 in long launches, else 2).
 template <int SPG, int MB, bool A8>
 __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P, int pi, int group, int ku,
                                           int m0, WideLds<MB> &lds)

@@ -61,9 +61,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t shared_buffer(const float *bas
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, bytes, 0x00020000);
 }
-__device__ __forceinline__ f32x4_t load_shared16(__amdgpu_buffer_rsrc_t rsrc, int byte_offset)
+__device__ __forceinline__ f32x4_t load_shared16(__amdgpu_buffer_rsrc_t rsrc, int byte_offset, int uniform_offset = 0)
 {
-    return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, byte_offset, 0, 16));
+    return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, byte_offset, uniform_offset, 16));
 }
 
 // descriptor over `bytes` bytes at `base`, both the same for every lane of a wave (raw buffer, no
@@ -1496,7 +1496,8 @@ struct WideLds {
 // x 32, two blocks).  A group of 128 inputs is two runs of two k-steps: in one run its fragments of x do
 // not fit (10 registers spilled inside the loop, the same launch in groups of 128 163 us against 146).
 // 64 rows: products of 16 x 16 x 32, whose 64 sums per lane leave the registers for it; with products
-// of 32 x 32 x 16 the same launch at 512 rows took 1684 us instead of 1625.
+// of 32 x 32 x 16 the same launch at 512 rows took 1684 us instead of 1625.  No spills in the loop; the
+// sum of partial tiles keeps 9 registers (int8 rows: 16) in scratch memory.
 // int8 rows are widened to bf16 (exact: seven bits and a sign) on their way into LDS: sums of a group
 // stay integers below 2^24, exact in fp32, and the loop has fewer vector instructions than one
 // over int8 products, whose int32 sums need a conversion each (16 layers at 32 rows 188 -> 171 us).
@@ -1977,7 +1978,7 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
             const float *base = P.partial + (((size_t)u * tiles + tile) * a.m_pad + m0) * TILE_N;
             const __amdgpu_buffer_rsrc_t rsrc = shared_buffer(base, NP * 1024);
 #pragma unroll
-            for (int i = 0; i < NP; ++i) pv[i] = load_shared16(rsrc, lane * 16 + i * 1024);
+            for (int i = 0; i < NP; ++i) pv[i] = load_shared16(rsrc, lane * 16, i * 1024);
         };
         auto fold = [&](const f32x4_t (&pv)[NP]) {
 #pragma unroll
@@ -1985,15 +1986,23 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[i / 8][(i / 4) % 2][(i % 4) * 4 + e] += pv[i][e];
         };
+        // (inside the loop every request is unconditional: the waits can then count the requests behind
+        // the data they need, where a branch would make them wait for everything in flight)
         f32x4_t pa[NP], pb[NP];
-        if (np > 0) request(pa, 0);
-        for (int u = 0; u < np; u += 2) {
-            if (u + 1 < np) request(pb, u + 1);
+        request(pa, 0);
+        int u = 0;
+        for (; u + 2 < np; u += 2) {
+            request(pb, u + 1);
             fold(pa);
-            if (u + 1 < np) {
-                if (u + 2 < np) request(pa, u + 2);
-                fold(pb);
-            }
+            request(pa, u + 2);
+            fold(pb);
+        }
+        if (u + 1 < np) {
+            request(pb, u + 1);
+            fold(pa);
+            fold(pb);
+        } else {
+            fold(pa);
         }
     }
     if (poisoned) {

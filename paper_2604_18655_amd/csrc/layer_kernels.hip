@@ -1498,11 +1498,14 @@ struct WideLds {
 // 64 rows: products of 16 x 16 x 32, whose 64 sums per lane leave the registers for it; with products
 // of 32 x 32 x 16 the same launch at 512 rows took 1684 us instead of 1625.  No spills in the loop; the
 // sum of partial tiles keeps 9 registers (int8 rows: 16) in scratch memory.
+// Codes that one block of rows reads (AGAIN false) are marked as used once; where several blocks of rows
+// read them, they stay in the cache for the next one (14336 x 4096 in groups of 128 at 64 rows, 32
+// adapters of rank 64: 46.1 -> 43.7 us; unmarked where one block reads them, 16 layers at 32 rows: 159 -> 168).
 // int8 rows are widened to bf16 (exact: seven bits and a sign) on their way into LDS: sums of a group
 // stay integers below 2^24, exact in fp32, and the loop has fewer vector instructions than one
 // over int8 products, whose int32 sums need a conversion each (16 layers at 32 rows 188 -> 171 us).
 // ------------------------------------------------------------------------------------------
-template <int SPG, int MB, bool A8, class Acc, class Early>
+template <int SPG, int MB, bool A8, bool AGAIN, class Acc, class Early>
 __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t codes, __amdgpu_buffer_rsrc_t scales,
                                             __amdgpu_buffer_rsrc_t xsrc, const int (&xoff)[A8 ? 2 : 4], int piece16, int xdst0,
                                             unsigned char *lds_x, const unsigned char *xfrag, int n_ksteps,
@@ -1522,7 +1525,7 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
     constexpr int RPI = 256 / (S * (A8 ? 2 : 4));          // rows a block moves per instruction
     u32x4 xr[XP];
     // (requests past the unit's end re-read its last k-step: all loads stay unconditional)
-    auto load_codes = [&](int k) { return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(codes, lane16, min(k, last) * 1024, 2)); };
+    auto load_codes = [&](int k) { return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(codes, lane16, min(k, last) * 1024, AGAIN ? 0 : 2)); };
     auto load_scales = [&](int k) { return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(scales, col8, min(k, last) / SPG * 128, 0)); };
     // (a last stage of half its length re-reads the unit's last inputs in place of those past it)
     constexpr int XB = A8 ? 32 : 64;                       // bytes of a row of x per k-step
@@ -1666,8 +1669,8 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
 
 // group = index of the block's four tiles among the projection's; ku as in base_unit.  SPG =
 // k-steps per scale group, the same for every projection of the launch; MB = blocks of 16 rows
-// per base block (4 in long launches, else 2).
-template <int SPG, int MB, bool A8>
+// per base block (4 in long launches, else 2); AGAIN = other blocks of rows read the same codes.
+template <int SPG, int MB, bool A8, bool AGAIN>
 __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P, int pi, int group, int ku,
                                           int m0, WideLds<MB> &lds)
 {
@@ -1804,7 +1807,7 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
         const __amdgpu_buffer_rsrc_t rs = wave_buffer(sp, (unsigned)unit_cnt * (unsigned)(gs * 128));
         const int xdst0 = (tid / PPR) * L::XROW + piece16 * (2 / EB);
         if constexpr (MB == 2) {
-            stream_loop<SPG, MB, A8>(acc[0], rw, rs, rx, xoff, piece16, xdst0, lds.buf, lds.buf + l32 * L::XROW + hi * 32,
+            stream_loop<SPG, MB, A8, AGAIN>(acc[0], rw, rs, rx, xoff, piece16, xdst0, lds.buf, lds.buf + l32 * L::XROW + hi * 32,
                                      unit_cnt * 4, mask, bias, lane, early);
         } else {
             // Products of 16 x 16: lane (l16, lq) gets rows 4 * lq + e of a block of 16 and columns 16 * j +
@@ -1816,7 +1819,7 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) acc16[mb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            stream_loop<SPG, MB, A8>(acc16, rw, rs, rx, xoff, piece16, xdst0, lds.buf, lds.buf + arow * L::XROW + (lane >> 4) * 16,
+            stream_loop<SPG, MB, A8, AGAIN>(acc16, rw, rs, rx, xoff, piece16, xdst0, lds.buf, lds.buf + arow * L::XROW + (lane >> 4) * 16,
                                      unit_cnt * 4, mask, bias, lane, early);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
@@ -2101,7 +2104,7 @@ constexpr int wide_lds_bytes()
     return sizeof(WideLds<MB>) > sizeof(ShrinkLds) ? (int)sizeof(WideLds<MB>) : (int)sizeof(ShrinkLds);
 }
 
-template <int SPG, int MB, bool A8>
+template <int SPG, int MB, bool A8, bool AGAIN>
 __global__ __launch_bounds__(256, (MB == 2 ? 3 : 2)) void wide_kernel(const LayerArgs a)
 {
     __shared__ __align__(16) unsigned char smem[wide_lds_bytes<MB>()];
@@ -2126,7 +2129,7 @@ __global__ __launch_bounds__(256, (MB == 2 ? 3 : 2)) void wide_kernel(const Laye
     const int local = bb - first;
     const int groups = (tiles_n(P.N) + WIDE_TILES - 1) / WIDE_TILES;
     const int unit = pre ? local / groups : 0;
-    wide_unit<SPG, MB, A8>(a, P, pi, local - unit * groups, pre ? 1 + unit : 0, chunk * 16 * MB, lds);
+    wide_unit<SPG, MB, A8, AGAIN>(a, P, pi, local - unit * groups, pre ? 1 + unit : 0, chunk * 16 * MB, lds);
 }
 
 template <int MB, int XR>
@@ -2149,8 +2152,11 @@ hipError_t launch_layer(const LayerArgs &a, int grid_x, int groups, hipStream_t 
         const int spg = a.p[0].spg;
         auto go = [&](auto kernel) { kernel<<<grid, dim3(256), 0, s>>>(a); };
         auto by_rows = [&](auto spg_c, auto a8_c) {
-            if (a.block_rows == 32) go(wide_kernel<decltype(spg_c)::value, 2, decltype(a8_c)::value>);
-            else             go(wide_kernel<decltype(spg_c)::value, 4, decltype(a8_c)::value>);
+            constexpr int SPG = decltype(spg_c)::value;
+            constexpr bool A8 = decltype(a8_c)::value;
+            if (a.block_rows == 64)    go(wide_kernel<SPG, 4, A8, true>);
+            else if (a.row_blocks > 1) go(wide_kernel<SPG, 2, A8, true>);
+            else                       go(wide_kernel<SPG, 2, A8, false>);
         };
         auto by_group = [&](auto a8_c) {
             if (spg == 1)      by_rows(std::integral_constant<int, 1>{}, a8_c);

@@ -1760,7 +1760,7 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
         if (quads <= TPR) {
             if (q0 < quads) quads_of(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{}, q0);
         } else {
-            for (int qb = q0; qb < quads; qb += 4 * TPR) quads_of(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{}, qb);
+            for (int qb = q0; qb < quads; qb += 2 * TPR) quads_of(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{}, qb);
         }
         // the row of zeros that stands for rows of other adapters
         if (tid < L::T_ROW / 16) {

@@ -1,5 +1,5 @@
 """Blocks of four column tiles from 33 rows on: two blocks of 32 rows per chunk of 64 in ordinary
-launches, blocks of 64 rows in launches of 2048 of them and more.  Edges of both against the
+launches, blocks of 64 rows in long ones.  Edges of both against the
 oracle: rows around the block sizes, spare waves (column tiles not a multiple of four), units that
 end on half a stage, ranks from one run of 16 to the largest, all group sizes, every output stage.
 Bars as everywhere: 5e-3 of max|y_ref| with bf16 outputs (rounding alone reaches 2^-8), 2e-4 with
@@ -30,12 +30,14 @@ def rows_and_x(seed, M, K, n_ad):
 ])
 def test_blocks_of_32_rows(gpu, K, N, G, r, n_ad, M):
     x, rows = rows_and_x(M, M, K, n_ad)
+    assert gpu[0].layer_step_block_rows([gpu[0].Proj(K, N, G, None)], M) == 32
     check_linear(gpu, random_problem(K + N + M, K, N, G, r, n_ad), x, rows, f"K{K} N{N} G{G} r{r} a{n_ad} M{M}")
 
 
 def plan_of_many(gpu, prob, xs, ys, rows, M, y_dtype, n, scales=None):
     lib, device, torch = gpu
     p = device.upload_problem(prob)
+    assert lib.layer_step_block_rows([p] * n, M, scales is not None) == 64
     size = lib.a8_workspace_bytes if scales is not None else lib.workspace_bytes
     ws = torch.zeros(size([p] * n, M), dtype=torch.uint8, device="cuda")
     ra = torch.from_numpy(rows).cuda()
@@ -88,6 +90,7 @@ def test_fused_output_stage(gpu, M, n):
     ref = oracle.linear(prob.wq, prob.scales, 32, prob.lora_a, prob.lora_b, prob.shape.alpha, x, rows) * scale[:, None].astype(np.float64)
     ref = ref + wl.bf16_bits_to_f32(res).astype(np.float64)
     p = device.upload_problem(prob)
+    assert lib.layer_step_block_rows([p] * n, M) == (32 if M == 70 else 64)
     ws = device.alloc_workspace([p] * n, M)
     ys = [device.alloc_y(M, N, 1) for _ in range(n)]
     epi = lib.Epilogue(row_scale=torch.from_numpy(scale).cuda(), residual=device.to_device(res))
@@ -96,3 +99,28 @@ def test_fused_output_stage(gpu, M, n):
     assert lib.workspace_status(ws) == 0
     assert all(torch.equal(ys[0], y) for y in ys[1:])
     assert rel_err(device.y_to_numpy(ys[0]), ref) <= TOL_F32
+
+
+def test_offset_of_long_groups_cancels_early(gpu):
+    """The stored codes carry an offset of 24 that is taken out again per run of 64 inputs, also in groups
+    of 128: with rows of mean 2 (sums of the offset far above the result) the error against 64 bits in
+    groups of 128 is that of groups of 64 (1.1 times, the scales differ), and 2.8 times if the sums run
+    over 128 inputs."""
+    lib, device, torch = gpu
+    K, N, M = 2048, 512, 64
+    rng = np.random.default_rng(7)
+    x = wl.f32_to_bf16_bits((rng.standard_normal((M, K)) + 2.0).astype(np.float32))
+    errors = {}
+    for G in (64, 128):
+        prob = random_problem(11, K, N, G, 8, 1)
+        scales = prob.scales.view(np.float16).astype(np.float64).reshape(N, K // G, 1)
+        w = oracle.unpack_codes(prob.wq).astype(np.float64).reshape(N, K // G, G) * scales
+        ref = wl.bf16_bits_to_f32(x).astype(np.float64) @ w.reshape(N, K).T
+        p = device.upload_problem(prob)
+        y = device.alloc_y(M, N, 1)
+        lib.LayerPlan([p], [device.to_device(x)], [y], torch.full((M,), -1, dtype=torch.int32, device="cuda"), M, 1,
+                      device.alloc_workspace([p], M)).run()
+        torch.cuda.synchronize()
+        d = device.y_to_numpy(y).astype(np.float64) - ref
+        errors[G] = np.linalg.norm(d) / np.linalg.norm(ref)
+    assert errors[128] <= 1.8 * errors[64], errors

@@ -633,10 +633,9 @@ def main():
     achieved = base_bytes / kern_s / 1e9
     wide = info["wide"]
     spg = w.projs[0].group // 32
-    # blocks of 64 rows in launches of 2048 of them and more, else of 32
-    blocks64 = sum(-(-p.N // 256) * -(-M // 64) * -(-p.K // 2048) for p in w.projs) * w.layers // max(1, calls_per_step)
-    kernel_name = ("wide_kernel<%d, %d, %s>" % (spg, 2 if M <= 32 or blocks64 < 2048 else 4, "true" if args.a8 else "false")) if wide else \
-        "layer_kernel<%s>" % ("1, 8" if M <= 8 else "1, 16" if info["rows_per_chunk"] == 16 else "2, 24" if M <= 24 else "2, 32")
+    rows = lib.layer_step_block_rows(plans[0][0].keep[0], M, args.a8)
+    kernel_name = ("wide_kernel<%d, %d, %s, %s>" % (spg, rows // 16, "true" if args.a8 else "false", "true" if rows == 64 or M > 32 else "false")) if wide else \
+        "layer_kernel<%s>" % ("1, 8" if M <= 8 else "1, 16" if rows == 16 else "2, 24" if M <= 24 else "2, 32")
     kernel_tag = ("wide_kernel_a8" if args.a8 else "wide_kernel") if wide else "layer_kernel"
     achieved_tflops = (step_flops / launches_per_step) / kern_s / 1e12
     bound = BOUND.get(w.key, "hbm")

@@ -129,12 +129,16 @@ size_t mlora_w4_workspace_bytes(const mlora_w4_proj *projs, int32_t n_proj, int3
  * 128 projections; from 17 rows on also a new one where the group size changes),
  * [1] 1 if the first launch runs blocks of four column tiles ("wide_kernel"), 0 if blocks of
  * one column tile ("layer_kernel"), [2] rows per row chunk (16, 32 or 64; a short launch of 17
- * to 32 rows runs as two chunks of 16; unless a launch is long, a chunk of 64 rows is worked
- * through by two blocks of 32), [3] and [4] the first launch's grid: blocks per block of rows
+ * to 32 rows runs as two chunks of 16; a chunk of 64 rows is worked through by a block of 64 or two
+ * of 32, see mlora_w4_layer_step_block_rows), [3] and [4] the first launch's grid: blocks per block of rows
  * (grid.x is that times the number of blocks of rows, rounded up to runs of 8 when there are
  * several) and groups of 16 projections along z.
  * MLORA_EINVAL for null pointers or n_proj <= 0, MLORA_ESHAPE for shapes the library refuses. */
 mlora_status mlora_w4_layer_step_plan(const mlora_w4_proj *projs, int32_t n_proj, int32_t M, int32_t *info);
+
+/* Rows a base block of the first launch of such a call works on (16, 32 or 64; int8_rows != 0: of
+ * mlora_w4a8_layer_step), 0 for what the library refuses.  Host only, nothing is launched. */
+int32_t mlora_w4_layer_step_block_rows(const mlora_w4_proj *projs, int32_t n_proj, int32_t M, int32_t int8_rows);
 
 /* Zero-fill a workspace (a small kernel on `stream`; no memset node, so it can be captured). */
 mlora_status mlora_w4_workspace_init(void *workspace, size_t workspace_bytes, void *stream);

@@ -16,7 +16,7 @@ exported_symbols = (
     "mlora_strerror", "mlora_w4_blob_bytes", "mlora_w4_prepack", "mlora_w4_unpack",
     "mlora_group_rows", "mlora_w4_workspace_bytes", "mlora_w4_linear", "mlora_w4_layer_step",
     "mlora_w4_workspace_init", "mlora_w4_workspace_status", "mlora_w4_debug_spin_limit",
-    "mlora_w4_layer_step_static", "mlora_w4_layer_step_plan",
+    "mlora_w4_layer_step_static", "mlora_w4_layer_step_plan", "mlora_w4_layer_step_block_rows",
     "mlora_tree_attention_workspace_bytes", "mlora_tree_attention",
     "mlora_w4a8_workspace_bytes", "mlora_w4a8_layer_step",
     "mlora_w4_layer_step_fused", "mlora_rms_scale", "mlora_lora_int16_expand",
@@ -226,6 +226,11 @@ def layer_step_plan(projs: Sequence[Proj], M: int) -> dict:
     _check(load_library().mlora_w4_layer_step_plan(arr, len(projs), M, info), "mlora_w4_layer_step_plan")
     return {"launches": info[0], "wide": bool(info[1]), "rows_per_chunk": info[2],
             "grid_x": info[3], "grid_z": info[4]}
+
+
+def layer_step_block_rows(projs: Sequence[Proj], M: int, int8_rows: bool = False) -> int:
+    """Rows per base block of such a call's first launch (see mlora_w4_layer_step_block_rows)."""
+    return load_library().mlora_w4_layer_step_block_rows(_proj_array(projs), len(projs), M, int(int8_rows))
 
 
 def linear(proj: Proj, x, row_adapter, M: int, y, y_dtype: int = Y_BF16, workspace=None) -> None:

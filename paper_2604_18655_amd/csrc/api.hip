@@ -86,25 +86,29 @@ int kch_of(const mlora_w4_proj &p, int M, bool wide)
 int plan_rows(int M, bool a8) { return a8 && M < WIDE32_MIN_ROWS ? WIDE32_MIN_ROWS : M; }
 
 // K units per column tile.  Tile blocks: units of at most 2048 inputs (16 super-steps: what a
-// block stages of x).  Wide blocks: any unit length works; a wide launch of fewer than 200 base
+// block stages of x).  Wide blocks: any unit length works; a wide launch of fewer than 210 base
 // blocks (`launch_blocks`, counted with units of 2048 inputs) has units of about 1024, which fills
 // more compute units.  Measured in us, units of 2048 against 1024 inputs: 4096 x 4096 at 64 rows (64
 // blocks) 24.8 -> 18.0, 2048 x 8192 at 96 rows (96) 22.2 -> 17.2, 2048 x 2048 at 512 rows (128) 24.2
-// -> 19.1; above the line the partial tiles and the shorter loops cost more than they bring: a whole
-// layer at 64 rows (232) 27.2 -> 28.8, 14336 x 4096 with 32 adapters of rank 64 (224) 41 -> 61.
+// -> 19.1, int8 rows, 2048 x 2048 at 8 rows (8) 21.1 -> 15.3.  Over drawn calls of 200 to 209 blocks
+// units of 1024 take 0.92 of the time; of 210 to 220 and of 221 to 240 blocks as many calls lose by them as
+// gain: the partial tiles and the shorter loops cost what they bring.  Units of 512, int8 rows, 8 rows:
+// 2048 x 2048 15.3 -> 14.7, 8192 x 2048 20.5 -> 23.2, in groups of 128 14.0 -> 14.5 and 20.5 -> 23.2.
 int ksplit_of(const mlora_w4_proj &p, bool wide, int launch_blocks)
 {
     const int nss = p.K / SUPER_K;
     int ks = (nss + UNIT_SUPER_STEPS - 1) / UNIT_SUPER_STEPS;
-    if (wide && launch_blocks > 0 && launch_blocks < 200) {
+    if (wide && launch_blocks > 0 && launch_blocks < 210) {
         constexpr int unit = 8;
         const int cut = (nss + unit / 2) / unit;
         if (cut > ks) ks = cut;
     }
     return ks;
 }
-// Upper bound of that for every launch, which sizes a workspace: a launch of up to 240 base blocks
-// with chunks of 64 rows may take units of 1024 inputs, one of fewer than 80 units of 512.
+// Upper bound of that for every launch, which sizes a workspace and decides what is refused: units of
+// 1024 inputs up to 240 base blocks (counted with chunks of 64 rows), of 512 below 80.  No launch cuts its
+// inputs that fine; the sizes handed out and asked for stay what they have been, so that callers who
+// keep a size or a workspace need not care.
 int ksplit_bound(const mlora_w4_proj &p, bool wide, int launch_blocks64)
 {
     const int nss = p.K / SUPER_K;
@@ -210,7 +214,7 @@ static int launch_run(const mlora_w4_proj *projs, int n_left, int M)
 struct LaunchNeed {
     size_t ctrl_bytes, data_bytes;     // of this launch
     size_t ctrl_bound, data_bound;     // what a workspace is sized for (never less)
-    int grid_x, groups, rpc;
+    int grid_x, groups, rpc, block_rows;
 };
 
 static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *xs, void *const *ys,
@@ -219,10 +223,10 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
 {
     const bool wide = launch_is_wide(projs, count, M, a8);
     const int lb_chunk = launch_blocks_of(projs, count, M, wide, rows_per_chunk(M));
-    // Wide blocks above 32 rows: unless the launch is long, a chunk of 64 rows is worked through by
-    // two blocks of 32 rows each, see WIDE64_MIN_BLOCKS.
-    const bool halves = wide && M > 32 && lb_chunk < WIDE64_MIN_BLOCKS;
-    const int lb = halves ? launch_blocks_of(projs, count, M, wide, 32) : lb_chunk;
+    // Wide blocks above 32 rows: blocks of 64 rows, or two of 32 rows per chunk, see WIDE64_MIN_BLOCKS
+    const int lb_half = wide && M > 32 ? launch_blocks_of(projs, count, M, wide, 32) : lb_chunk;
+    const bool halves = wide && M > 32 && !wide64_pays(lb_chunk, lb_half);
+    const int lb = halves ? lb_half : lb_chunk;
     // A short launch of tile blocks at 17 to 32 rows (a few projections: the calls of a decoder
     // layer taken one after another) is a chain of latencies, not a stream: it runs as two chunks
     // of 16 rows on the kernel for up to 16 rows, with a shrink block per row, which reads the
@@ -235,6 +239,18 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
     const int block_rows = halves ? 32 : rpc;
     const int row_blocks = halves ? (M + 31) / 32 : chunks;    // blocks along the rows
     const int groups = (count + GROUP_PROJ - 1) / GROUP_PROJ;
+    const int shrink_chunks = (M + SHRINK_CHUNK_ROWS - 1) / SHRINK_CHUNK_ROWS;
+    bool fine = M > 32 && M < 2 * SHRINK_CHUNK_ROWS;       // one tile per wave in the grouped shrink blocks
+    if (fine) {
+        long long live = 0;
+        for (int i = 0; i < count; ++i) {
+            const mlora_w4_proj &p = projs[i];
+            live += (long long)((tiles_n(p.N) + tiles_per_block(wide) - 1) / tiles_per_block(wide)) * row_blocks * ksplit_of(p, wide, lb);
+            if (lora_on && p.n_adapters > 0)
+                live += (long long)shrink_chunks * shrink_tile_shares(M, p.n_adapters, true) * (r16_of(p) / 16) * kch_of(p, M, wide);
+        }
+        fine = live <= SHRINK_FINE_MAX_BLOCKS;
+    }
     bool shared = false;                       // anything handed from block to block?
     size_t part_lines = 0, data_bytes = 0, bound_lines = 0, data_bound = 0;
     int part_ctr = count * CTR_REPL * CTR_STRIDE;
@@ -265,7 +281,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
             const int kch = chunk16 && kch_of(p, Mc, wide) > 4 ? 4 : kch_of(p, Mc, wide);
             const size_t t_bytes = lora ? round_up((size_t)kch * (size_t)M * (size_t)r16_of(p) * sizeof(float), 256) : 0;
             const int n_shrink = !lora ? 0
-                : (Mc <= 16 && !wide ? M : (M + SHRINK_CHUNK_ROWS - 1) / SHRINK_CHUNK_ROWS * shrink_tile_shares(M, p.n_adapters)) *
+                : (Mc <= 16 && !wide ? M : shrink_chunks * shrink_tile_shares(M, p.n_adapters, fine)) *
                       (r16_of(p) / 16) * kch;
             if (a) {
                 ProjArgs &d = a->p[i];
@@ -338,12 +354,14 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
     need.grid_x = grid_x;
     need.groups = groups;
     need.rpc = rpc;
+    need.block_rows = block_rows;
     if (a) {
         a->ctrl = reinterpret_cast<unsigned *>(ctrl);
         a->wide = wide;
         a->block_rows = block_rows;
         a->row_blocks = row_blocks;
         a->half_shift = halves ? 1 : 0;
+        a->shrink_fine = fine;
         a->m_pad = m_pad;
         if (chunk16) a->M_plan = 16;
     }
@@ -414,6 +432,18 @@ mlora_status mlora_w4_layer_step_plan(const mlora_w4_proj *projs, int32_t n_proj
     }
     info[0] = launches;
     return MLORA_OK;
+}
+
+int32_t mlora_w4_layer_step_block_rows(const mlora_w4_proj *projs, int32_t n_proj, int32_t M, int32_t int8_rows)
+{
+    if (!projs || n_proj <= 0 || M <= 0 || M > MLORA_MAX_ROWS) return 0;
+    for (int i = 0; i < n_proj; ++i)
+        if (check_weight_shape(projs[i].K, projs[i].N, projs[i].group) != MLORA_OK) return 0;
+    const int Mp = plan_rows(M, int8_rows != 0);
+    LaunchNeed need;
+    const int count = launch_run(projs, n_proj, Mp);
+    if (plan_launch(projs, nullptr, nullptr, count, Mp, int8_rows != 0, true, need, nullptr, nullptr, nullptr) != MLORA_OK) return 0;
+    return need.block_rows;
 }
 
 mlora_status mlora_w4_workspace_init(void *workspace, size_t workspace_bytes, void *stream)

@@ -148,6 +148,7 @@ struct LayerArgs {
                                // that calls with int8 activations always run wide blocks and are
                                // laid out as for at least 17 rows
     int a8;                    // x is int8 with one scale per tensor (ProjArgs::x_scale)
+    int shrink_fine;           // grouped shrink blocks: at most one tile per wave (see shrink_tile_shares)
     int fused;                 // outputs go through epi[] (one group of at most 16 projections)
     EpiArgs epi[GROUP_PROJ];
     int y_fp32;
@@ -204,9 +205,11 @@ __device__ inline f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
 // segment, at most a tile per row.  A block's four waves work through up to 16 tiles; a chunk
 // that can have more is shared out over several blocks.  Calls of 33 to 127 rows have at most two
 // chunks and base blocks that are done early: there the finishing blocks wait for t, so a wave
-// gets at most one tile (measured: c5 68 -> 60 us; at 128 rows and more the extra, mostly idle
-// blocks cost more than they gain).  Host (grid size) and device (block index -> chunk, share)
-// use the same figures.
+// gets at most one tile as long as base blocks and these more, mostly idle shrink blocks all find a
+// place at once (SHRINK_FINE_MAX_BLOCKS; 32 adapters of rank 64, us, one tile against four: 4096 x 14336
+// at 64 rows (368 blocks) 34 against 40, at 100 rows (736) 76 against 68; 14336 x 4096 at 64 rows (476)
+// 46 against 50, at 100 rows (952) 89 against 77).  Host (grid size) and device (block index -> chunk,
+// share) use the same figures.
 constexpr int SHRINK_CHUNK_ROWS = 64;
 __host__ __device__ inline int max_row_tiles(int rows, int n_adapters)
 {
@@ -214,10 +217,11 @@ __host__ __device__ inline int max_row_tiles(int rows, int n_adapters)
     const int bound = rows / 16 + segs;
     return bound < rows ? bound : rows;
 }
-__host__ __device__ inline int shrink_tile_shares(int M, int n_adapters)
+constexpr int SHRINK_FINE_MAX_BLOCKS = 500;
+__host__ __device__ inline int shrink_tile_shares(int M, int n_adapters, bool fine)
 {
     const int tiles = max_row_tiles(M < SHRINK_CHUNK_ROWS ? M : SHRINK_CHUNK_ROWS, n_adapters);
-    return (M > 32 && M < 2 * SHRINK_CHUNK_ROWS) ? (tiles + 3) / 4 : (tiles + 15) / 16;
+    return fine ? (tiles + 3) / 4 : (tiles + 15) / 16;
 }
 
 // host launchers (each file defines its own)
@@ -245,11 +249,15 @@ constexpr int WIDE32_MIN_ROWS = 17;
 constexpr int WIDE32_MIN_BLOCKS = 300;
 // From 33 rows on a chunk of 64 rows is the unit of the workspace's layout.  Blocks of 64 rows unpack a
 // weight once for twice the rows, but two of them fill a compute unit's registers where three of 32
-// rows fit, and their latencies are longer; they pay in a launch of several rounds of blocks only.
-// Measured in us, blocks of 64 rows against 32: 16 layers of a 1B-like model at 512 rows (14848
-// blocks of 64 rows) 1684 -> 1813; one such layer at 512 rows (928) 137 -> 137, at 128 rows (232) 65 ->
-// 41, at 64 rows (116) 45 -> 28; 4096 x 4096 at 64 rows (32) 37 -> 18.
-constexpr int WIDE64_MIN_BLOCKS = 2048;
+// rows fit, and their latencies are longer; they pay where the launch has more than about one of them
+// per compute unit, and where the rows fill them: with rows a little above a multiple of 64, blocks of 32
+// rows waste half as many (lines drawn from 2592 calls of 33 to 1024 rows, ranks 8 to 128, 1 to 32 adapters).
+// Measured in us, blocks of 64 rows against 32, groups of 32 / of 128 inputs: 16 layers of a 1B-like
+// model at 512 rows (14848 blocks of 64 rows) 1519 against 1679 / 1348 against 1483; one such layer at 512
+// rows (928) 116 against 123 / 95 against 100, at 128 rows (232) 41 against 38 / 34 against 33; 3072 x 9216
+// twice at 72 rows (288 of 64, 432 of 32) 36 against 25.
+constexpr int WIDE64_MIN_BLOCKS = 320;
+__host__ inline bool wide64_pays(int blocks64, int blocks32) { return blocks64 >= WIDE64_MIN_BLOCKS && 5ll * blocks32 >= 9ll * blocks64; }
 constexpr int WIDE_TILES_PER_BLOCK = 4;
 constexpr int CHUNK16_MAX_BLOCKS = 300;    // tile launches of 17 to 32 rows below this run chunks of 16 rows
 __host__ inline int rows_per_chunk(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : 64; }

@@ -1117,7 +1117,7 @@ __device__ __forceinline__ void shrink_block(const LayerArgs &a, const ProjArgs 
     constexpr int SB = L::SB;
     GroupLds64 &g = lds.g;
     const int jblocks = P.r16 / 16;
-    const int shares = shrink_tile_shares(a.M_plan, P.n_adapters);
+    const int shares = shrink_tile_shares(a.M_plan, P.n_adapters, a.shrink_fine != 0);
     const int kc = local % P.kch;
     const int jb = (local / P.kch) % jblocks;
     const int share = (local / (P.kch * jblocks)) % shares;
@@ -1669,7 +1669,7 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
 
 // group = index of the block's four tiles among the projection's; ku as in base_unit.  SPG =
 // k-steps per scale group, the same for every projection of the launch; MB = blocks of 16 rows
-// per base block (4 in long launches, else 2); AGAIN = other blocks of rows read the same codes.
+// per base block (4 where wide64_pays, else 2); AGAIN = other blocks of rows read the same codes.
 template <int SPG, int MB, bool A8, bool AGAIN>
 __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P, int pi, int group, int ku,
                                           int m0, WideLds<MB> &lds)

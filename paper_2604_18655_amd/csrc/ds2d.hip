@@ -83,8 +83,8 @@ __device__ inline unsigned long long wave_max(unsigned long long v)
     return v;
 }
 
-// element j of a 16-byte vector of logits: the bit pattern as a signed number.  Among positive numbers
-// it orders like the logit, and it is negative where the logit is.
+// element j of a 16-byte vector of logits: the bit pattern as a signed number (among positive numbers it
+// orders like the logit, and it is negative where the logit is), or what ordered() made of it.
 template <bool FP32>
 __device__ __forceinline__ int element(const u32x4 &q, int j)
 {
@@ -108,8 +108,40 @@ __device__ __forceinline__ int vector_max(const u32x4 &q)
     }
 }
 
-// Slices whose winners are not all above zero (and finite or infinite numbers): all elements by their
-// keys, the best one below the last winner's per round.
+// Bit patterns -> signed numbers that order like all logits: sign and magnitude become a two's
+// complement, which makes one of +0 and -0, and a shift that wraps around puts NaN below -inf.
+template <bool FP32>
+struct Order {
+    static constexpr int SHIFT = FP32 ? 0x7FFFFF : 0x7F;                // +inf + SHIFT is the largest number
+    static constexpr int LEAST = FP32 ? -0x7F000001 : -0x7F01;          // -inf + SHIFT; what lies below is NaN
+    static __device__ __forceinline__ unsigned bits(int ordered)        // back again (of a number)
+    {
+        const int v = ordered - SHIFT;
+        return v < 0 ? (FP32 ? 0x80000000u : 0x8000u) | (unsigned)-v : (unsigned)v;
+    }
+};
+template <bool FP32>
+__device__ __forceinline__ u32x4 ordered(u32x4 q)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const unsigned w = q[i];
+        if constexpr (FP32) {
+            const unsigned s = (unsigned)((int)w >> 31);
+            q[i] = ((w & 0x7FFFFFFFu) ^ s) - s + (unsigned)Order<true>::SHIFT;
+        } else {
+            typedef short s16x2 __attribute__((ext_vector_type(2)));
+            typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+            const u16x2 s = __builtin_bit_cast(u16x2, __builtin_bit_cast(s16x2, w) >> (short)15);
+            const u16x2 a = __builtin_bit_cast(u16x2, w & 0x7FFF7FFFu);
+            q[i] = __builtin_bit_cast(unsigned, (u16x2)((a ^ s) - s + (unsigned short)Order<false>::SHIFT));
+        }
+    }
+    return q;
+}
+
+// Slices with fewer numbers than winners wanted (short ones, NaN): all elements by their keys, the best
+// one below the last winner's per round.
 // (Reads the slice again every round: what matters here is that the common path keeps its registers.)
 template <bool FP32>
 __device__ __forceinline__ void slice_by_keys(const Ds2dArgs &a, long long slice_first, int pos_lo, int pos_hi, unsigned token_lo, int k,
@@ -134,11 +166,12 @@ __device__ __forceinline__ void slice_by_keys(const Ds2dArgs &a, long long slice
 
 // What bounds it: reading the logits once.  A wavefront owns a slice and needs no barrier: 16-byte
 // loads, eight (bf16) in flight per lane, a packed maximum per vector, and only one vector per lane and
-// round is looked at element by element.  That works on bit patterns as signed numbers, so it holds
-// for winners above zero; a slice whose next best logit is zero, negative, NaN or missing goes to
-// slice_by_keys.  240 rows of 128256 bf16 logits (61.6 MB): a block per slice with keys for all
-// elements 25.3 us, this 15.3 us (4.0 TB/s).  Four wavefronts per SIMD: the registers for eight spill
-// (35 us).
+// round is looked at element by element.  That works on bit patterns as signed numbers, as long as the
+// winners lie above zero; a slice whose next best logit does not is put in order in its registers
+// (four packed operations per two logits) and starts again.  240 rows of 128256 bf16 logits (61.6 MB): a
+// block per slice with keys for all elements 25.3 us, this 15.3 us (4.0 TB/s); the whole step 20.7
+// us, on the same logits less 50, all negative, 25.4 (31.2 with keys for all, 63 with rounds over memory).  Four wavefronts per SIMD: the registers for
+// eight spill (35 us).
 template <bool FP32>
 __global__ __launch_bounds__(DS_THREADS, 4) void ds2d_best_partial(const Ds2dArgs a)
 {
@@ -189,54 +222,62 @@ __global__ __launch_bounds__(DS_THREADS, 4) void ds2d_best_partial(const Ds2dArg
         }
         return m;
     };
-    int vm[VPT], best = LOWEST;
     const bool whole = pos_lo == 0 && pos_hi == DS_SLICE;
+    // the k winners in turn; false if they run out (two copies of the code: the first one, which nearly all
+    // slices take, has no choices to make)
+    auto take = [&](auto order) {
+        constexpr bool in_order = decltype(order)::value;
+        int vm[VPT], best = LOWEST;
 #pragma unroll
-    for (int u = 0; u < VPT; ++u) {
-        vm[u] = whole ? vector_max<FP32>(q[u]) : rest_max(q[u], (u * 64 + lane) * EPV, 0x7FFFFFFF, DS_SLICE);
-        best = max(best, vm[u]);
-    }
-    int last_top = 0x7FFFFFFF, last_winner = -1;
-    for (int round = 0; round < k; ++round) {
-        const int top = wave_max_i32(best);
-        if (top <= 0 || top > (FP32 ? 0x7F800000 : 0x7F80)) {           // (uniform)
-            slice_by_keys<FP32>(a, slice_first, pos_lo, pos_hi, token_lo, k, out, lane);
-            return;
+        for (int u = 0; u < VPT; ++u) {
+            vm[u] = whole ? vector_max<FP32>(q[u]) : rest_max(q[u], (u * 64 + lane) * EPV, 0x7FFFFFFF, -1);
+            best = max(best, vm[u]);
         }
-        // lowest position that holds it: the first vector of a lane that does (a lane's vectors are in the
-        // order of positions), then the first element that has not been a winner before
-        // (every lane does it, with its own first vector that reaches its maximum: branches would cost more)
-        int pos = DS_SLICE, at = 0;
-        u32x4 v = q[0];
+        int last_top = 0x7FFFFFFF, last_winner = -1;
+        for (int round = 0; round < k; ++round) {
+            const int top = wave_max_i32(best);
+            if (in_order ? top < Order<FP32>::LEAST : top <= 0 || top > (FP32 ? 0x7F800000 : 0x7F80)) return false;   // (uniform)
+            // lowest position that holds it: the first vector of a lane that does (a lane's vectors are in the
+            // order of positions), then the first element that has not been a winner before
+            // (every lane does it, with its own first vector that reaches its maximum: branches would cost more)
+            int pos = DS_SLICE, at = 0;
+            u32x4 v = q[0];
 #pragma unroll
-        for (int u = VPT - 1; u >= 1; --u) at = vm[u] == best ? u : at;
-        at = vm[0] == best ? 0 : at;
+            for (int u = VPT - 1; u >= 1; --u) at = vm[u] == best ? u : at;
+            at = vm[0] == best ? 0 : at;
 #pragma unroll
-        for (int u = 1; u < VPT; ++u)
+            for (int u = 1; u < VPT; ++u)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = at == u ? q[u][e] : v[e];
-        const int base = (at * 64 + lane) * EPV, from = top == last_top ? max(pos_lo, last_winner + 1) : pos_lo;
+                for (int e = 0; e < 4; ++e) v[e] = at == u ? q[u][e] : v[e];
+            const int base = (at * 64 + lane) * EPV, from = top == last_top ? max(pos_lo, last_winner + 1) : pos_lo;
 #pragma unroll
-        for (int j = EPV - 1; j >= 0; --j)
-            if (element<FP32>(v, j) == top && base + j >= from && base + j < pos_hi) pos = base + j;
-        const int winner = -wave_max_i32(-pos);
-        if (lane == 0) {
-            const unsigned bits = FP32 ? (unsigned)top : (unsigned)top << 16;
-            out[round] = key_of(__uint_as_float(bits), (unsigned)(winner - pos_lo) + token_lo);
-        }
-        if (round + 1 < k) {                                            // the winner's lane: its next best
-            const int rest = rest_max(v, base, top, winner);
-            const bool mine = pos == winner;
-            best = LOWEST;
-#pragma unroll
-            for (int u = 0; u < VPT; ++u) {
-                vm[u] = mine && at == u ? rest : vm[u];
-                best = max(best, vm[u]);
+            for (int j = EPV - 1; j >= 0; --j)
+                if (element<FP32>(v, j) == top && base + j >= from && base + j < pos_hi) pos = base + j;
+            const int winner = -wave_max_i32(-pos);
+            if (lane == 0) {
+                const unsigned bits = in_order ? Order<FP32>::bits(top) : (unsigned)top;
+                out[round] = key_of(__uint_as_float(FP32 ? bits : bits << 16), (unsigned)(winner - pos_lo) + token_lo);
             }
+            if (round + 1 < k) {                                        // the winner's lane: its next best
+                const int rest = rest_max(v, base, top, winner);
+                const bool mine = pos == winner;
+                best = LOWEST;
+#pragma unroll
+                for (int u = 0; u < VPT; ++u) {
+                    vm[u] = mine && at == u ? rest : vm[u];
+                    best = max(best, vm[u]);
+                }
+            }
+            last_top = top;
+            last_winner = winner;
         }
-        last_top = top;
-        last_winner = winner;
-    }
+        return true;
+    };
+    if (__builtin_expect(take(std::false_type{}), 1)) return;
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) q[u] = ordered<FP32>(q[u]);
+    if (take(std::true_type{})) return;
+    slice_by_keys<FP32>(a, slice_first, pos_lo, pos_hi, token_lo, k, out, lane);
 }
 
 // One block per stream: a chain of latencies, kept short.  Sixteen lanes reduce a token row's slices

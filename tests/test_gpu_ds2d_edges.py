@@ -30,6 +30,64 @@ def test_few_values_and_slice_edges(gpu, V, bf16):
     check(gpu, S, m, branch, nxt, V, logits, tokens, bf16)
 
 
+@pytest.mark.parametrize("bf16", [True, False])
+@pytest.mark.parametrize("V", [1200, 4099, 9000])
+def test_logits_not_above_zero(gpu, V, bf16):
+    """Winners of either sign, zeros of both signs, infinities and NaN: every order a slice can be taken in."""
+    S, m, branch, nxt = 4, 2, (2,), (10, 1)
+    rng = np.random.default_rng(V)
+    _, tokens = make_ds2d_inputs(V, S, branch, m, V, True)
+    R = 3 * 3
+    logits = (rng.standard_normal((S * R, V)) - 50.0).astype(np.float32)                   # all negative
+    logits[1] = -np.inf
+    logits[1, 700:703] = -1e30
+    logits[2, :] = np.where(rng.random(V) < 0.5, np.float32(-0.0), np.float32(0.0))        # only zeros
+    logits[R:2 * R] = np.where(rng.random((R, V)) < 0.997, -np.abs(logits[R:2 * R]), 3.0)  # a few above zero
+    logits[R, ::3] = 0.0
+    logits[R + 4, 5::7] = -0.0
+    logits[R + 5, :] = -0.0
+    logits[R + 5, 11] = 0.0
+    logits[2 * R:3 * R, 1::2] = np.nan                                                     # every other one
+    logits[2 * R + 3, :] = np.nan
+    logits[2 * R + 4, 5:] = -np.nan
+    logits[2 * R + 5, 9:] = -np.inf
+    logits[3 * R:] = rng.choice(np.array([-2.0, -1.0, -np.inf, np.inf, -0.0, 0.0], np.float32), size=(R, V))
+    if bf16:
+        nan = np.isnan(logits)
+        sign = np.signbit(logits)
+        logits = f32_to_bf16_bits(np.where(nan, np.float32(0.0), logits))
+        logits[nan & ~sign] = 0x7FC1
+        logits[nan & sign] = 0xFFFF
+    check(gpu, S, m, branch, nxt, V, logits, tokens, bf16)
+
+
+def test_time_does_not_depend_on_the_logits_sign(gpu):
+    """A soft-max does not care about a shift, nor may the step's time (three times as long where a slice
+    without winners above zero was read again per winner; 1.6 leaves room for a noisy box)."""
+    lib, device, torch = gpu
+    S, m, branch, V = 8, 2, (3, 2), 128256
+    step = lib.Ds2dStep(S, m, list(branch), list(branch), V, lib.Y_BF16)
+    logits = torch.randn((S * 30, V), generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+    tokens = torch.zeros((S, 10), dtype=torch.int32, device="cuda")
+    out = [torch.zeros(n, dtype=torch.int32, device="cuda") for n in ((S,), (S, m + 1), (S, m + 1), (S, 10))]
+    ws = torch.empty(step.workspace_bytes(), dtype=torch.uint8, device="cuda")
+    times = []
+    for shift in (0.0, -50.0):
+        rows = (logits + shift).to(torch.bfloat16)
+        best = float("inf")
+        for _ in range(30):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            begin.record()
+            for _ in range(10):
+                step.run(rows, tokens, *out, ws)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, begin.elapsed_time(end))
+        times.append(best)
+    assert times[1] <= 1.6 * times[0], times
+
+
 @pytest.mark.parametrize("V,S,branch,nxt,m", [
     (128256, 1, (15,), (16,), 1),       # candidates of all nodes do not fit the block, those of one do
     (540000, 1, (1,), (16,), 1),        # one level of one node does not fit either

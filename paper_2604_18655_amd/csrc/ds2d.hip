@@ -282,9 +282,15 @@ __global__ __launch_bounds__(DS_THREADS, 4) void ds2d_best_partial(const Ds2dArg
 
 // One block per stream: a chain of latencies, kept short.  Sixteen lanes reduce a token row's slices
 // without atomics; the walk is a ballot per level; the best candidates of a level are ranked by
-// counting, without rounds.  8 streams of 30 rows over 128256 logits: 7.6 -> 6.8 us, of which about half
-// are the launch and two dependent trips to memory.
+// counting, without rounds; many of them in two steps: the best of every slice, then the lists of the slices
+// that have the b' best of those (the others hold no winner), at most 16 x 16 keys.
+// 8 streams of 30 rows over 128256 logits: 7.6 -> 6.8 us, of which about half are the launch and two
+// dependent trips to memory.
 constexpr int DS_POOL = 2048;                          // candidate keys held in LDS
+// Up to this many candidates of a level all are ranked among all: one barrier less and no lists to look up.
+// 4 streams, in us, all against the best of the slices first: 9 slices x 16 20.4 against 23.5, 33 x 4 11.4
+// and 11.5, 33 x 8 16.3 and 16.0, 65 x 4 18.6 and 13.2, 33 x 16 32.9 and 27.0, 129 x 16 217 and 39.7.
+constexpr int DS_COUNT_ALL = 160;
 __device__ __forceinline__ unsigned long long row16_max(unsigned long long v)
 {
     auto step = [&](auto n) {
@@ -304,6 +310,7 @@ __global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a
     __shared__ unsigned long long pool[DS_POOL];
     __shared__ int walk_end, walk_token;
     __shared__ int cand[MLORA_DS2D_MAX_FORECAST][DS_KMAX];
+    __shared__ int lists[MLORA_DS2D_MAX_FORECAST][DS_KMAX];    // slices whose best is among the b' best of all
     const int s = blockIdx.x, tid = threadIdx.x;
     const unsigned long long *base = a.partial + (size_t)s * a.R * a.slices * DS_KMAX;
 
@@ -358,13 +365,16 @@ __global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a
     if (tid == 0) nt[0] = walk_token;
 
     // Level i of the next tree: the b'_i best of forecast embedding i of the node `cur`, by rank: a
-    // candidate with r better ones is number r (keys differ).  Thread t looks at candidate t % 16 of
-    // slices t / 16, t / 16 + 16, ...  Common case: the candidates of all levels fit the pool and are
-    // requested at once.
+    // candidate with r better ones is number r (keys differ).  Common case: the candidates of all levels
+    // fit the pool and are requested at once, candidate t % 16 of slices t / 16, t / 16 + 16, ... by thread t.
     const unsigned long long *rows_of_cur = base + (size_t)(a.T + cur * a.m) * a.slices * DS_KMAX;
     const int r16 = tid & 15, s16 = tid >> 4;
-    int total = 0;
-    for (int i = 0; i < a.next_depth; ++i) total += a.slices * a.next_branch[i];
+    int total = 0, most = 0;
+    for (int i = 0; i < a.next_depth; ++i) {
+        total += a.slices * a.next_branch[i];
+        most = max(most, a.slices * a.next_branch[i]);
+    }
+    if (most > DS_COUNT_ALL && tid < MLORA_DS2D_MAX_FORECAST * DS_KMAX) lists[tid / DS_KMAX][tid % DS_KMAX] = -1;
     if (total <= DS_POOL) {
         int at = 0;
         for (int i = 0; i < a.next_depth; ++i) {
@@ -376,29 +386,61 @@ __global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a
         }
         __syncthreads();
         at = 0;
-        for (int i = 0; i < a.next_depth; ++i) {
-            const int b = a.next_branch[i], n_cand = a.slices * b;
-            const unsigned long long *list = pool + at;
-            for (int c = tid; c < n_cand; c += DS_THREADS) {
-                const unsigned long long key = list[c];
-                int better = 0;
+        if (most <= DS_COUNT_ALL) {
+            for (int i = 0; i < a.next_depth; ++i) {
+                const int b = a.next_branch[i], n_cand = a.slices * b;
+                const unsigned long long *list = pool + at;
+                if (tid < n_cand) {
+                    const unsigned long long key = list[tid];
+                    int better = 0;
 #pragma unroll 8
-                for (int o = 0; o < n_cand; ++o) better += list[o] > key ? 1 : 0;
-                if (key && better < b) cand[i][better] = (int)(~(unsigned)(key & 0xFFFFFFFFull));
+                    for (int o = 0; o < n_cand; ++o) better += list[o] > key ? 1 : 0;
+                    if (key && better < b) cand[i][better] = (int)(~(unsigned)(key & 0xFFFFFFFFull));
+                }
+                at += n_cand;
             }
-            at += n_cand;
+        } else {
+            for (int i = 0; i < a.next_depth; ++i) {
+                const int b = a.next_branch[i];
+                const unsigned long long *heads = pool + at;
+                for (int c = tid; c < a.slices; c += DS_THREADS) {
+                    const unsigned long long key = heads[c * b];
+                    int better = 0;
+#pragma unroll 8
+                    for (int o = 0; o < a.slices; ++o) better += heads[o * b] > key ? 1 : 0;
+                    if (key && better < b) lists[i][better] = c;
+                }
+                at += a.slices * b;
+            }
+            __syncthreads();
+            at = 0;
+            for (int i = 0; i < a.next_depth; ++i) {
+                const int b = a.next_branch[i];
+                const unsigned long long *all = pool + at;
+                if (tid < b * b && lists[i][tid / b] >= 0) {
+                    int better = 0;
+                    const unsigned long long key = all[lists[i][tid / b] * b + tid % b];
+                    for (int l = 0; l < b && lists[i][l] >= 0; ++l) {
+                        const unsigned long long *list = all + lists[i][l] * b;
+#pragma unroll 4
+                        for (int o = 0; o < b; ++o) better += list[o] > key ? 1 : 0;
+                    }
+                    if (key && better < b) cand[i][better] = (int)(~(unsigned)(key & 0xFFFFFFFFull));
+                }
+                at += a.slices * b;
+            }
         }
     } else {
-        // a level's candidates in pieces of whole slices, the best so far at the front of the pool
+        // the best of a level's slices in pieces, the b' best so far at the front of the pool
+        const int epv = a.fp32 ? 4 : 8;
         for (int i = 0; i < a.next_depth; ++i) {
             const int b = a.next_branch[i];
             const unsigned long long *p = rows_of_cur + (size_t)i * a.slices * DS_KMAX;
             int kept = 0;
             for (int c0 = 0; c0 < a.slices;) {
-                const int n_slices = min(a.slices - c0, (DS_POOL - kept) / b), n = kept + n_slices * b;
+                const int n_new = min(a.slices - c0, DS_POOL - kept), n = kept + n_new;
                 __syncthreads();
-                if (r16 < b)
-                    for (int c = s16; c < n_slices; c += 16) pool[kept + c * b + r16] = p[(size_t)(c0 + c) * DS_KMAX + r16];
+                for (int c = tid; c < n_new; c += DS_THREADS) pool[kept + c] = p[(size_t)(c0 + c) * DS_KMAX];
                 __syncthreads();
                 constexpr int OWN = DS_POOL / DS_THREADS;
                 unsigned long long own[OWN];
@@ -421,10 +463,24 @@ __global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a
                 for (int u = 0; u < OWN; ++u)
                     if (own[u] && rank[u] < b) pool[rank[u]] = own[u];
                 kept = b;
-                c0 += n_slices;
+                c0 += n_new;
             }
             __syncthreads();
-            if (tid < b) cand[i][tid] = (int)(~(unsigned)(pool[tid] & 0xFFFFFFFFull));
+            // their lists (a token's slice follows from its id: slices are counted from the vector of 16
+            // bytes that the row starts in), then the candidates' ranks
+            const long long first = ((long long)s * a.R + a.T + cur * a.m + i) * a.V;
+            unsigned long long key = 0ull;
+            if (tid < b * b) {
+                const unsigned long long head = pool[tid / b];
+                const int slice = (int)(((unsigned)(first % epv) + ~(unsigned)(head & 0xFFFFFFFFull)) / DS_SLICE);
+                if (head) key = p[(size_t)slice * DS_KMAX + tid % b];
+            }
+            __syncthreads();
+            if (tid < b * b) pool[tid] = key;
+            __syncthreads();
+            int better = 0;
+            for (int o = 0; o < b * b; ++o) better += pool[o] > key ? 1 : 0;
+            if (key && better < b) cand[i][better] = (int)(~(unsigned)(key & 0xFFFFFFFFull));
         }
     }
     __syncthreads();

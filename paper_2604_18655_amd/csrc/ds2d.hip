@@ -198,17 +198,30 @@ __global__ __launch_bounds__(DS_THREADS, 4) void ds2d_best_partial(const Ds2dArg
         if (lane < k) out[lane] = 0ull;
         return;
     }
-    // (a slice with the last, partial vector of the array: element by element)
-    if (pos_hi > (full_vectors - vec0) * EPV) {
+    if (__builtin_expect(pos_hi - pos_lo <= 64, 0)) {                   // (the last few logits of a row: one per lane)
         slice_by_keys<FP32>(a, slice_first, pos_lo, pos_hi, token_lo, k, out, lane);
         return;
     }
     u32x4 q[VPT];
 #pragma unroll
     for (int u = 0; u < VPT; ++u) {
-        // (vectors past the array: re-reads of its last one, outside the row)
+        // (vectors past the array: re-reads of its last whole one, outside the row; there is one)
         const long long vi = min(vec0 + u * 64 + lane, full_vectors - 1);
         q[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.logits) + vi);
+    }
+    if (__builtin_expect(pos_hi > (full_vectors - vec0) * EPV, 0)) {
+        // the slice with the last, partial vector of the array: that one element by element, zeros past its end
+        u32x4 last_vector = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int j = 0; j < EPV; ++j) {
+            const long long e = full_vectors * EPV + j;
+            if (e >= a.total) continue;
+            if constexpr (FP32) last_vector[j] = reinterpret_cast<const unsigned *>(a.logits)[e];
+            else last_vector[j >> 1] |= (unsigned)reinterpret_cast<const unsigned short *>(a.logits)[e] << (16 * (j & 1));
+        }
+#pragma unroll
+        for (int u = 0; u < VPT; ++u)
+            if (vec0 + u * 64 + lane == full_vectors) q[u] = last_vector;
     }
     constexpr int LOWEST = FP32 ? (int)0x80000000 : -32768;             // below every positive number; never a winner
     // the largest element of a vector (its first position: base) that lies in the row and comes after (top,

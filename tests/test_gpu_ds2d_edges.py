@@ -61,37 +61,54 @@ def test_logits_not_above_zero(gpu, V, bf16):
     check(gpu, S, m, branch, nxt, V, logits, tokens, bf16)
 
 
+def step_time(gpu, S, m, branch, nxt, V, shift):
+    """Best time of ten steps in a row, in ms."""
+    lib, device, torch = gpu
+    T, R = lib.ds2d_rows(branch, m)
+    step = lib.Ds2dStep(S, m, branch, nxt, V, lib.Y_BF16)
+    rows = (torch.randn((S * R, V), generator=torch.Generator("cuda").manual_seed(1), device="cuda") + shift).to(torch.bfloat16)
+    tokens = torch.zeros((S, T), dtype=torch.int32, device="cuda")
+    sizes = ((S,), (S, m + 1), (S, m + 1), (S, lib.ds2d_rows(nxt, m)[0]))
+    out = [torch.zeros(n, dtype=torch.int32, device="cuda") for n in sizes]
+    ws = torch.empty(step.workspace_bytes(), dtype=torch.uint8, device="cuda")
+    best = float("inf")
+    for _ in range(30):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda.synchronize()
+        begin.record()
+        for _ in range(10):
+            step.run(rows, tokens, *out, ws)
+        end.record()
+        torch.cuda.synchronize()
+        best = min(best, begin.elapsed_time(end))
+    return best
+
+
 def test_time_does_not_depend_on_the_logits_sign(gpu):
     """A soft-max does not care about a shift, nor may the step's time (three times as long where a slice
     without winners above zero was read again per winner; 1.6 leaves room for a noisy box)."""
-    lib, device, torch = gpu
-    S, m, branch, V = 8, 2, (3, 2), 128256
-    step = lib.Ds2dStep(S, m, list(branch), list(branch), V, lib.Y_BF16)
-    logits = torch.randn((S * 30, V), generator=torch.Generator("cuda").manual_seed(1), device="cuda")
-    tokens = torch.zeros((S, 10), dtype=torch.int32, device="cuda")
-    out = [torch.zeros(n, dtype=torch.int32, device="cuda") for n in ((S,), (S, m + 1), (S, m + 1), (S, 10))]
-    ws = torch.empty(step.workspace_bytes(), dtype=torch.uint8, device="cuda")
-    times = []
-    for shift in (0.0, -50.0):
-        rows = (logits + shift).to(torch.bfloat16)
-        best = float("inf")
-        for _ in range(30):
-            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            torch.cuda.synchronize()
-            begin.record()
-            for _ in range(10):
-                step.run(rows, tokens, *out, ws)
-            end.record()
-            torch.cuda.synchronize()
-            best = min(best, begin.elapsed_time(end))
-        times.append(best)
-    assert times[1] <= 1.6 * times[0], times
+    args = (gpu, 8, 2, (3, 2), (3, 2), 128256)
+    assert step_time(*args, -50.0) <= 1.6 * step_time(*args, 0.0)
+
+
+def test_time_does_not_depend_on_the_last_vector(gpu):
+    """Rows that end inside a vector of 16 bytes (2.6 times as long where the array's last slice was read
+    element by element once per winner)."""
+    args = (gpu, 1, 1, (1,), (16,))
+    assert step_time(*args, 32001, 0.0) <= 1.6 * step_time(*args, 32000, 0.0)
 
 
 @pytest.mark.parametrize("V,S,branch,nxt,m", [
     (128256, 1, (15,), (16,), 1),       # candidates of all nodes do not fit the block, those of one do
     (540000, 1, (1,), (16,), 1),        # one level of one node does not fit either
     (540001, 2, (1,), (9, 1), 2),       # rows at odd offsets, a second level after a long one
+    (262144, 3, (1,), (4, 2), 2),       # candidates just above those that are all ranked at once
+    (66000, 1, (1,), (16,), 1),         # one slice more than winners
+    (61435, 1, (2,), (16,), 1),         # a last slice of few logits
+    (32001, 1, (1,), (16,), 1),         # the array ends inside a vector
+    (4163, 1, (1,), (8,), 1),           # a last slice of 66 or 67 logits, and that vector in it
+    (4099, 1, (1,), (16,), 1),
+    (5, 1, (), (5,), 1),                # less than two vectors in all
 ])
 def test_many_candidates(gpu, V, S, branch, nxt, m):
     logits, tokens = make_ds2d_inputs(V, S, branch, m, V, True, accept=0.5)

@@ -1475,6 +1475,7 @@ struct WideLds {
     static_assert(WIDE_TILES * OUT_BYTES <= 2 * X_STAGE, "the outputs fit the stages");
     alignas(16) unsigned char buf[2 * X_STAGE];
     alignas(16) unsigned char t[2 * T_HALF];
+    int waited_out;                                        // a wave gave up waiting for t: the block's share of it is not known
     __device__ float *out(int wave) { return reinterpret_cast<float *>(buf + wave * OUT_BYTES); }
 };
 
@@ -1714,6 +1715,8 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
     uint32_t bias = a.code_bias;
     asm volatile("" : "+v"(bias));
 
+    if (tid == 0) lds.waited_out = 0;                      // (ahead of the K loop's barriers)
+
     // t = alpha * sum over the K chunks of the shrink partials, in fixed order, as two bf16 halves
     // that make up its first 17 bits.  A thread takes four neighbouring ranks of one row (16
     // bytes of a partial sum); the requests of several quads and K chunks overlap.  A wave's share:
@@ -1900,17 +1903,24 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
         request(bfa, ra_);
     }
 
-    // (a wave whose wait runs out sets the status word and stores NaN in place of its outputs;
-    // a spare wave waits too: it gathers its share of t)
-    bool poisoned = false;
+    // (a wave whose wait runs out sets the status word, and the whole block, all of whose waves use the
+    // rows of t it gathers, stores NaN in place of its outputs or partial tiles; a spare wave waits
+    // too: it gathers its share of t)
     if (need_s && !have_t) {
-        if (!wait_count(sctr, (unsigned)P.n_shrink_blocks, a.spin_limit)) {
-            poisoned = true;
-            if (lane == 0) atomicOr(a.status, 1u);
+        if (!wait_count(sctr, (unsigned)P.n_shrink_blocks, a.spin_limit) && lane == 0) {
+            lds.waited_out = 1;
+            atomicOr(a.status, 1u);
         }
         gather_t();
     }
     __syncthreads();                                       // t is in place; every wave is done with the x buffers
+    bool poisoned = lds.waited_out != 0;
+    auto poison = [&]() {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = f32x16{0.f} + __uint_as_float(0x7FC00000u);
+    };
     if (lora) {                                            // (uniform over the block)
         if (tile_ok) {
             auto compute = [&](const u32x4 (&bf)[NB][2], const Round &r) {
@@ -1947,6 +1957,7 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
         }
     }
     if (ku > 0) {
+        if (poisoned) poison();
         // A partial tile (the chunk's rows x 64 columns) lies in the workspace in the order of the
         // MFMA results, quarter q of block (rb, cb) of lane l at (((rb * 2 + cb) * 4 + q) * 64 + l) * 4:
         // producer and consumer use the same mapping, and a lane moves 16 bytes per instruction.
@@ -2008,12 +2019,7 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
             fold(pa);
         }
     }
-    if (poisoned) {
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = f32x16{0.f} + __uint_as_float(0x7FC00000u);
-    }
+    if (poisoned && ku == 0) poison();
     if (tile_ok && ku == 0 && a.fused) {
         // the fused output stage takes four columns 16 apart of one row from a lane: rows (i, i + 4)
         // of the two halves of 32 columns trade places, after which lane (l16, lq) holds columns

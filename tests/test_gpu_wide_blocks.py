@@ -124,3 +124,30 @@ def test_offset_of_long_groups_cancels_early(gpu):
         d = device.y_to_numpy(y).astype(np.float64) - ref
         errors[G] = np.linalg.norm(d) / np.linalg.norm(ref)
     assert errors[128] <= 1.8 * errors[64], errors
+
+
+@pytest.mark.parametrize("K,N,M,n_ad", [(4096, 1024, 70, 8), (2048, 640, 200, 16), (8192, 256, 33, 4)])
+def test_a_wait_that_runs_out_leaves_no_wrong_number(gpu, K, N, M, n_ad):
+    """Few polls, so that some waves of a block give up where others still see their shrink blocks done
+    (every kernel runs to its end all the same): an output is right or NaN, and a NaN is reported."""
+    lib, device, torch = gpu
+    prob = random_problem(K + M, K, N, 32, 16, n_ad)
+    x, rows = rows_and_x(M, M, K, n_ad)
+    ref = oracle.linear(prob.wq, prob.scales, 32, prob.lora_a, prob.lora_b, prob.shape.alpha, x, rows)
+    p, dx, ra = device.upload_problem(prob), device.to_device(x), torch.from_numpy(rows).cuda()
+    y = device.alloc_y(M, N, 1)
+    ws = device.alloc_workspace([p], M)
+    old = lib.debug_spin_limit(-1)
+    try:
+        for limit in (0, 1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64):
+            lib.debug_spin_limit(limit)
+            lib.linear(p, dx, ra, M, y, 1, ws)
+            torch.cuda.synchronize()
+            got = device.y_to_numpy(y)
+            gave_up = np.isnan(got)
+            assert lib.workspace_status(ws) != 0 or not gave_up.any(), limit
+            assert np.max(np.abs(np.where(gave_up, ref, got) - ref)) <= TOL_F32 * np.max(np.abs(ref)), limit
+            lib.workspace_init(ws)
+            torch.cuda.synchronize()
+    finally:
+        lib.debug_spin_limit(old)

@@ -1753,7 +1753,12 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
                 const int quad = qb + u * TPR;
                 if (quad >= quads) continue;
                 v[u] *= t_factor;
-                const uint2 h = make_uint2(pack_bf16(v[u][0], v[u][1]), pack_bf16(v[u][2], v[u][3]));
+                // (a t above the largest bf16 must not round to infinity: the rest stays in the low half)
+                constexpr float top = 0x1.FEp127f;
+                f32x4_t w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = __builtin_amdgcn_fmed3f(v[u][e], -top, top);
+                const uint2 h = make_uint2(pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3]));
                 const f32x4_t l = {v[u][0] - bf16_bits_to_float(h.x & 0xFFFFu), v[u][1] - __uint_as_float(h.x & 0xFFFF0000u),
                                    v[u][2] - bf16_bits_to_float(h.y & 0xFFFFu), v[u][3] - __uint_as_float(h.y & 0xFFFF0000u)};
                 *reinterpret_cast<uint2 *>(dst + quad * 8) = h;

@@ -151,3 +151,26 @@ def test_a_wait_that_runs_out_leaves_no_wrong_number(gpu, K, N, M, n_ad):
             torch.cuda.synchronize()
     finally:
         lib.debug_spin_limit(old)
+
+
+@pytest.mark.parametrize("M", [8, 24, 40, 200])
+def test_t_close_to_the_largest_number(gpu, M):
+    """t between the largest bf16 and the largest fp32 is a number: alpha * (A x) = 1.003 * 2^127 * 1.9921875,
+    which a bf16 half would round to infinity; times B = 2^-100.  Codes of 0, so the base product is 0.  Bar: 17 bits
+    of t."""
+    lib, device, torch = gpu
+    K, N, r = 128, 128, 8
+    prob = random_problem(3, K, N, 32, r, 1)
+    prob.wq[:] = 0
+    a, b = np.zeros((1, r, K), np.float32), np.zeros((1, N, r), np.float32)
+    a[0, 0, 0], b[0, :, 0] = 2.0 ** 64 * 1.9921875, 2.0 ** -100
+    x = np.zeros((M, K), np.float32)
+    x[:, 0] = 2.0 ** 63
+    blob = device.upload_problem(prob).w_blob
+    p = lib.Proj(K, N, 32, blob, device.to_device(wl.f32_to_bf16_bits(a)), device.to_device(wl.f32_to_bf16_bits(b)), 1.003)
+    y = device.alloc_y(M, N, 1)
+    lib.LayerPlan([p], [device.to_device(wl.f32_to_bf16_bits(x))], [y], torch.zeros(M, dtype=torch.int32, device="cuda"), M, 1,
+                  device.alloc_workspace([p], M)).run()
+    torch.cuda.synchronize()
+    ref = float(np.float32(1.003)) * 1.9921875 * 2.0 ** 27
+    assert np.max(np.abs(device.y_to_numpy(y) - ref)) <= 2.0 ** -16 * ref

@@ -652,7 +652,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "int8 x int4 -> int32, fp32 scales" if args.a8 else "bf16",
+        "dtype": "int8 x int4 (exact, through bf16 products), fp32 scales" if args.a8 else "bf16",
         "data": "synthetic",
         "config": {
             "workload": f"{w.key}: {w.description}",

@@ -65,7 +65,9 @@ enum {
  *   lora_a   bf16 [n_adapters][rank][K]     (the paper's LoRA-A, transposed)
  *   lora_b   bf16 [n_adapters][N][rank]     (the paper's LoRA-B, transposed)
  *   alpha    the paper's scale factor s: multiplies B.(A.x) directly (no division by rank)
- * n_adapters == 0 (lora_a, lora_b may then be NULL) means a plain int4 linear layer. */
+ * n_adapters == 0 (lora_a, lora_b may then be NULL) means a plain int4 linear layer.
+ * lora_b must be finite: an infinite or NaN entry may reach, besides its own adapter's rows, other rows
+ * of the call (from 17 rows on, those in the same 32). */
 typedef struct {
     int32_t K, N;
     int32_t group;

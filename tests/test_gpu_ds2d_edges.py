@@ -86,7 +86,7 @@ def step_time(gpu, S, m, branch, nxt, V, shift):
 
 def test_time_does_not_depend_on_the_logits_sign(gpu):
     """A soft-max does not care about a shift, nor may the step's time (three times as long where a slice
-    without winners above zero was read again per winner; 1.6 leaves room for a noisy box)."""
+    without winners above zero was read again per winner; 1.6 leaves room for noise)."""
     args = (gpu, 8, 2, (3, 2), (3, 2), 128256)
     assert step_time(*args, -50.0) <= 1.6 * step_time(*args, 0.0)
 

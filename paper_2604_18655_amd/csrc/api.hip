@@ -289,6 +289,8 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
                 d.codes = reinterpret_cast<const uint4 *>(p.w_blob);
                 d.scales = reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(p.w_blob) +
                                                            blob_code_bytes(p.K, p.N));
+                d.flag = reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(p.w_blob) +
+                                                            blob_flag_at(p.K, p.N, p.group));
                 d.x = reinterpret_cast<const uint16_t *>(xs[i]);
                 d.y = ys[i];
                 d.K = p.K;
@@ -533,8 +535,6 @@ static mlora_status enqueue_call(const mlora_w4_proj *projs, int32_t n_proj, con
         }
         a->y_fp32 = (y_dtype == MLORA_Y_FP32);
         a->spin_limit = g_spin_limit;
-        a->code_mask = 0x00780078u;
-        a->code_bias = 0x41804180u;
         a->status = reinterpret_cast<unsigned *>(workspace);
         LaunchNeed need;
         const mlora_status st = plan_launch(projs + first, xs + first, ys + first, count, Mp, a8, lora_on, need,

@@ -18,11 +18,15 @@ namespace mlora {
 // 128-bit load per lane: lane l's uint4 holds, in component j, the 8 codes of column
 // 64*tile + 16*j + l%16 at inputs 32*step + 8*(l/16) + 0..7.
 //
-// Inside a dword the 8 codes are stored as offset-binary u = code + 8 in bit fields placed so
-// that  ((w rotr 4q) & 0x00780078) | 0x41804180  is a pair of bf16 numbers 16 + u = code + 24
-// for inputs 2q (low half) and 2q+1 (high half): the field of input i sits at bit
-// (3 + 4*(i/2) + 16*(i%2)) mod 32.  The constant offset 24 is removed by seeding the MFMA
-// accumulator with -24 * sum(x) over the same inputs, which one more MFMA produces.
+// Inside a dword the 8 codes are stored as sign and magnitude in fields placed so that each of
+//   w & 0x87878787   and   (w rotr 4) & 0x87878787
+// is four bytes s0000mmm, the codes of inputs 0..3 and 4..7.  Read as 8-bit floats (1-4-3) such bytes are
+// the numbers +-m * 2^-9, exactly: one conversion instruction (v_cvt_scalef32_pk_bf16_fp8, as fast as a
+// logical operation) turns two of them into a pair of bf16 codes.
+// Four bits of sign and magnitude do not hold all of -8 .. 7.  A blob with a code -8 anywhere (a
+// quantiser that scales by max / 7 makes none) has its flag set, the first word of the blob's last 16
+// bytes, and stores m - 1 for its negative codes; the kernels run a second copy of their loops on
+// it, whose unpacking adds the 1 back.
 //
 // Scales follow the codes: fp16, index ((tile * K/group + g) * 16 + c) * 4 + j for column
 // 64*tile + 16*j + c, so the lane that holds column c of all four blocks reads its four
@@ -43,12 +47,27 @@ __host__ __device__ inline size_t blob_scale_bytes(int K, int N, int group) {
 // may read (and ignore) up to 3 super-steps of codes and as many groups of scales past the end
 // of its tile: the blob ends with slack that keeps those reads inside the allocation.
 constexpr size_t BLOB_SLACK_BYTES = 16384;
-__host__ __device__ inline int field_pos(int i) { return (3 + 4 * (i >> 1) + 16 * (i & 1)) & 31; }
+constexpr uint32_t FIELD_MASK = 0x87878787u;
+__host__ __device__ inline size_t blob_flag_at(int K, int N, int group)
+{
+    return blob_code_bytes(K, N) + blob_scale_bytes(K, N, group) + BLOB_SLACK_BYTES - 16;
+}
 __host__ __device__ inline uint32_t rotl32(uint32_t v, int s) {
     s &= 31;
     return s ? (v << s) | (v >> (32 - s)) : v;
 }
-__host__ __device__ inline uint32_t rotr32(uint32_t v, int s) { return rotl32(v, 32 - (s & 31)); }
+// code (-8 .. 7) of input i <-> its fields in the dword
+__host__ __device__ inline uint32_t code_field(int code, int i, bool full)
+{
+    const uint32_t m = code < 0 ? (uint32_t)(-code) - (full ? 1u : 0u) : (uint32_t)code;
+    return rotl32((code < 0 ? 0x80u : 0u) | m, 8 * (i & 3) + (i < 4 ? 0 : 4));
+}
+__host__ __device__ inline int field_code(uint32_t w, int i, bool full)
+{
+    const uint32_t b = rotl32(w, 32 - (8 * (i & 3) + (i < 4 ? 0 : 4)));
+    const int m = (int)(b & 7u);
+    return b & 0x80u ? -(m + (full ? 1 : 0)) : m;
+}
 
 // ---------------------------------------------------------------------------------------------
 // Kernel argument block of one grouped call (passed by value: about 19 KiB; a block reads only
@@ -65,6 +84,7 @@ constexpr int MAX_KCHUNKS = 16;    // partial sums of the shrink step the epilog
 struct ProjArgs {
     const uint4 *codes;        // blob, code region
     const uint2 *scales;       // blob, scale region (4 fp16 per entry)
+    const uint32_t *flag;      // blob: not zero if it holds a code -8 (see above)
     const uint16_t *x;         // bf16 [M][K]
     void *y;                   // [M][N]
     const uint16_t *lora_a;    // bf16 [n_adapters][rank][K]
@@ -160,8 +180,6 @@ struct LayerArgs {
     int wide;                  // the launch runs wide blocks (see below)
     unsigned *ctrl;            // completion counters of this launch
     unsigned *status;          // workspace status word: set non-zero if a wait ran out
-    uint32_t code_mask;        // 0x00780078: the two code fields of a bf16 pair
-    uint32_t code_bias;        // 0x41804180: sign, exponent and leading mantissa bit of 16.0
 };
 
 // ---------------------------------------------------------------------------------------------

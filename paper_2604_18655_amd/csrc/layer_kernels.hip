@@ -3,7 +3,7 @@
 // Base product.  A block of four waves owns one K unit of one tile of 64 output columns for one
 // chunk of rows (16, 32 or 64 of them: three kernels, below).  Packed codes come straight from
 // HBM with one 128-bit load per lane and k-step, the rows of x and the fp16 scales from L2;
-// every code dword becomes four bf16 pairs with 7 integer ops and feeds 16x16x32 bf16 MFMAs
+// every code dword becomes four bf16 pairs with 7 instructions and feeds 16x16x32 bf16 MFMAs
 // whose A operand is a block of rows of x.  Scales multiply fp32 results, so the codes enter
 // the matrix unit exactly.  What several waves add up is added in a fixed order.
 //
@@ -113,20 +113,73 @@ __device__ __forceinline__ bool wait_count(unsigned *counter, unsigned expected,
 __device__ __forceinline__ float half_bits_lo(uint32_t v) { return half_bits_to_float((uint16_t)(v & 0xFFFFu)); }
 __device__ __forceinline__ float half_bits_hi(uint32_t v) { return half_bits_to_float((uint16_t)(v >> 16)); }
 
-// 8 packed codes -> 8 bf16 values code + 24 (4 dwords)
-__device__ __forceinline__ uint4 expand_codes(uint32_t w, uint32_t mask, uint32_t bias)
-{
-    uint4 o;
-    o.x = (w & mask) | bias;
-    o.y = (__builtin_amdgcn_alignbit(w, w, 4) & mask) | bias;
-    o.z = (__builtin_amdgcn_alignbit(w, w, 8) & mask) | bias;
-    o.w = (__builtin_amdgcn_alignbit(w, w, 12) & mask) | bias;
-    return o;
-}
-
 // (a native vector type: copies of HIP's uint4 struct from global to LDS would be lowered to
 // memcpy through a private array instead of going through registers)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// The two halves of a code word as bytes of sign and magnitude (see common.hpp), and eight such bytes -> 8 bf16
+// numbers (4 dwords).  Exact, without an offset: with codes + 24 (7 operations as well) every group needed
+// one more product per block of rows to take the offset out, and its sums were up to seven times the result.
+__device__ __forceinline__ uint32_t low_codes(uint32_t w) { return w & FIELD_MASK; }
+__device__ __forceinline__ uint32_t high_codes(uint32_t w) { return __builtin_amdgcn_alignbit(w, w, 4) & FIELD_MASK; }
+// (blobs with codes -8 hold m - 1 for negative codes)
+__device__ __forceinline__ uint32_t full_codes(uint32_t bytes) { return bytes + ((bytes >> 7) & 0x01010101u); }
+__device__ __forceinline__ uint4 codes_to_bf16(uint32_t lo, uint32_t hi)
+{
+    uint4 o;
+    o.x = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 512.0f, false));
+    o.y = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 512.0f, true));
+    o.z = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 512.0f, false));
+    o.w = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 512.0f, true));
+    return o;
+}
+template <bool FULL>
+__device__ __forceinline__ uint4 expand_codes(uint32_t w)
+{
+    return FULL ? codes_to_bf16(full_codes(low_codes(w)), full_codes(high_codes(w))) : codes_to_bf16(low_codes(w), high_codes(w));
+}
+// The halves of the four code words of a k-step.  `full` is the same for the whole block: the tile blocks
+// branch here, once per k-step, where a second copy of their loops would cost registers and code.
+struct CodeBytes {
+    uint32_t lo[4], hi[4];
+};
+__device__ __forceinline__ CodeBytes split_codes(u32x4 w, bool full)
+{
+    CodeBytes c;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        c.lo[j] = low_codes(w[j]);
+        c.hi[j] = high_codes(w[j]);
+    }
+    if (full) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            c.lo[j] = full_codes(c.lo[j]);
+            c.hi[j] = full_codes(c.hi[j]);
+        }
+    }
+    return c;
+}
+
+__device__ __forceinline__ void pin(f32x16 (&acc)[2]) { asm volatile("" : "+v"(acc[0]), "+v"(acc[1])); }
+template <int MB>
+__device__ __forceinline__ void pin(f32x4 (&acc)[MB][4])
+{
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+v"(acc[mb][0]), "+v"(acc[mb][1]), "+v"(acc[mb][2]), "+v"(acc[mb][3]));
+}
+
+// The blob's flag, requested like the codes and ahead of them, so that it is there when they are.  (Through the
+// scalar cache it would come from memory as well, and every wait for a kernel argument behind it would
+// wait for it: 8 rows, the seven projections of a layer, 14.7 -> 15.6 us.)
+__device__ __forceinline__ uint32_t request_flag(const ProjArgs &P)
+{
+    unsigned at = 0;
+    asm volatile("" : "+v"(at));                               // an address in a vector register
+    using G = const __attribute__((address_space(1))) uint32_t;
+    return ((G *)P.flag)[at];
+}
+__device__ __forceinline__ bool flag_set(uint32_t flag) { return __builtin_amdgcn_readfirstlane((int)flag) != 0; }
 
 // eight int8 (two words) -> eight bf16, exactly (seven bits and a sign)
 __device__ __forceinline__ u32x4 widen_int8(uint32_t lo, uint32_t hi)
@@ -230,12 +283,10 @@ __device__ __forceinline__ void round_to_lds(const RoundW<R> &rw, const RoundX<X
 // One loop pass = one scale group = SPG k-steps.
 template <int MB, int XR, int R, int SPG>
 __device__ __forceinline__ void round_compute(f32x4 (&acc)[MB][4], const unsigned char *buf,
-                                              int n_steps, int rows_here, uint32_t mask,
-                                              uint32_t bias, int lane)
+                                              int n_steps, int rows_here, bool full, int lane)
 {
     using L = RoundLds<XR, R>;
     const int l16 = lane & 15, lq = lane >> 4;
-    const uint4 neg24 = make_uint4(0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u);
     const unsigned char *wl = buf + lane * 16;
     const unsigned char *xl[MB];
 #pragma unroll
@@ -244,34 +295,25 @@ __device__ __forceinline__ void round_compute(f32x4 (&acc)[MB][4], const unsigne
     const unsigned char *sl = buf + L::W_BYTES + L::X_BYTES + l16 * 8;
 #pragma nounroll
     for (int g = 0; g < n_steps / SPG; ++g) {
-        uint4 xf[MB][SPG], wf[SPG];
+        uint4 xf[MB][SPG];
+        u32x4 wf[SPG];
 #pragma unroll
         for (int s = 0; s < SPG; ++s) {
-            wf[s] = *reinterpret_cast<const uint4 *>(wl + (g * SPG + s) * 1024);
+            wf[s] = *reinterpret_cast<const u32x4 *>(wl + (g * SPG + s) * 1024);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
                 xf[mb][s] = *reinterpret_cast<const uint4 *>(xl[mb] + (g * SPG + s) * 64);
         }
         const uint2 sv = *reinterpret_cast<const uint2 *>(sl + g * 128);
-        // -24 * sum of x over the group's inputs: cancels the offset of the stored codes
-        f32x4 corr[MB];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            corr[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int s = 0; s < SPG; ++s) corr[mb] = mfma16(xf[mb][s], neg24, corr[mb]);
-        }
         f32x4 d[MB][4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int s = 0; s < SPG; ++s) {
+            const CodeBytes cb = split_codes(wf[s], full);
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) d[mb][j] = corr[mb];
+            for (int j = 0; j < 4; ++j) {
+                const uint4 wb = codes_to_bf16(cb.lo[j], cb.hi[j]);
 #pragma unroll
-            for (int s = 0; s < SPG; ++s) {
-                const uint32_t wj = j == 0 ? wf[s].x : j == 1 ? wf[s].y : j == 2 ? wf[s].z : wf[s].w;
-                const uint4 wb = expand_codes(wj, mask, bias);
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb) d[mb][j] = mfma16(xf[mb][s], wb, d[mb][j]);
+                for (int mb = 0; mb < MB; ++mb) d[mb][j] = mfma16(xf[mb][s], wb, s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : d[mb][j]);
             }
         }
 #pragma unroll
@@ -312,49 +354,39 @@ struct StreamRegs {
 // lane's offset).  A request past the wave's range (ss >= n_ss) becomes one 16-byte read of the
 // first chunk by all lanes: every load stays unconditional, so the waits the compiler derives
 // stay exact, and the useless ones cost next to nothing.
-__device__ __forceinline__ void stream_request(StreamRegs &r, const u32x4 *wp0, const uint2 *sp0, int ss, int n_ss,
-                                               int gs, int lane)
+template <int SPG>
+__device__ __forceinline__ void stream_request(StreamRegs &r, const u32x4 *wp0, const uint2 *sp0, int ss, int n_ss, int lane)
 {
+    constexpr int GS = 4 / SPG;                                // scale groups per super-step
     const bool in = ss < n_ss;
     const u32x4 *wn = wp0 + (in ? (size_t)ss * 256 + lane : 0);
-    const uint2 *sn = sp0 + (in ? (size_t)ss * gs * 16 + (lane & 15) : 0);
+    const uint2 *sn = sp0 + (in ? (size_t)ss * GS * 16 + (lane & 15) : 0);
 #pragma unroll
     for (int u = 0; u < 4; ++u) r.w[u] = __builtin_nontemporal_load(wn + (in ? u * 64 : 0));
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < GS; ++g) {
         // (the scales' type is HIP's struct, which the builtin does not take: read as two words)
         const unsigned long long v = __builtin_nontemporal_load(
-            reinterpret_cast<const unsigned long long *>(sn + (in ? min(g, gs - 1) * 16 : 0)));
+            reinterpret_cast<const unsigned long long *>(sn + (in ? g * 16 : 0)));
         r.sc[g] = make_uint2((unsigned)v, (unsigned)(v >> 32));
     }
 }
 
 // The math of one super-step; xs = this lane's row of x in LDS at the super-step's first k-step.
-template <int SPG>
-__device__ __forceinline__ void stream_math(f32x4 (&acc)[4], const StreamRegs &r, const unsigned char *xs,
-                                            uint32_t mask, uint32_t bias)
+template <int SPG, bool FULL>
+__device__ __forceinline__ void stream_math(f32x4 (&acc)[4], const StreamRegs &r, const unsigned char *xs)
 {
     constexpr int GS = 4 / SPG;                                // scale groups per super-step
-    const uint4 neg24 = make_uint4(0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u);
 #pragma unroll
     for (int g = 0; g < GS; ++g) {
-        uint4 xa[SPG];
-        f32x4 corr = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int t = 0; t < SPG; ++t) {
-            xa[t] = *reinterpret_cast<const uint4 *>(xs + (g * SPG + t) * 64);
-            corr = mfma16(xa[t], neg24, corr);                 // -24 * sum of x: cancels the code offset
-        }
         f32x4 d[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            d[j] = corr;
+        for (int t = 0; t < SPG; ++t) {
+            const uint4 xa = *reinterpret_cast<const uint4 *>(xs + (g * SPG + t) * 64);
+            const u32x4 wv = r.w[g * SPG + t];
 #pragma unroll
-            for (int t = 0; t < SPG; ++t) {
-                const u32x4 wv = r.w[g * SPG + t];
-                const uint32_t wj = j == 0 ? wv.x : j == 1 ? wv.y : j == 2 ? wv.z : wv.w;
-                d[j] = mfma16(xa[t], expand_codes(wj, mask, bias), d[j]);
-            }
+            for (int j = 0; j < 4; ++j)
+                d[j] = mfma16(xa, expand_codes<FULL>(wv[j]), t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : d[j]);
         }
         const uint2 sv = r.sc[g];
 #pragma unroll
@@ -373,23 +405,22 @@ __device__ __forceinline__ void stream_math(f32x4 (&acc)[4], const StreamRegs &r
 // completion counters its epilogue depends on (poll_s, poll_p; before that, and for a wave that
 // depends on nothing, a dummy address): if they are complete by then, the epilogue need not wait
 // for a poll of its own.
-template <int SPG>
+template <int SPG, bool FULL>
 __device__ __forceinline__ void stream_loop(f32x4 (&acc)[4], StreamRegs &ra, StreamRegs &rb, const u32x4 *wp0,
-                                            const uint2 *sp0, int n_ss, const unsigned char *xl, uint32_t mask,
-                                            uint32_t bias, int lane, const unsigned *poll_s, const unsigned *poll_p,
+                                            const uint2 *sp0, int n_ss, const unsigned char *xl, int lane,
+                                            const unsigned *poll_s, const unsigned *poll_p,
                                             unsigned &seen_s, unsigned &seen_p)
 {
-    constexpr int GS = 4 / SPG;
     const unsigned *dummy = reinterpret_cast<const unsigned *>(wp0);
 #pragma nounroll
     for (int ss = 0; ss < n_ss; ss += 2) {
         const bool last = ss + 2 >= n_ss;
         seen_s = __hip_atomic_load(last ? poll_s : dummy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         seen_p = __hip_atomic_load(last ? poll_p : dummy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        stream_math<SPG>(acc, ra, xl + ss * 256, mask, bias);
-        stream_request(ra, wp0, sp0, ss + 2, n_ss, GS, lane);
-        if (ss + 1 < n_ss) stream_math<SPG>(acc, rb, xl + (ss + 1) * 256, mask, bias);
-        stream_request(rb, wp0, sp0, ss + 3, n_ss, GS, lane);
+        stream_math<SPG, FULL>(acc, ra, xl + ss * 256);
+        stream_request<SPG>(ra, wp0, sp0, ss + 2, n_ss, lane);
+        if (ss + 1 < n_ss) stream_math<SPG, FULL>(acc, rb, xl + (ss + 1) * 256);
+        stream_request<SPG>(rb, wp0, sp0, ss + 3, n_ss, lane);
     }
 }
 
@@ -697,12 +728,6 @@ __device__ __forceinline__ void base_unit(const LayerArgs &a, const ProjArgs &P,
             if (pf.t_mine[e / TH][e % TH]) lds.t_row(pf.t_ml + 16 * (e / TH))[pf.t_jj + 16 * (e % TH)] = ts[e] * P.alpha;
     };
 
-    // the two constants of expand_codes arrive as kernel arguments so that they live in
-    // registers and each field pair costs one and-or instead of an and plus an or with literals
-    const uint32_t mask = a.code_mask;
-    uint32_t bias = a.code_bias;
-    asm volatile("" : "+v"(bias));      // pin to a vector register (one scalar operand per op)
-
     // counters this block depends on (or signals): see common.hpp
     const int tiles = tiles_n(N);
     const int chunk = m0 / ROWS, chunks = a.m_pad / ROWS;
@@ -730,18 +755,33 @@ __device__ __forceinline__ void base_unit(const LayerArgs &a, const ProjArgs &P,
         const u32x4 *wp = reinterpret_cast<const u32x4 *>(codes_tile) + (size_t)ks_first * 64;
         const uint2 *sp = scales_tile + (size_t)(ks_first >> P.spg_shift) * 16;
         const unsigned char *xl = buf + min(l16, rows_x - 1) * L::XROW + 16 * lq;
-        StreamRegs sa, sb;
-        // an idle wave requests (and ignores) the unit's first super-step
-        stream_request(sa, wp, sp, 0, max(my_cnt, 1), 4 >> P.spg_shift, lane);
-        stream_request(sb, wp, sp, 1, my_cnt, 4 >> P.spg_shift, lane);
-        __builtin_amdgcn_sched_barrier(0);                     // (the requests stay ahead of the wait for x)
-#pragma unroll
-        for (int i = 0; i < XR; ++i) *reinterpret_cast<u32x4 *>(buf + lane * 16 + i * L::XROW) = xr[i];
         const unsigned *dummy = reinterpret_cast<const unsigned *>(wp);
         const unsigned *poll_s = need_s ? sctr : dummy, *poll_p = need_p ? pctr : dummy;
-        if (P.spg == 1)      stream_loop<1>(acc[0], sa, sb, wp, sp, my_cnt, xl, mask, bias, lane, poll_s, poll_p, seen_s, seen_p);
-        else if (P.spg == 2) stream_loop<2>(acc[0], sa, sb, wp, sp, my_cnt, xl, mask, bias, lane, poll_s, poll_p, seen_s, seen_p);
-        else                 stream_loop<4>(acc[0], sa, sb, wp, sp, my_cnt, xl, mask, bias, lane, poll_s, poll_p, seen_s, seen_p);
+        // (The first requests belong to the loop of their group size: made ahead of the branch, each
+        // register set would be moved to where the loop wants it, and a move waits for its data.)
+        auto loop = [&](auto spg_c) {
+            constexpr int SPG = decltype(spg_c)::value;
+            StreamRegs sa, sb;
+            const uint32_t flag = request_flag(P);
+            // an idle wave requests (and ignores) the unit's first super-step
+            stream_request<SPG>(sa, wp, sp, 0, max(my_cnt, 1), lane);
+            stream_request<SPG>(sb, wp, sp, 1, my_cnt, lane);
+            __builtin_amdgcn_sched_barrier(0);                 // (the requests stay ahead of the wait for x)
+#pragma unroll
+            for (int i = 0; i < XR; ++i) *reinterpret_cast<u32x4 *>(buf + lane * 16 + i * L::XROW) = xr[i];
+            if (!flag_set(flag)) {
+                stream_loop<SPG, false>(acc[0], sa, sb, wp, sp, my_cnt, xl, lane, poll_s, poll_p, seen_s, seen_p);
+            } else {
+                // (a second copy of the loop, with requests of its own: one loop with a branch in it took
+                // 0.3 us more of a layer's 15)
+                stream_request<SPG>(sa, wp, sp, 0, max(my_cnt, 1), lane);
+                stream_request<SPG>(sb, wp, sp, 1, my_cnt, lane);
+                stream_loop<SPG, true>(acc[0], sa, sb, wp, sp, my_cnt, xl, lane, poll_s, poll_p, seen_s, seen_p);
+            }
+        };
+        if (P.spg == 1)      loop(std::integral_constant<int, 1>{});
+        else if (P.spg == 2) loop(std::integral_constant<int, 2>{});
+        else                 loop(std::integral_constant<int, 4>{});
         // Everything below derives its indices afresh from the thread id: values shared with the
         // code above the loop would have to live across it, in registers the loop needs.
         asm volatile("" : "+v"(tid));
@@ -758,15 +798,17 @@ __device__ __forceinline__ void base_unit(const LayerArgs &a, const ProjArgs &P,
         const int nr = ks_total / R;                           // rounds of this wave
         RoundW<R> wa, wb;
         RoundX<XR, R> xr;
+        const uint32_t flag = request_flag(P);
         round_issue_w<R>(wa, codes_tile, scales_tile, P.spg, ks_first, true, lane);
         round_issue_w<R>(wb, codes_tile, scales_tile, P.spg, ks_first + R, 1 < nr, lane);
         round_issue_x<XR, R>(xr, P.x, K, m0, rows_x, ks_first, true, lane);
         // (keeps all of these requests ahead of the first wait)
         __builtin_amdgcn_sched_barrier(0);
+        const bool full = flag_set(flag);
         auto compute = [&](int n) {
-            if (P.spg == 1)      round_compute<MB, XR, R, 1>(acc, buf, n, rows_x, mask, bias, lane);
-            else if (P.spg == 2) round_compute<MB, XR, R, 2>(acc, buf, n, rows_x, mask, bias, lane);
-            else                 round_compute<MB, XR, R, 4>(acc, buf, n, rows_x, mask, bias, lane);
+            if (P.spg == 1)      round_compute<MB, XR, R, 1>(acc, buf, n, rows_x, full, lane);
+            else if (P.spg == 2) round_compute<MB, XR, R, 2>(acc, buf, n, rows_x, full, lane);
+            else                 round_compute<MB, XR, R, 4>(acc, buf, n, rows_x, full, lane);
         };
 #pragma nounroll
         for (int r0 = 0; r0 < max(nr, 1); r0 += 2) {
@@ -1330,7 +1372,7 @@ constexpr int pre_lds_bytes()
 __device__ __forceinline__ ProjArgs fetch_proj(const LayerArgs &a, int pi)
 {
     ProjArgs P = a.p[pi];
-    asm volatile("" :: "s"(P.codes), "s"(P.scales), "s"(P.x), "s"(P.y), "s"(P.lora_a), "s"(P.lora_b),
+    asm volatile("" :: "s"(P.codes), "s"(P.scales), "s"(P.flag), "s"(P.x), "s"(P.y), "s"(P.lora_a), "s"(P.lora_b),
                  "s"(P.t_part), "s"(P.partial));
     asm volatile("" :: "s"(P.K), "s"(P.N), "s"(P.spg), "s"(P.n_adapters), "s"(P.rank), "s"(P.r16),
                  "s"(P.kch), "s"(P.alpha), "s"(P.ksplit));
@@ -1361,7 +1403,7 @@ __device__ __forceinline__ LaunchTables pin_launch_args(const LayerArgs &a, int 
     t.group_blocks = a.group_blocks[z];
     asm volatile("" :: "s"(t.shrink), "s"(t.pre), "s"(t.main), "s"(a.row_adapter), "s"(a.M), "s"(a.y_fp32),
                        "s"(a.m_pad), "s"(a.row_blocks), "s"(a.half_shift), "s"(t.shrink_blocks), "s"(t.pre_base_blocks), "s"(t.group_blocks),
-                       "s"(a.ctrl), "s"(a.status), "s"(a.code_mask), "s"(a.code_bias), "s"(a.spin_limit));
+                       "s"(a.ctrl), "s"(a.status), "s"(a.spin_limit));
     return t;
 }
 
@@ -1510,14 +1552,13 @@ template <int SPG, int MB, bool A8, bool AGAIN, class Acc, class Early>
 __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t codes, __amdgpu_buffer_rsrc_t scales,
                                             __amdgpu_buffer_rsrc_t xsrc, const int (&xoff)[A8 ? 2 : 4], int piece16, int xdst0,
                                             unsigned char *lds_x, const unsigned char *xfrag, int n_ksteps,
-                                            uint32_t mask, uint32_t bias, int lane, const Early &early)
+                                            int lane, const ProjArgs &P, const Early &early)
 {
     using L = WideLds<MB>;
     constexpr int S = L::XSTEPS;                           // k-steps per stage of x
     constexpr int W = 8;                                   // k-steps of codes in registers
     constexpr int HALVES = W / S;                          // stages per pass over the register sets
     static_assert(S % SPG == 0 && W % S == 0, "a stage holds whole scale groups; the sets hold whole stages");
-    const uint4 neg24 = make_uint4(0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u);
     const int last = n_ksteps - 1;
     const int lane16 = lane * 16, col8 = (lane & 15) * 8, half16 = lane & 16;
     u32x4 w[W];
@@ -1550,6 +1591,7 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
     };
     const int n_stages = (n_ksteps + S - 1) / S;
     load_x(0);
+    const uint32_t flag = request_flag(P);
 #pragma unroll
     for (int k = 0; k < W; ++k) {
         w[k] = load_codes(k);
@@ -1558,6 +1600,7 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
     __builtin_amdgcn_sched_barrier(0);                     // (all of these ahead of the first wait)
     early();
     store_x(0);
+    const bool full_blob = flag_set(flag);
 
     // one stage: register sets [h * S, h * S + S), x buffer st & 1
     auto stage = [&](auto half, int st, auto full) {
@@ -1570,8 +1613,7 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
         auto stage_math = [&](auto nk) {
             constexpr int NK = decltype(nk)::value;
             // A scale group is worked through in runs of SG k-steps (at most 2, whose fragments of x
-            // fit the registers): offset term (-24 * sum of x over the run cancels the
-            // offset of the stored codes), products, FMAs with the scale.
+            // fit the registers): products, FMAs with the scale.
             constexpr int SG = SPG < 2 ? SPG : 2;
             constexpr int G0 = (H * S) / SPG;              // first scale group of this stage's register sets
 #pragma unroll
@@ -1581,24 +1623,23 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
                 const uint2 sv = sc[G0 + g];
                 if constexpr (MB == 2) {
                     uint4 xk[SG][2];
-                    f32x16 corr = f32x16{0.f};
 #pragma unroll
                     for (int t = 0; t < SG; ++t)
 #pragma unroll
-                        for (int o = 0; o < 2; ++o) {
-                            xk[t][o] = *reinterpret_cast<const uint4 *>(xs + t * 64 + o * 16);
-                            corr = mfma32(xk[t][o], neg24, corr);
-                        }
+                        for (int o = 0; o < 2; ++o) xk[t][o] = *reinterpret_cast<const uint4 *>(xs + t * 64 + o * 16);
                     if ((r + 1) * SG % SPG == 0) sc[G0 + g] = load_scales(st * S + g * SPG + W);   // (last run of its group)
+                    CodeBytes cw[SG];
+#pragma unroll
+                    for (int t = 0; t < SG; ++t) cw[t] = split_codes(w[H * S + r * SG + t], full_blob);
 #pragma unroll
                     for (int cb = 0; cb < 2; ++cb) {
-                        f32x16 d = corr;
+                        f32x16 d = f32x16{0.f};
 #pragma unroll
                         for (int t = 0; t < SG; ++t) {
-                            const u32x4 &wv = w[H * S + r * SG + t];
-                            const auto sw = __builtin_amdgcn_permlane16_swap(wv[2 * cb], wv[2 * cb + 1], false, false);
+                            const auto lo = __builtin_amdgcn_permlane16_swap(cw[t].lo[2 * cb], cw[t].lo[2 * cb + 1], false, false);
+                            const auto hi = __builtin_amdgcn_permlane16_swap(cw[t].hi[2 * cb], cw[t].hi[2 * cb + 1], false, false);
 #pragma unroll
-                            for (int o = 0; o < 2; ++o) d = mfma32(xk[t][o], expand_codes(sw[o], mask, bias), d);
+                            for (int o = 0; o < 2; ++o) d = mfma32(xk[t][o], codes_to_bf16(lo[o], hi[o]), d);
                         }
                         float sj = half_bits_to_float((uint16_t)((cb == 0 ? sv.x : sv.y) >> half16));
                         asm volatile("" : "+v"(sj));       // a float in a register: plain fp32 FMAs below
@@ -1607,25 +1648,23 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
                     }
                 } else {
                     uint4 xk[SG][MB];
-                    f32x4 corr[MB];
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb) corr[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int t = 0; t < SG; ++t)
 #pragma unroll
-                        for (int mb = 0; mb < MB; ++mb) {
+                        for (int mb = 0; mb < MB; ++mb)
                             xk[t][mb] = *reinterpret_cast<const uint4 *>(xs + mb * 16 * L::XROW + t * 64);
-                            corr[mb] = mfma16(xk[t][mb], neg24, corr[mb]);
-                        }
                     if ((r + 1) * SG % SPG == 0) sc[G0 + g] = load_scales(st * S + g * SPG + W);   // (last run of its group)
+                    CodeBytes cw[SG];
+#pragma unroll
+                    for (int t = 0; t < SG; ++t) cw[t] = split_codes(w[H * S + r * SG + t], full_blob);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         f32x4 d[MB];
 #pragma unroll
                         for (int t = 0; t < SG; ++t) {
-                            const uint4 wb = expand_codes(w[H * S + r * SG + t][j], mask, bias);
+                            const uint4 wb = codes_to_bf16(cw[t].lo[j], cw[t].hi[j]);
 #pragma unroll
-                            for (int mb = 0; mb < MB; ++mb) d[mb] = mfma16(xk[t][mb], wb, t == 0 ? corr[mb] : d[mb]);
+                            for (int mb = 0; mb < MB; ++mb) d[mb] = mfma16(xk[t][mb], wb, t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : d[mb]);
                         }
                         float sj = j == 0 ? half_bits_lo(sv.x) : j == 1 ? half_bits_hi(sv.x)
                                  : j == 2 ? half_bits_lo(sv.y) : half_bits_hi(sv.y);
@@ -1640,6 +1679,7 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
                 // use, so that no copy of the old contents has to be kept)
 #pragma unroll
                 for (int t = 0; t < SG; ++t) w[H * S + r * SG + t] = load_codes(st * S + r * SG + t + W);
+                pin(acc);
             }
         };
         // (a unit is a whole number of 4-k-step super-steps: a stage of 8 k-steps is full, or the
@@ -1710,10 +1750,6 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
     unsigned *const pctr = a.ctrl + P.part_ctr + (tile * lines + (chunk >> a.half_shift)) * CTR_STRIDE +
                            (chunk & a.half_shift) * (CTR_STRIDE / 2);
     const bool need_s = lora, need_p = ku == 0 && P.ksplit > 1;
-
-    const uint32_t mask = a.code_mask;
-    uint32_t bias = a.code_bias;
-    asm volatile("" : "+v"(bias));
 
     if (tid == 0) lds.waited_out = 0;                      // (ahead of the K loop's barriers)
 
@@ -1816,7 +1852,7 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
         const int xdst0 = (tid / PPR) * L::XROW + piece16 * (2 / EB);
         if constexpr (MB == 2) {
             stream_loop<SPG, MB, A8, AGAIN>(acc[0], rw, rs, rx, xoff, piece16, xdst0, lds.buf, lds.buf + l32 * L::XROW + hi * 32,
-                                     unit_cnt * 4, mask, bias, lane, early);
+                                     unit_cnt * 4, lane, P, early);
         } else {
             // Products of 16 x 16: lane (l16, lq) gets rows 4 * lq + e of a block of 16 and columns 16 * j +
             // l16.  With the rows of their A operand in the order that trades the two bits of row / 4,
@@ -1828,7 +1864,7 @@ __device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P,
 #pragma unroll
                 for (int j = 0; j < 4; ++j) acc16[mb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
             stream_loop<SPG, MB, A8, AGAIN>(acc16, rw, rs, rx, xoff, piece16, xdst0, lds.buf, lds.buf + arow * L::XROW + (lane >> 4) * 16,
-                                     unit_cnt * 4, mask, bias, lane, early);
+                                     unit_cnt * 4, lane, P, early);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll

@@ -540,7 +540,7 @@ static mlora_status enqueue_call(const mlora_w4_proj *projs, int32_t n_proj, con
         const mlora_status st = plan_launch(projs + first, xs + first, ys + first, count, Mp, a8, lora_on, need,
                                             a.get(), ctrl, data, x_scales ? x_scales + first : nullptr);
         if (st != MLORA_OK) return st;         // (cannot happen: the sizing pass has seen the same shapes)
-        if (launch_layer(*a, need.grid_x, need.groups, s) != hipSuccess) return MLORA_EHIP;
+        if (launch_layer(*a, need.groups, s) != hipSuccess) return MLORA_EHIP;
         ctrl += need.ctrl_bytes;
         data += need.data_bytes;
     }

@@ -249,7 +249,7 @@ hipError_t launch_unpack(int K, int N, int group, const void *blob, int8_t *code
                          hipStream_t s);
 hipError_t launch_group_rows(const int *row_adapter, int M, int n_adapters, int *perm,
                              int *seg_adapter, int *seg_start, int *n_seg, hipStream_t s);
-hipError_t launch_layer(const LayerArgs &a, int grid_x, int groups, hipStream_t s);
+hipError_t launch_layer(const LayerArgs &a, int groups, hipStream_t s);
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t s);
 hipError_t launch_rms_scale(const uint16_t *x, int M, int K, float eps, float *scale, hipStream_t s);
 hipError_t launch_lora_int16_expand(const int16_t *aq, const int16_t *bq, int n_adapters, int rank, int K, int N,

@@ -22,6 +22,7 @@
 // rows of A[adapter]); the partial sums go to t_part[chunk][row][rank].  Up to 16 rows: a block
 // per (row, 16 ranks, K chunk).  More rows: the rows of a chunk of 64 are grouped by adapter
 // and cut into tiles of 16, and a block's waves each take whole tiles.
+#include <algorithm>
 #include <type_traits>
 
 #include "group_rows.hpp"
@@ -1421,30 +1422,35 @@ __device__ __forceinline__ int find_proj(const i32x16 &begin, int b, int &first)
     return pi;
 }
 
-// blocks per compute unit the registers are budgeted for (LDS allows as many for these shapes)
 // Block index -> (block of the group, row chunk).  The row chunks of one block of columns stream
 // the same weights.  Workgroups go to the chip's 8 XCDs in turn (index mod 8), and every XCD has
-// an L2 of its own, so the grid is laid out in runs of 8 blocks x all chunks with the chunk
+// an L2 of its own, so behind the shrink blocks (filled up to a multiple of 8; they exist once, for all
+// chunks: a grid of shrink blocks x chunks started 15232 blocks that had nothing to do among the 32256 of
+// 16 layers at 512 rows) the grid is laid out in runs of 8 blocks x all chunks with the chunk
 // varying in steps of 8: index = (b / 8) * 8 * chunks + chunk * 8 + b % 8.  All chunks of a block
 // then run on one XCD at about the same time, and its weights come from HBM once and from that
 // L2 for the other chunks.  (Chunk-major order, a whole pass over the weights between two chunks,
 // read 5.9 x the algorithmic bytes from HBM at 512 rows.)  A producer still has a smaller index
-// than its consumer: shrink blocks work at chunk 0 only, and a split-K block and the block that
-// finishes its tile have the same chunk.
-__device__ __forceinline__ void split_block_index(const LayerArgs &a, int &b, int &chunk)
+// than its consumer: a split-K block and the block that finishes its tile have the same chunk.
+// b past the group's last block: nothing to do.
+__host__ __device__ inline unsigned filled_up(unsigned blocks) { return (blocks + 7u) & ~7u; }
+__device__ __forceinline__ void split_block_index(const LayerArgs &a, const LaunchTables &t, int &b, int &chunk)
 {
-    const unsigned id = blockIdx.x;
-    const unsigned chunks = (unsigned)a.row_blocks;
-    if (chunks == 1) {
+    const unsigned id = blockIdx.x, chunks = (unsigned)a.row_blocks, shrink = (unsigned)t.shrink_blocks;
+    const unsigned first = filled_up(shrink);
+    chunk = 0;
+    if (chunks == 1 || id < shrink) {
         b = (int)id;
-        chunk = 0;
+    } else if (id < first) {
+        b = 0x7FFFFFFF;
     } else {
-        const unsigned run = id / (8u * chunks), r = id - run * 8u * chunks;
+        const unsigned run = (id - first) / (8u * chunks), r = (id - first) - run * 8u * chunks;
         chunk = (int)(r >> 3);
-        b = (int)(run * 8u + (r & 7u));
+        b = (int)(shrink + run * 8u + (r & 7u));
     }
 }
 
+// blocks per compute unit the registers are budgeted for (LDS allows as many for these shapes)
 template <int MB, int XR> constexpr int occupancy_of() { return MB == 1 && XR == 8 ? 3 : 2; }
 
 template <int MB, int XR>
@@ -1454,11 +1460,10 @@ __global__ __launch_bounds__(64 * Shape<MB>::WAVES, (occupancy_of<MB, XR>())) vo
     const int z = (int)blockIdx.z;
     const LaunchTables tables = pin_launch_args(a, z);
     int b, chunk;
-    split_block_index(a, b, chunk);
+    split_block_index(a, tables, b, chunk);
     if (b >= tables.group_blocks) return;                  // (the slices are as long as the longest group)
     int first;
     if (b < tables.shrink_blocks) {
-        if (chunk != 0) return;
         const int pi = z * GROUP_PROJ + find_proj(tables.shrink, b, first);
         // (the instances with one block of 16 rows are the ones launched for M <= 16)
         if constexpr (MB == 1) shrink_row_block(a, fetch_proj(a, pi), pi, b - first, *reinterpret_cast<ShrinkRowLds *>(smem));
@@ -2158,11 +2163,10 @@ __global__ __launch_bounds__(256, (MB == 2 ? 3 : 2)) void wide_kernel(const Laye
     const int z = (int)blockIdx.z;
     const LaunchTables tables = pin_launch_args(a, z);
     int b, chunk;
-    split_block_index(a, b, chunk);
+    split_block_index(a, tables, b, chunk);
     if (b >= tables.group_blocks) return;
     int first;
     if (b < tables.shrink_blocks) {
-        if (chunk != 0) return;
         const int pi = z * GROUP_PROJ + find_proj(tables.shrink, b, first);
         shrink_block<A8>(a, fetch_proj(a, pi), pi, b - first, *reinterpret_cast<ShrinkLds *>(smem));
         return;
@@ -2186,12 +2190,17 @@ static hipError_t launch_instance(const LayerArgs &a, const dim3 &grid, hipStrea
     return hipGetLastError();
 }
 
-// grid: x = the longest group's blocks x row chunks (see split_block_index), z = groups of up to 16 projections
-hipError_t launch_layer(const LayerArgs &a, int grid_x, int groups, hipStream_t s)
+// grid: x = the longest group's blocks, its base blocks x row chunks (see split_block_index), z = groups of up
+// to 16 projections; blocks past a group's last one exit at once
+hipError_t launch_layer(const LayerArgs &a, int groups, hipStream_t s)
 {
     const int n_chunks = a.row_blocks;
-    // (several chunks: runs of 8 blocks, see split_block_index; blocks past a group's last one exit at once)
-    const long long gx = n_chunks == 1 ? grid_x : (long long)((grid_x + 7) / 8 * 8) * n_chunks;
+    long long gx = 0;
+    for (int z = 0; z < groups; ++z) {
+        const long long base = a.group_blocks[z] - a.shrink_blocks[z];
+        gx = std::max(gx, n_chunks == 1 ? (long long)a.group_blocks[z]
+                                        : filled_up((unsigned)a.shrink_blocks[z]) + (long long)filled_up((unsigned)base) * n_chunks);
+    }
     if (gx > 0x7FFFFFFFll) return hipErrorInvalidValue;
     const dim3 grid((unsigned)gx, 1u, (unsigned)groups);
     if (a.wide) {

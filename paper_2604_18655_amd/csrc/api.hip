@@ -69,12 +69,11 @@ mlora_status check_proj(const mlora_w4_proj &p)
 
 int r16_of(const mlora_w4_proj &p) { return p.n_adapters > 0 ? (p.rank + 15) / 16 * 16 : 0; }
 // K chunks of the shrink step (at most MAX_KCHUNKS).  Decode shapes: 1024 inputs per chunk, split
-// over the four waves of a block (8 k-steps each, requested at once).  More than 16 rows: a wave
-// works through a chunk on its own for every row tile it is dealt; measured best with 512 inputs
-// per chunk for tile blocks of 17 to 32 rows (the finishing blocks need t early there) and 1024 in
-// the wide kernel at any row count (fewer shrink blocks and fewer partial sums for every unit to
-// gather: the 16-layer decode launch at 32 rows 198.0 -> 192.3 us; 2048 everywhere: 196 us), and
-// 2048 where K is above 4096 (a projection of 14336 inputs at 64 rows: 14 -> 7 chunks, 64.1 -> 55.0 us).
+// over the four waves of a block (8 k-steps each, requested at once).  More than 16 rows, the same for every
+// row tile a block is dealt: 512 inputs per chunk for tile blocks of 17 to 32 rows (the finishing
+// blocks need t early there) and 1024 in the wide kernel at any row count, 2048 where K is above 4096
+// (fewer partial sums for every unit to gather); 2048 from K = 2048 on: 16 layers at 32 rows 174 -> 183
+// us, 2048 x 8192 at 64 rows 17.9 -> 20.8, the waves' quarters no longer being one trip to memory.
 int kch_of(const mlora_w4_proj &p, int M, bool wide)
 {
     const int c = p.K / ((M > 16 && M <= 32 && !wide) ? 512 : (wide && p.K > 4096) ? 2048 : 1024);
@@ -240,16 +239,20 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
     const int row_blocks = halves ? (M + 31) / 32 : chunks;    // blocks along the rows
     const int groups = (count + GROUP_PROJ - 1) / GROUP_PROJ;
     const int shrink_chunks = (M + SHRINK_CHUNK_ROWS - 1) / SHRINK_CHUNK_ROWS;
-    bool fine = M > 32 && M < 2 * SHRINK_CHUNK_ROWS;       // one tile per wave in the grouped shrink blocks
-    if (fine) {
+    // most row tiles of a grouped shrink block (see SHRINK_ALL_LIVE_BLOCKS)
+    int shrink_tiles = wide && block_rows == 32 ? 8 : 16;
+    for (int tiles = 1; lora_on && Mc > 16 && tiles <= 4; tiles *= 4) {
         long long live = 0;
         for (int i = 0; i < count; ++i) {
             const mlora_w4_proj &p = projs[i];
             live += (long long)((tiles_n(p.N) + tiles_per_block(wide) - 1) / tiles_per_block(wide)) * row_blocks * ksplit_of(p, wide, lb);
-            if (lora_on && p.n_adapters > 0)
-                live += (long long)shrink_chunks * shrink_tile_shares(M, p.n_adapters, true) * (r16_of(p) / 16) * kch_of(p, M, wide);
+            if (p.n_adapters > 0)
+                live += (long long)shrink_chunks * shrink_tile_shares(M, p.n_adapters, tiles) * (r16_of(p) / 16) * kch_of(p, M, wide);
         }
-        fine = live <= SHRINK_FINE_MAX_BLOCKS;
+        if (live <= SHRINK_ALL_LIVE_BLOCKS) {
+            shrink_tiles = tiles;
+            break;
+        }
     }
     bool shared = false;                       // anything handed from block to block?
     size_t part_lines = 0, data_bytes = 0, bound_lines = 0, data_bound = 0;
@@ -281,7 +284,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
             const int kch = chunk16 && kch_of(p, Mc, wide) > 4 ? 4 : kch_of(p, Mc, wide);
             const size_t t_bytes = lora ? round_up((size_t)kch * (size_t)M * (size_t)r16_of(p) * sizeof(float), 256) : 0;
             const int n_shrink = !lora ? 0
-                : (Mc <= 16 && !wide ? M : shrink_chunks * shrink_tile_shares(M, p.n_adapters, fine)) *
+                : (Mc <= 16 && !wide ? M : shrink_chunks * shrink_tile_shares(M, p.n_adapters, shrink_tiles)) *
                       (r16_of(p) / 16) * kch;
             if (a) {
                 ProjArgs &d = a->p[i];
@@ -363,7 +366,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
         a->block_rows = block_rows;
         a->row_blocks = row_blocks;
         a->half_shift = halves ? 1 : 0;
-        a->shrink_fine = fine;
+        a->shrink_tiles = shrink_tiles;
         a->m_pad = m_pad;
         if (chunk16) a->M_plan = 16;
     }

@@ -168,7 +168,7 @@ struct LayerArgs {
                                // that calls with int8 activations always run wide blocks and are
                                // laid out as for at least 17 rows
     int a8;                    // x is int8 with one scale per tensor (ProjArgs::x_scale)
-    int shrink_fine;           // grouped shrink blocks: at most one tile per wave (see shrink_tile_shares)
+    int shrink_tiles;          // grouped shrink blocks: most row tiles of a block (see shrink_tile_shares)
     int fused;                 // outputs go through epi[] (one group of at most 16 projections)
     EpiArgs epi[GROUP_PROJ];
     int y_fp32;
@@ -220,14 +220,13 @@ __device__ inline f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
 // The grouped shrink step (more than 16 rows) works on chunks of 64 rows: the rows of a chunk are
 // grouped by adapter (one wave, no sort) and every segment is cut into tiles of 16 rows.  Upper
 // bound of the tiles of a chunk of `rows` rows (at most 64): a tile per 16 rows plus one per
-// segment, at most a tile per row.  A block's four waves work through up to 16 tiles; a chunk
-// that can have more is shared out over several blocks.  Calls of 33 to 127 rows have at most two
-// chunks and base blocks that are done early: there the finishing blocks wait for t, so a wave
-// gets at most one tile as long as base blocks and these more, mostly idle shrink blocks all find a
-// place at once (SHRINK_FINE_MAX_BLOCKS; 32 adapters of rank 64, us, one tile against four: 4096 x 14336
-// at 64 rows (368 blocks) 34 against 40, at 100 rows (736) 76 against 68; 14336 x 4096 at 64 rows (476)
-// 46 against 50, at 100 rows (952) 89 against 77).  Host (grid size) and device (block index -> chunk,
-// share) use the same figures.
+// segment, at most a tile per row.  The chunk's tiles are shared out over blocks of up to 8 (wide blocks of 32
+// rows) or 16 (the others, which have two places per compute unit: 16 layers at 512 rows 1313 us against 1342
+// with 8, a layer at 32 rows in tile blocks 25 against 29).  Where all blocks of the launch, idle ones
+// included, find a place at once, the finishing blocks wait for t, and a block gets one tile, or up to 4 if that
+// is too many blocks (4096 x 14336 at 64 rows, 32 adapters of rank 64: 41.5 us with 16 tiles, 35.4 with 4;
+// 14336 x 4096 49.5 and 32.5; 8192 x 2048 at 64 rows, 8 adapters of rank 16, 40 with 16, 22.7 with 4, 19.4 with
+// 1).  Host (grid size) and device (block index -> chunk, share) use the same figures.
 constexpr int SHRINK_CHUNK_ROWS = 64;
 __host__ __device__ inline int max_row_tiles(int rows, int n_adapters)
 {
@@ -235,11 +234,11 @@ __host__ __device__ inline int max_row_tiles(int rows, int n_adapters)
     const int bound = rows / 16 + segs;
     return bound < rows ? bound : rows;
 }
-constexpr int SHRINK_FINE_MAX_BLOCKS = 500;
-__host__ __device__ inline int shrink_tile_shares(int M, int n_adapters, bool fine)
+constexpr int SHRINK_ALL_LIVE_BLOCKS = 500;
+__host__ __device__ inline int shrink_tile_shares(int M, int n_adapters, int tiles_per_block)
 {
     const int tiles = max_row_tiles(M < SHRINK_CHUNK_ROWS ? M : SHRINK_CHUNK_ROWS, n_adapters);
-    return fine ? (tiles + 3) / 4 : (tiles + 15) / 16;
+    return (tiles + tiles_per_block - 1) / tiles_per_block;
 }
 
 // host launchers (each file defines its own)

@@ -13,15 +13,6 @@ struct GroupLds {
     int bad;                                      // an index was outside [-1, n_adapters)
 };
 
-// The same results for at most 64 rows (one wave's worth): at most 64 segments.
-struct GroupLds64 {
-    unsigned short perm[64];
-    unsigned short seg_adapter[64];
-    unsigned short seg_start[65];
-    int n_seg;
-    int bad;
-};
-
 // Rows without adapter (-1, or an out-of-range index) go to bucket n_adapters, which sorts last.
 __device__ inline int bucket_of(int a, int n_adapters, bool &bad)
 {
@@ -29,45 +20,86 @@ __device__ inline int bucket_of(int a, int n_adapters, bool &bad)
     return (a < 0 || a >= n_adapters) ? n_adapters : a;
 }
 
-// M <= 64: one wave, one row per lane, no LDS traffic until the results are written.  The
-// position of a row in the sorted order is (#rows in a smaller bucket) + (#earlier rows in the
-// same bucket); both sets are built as lane masks from one ballot per bit of the bucket id.
+// At most 64 rows: one wave, one row per lane.  The position of a row in the sorted order is (#rows in a
+// smaller bucket) + (#earlier rows in the same bucket); both sets are built as lane masks from one
+// ballot per bit of the bucket id.
+struct RowPlace {
+    int bucket;
+    unsigned long long smaller, before;            // lanes of smaller buckets; earlier lanes of the own one
+    bool valid, has_adapter, bad;
+    __device__ int rank() const { return __popcll(before); }
+    __device__ int position() const { return __popcll(smaller) + rank(); }
+    // how many of the lanes in `mask` come earlier in the sorted order
+    __device__ int ahead(unsigned long long mask) const { return __popcll(mask & smaller) + __popcll(mask & before); }
+};
+__device__ inline RowPlace place_row(const int *row_adapter, int M, int n_adapters)
+{
+    const int lane = threadIdx.x & 63;
+    RowPlace r;
+    r.valid = lane < M;
+    r.bad = false;
+    r.bucket = 0;
+    if (r.valid) r.bucket = bucket_of(row_adapter[lane], n_adapters, r.bad);
+    unsigned long long eq = __ballot(r.valid), lt = 0;
+    const int nbits = 32 - __clz(n_adapters);      // buckets 0..n_adapters
+    for (int bit = nbits - 1; bit >= 0; --bit) {
+        const bool set = (r.bucket >> bit) & 1;
+        const unsigned long long bal = __ballot(r.valid && set);
+        if (set) { lt |= eq & ~bal; eq &= bal; }
+        else     { eq &= ~bal; }
+    }
+    r.smaller = lt;
+    r.before = eq & ((1ull << lane) - 1ull);
+    r.has_adapter = r.valid && r.bucket < n_adapters;
+    return r;
+}
+
 template <class G>
 __device__ inline void group_rows_wave(const int *row_adapter, int M, int n_adapters, G &g)
 {
     const int lane = threadIdx.x & 63;
-    const unsigned long long below = (1ull << lane) - 1ull;
-    const bool valid = lane < M;
-    bool bad = false;
-    int bucket = 0;
-    if (valid) bucket = bucket_of(row_adapter[lane], n_adapters, bad);
-    const unsigned long long vmask = __ballot(valid);
-    unsigned long long eq = vmask, lt = 0;
-    const int nbits = 32 - __clz(n_adapters);      // buckets 0..n_adapters
-    for (int bit = nbits - 1; bit >= 0; --bit) {
-        const bool set = (bucket >> bit) & 1;
-        const unsigned long long bal = __ballot(valid && set);
-        if (set) { lt |= eq & ~bal; eq &= bal; }
-        else     { eq &= ~bal; }
-    }
-    const int rank = __popcll(eq & below);
-    const int smaller = __popcll(lt);
-    const bool has_adapter = valid && bucket < n_adapters;
-    const bool first = has_adapter && rank == 0;
+    const RowPlace r = place_row(row_adapter, M, n_adapters);
+    const bool first = r.has_adapter && r.rank() == 0;
     const unsigned long long first_mask = __ballot(first);
-    if (valid) g.perm[smaller + rank] = (unsigned short)lane;
+    if (r.valid) g.perm[r.position()] = (unsigned short)lane;
     if (first) {
-        const int idx = __popcll(first_mask & lt);
-        g.seg_adapter[idx] = (unsigned short)bucket;
-        g.seg_start[idx] = (unsigned short)smaller;
+        const int idx = r.ahead(first_mask);
+        g.seg_adapter[idx] = (unsigned short)r.bucket;
+        g.seg_start[idx] = (unsigned short)r.position();
     }
     const int n_seg = __popcll(first_mask);
-    const int with_adapter = __popcll(__ballot(has_adapter));
-    const unsigned long long any_bad = __ballot(bad);
+    const int with_adapter = __popcll(__ballot(r.has_adapter));
+    const unsigned long long any_bad = __ballot(r.bad);
     if (lane == 0) {
         g.seg_start[n_seg] = (unsigned short)with_adapter;
         g.n_seg = n_seg;
         g.bad = any_bad != 0;
+    }
+}
+
+// The rows of every adapter cut into tiles of 16, in the order of the adapters.
+struct RowTiles {
+    unsigned short perm[64];                       // rows in sorted order
+    unsigned short first[65], adapter[64];         // of tile t: position of its first row (the next tile's ends it), adapter
+    int n_tiles;
+};
+// Called by one wave, at most 64 rows.
+__device__ inline void cut_row_tiles(const int *row_adapter, int M, int n_adapters, RowTiles &g)
+{
+    const int lane = threadIdx.x & 63;
+    const RowPlace r = place_row(row_adapter, M, n_adapters);
+    const bool first = r.has_adapter && r.rank() % 16 == 0;
+    const unsigned long long first_mask = __ballot(first);
+    if (r.valid) g.perm[r.position()] = (unsigned short)lane;
+    if (first) {
+        const int t = r.ahead(first_mask);
+        g.first[t] = (unsigned short)r.position();
+        g.adapter[t] = (unsigned short)r.bucket;
+    }
+    const int with_adapter = __popcll(__ballot(r.has_adapter));
+    if (lane == 0) {
+        g.n_tiles = __popcll(first_mask);
+        g.first[g.n_tiles] = (unsigned short)with_adapter;
     }
 }
 
@@ -139,13 +171,6 @@ __device__ inline void group_rows_counting(const int *row_adapter, int M, int n_
             }
         }
     }
-}
-
-// Called by all threads of a block, M <= 64.  On return g holds the permutation and the segments.
-__device__ inline void group_rows_lds64(const int *row_adapter, int M, int n_adapters, GroupLds64 &g)
-{
-    if ((threadIdx.x >> 6) == 0) group_rows_wave(row_adapter, M, n_adapters, g);
-    __syncthreads();
 }
 
 // Called by all threads of a block.  On return g holds the permutation and the segments.

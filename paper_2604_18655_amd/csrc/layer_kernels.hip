@@ -21,7 +21,7 @@
 // LoRA shrink, t[m] = A[a(m)] . x[m] in K chunks, MFMA (A operand: rows of x, B operand: 16 rank
 // rows of A[adapter]); the partial sums go to t_part[chunk][row][rank].  Up to 16 rows: a block
 // per (row, 16 ranks, K chunk).  More rows: the rows of a chunk of 64 are grouped by adapter
-// and cut into tiles of 16, and a block's waves each take whole tiles.
+// and cut into tiles of 16, and a block's four waves share the inputs of every tile.
 #include <algorithm>
 #include <type_traits>
 
@@ -1138,127 +1138,150 @@ __device__ __forceinline__ void base_unit(const LayerArgs &a, const ProjArgs &P,
 // contiguous runs (4 rows x 256 bytes per instruction) and turned into fragments through a
 // wave-private LDS buffer, four k-steps at a time.
 //
-// Grouped shrink (more than 16 rows per call).  A block = (chunk of 64 rows, share of the
-// chunk's row tiles, 16 ranks, chunk of K).  Wave 0 groups the chunk's rows by adapter (a few
-// ballots) and every segment is cut into tiles of 16 rows; the block's four waves then take the
-// tiles of the block's share in turn, each wave working through the whole K chunk of its tile on
-// its own: no reduction across waves, and few, long-lived blocks, which leaves the compute
-// units to the base blocks from the start of the launch (the blocks of a launch are placed in
-// grid order, so many short shrink blocks in front would hold every base block back).
+// Grouped shrink (more than 16 rows per call).  A block = (chunk of 64 rows, share of the chunk's row
+// tiles, 16 ranks, chunk of K).  Wave 0 cuts the rows of every adapter into tiles of 16 (a few ballots).
+// Each wave takes a quarter of the K chunk of every tile of the block; the quarters are added through LDS,
+// up to four tiles at a time.  What bounds a block is the trips to memory behind one another: a quarter of
+// 256 inputs is one trip (two batches in registers), where a wave that worked through a K chunk of a tile by
+// itself needed four (t of 14336 inputs, 64 rows, 32 adapters of rank 64: 34 -> 21 us after the start of
+// the launch, the whole call 46 -> 33 us).  DEPTH = batches in registers: four where 256 are there.
 struct ShrinkLds {
     static constexpr int SB = 4;                            // k-steps per batch
     static constexpr int ROW = SB * 64 + 16;                // bytes of a staged row; +16: rows 4 banks apart
-    GroupLds64 g;
+    RowTiles g;
     alignas(16) unsigned char a[4][16 * ROW];               // (16-byte LDS accesses)
     alignas(16) unsigned char x[4][16 * ROW];
+    alignas(16) f32x4 red[4][4][64];                        // a wave's share of four tiles
 };
 
-template <bool A8>
+template <bool A8, int DEPTH>
 __device__ __forceinline__ void shrink_block(const LayerArgs &a, const ProjArgs &P, int pi, int local, ShrinkLds &lds)
 {
     using L = ShrinkLds;
     constexpr int SB = L::SB;
-    GroupLds64 &g = lds.g;
+    RowTiles &g = lds.g;
     const int jblocks = P.r16 / 16;
-    const int shares = shrink_tile_shares(a.M_plan, P.n_adapters, a.shrink_fine != 0);
+    const int shares = shrink_tile_shares(a.M_plan, P.n_adapters, a.shrink_tiles);
     const int kc = local % P.kch;
     const int jb = (local / P.kch) % jblocks;
     const int share = (local / (P.kch * jblocks)) % shares;
     const int chunk = local / (P.kch * jblocks * shares);
     const int m_base = chunk * SHRINK_CHUNK_ROWS;
 
-    group_rows_lds64(a.row_adapter + m_base, min(SHRINK_CHUNK_ROWS, a.M - m_base), P.n_adapters, g);
-
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, lq = lane >> 4;
-    // k-steps of this block's K chunk (balanced split)
+    if (wave == 0) cut_row_tiles(a.row_adapter + m_base, min(SHRINK_CHUNK_ROWS, a.M - m_base), P.n_adapters, g);
+    __syncthreads();
+
+    // k-steps of this block's K chunk, then of this wave (balanced splits; a K chunk has at least four)
     const int nks = P.K / KSTEP;
     const int q = nks / P.kch, r = nks % P.kch;
     const int blk_beg = kc * q + min(kc, r), blk_cnt = q + (kc < r ? 1 : 0);
+    const int wq = blk_cnt / 4, wr = blk_cnt % 4;
+    const int my_beg = blk_beg + wave * wq + min(wave, wr), my_cnt = wq + (wave < wr ? 1 : 0);
     unsigned char *la = lds.a[wave], *lx = lds.x[wave];
     const u32x4 zero = {0u, 0u, 0u, 0u};
+    const int n_tiles = g.n_tiles;
+    const int batches = (my_cnt + SB - 1) / SB;
 
-    // tiles of the chunk in segment order; tile t belongs to wave (t mod 4 * shares) - 4 * share
-    const int n_seg = g.n_seg;
-    int t = 0;
-    for (int sg = 0; sg < n_seg; ++sg) {
-        const int seg_first = (int)g.seg_start[sg], seg_len = (int)g.seg_start[sg + 1] - seg_first;
-        const int adapter = g.seg_adapter[sg];
-        for (int u = 0; u < seg_len; u += 16, ++t) {
-            if (t % (4 * shares) != 4 * share + wave) continue;
-            const int first = seg_first + u;
-            const int rows_here = min(16, seg_len - u);
-            // loads: instruction i covers staged rows 4*i + lane/16, 16 bytes per lane (lane%16 of 16)
-            const uint16_t *xsrc[4], *asrc[4];
-            bool x_ok[4], a_ok[4];
+    // the block's tiles are share, share + shares, ..., four at a time
+    for (int t0 = share; t0 < n_tiles; t0 += 4 * shares) {
+        const int n_here = min(4, (n_tiles - t0 + shares - 1) / shares);
+        // what is requested next: tile and first k-step.  Instruction i covers staged rows 4*i + lane/16
+        // (rows of x; rank rows of A), 16 bytes per lane (lane%16 of 16).
+        int rq_tile = 0, rq_s0 = 0;
+        const uint16_t *xsrc[4], *asrc[4];
+        bool x_ok[4], a_ok[4];
+        u32x4 xv[DEPTH][4], av[DEPTH][4];
+        auto request = [&](int set) {
+            if (rq_tile >= n_here) return;
+            if (rq_s0 == 0) {
+                const int t = t0 + rq_tile * shares;
+                const int first = g.first[t], rows_here = (int)g.first[t + 1] - first, adapter = g.adapter[t];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int rr = 4 * i + lq;
+                    x_ok[i] = rr < rows_here;
+                    const int row = m_base + (x_ok[i] ? (int)g.perm[first + rr] : 0);
+                    // (int8 rows: the same element offsets, one byte each; kept as a uint16 pointer and
+                    // turned into a byte address where it is used)
+                    const size_t at = (size_t)row * P.K + (size_t)my_beg * KSTEP + l16 * 8;
+                    xsrc[i] = A8 ? reinterpret_cast<const uint16_t *>(reinterpret_cast<const unsigned char *>(P.x) + at) : P.x + at;
+                    const int j = jb * 16 + rr;
+                    a_ok[i] = j < P.rank;
+                    asrc[i] = P.lora_a + ((size_t)adapter * P.rank + (a_ok[i] ? j : 0)) * P.K + (size_t)my_beg * KSTEP + l16 * 8;
+                }
+            }
+            const bool k_ok = (l16 >> 2) < my_cnt - rq_s0;  // this lane's 8 inputs lie in k-step rq_s0 + l16/4
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int rr = 4 * i + lq;                  // staged row: tile row of x, rank row of A
-                x_ok[i] = rr < rows_here;
-                const int row = m_base + (x_ok[i] ? (int)g.perm[first + rr] : 0);
-                // (int8 rows: the same element offsets, one byte each; kept as a uint16 pointer and
-                // turned into a byte address where it is used)
-                xsrc[i] = A8 ? reinterpret_cast<const uint16_t *>(reinterpret_cast<const unsigned char *>(P.x) + (size_t)row * P.K + (size_t)blk_beg * KSTEP + l16 * 8)
-                             : P.x + (size_t)row * P.K + (size_t)blk_beg * KSTEP + l16 * 8;
-                const int j = jb * 16 + rr;
-                a_ok[i] = j < P.rank;
-                asrc[i] = P.lora_a + ((size_t)adapter * P.rank + (a_ok[i] ? j : 0)) * P.K + (size_t)blk_beg * KSTEP + l16 * 8;
+                if constexpr (A8) {
+                    uint2 v = make_uint2(0u, 0u);
+                    if (x_ok[i] && k_ok) v = *reinterpret_cast<const uint2 *>(reinterpret_cast<const unsigned char *>(xsrc[i]) + (size_t)rq_s0 * KSTEP);
+                    xv[set][i] = u32x4{v.x, v.y, 0u, 0u};   // (widened where it is used: here it would be waited for)
+                } else {
+                    xv[set][i] = (x_ok[i] && k_ok) ? *reinterpret_cast<const u32x4 *>(xsrc[i] + (size_t)rq_s0 * KSTEP) : zero;
+                }
+                av[set][i] = (a_ok[i] && k_ok) ? *reinterpret_cast<const u32x4 *>(asrc[i] + (size_t)rq_s0 * KSTEP) : zero;
             }
-            // four batches (a K chunk of 512 inputs, whole) in flight: the base blocks fill the
-            // memory queues at the same time, and a tile should cost one round trip, not four
-            constexpr int DEPTH = 2;
-            u32x4 xv[DEPTH][4], av[DEPTH][4];
-            auto request = [&](int set, int s0) {
-                const bool k_ok = (l16 >> 2) < blk_cnt - s0;    // this lane's 8 inputs lie in k-step s0 + l16/4
+            rq_s0 += SB;
+            if (rq_s0 >= my_cnt) {
+                rq_s0 = 0;
+                ++rq_tile;
+            }
+        };
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        int tile = 0, batch = 0;
+        auto consume = [&](int set) {
+            // (wave-private buffers: the wave's own LDS accesses are ordered, no barrier)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if constexpr (A8) {
-                        uint2 q = make_uint2(0u, 0u);
-                        if (x_ok[i] && k_ok) q = *reinterpret_cast<const uint2 *>(reinterpret_cast<const unsigned char *>(xsrc[i]) + (size_t)s0 * KSTEP);
-                        xv[set][i] = widen_int8(q.x, q.y);
-                    } else {
-                        xv[set][i] = (x_ok[i] && k_ok) ? *reinterpret_cast<const u32x4 *>(xsrc[i] + (size_t)s0 * KSTEP) : zero;
-                    }
-                    av[set][i] = (a_ok[i] && k_ok) ? *reinterpret_cast<const u32x4 *>(asrc[i] + (size_t)s0 * KSTEP) : zero;
-                }
-            };
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-            auto consume = [&](int set) {
-                // (wave-private buffers: the wave's own LDS accesses are ordered, no barrier)
+            for (int i = 0; i < 4; ++i) {
+                *reinterpret_cast<u32x4 *>(lx + (4 * i + lq) * L::ROW + l16 * 16) = A8 ? widen_int8(xv[set][i][0], xv[set][i][1]) : xv[set][i];
+                *reinterpret_cast<u32x4 *>(la + (4 * i + lq) * L::ROW + l16 * 16) = av[set][i];
+            }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    *reinterpret_cast<u32x4 *>(lx + (4 * i + lq) * L::ROW + l16 * 16) = xv[set][i];
-                    *reinterpret_cast<u32x4 *>(la + (4 * i + lq) * L::ROW + l16 * 16) = av[set][i];
-                }
+            for (int s = 0; s < SB; ++s) {
+                const uint4 xa = *reinterpret_cast<const uint4 *>(lx + l16 * L::ROW + s * 64 + 16 * lq);
+                const uint4 ab = *reinterpret_cast<const uint4 *>(la + l16 * L::ROW + s * 64 + 16 * lq);
+                acc = mfma16(xa, ab, acc);
+            }
+            if (++batch == batches) {
+                lds.red[wave][tile][lane] = acc;
+                acc = f32x4{0.f, 0.f, 0.f, 0.f};
+                batch = 0;
+                ++tile;
+            }
+        };
 #pragma unroll
-                for (int s = 0; s < SB; ++s) {
-                    const uint4 xa = *reinterpret_cast<const uint4 *>(lx + l16 * L::ROW + s * 64 + 16 * lq);
-                    const uint4 ab = *reinterpret_cast<const uint4 *>(la + l16 * L::ROW + s * 64 + 16 * lq);
-                    acc = mfma16(xa, ab, acc);
-                }
-            };
+        for (int d = 0; d < DEPTH; ++d) request(d);
+        const int items = n_here * batches;
+        for (int i = 0; i < items; i += DEPTH) {
 #pragma unroll
-            for (int d = 0; d < DEPTH; ++d)
-                if (d * SB < blk_cnt) request(d, d * SB);
-            for (int s0 = 0; s0 < blk_cnt; s0 += DEPTH * SB) {
-#pragma unroll
-                for (int d = 0; d < DEPTH; ++d) {
-                    if (s0 + d * SB < blk_cnt) {
-                        consume(d);
-                        if (s0 + (d + DEPTH) * SB < blk_cnt) request(d, s0 + (d + DEPTH) * SB);
-                    }
+            for (int d = 0; d < DEPTH; ++d) {
+                if (i + d < items) {
+                    consume(d);
+                    request(d);
                 }
             }
+        }
+        __syncthreads();
+        if (wave < n_here) {
+            const int t = t0 + wave * shares;
+            const int first = g.first[t], rows_here = (int)g.first[t + 1] - first;
+            f32x4 v = lds.red[0][wave][lane];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) v += lds.red[w][wave][lane];
             // lane (rank column l16, quarter lq) holds tile rows 4*lq + e
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int i = 4 * lq + e;
                 if (i < rows_here) {
                     const int m = m_base + g.perm[first + i];
-                    store_shared(P.t_part + ((size_t)kc * a.M + m) * P.r16 + jb * 16 + l16, acc[e]);
+                    store_shared(P.t_part + ((size_t)kc * a.M + m) * P.r16 + jb * 16 + l16, v[e]);
                 }
             }
         }
+        if (t0 + 4 * shares < n_tiles) __syncthreads();     // (the next tiles' sums go to the same place)
     }
     signal_done(a.ctrl + shrink_ctr(pi, 0), P.ctr_copies);
 }
@@ -1467,7 +1490,7 @@ __global__ __launch_bounds__(64 * Shape<MB>::WAVES, (occupancy_of<MB, XR>())) vo
         const int pi = z * GROUP_PROJ + find_proj(tables.shrink, b, first);
         // (the instances with one block of 16 rows are the ones launched for M <= 16)
         if constexpr (MB == 1) shrink_row_block(a, fetch_proj(a, pi), pi, b - first, *reinterpret_cast<ShrinkRowLds *>(smem));
-        else                   shrink_block<false>(a, fetch_proj(a, pi), pi, b - first, *reinterpret_cast<ShrinkLds *>(smem));
+        else                   shrink_block<false, 4>(a, fetch_proj(a, pi), pi, b - first, *reinterpret_cast<ShrinkLds *>(smem));
         return;
     }
     const BaseLdsOf<MB, XR> lds{smem};
@@ -2168,7 +2191,7 @@ __global__ __launch_bounds__(256, (MB == 2 ? 3 : 2)) void wide_kernel(const Laye
     int first;
     if (b < tables.shrink_blocks) {
         const int pi = z * GROUP_PROJ + find_proj(tables.shrink, b, first);
-        shrink_block<A8>(a, fetch_proj(a, pi), pi, b - first, *reinterpret_cast<ShrinkLds *>(smem));
+        shrink_block<A8, MB == 2 ? 2 : 4>(a, fetch_proj(a, pi), pi, b - first, *reinterpret_cast<ShrinkLds *>(smem));
         return;
     }
     WideLds<MB> &lds = *reinterpret_cast<WideLds<MB> *>(smem);

@@ -1,0 +1,56 @@
+"""Grouped shrink blocks (more than 16 rows): row tiles with one row and with sixteen, more tiles than a block
+takes at a time, waves with fewer k-steps than others, ranks that end inside a block of 16, rows without
+adapter, K units of 512 inputs, against the oracle.  Bars as everywhere: 5e-3 of max|y_ref| with bf16 outputs
+(rounding alone reaches 2^-8), 2e-4 with fp32 outputs, 5e-3 of the LoRA term's own maximum."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from gpu_util import check_linear, random_problem
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_of(kind, M, n_ad):
+    if kind == "one":
+        return np.zeros(M, np.int32)                               # full tiles
+    if kind == "each":
+        return (np.arange(M) % n_ad).astype(np.int32)              # as many tiles as adapters
+    if kind == "seventeen":
+        return (np.arange(M) // 17 % n_ad).astype(np.int32)        # a full tile and one of a row
+    rows = np.random.default_rng(M).integers(-1, n_ad, size=M).astype(np.int32)
+    rows[: M // 2] = -1                                            # whole chunks without adapter
+    return rows
+
+
+@pytest.mark.parametrize("kind", ["one", "each", "seventeen", "absent"])
+@pytest.mark.parametrize("M,K,N,G,r,n_ad", [(17, 128, 19264, 32, 8, 3),        # tile blocks; one k-step per wave
+                                            (32, 640, 19264, 64, 40, 32),      # 512 inputs per K chunk, 5 k-steps each
+                                            (33, 128, 70, 32, 16, 33),         # wide blocks; one tile per block
+                                            (64, 2176, 321, 128, 24, 64),      # 17 super-steps: units of 512 inputs
+                                            (65, 4224, 64, 32, 8, 5),          # two chunks, the second of one row
+                                            (127, 1152, 130, 64, 72, 16),
+                                            (200, 8320, 64, 32, 16, 64)])      # 2048 inputs per K chunk
+def test_row_tiles(gpu, kind, M, K, N, G, r, n_ad):
+    prob = random_problem(M + K, K, N, G, r, n_ad)
+    x = wl.f32_to_bf16_bits(np.random.default_rng(K).standard_normal((M, K)).astype(np.float32))
+    check_linear(gpu, prob, x, rows_of(kind, M, n_ad), f"{kind} M{M} K{K} N{N} G{G} r{r}")
+
+
+@pytest.mark.parametrize("n_proj", [1, 30, 120])                   # one, four, and eight or sixteen tiles per block
+@pytest.mark.parametrize("M", [40, 150])
+def test_tiles_per_block(gpu, n_proj, M):
+    lib, device, torch = gpu
+    K, N, n_ad = 256, 256, 40
+    prob = random_problem(7, K, N, 32, 16, n_ad)
+    p = device.upload_problem(prob)
+    x = device.to_device(wl.f32_to_bf16_bits(np.random.default_rng(1).standard_normal((M, K)).astype(np.float32)))
+    ra = torch.from_numpy(rows_of("each", M, n_ad)).cuda()
+    alone = device.alloc_y(M, N, 1)
+    lib.linear(p, x, ra, M, alone, 1, device.alloc_workspace([p], M))
+    ys = [device.alloc_y(M, N, 1) for _ in range(n_proj)]
+    lib.layer_step([p] * n_proj, [x] * n_proj, ys, ra, M, 1, device.alloc_workspace([p] * n_proj, M))
+    torch.cuda.synchronize()
+    # sums of 256 products in another order, fp32: far below 2e-4 of the largest
+    bar = 2e-4 * float(alone.abs().max())
+    assert all(float((y - alone).abs().max()) <= bar for y in ys)

@@ -85,29 +85,31 @@ int kch_of(const mlora_w4_proj &p, int M, bool wide)
 int plan_rows(int M, bool a8) { return a8 && M < WIDE32_MIN_ROWS ? WIDE32_MIN_ROWS : M; }
 
 // K units per column tile.  Tile blocks: units of at most 2048 inputs (16 super-steps: what a
-// block stages of x).  Wide blocks: any unit length works; a wide launch of fewer than 210 base
-// blocks (`launch_blocks`, counted with units of 2048 inputs) has units of about 1024, which fills
-// more compute units.  Measured in us, units of 2048 against 1024 inputs: 4096 x 4096 at 64 rows (64
-// blocks) 24.8 -> 18.0, 2048 x 8192 at 96 rows (96) 22.2 -> 17.2, 2048 x 2048 at 512 rows (128) 24.2
-// -> 19.1, int8 rows, 2048 x 2048 at 8 rows (8) 21.1 -> 15.3.  Over drawn calls of 200 to 209 blocks
-// units of 1024 take 0.92 of the time; of 210 to 220 and of 221 to 240 blocks as many calls lose by them as
-// gain: the partial tiles and the shorter loops cost what they bring.  Units of 512, int8 rows, 8 rows:
-// 2048 x 2048 15.3 -> 14.7, 8192 x 2048 20.5 -> 23.2, in groups of 128 14.0 -> 14.5 and 20.5 -> 23.2.
+// block stages of x).  Wide blocks: any unit length works, and a launch of few base blocks (`launch_blocks`,
+// counted with units of 2048 inputs) has shorter ones, which fill more compute units: a wave that has a
+// SIMD to itself takes 240 ns per k-step whatever the order of its instructions (unpacking beside the products
+// or before them), as it issues one in five cycles.  Below 210 blocks about 1024 inputs: over drawn calls
+// of 200 to 209 blocks they take 0.92 of the time; of 210 to 220 and of 221 to 240 blocks as many calls lose by
+// them as gain: the partial tiles and the shorter loops cost what they bring.  Below 80 blocks about 512 up to K =
+// 4096 (us, 1024 against 512: 1024 x 1024 at 40, 128 and 400 rows 15.9 -> 13.1, 15.9 -> 13.2 and 16.1 -> 13.8,
+// 2048 x 8192 at 64 (64 blocks) 18.0 -> 15.7, 4096 x 4096 at 64 (64) 18.2 -> 16.7, 3072 x 3072 at 40 20.1 -> 18.3),
+// not above, where a dozen partial tiles are added one trip after another: 8192 x 2048 at 64 19.6 -> 22.4; nor from 80
+// blocks on: 4096 x 4096 at 128 rows (128) 19.5 -> 25.2, 1024 x 4096 at 200 (112) 16.6 -> 14.3, 3072 x 3072 at
+// 100 (96) 21.9 -> 26.2.
 int ksplit_of(const mlora_w4_proj &p, bool wide, int launch_blocks)
 {
     const int nss = p.K / SUPER_K;
     int ks = (nss + UNIT_SUPER_STEPS - 1) / UNIT_SUPER_STEPS;
     if (wide && launch_blocks > 0 && launch_blocks < 210) {
-        constexpr int unit = 8;
+        const int unit = launch_blocks < 80 && nss <= 32 ? 4 : 8;
         const int cut = (nss + unit / 2) / unit;
         if (cut > ks) ks = cut;
     }
     return ks;
 }
 // Upper bound of that for every launch, which sizes a workspace and decides what is refused: units of
-// 1024 inputs up to 240 base blocks (counted with chunks of 64 rows), of 512 below 80.  No launch cuts its
-// inputs that fine; the sizes handed out and asked for stay what they have been, so that callers who
-// keep a size or a workspace need not care.
+// 1024 inputs up to 240 base blocks (counted with chunks of 64 rows), of 512 below 80.  The sizes handed out and
+// asked for stay what they have been, so that callers who keep a size or a workspace need not care.
 int ksplit_bound(const mlora_w4_proj &p, bool wide, int launch_blocks64)
 {
     const int nss = p.K / SUPER_K;

@@ -1560,15 +1560,16 @@ struct WideLds {
 //
 // 32 rows: products of 32 x 32 x 16 (a permlane swap of two code words turns the blob's order, made for
 // 16 columns, into theirs).  Per k-step of a group of 32 inputs 70 vector instructions (28 to unpack, 32
-// FMAs) and 6 products of 32 cycles, which run beside them: what bounds a compute unit's work is
+// FMAs) and 4 products of 32 cycles, which run beside them: what bounds a compute unit's work is
 // then the vector instructions, and what bounds a launch is how many blocks wait at once for memory.
 // The loop and all that follows it fit 168 registers without spills for every group size, so that three
 // blocks share a compute unit: 16 layers of a 1B-like model at 32 rows 191 -> 170 us (products of 16 x 16
 // x 32, two blocks).  A group of 128 inputs is two runs of two k-steps: in one run its fragments of x do
 // not fit (10 registers spilled inside the loop, the same launch in groups of 128 163 us against 146).
-// 64 rows: products of 16 x 16 x 32, whose 64 sums per lane leave the registers for it; with products
-// of 32 x 32 x 16 the same launch at 512 rows took 1684 us instead of 1625.  No spills in the loop; the
-// sum of partial tiles keeps 9 registers (int8 rows: 16) in scratch memory.
+// 64 rows: products of 16 x 16 x 32, whose 64 sums per lane leave the registers for it; with products of 32 x 32
+// x 16, whatever their order, 4 to 6 % fewer cycles of a clock that is 3 to 4 % slower (16 layers at 512 rows
+// 1391 us against 1394 and 1395).  No spills in the loop; the sum of partial tiles keeps 9 registers (int8
+// rows: 16) in scratch memory.
 // Codes that one block of rows reads (AGAIN false) are marked as used once; where several blocks of rows
 // read them, they stay in the cache for the next one (14336 x 4096 in groups of 128 at 64 rows, 32
 // adapters of rank 64: 46.1 -> 43.7 us; unmarked where one block reads them, 16 layers at 32 rows: 159 -> 168).

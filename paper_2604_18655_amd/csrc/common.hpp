@@ -270,9 +270,9 @@ constexpr int WIDE32_MIN_BLOCKS = 300;
 // per compute unit, and where the rows fill them: with rows a little above a multiple of 64, blocks of 32
 // rows waste half as many (lines drawn from 2592 calls of 33 to 1024 rows, ranks 8 to 128, 1 to 32 adapters).
 // Measured in us, blocks of 64 rows against 32, groups of 32 / of 128 inputs: 16 layers of a 1B-like
-// model at 512 rows (14848 blocks of 64 rows) 1519 against 1679 / 1348 against 1483; one such layer at 512
-// rows (928) 116 against 123 / 95 against 100, at 128 rows (232) 41 against 38 / 34 against 33; 3072 x 9216
-// twice at 72 rows (288 of 64, 432 of 32) 36 against 25.
+// model at 512 rows (14848 blocks of 64 rows) 1335 against 1529 / 1179 against 1321; one such layer at 512
+// rows (928) 98 against 110 / 85 against 94; with the lines drawn, at 128 rows (232) 41 against 38 / 34 against
+// 33, 3072 x 9216 twice at 72 rows (288 of 64, 432 of 32) 36 against 25.
 constexpr int WIDE64_MIN_BLOCKS = 320;
 __host__ inline bool wide64_pays(int blocks64, int blocks32) { return blocks64 >= WIDE64_MIN_BLOCKS && 5ll * blocks32 >= 9ll * blocks64; }
 constexpr int WIDE_TILES_PER_BLOCK = 4;

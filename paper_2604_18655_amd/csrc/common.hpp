@@ -25,8 +25,8 @@ namespace mlora {
 // logical operation) turns two of them into a pair of bf16 codes.
 // Four bits of sign and magnitude do not hold all of -8 .. 7.  A blob with a code -8 anywhere (a
 // quantiser that scales by max / 7 makes none) has its flag set, the first word of the blob's last 16
-// bytes, and stores m - 1 for its negative codes; the kernels run a second copy of their loops on
-// it, whose unpacking adds the 1 back.
+// bytes, and stores m - 1 for its negative codes; the kernels' unpacking adds the 1 back, six operations per
+// word (see split_codes for what that costs).
 //
 // Scales follow the codes: fp16, index ((tile * K/group + g) * 16 + c) * 4 + j for column
 // 64*tile + 16*j + c, so the lane that holds column c of all four blocks reads its four

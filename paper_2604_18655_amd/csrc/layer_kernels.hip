@@ -134,16 +134,18 @@ __device__ __forceinline__ uint4 codes_to_bf16(uint32_t lo, uint32_t hi)
     o.w = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 512.0f, true));
     return o;
 }
-template <bool FULL>
-__device__ __forceinline__ uint4 expand_codes(uint32_t w)
-{
-    return FULL ? codes_to_bf16(full_codes(low_codes(w)), full_codes(high_codes(w))) : codes_to_bf16(low_codes(w), high_codes(w));
-}
-// The halves of the four code words of a k-step.  `full` is the same for the whole block: the tile blocks
-// branch here, once per k-step, where a second copy of their loops would cost registers and code.
+// The halves of the four code words of a k-step.  `full` is the same for the whole block: every family of blocks
+// branches here, once per k-step, in the one loop that it has.  (A second copy of the loop for blobs with codes -8
+// costs registers and code: blocks of up to 8 rows spilled 24 registers and of up to 16 rows took 221 instead of 187;
+// with requests of its own, which had to wait for the flag, that copy took 17.3 us for the seven projections of a
+// layer at 8 rows, 166 for 16 layers, against 15.9 and 144 as it is and 15.0 and 141 for codes + 24.  Two
+// operations instead of three, a packed multiply-add on fields with the sign lowest, give nothing in the wide
+// blocks and 0.2 us in the layer.)  `RARE` keeps the loop without codes -8 free of jumps: 16.7 -> 16.4 us in a
+// graph for the layer at 8 rows; in the wide blocks it costs blobs with codes -8 3 % and the others nothing.
 struct CodeBytes {
     uint32_t lo[4], hi[4];
 };
+template <bool RARE>
 __device__ __forceinline__ CodeBytes split_codes(u32x4 w, bool full)
 {
     CodeBytes c;
@@ -152,7 +154,7 @@ __device__ __forceinline__ CodeBytes split_codes(u32x4 w, bool full)
         c.lo[j] = low_codes(w[j]);
         c.hi[j] = high_codes(w[j]);
     }
-    if (full) {
+    if (RARE ? __builtin_expect(full, 0) : full) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             c.lo[j] = full_codes(c.lo[j]);
@@ -309,7 +311,7 @@ __device__ __forceinline__ void round_compute(f32x4 (&acc)[MB][4], const unsigne
         f32x4 d[MB][4];
 #pragma unroll
         for (int s = 0; s < SPG; ++s) {
-            const CodeBytes cb = split_codes(wf[s], full);
+            const CodeBytes cb = split_codes<false>(wf[s], full);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint4 wb = codes_to_bf16(cb.lo[j], cb.hi[j]);
@@ -374,8 +376,8 @@ __device__ __forceinline__ void stream_request(StreamRegs &r, const u32x4 *wp0, 
 }
 
 // The math of one super-step; xs = this lane's row of x in LDS at the super-step's first k-step.
-template <int SPG, bool FULL>
-__device__ __forceinline__ void stream_math(f32x4 (&acc)[4], const StreamRegs &r, const unsigned char *xs)
+template <int SPG>
+__device__ __forceinline__ void stream_math(f32x4 (&acc)[4], const StreamRegs &r, const unsigned char *xs, bool full)
 {
     constexpr int GS = 4 / SPG;                                // scale groups per super-step
 #pragma unroll
@@ -384,10 +386,10 @@ __device__ __forceinline__ void stream_math(f32x4 (&acc)[4], const StreamRegs &r
 #pragma unroll
         for (int t = 0; t < SPG; ++t) {
             const uint4 xa = *reinterpret_cast<const uint4 *>(xs + (g * SPG + t) * 64);
-            const u32x4 wv = r.w[g * SPG + t];
+            const CodeBytes cb = split_codes<true>(r.w[g * SPG + t], full);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                d[j] = mfma16(xa, expand_codes<FULL>(wv[j]), t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : d[j]);
+                d[j] = mfma16(xa, codes_to_bf16(cb.lo[j], cb.hi[j]), t == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : d[j]);
         }
         const uint2 sv = r.sc[g];
 #pragma unroll
@@ -406,8 +408,8 @@ __device__ __forceinline__ void stream_math(f32x4 (&acc)[4], const StreamRegs &r
 // completion counters its epilogue depends on (poll_s, poll_p; before that, and for a wave that
 // depends on nothing, a dummy address): if they are complete by then, the epilogue need not wait
 // for a poll of its own.
-template <int SPG, bool FULL>
-__device__ __forceinline__ void stream_loop(f32x4 (&acc)[4], StreamRegs &ra, StreamRegs &rb, const u32x4 *wp0,
+template <int SPG>
+__device__ __forceinline__ void stream_loop(f32x4 (&acc)[4], bool full, StreamRegs &ra, StreamRegs &rb, const u32x4 *wp0,
                                             const uint2 *sp0, int n_ss, const unsigned char *xl, int lane,
                                             const unsigned *poll_s, const unsigned *poll_p,
                                             unsigned &seen_s, unsigned &seen_p)
@@ -418,9 +420,9 @@ __device__ __forceinline__ void stream_loop(f32x4 (&acc)[4], StreamRegs &ra, Str
         const bool last = ss + 2 >= n_ss;
         seen_s = __hip_atomic_load(last ? poll_s : dummy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         seen_p = __hip_atomic_load(last ? poll_p : dummy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        stream_math<SPG, FULL>(acc, ra, xl + ss * 256);
+        stream_math<SPG>(acc, ra, xl + ss * 256, full);
         stream_request<SPG>(ra, wp0, sp0, ss + 2, n_ss, lane);
-        if (ss + 1 < n_ss) stream_math<SPG, FULL>(acc, rb, xl + (ss + 1) * 256);
+        if (ss + 1 < n_ss) stream_math<SPG>(acc, rb, xl + (ss + 1) * 256, full);
         stream_request<SPG>(rb, wp0, sp0, ss + 3, n_ss, lane);
     }
 }
@@ -770,15 +772,7 @@ __device__ __forceinline__ void base_unit(const LayerArgs &a, const ProjArgs &P,
             __builtin_amdgcn_sched_barrier(0);                 // (the requests stay ahead of the wait for x)
 #pragma unroll
             for (int i = 0; i < XR; ++i) *reinterpret_cast<u32x4 *>(buf + lane * 16 + i * L::XROW) = xr[i];
-            if (!flag_set(flag)) {
-                stream_loop<SPG, false>(acc[0], sa, sb, wp, sp, my_cnt, xl, lane, poll_s, poll_p, seen_s, seen_p);
-            } else {
-                // (a second copy of the loop, with requests of its own: one loop with a branch in it took
-                // 0.3 us more of a layer's 15)
-                stream_request<SPG>(sa, wp, sp, 0, max(my_cnt, 1), lane);
-                stream_request<SPG>(sb, wp, sp, 1, my_cnt, lane);
-                stream_loop<SPG, true>(acc[0], sa, sb, wp, sp, my_cnt, xl, lane, poll_s, poll_p, seen_s, seen_p);
-            }
+            stream_loop<SPG>(acc[0], flag_set(flag), sa, sb, wp, sp, my_cnt, xl, lane, poll_s, poll_p, seen_s, seen_p);
         };
         if (P.spg == 1)      loop(std::integral_constant<int, 1>{});
         else if (P.spg == 2) loop(std::integral_constant<int, 2>{});
@@ -1659,7 +1653,7 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
                     if ((r + 1) * SG % SPG == 0) sc[G0 + g] = load_scales(st * S + g * SPG + W);   // (last run of its group)
                     CodeBytes cw[SG];
 #pragma unroll
-                    for (int t = 0; t < SG; ++t) cw[t] = split_codes(w[H * S + r * SG + t], full_blob);
+                    for (int t = 0; t < SG; ++t) cw[t] = split_codes<false>(w[H * S + r * SG + t], full_blob);
 #pragma unroll
                     for (int cb = 0; cb < 2; ++cb) {
                         f32x16 d = f32x16{0.f};
@@ -1685,7 +1679,7 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
                     if ((r + 1) * SG % SPG == 0) sc[G0 + g] = load_scales(st * S + g * SPG + W);   // (last run of its group)
                     CodeBytes cw[SG];
 #pragma unroll
-                    for (int t = 0; t < SG; ++t) cw[t] = split_codes(w[H * S + r * SG + t], full_blob);
+                    for (int t = 0; t < SG; ++t) cw[t] = split_codes<false>(w[H * S + r * SG + t], full_blob);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         f32x4 d[MB];

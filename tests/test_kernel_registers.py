@@ -1,6 +1,7 @@
 """Registers of the compiled kernels, from the code object that the build left: the wide blocks of 32
 rows must fit 168 registers, three blocks per compute unit, without spilling any of them (a spill
-inside their K loop cost 12 % of a decoding stack in groups of 128)."""
+inside their K loop cost 12 % of a decoding stack in groups of 128); so must the blocks of up to 8 rows, whose
+call is a chain of trips to memory that spills lengthen."""
 import os
 import re
 import subprocess
@@ -31,3 +32,10 @@ def test_wide_blocks_of_32_rows_fit_their_registers(tmp_path):
     assert wide
     for name, (registers, spilled) in wide.items():
         assert registers <= 168 and spilled == 0, (name, registers, spilled)
+
+
+def test_blocks_of_up_to_8_rows_fit_their_registers(tmp_path):
+    rows8 = [v for name, v in kernels(tmp_path).items() if "layer_kernelILi1ELi8E" in name]
+    assert rows8
+    for registers, spilled in rows8:
+        assert registers <= 168 and spilled == 0, (registers, spilled)

@@ -215,7 +215,8 @@ static int launch_run(const mlora_w4_proj *projs, int n_left, int M)
 struct LaunchNeed {
     size_t ctrl_bytes, data_bytes;     // of this launch
     size_t ctrl_bound, data_bound;     // what a workspace is sized for (never less)
-    int grid_x, groups, rpc, block_rows;
+    long long grid_x;
+    int groups, rpc, block_rows;
 };
 
 static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *xs, void *const *ys,
@@ -259,7 +260,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
     bool shared = false;                       // anything handed from block to block?
     size_t part_lines = 0, data_bytes = 0, bound_lines = 0, data_bound = 0;
     int part_ctr = count * CTR_REPL * CTR_STRIDE;
-    int grid_x = 0;
+    long long grid_x = 0;
     if (a) {
         for (int z = 0; z < MAX_GROUPS; ++z)
             for (int i = 0; i < GROUP_PROJ; ++i)
@@ -352,7 +353,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
             a->pre_base_blocks[z] = pre_blocks;
             a->group_blocks[z] = total;
         }
-        if (total > grid_x) grid_x = total;
+        grid_x = std::max(grid_x, group_grid_x(shrink_blocks, total - shrink_blocks, row_blocks));
     }
     need.ctrl_bound = shared || bound_lines > 0 ? ((size_t)count * CTR_REPL + bound_lines) * CTR_STRIDE * sizeof(unsigned) : 0;
     need.data_bound = data_bound;
@@ -433,7 +434,7 @@ mlora_status mlora_w4_layer_step_plan(const mlora_w4_proj *projs, int32_t n_proj
         if (first == 0) {
             info[1] = launch_is_wide(projs, count, M, false) ? 1 : 0;
             info[2] = need.rpc;
-            info[3] = need.grid_x;
+            info[3] = (int32_t)std::min<long long>(need.grid_x, 0x7FFFFFFF);
             info[4] = need.groups;
         }
     }
@@ -545,7 +546,7 @@ static mlora_status enqueue_call(const mlora_w4_proj *projs, int32_t n_proj, con
         const mlora_status st = plan_launch(projs + first, xs + first, ys + first, count, Mp, a8, lora_on, need,
                                             a.get(), ctrl, data, x_scales ? x_scales + first : nullptr);
         if (st != MLORA_OK) return st;         // (cannot happen: the sizing pass has seen the same shapes)
-        if (launch_layer(*a, need.groups, s) != hipSuccess) return MLORA_EHIP;
+        if (launch_layer(*a, need.grid_x, need.groups, s) != hipSuccess) return MLORA_EHIP;
         ctrl += need.ctrl_bytes;
         data += need.data_bytes;
     }

@@ -241,6 +241,15 @@ __host__ __device__ inline int shrink_tile_shares(int M, int n_adapters, int til
     return (tiles + tiles_per_block - 1) / tiles_per_block;
 }
 
+// Blocks along x of a group of projections in the grid (see split_block_index): shrink blocks once, base blocks for
+// every block of rows.
+__host__ __device__ inline unsigned filled_up(unsigned blocks) { return (blocks + 7u) & ~7u; }
+inline long long group_grid_x(int shrink_blocks, int base_blocks, int row_blocks)
+{
+    return row_blocks == 1 ? (long long)shrink_blocks + base_blocks
+                           : filled_up((unsigned)shrink_blocks) + (long long)filled_up((unsigned)base_blocks) * row_blocks;
+}
+
 // host launchers (each file defines its own)
 hipError_t launch_prepack(int K, int N, int group, const uint8_t *wq, const uint16_t *scales,
                           void *blob, hipStream_t s);
@@ -248,7 +257,7 @@ hipError_t launch_unpack(int K, int N, int group, const void *blob, int8_t *code
                          hipStream_t s);
 hipError_t launch_group_rows(const int *row_adapter, int M, int n_adapters, int *perm,
                              int *seg_adapter, int *seg_start, int *n_seg, hipStream_t s);
-hipError_t launch_layer(const LayerArgs &a, int groups, hipStream_t s);
+hipError_t launch_layer(const LayerArgs &a, long long grid_x, int groups, hipStream_t s);
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t s);
 hipError_t launch_rms_scale(const uint16_t *x, int M, int K, float eps, float *scale, hipStream_t s);
 hipError_t launch_lora_int16_expand(const int16_t *aq, const int16_t *bq, int n_adapters, int rank, int K, int N,

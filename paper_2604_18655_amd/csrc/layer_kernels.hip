@@ -22,7 +22,6 @@
 // rows of A[adapter]); the partial sums go to t_part[chunk][row][rank].  Up to 16 rows: a block
 // per (row, 16 ranks, K chunk).  More rows: the rows of a chunk of 64 are grouped by adapter
 // and cut into tiles of 16, and a block's four waves share the inputs of every tile.
-#include <algorithm>
 #include <type_traits>
 
 #include "group_rows.hpp"
@@ -1450,7 +1449,6 @@ __device__ __forceinline__ int find_proj(const i32x16 &begin, int b, int &first)
 // read 5.9 x the algorithmic bytes from HBM at 512 rows.)  A producer still has a smaller index
 // than its consumer: a split-K block and the block that finishes its tile have the same chunk.
 // b past the group's last block: nothing to do.
-__host__ __device__ inline unsigned filled_up(unsigned blocks) { return (blocks + 7u) & ~7u; }
 __device__ __forceinline__ void split_block_index(const LayerArgs &a, const LaunchTables &t, int &b, int &chunk)
 {
     const unsigned id = blockIdx.x, chunks = (unsigned)a.row_blocks, shrink = (unsigned)t.shrink_blocks;
@@ -2208,19 +2206,12 @@ static hipError_t launch_instance(const LayerArgs &a, const dim3 &grid, hipStrea
     return hipGetLastError();
 }
 
-// grid: x = the longest group's blocks, its base blocks x row chunks (see split_block_index), z = groups of up
+// grid: x = the longest of the groups (see group_grid_x), z = groups of up
 // to 16 projections; blocks past a group's last one exit at once
-hipError_t launch_layer(const LayerArgs &a, int groups, hipStream_t s)
+hipError_t launch_layer(const LayerArgs &a, long long grid_x, int groups, hipStream_t s)
 {
-    const int n_chunks = a.row_blocks;
-    long long gx = 0;
-    for (int z = 0; z < groups; ++z) {
-        const long long base = a.group_blocks[z] - a.shrink_blocks[z];
-        gx = std::max(gx, n_chunks == 1 ? (long long)a.group_blocks[z]
-                                        : filled_up((unsigned)a.shrink_blocks[z]) + (long long)filled_up((unsigned)base) * n_chunks);
-    }
-    if (gx > 0x7FFFFFFFll) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)gx, 1u, (unsigned)groups);
+    if (grid_x > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)grid_x, 1u, (unsigned)groups);
     if (a.wide) {
         // (the host puts only projections with the same group size into one such launch)
         const int spg = a.p[0].spg;
@@ -2243,7 +2234,7 @@ hipError_t launch_layer(const LayerArgs &a, int groups, hipStream_t s)
     }
     // (the rows per block the host laid the launch out for: a short launch of 17 to 32 rows has
     // blocks of 16 rows)
-    if (n_chunks * a.block_rows < a.M) return hipErrorInvalidValue;
+    if (a.row_blocks * a.block_rows < a.M) return hipErrorInvalidValue;
     if (a.block_rows == 16) return a.M <= 8 ? launch_instance<1, 8>(a, grid, s) : launch_instance<1, 16>(a, grid, s);
     if (a.M <= 24) return launch_instance<2, 24>(a, grid, s);
     return launch_instance<2, 32>(a, grid, s);

@@ -117,6 +117,19 @@ def test_layer_step_plan_names_the_kernel_family():
     assert plan(many, 130, 16)[:3] == [2, 0, 16]
     mixed = (binding._ProjStruct * 2)(proj(K=2048, group=32, rank=16), proj(K=2048, group=64, rank=16))
     assert plan(mixed, 2, 16)[0] == 1 and plan(mixed, 2, 17)[0] == 2   # group size changes
+    # grid.x: shrink blocks, filled up to runs of 8, once; base blocks, filled up as well, for every block of rows
+    def grid_x(arr, n, M):
+        return plan(arr, n, M)[3]
+
+    five = (binding._ProjStruct * 5)(*[proj(K=2048, N=704, rank=24, n_ad=3) for _ in range(5)])
+    bare = (binding._ProjStruct * 5)(*[proj(K=2048, N=704, n_ad=0) for _ in range(5)])
+    for M in (33, 64, 100, 512, 2000):
+        rows = cdll.mlora_w4_layer_step_block_rows(five, 5, M, 0)
+        base, shrink = grid_x(bare, 5, M), grid_x(five, 5, M) - grid_x(bare, 5, M)
+        assert base % (8 * -(-M // rows)) == 0 and shrink % 8 == 0
+        # at most as many as a tile of 16 rows, 16 ranks and 1024 inputs each, of every chunk of 64 rows
+        assert 0 < shrink <= 5 * -(-M // 64) * 7 * 2 * 2 + 7, (M, shrink)
+    assert grid_x(one, 1, 8) == 8 * 2 + 32                # one block of rows: 8 rows x 2 K chunks, 32 column tiles
     assert cdll.mlora_w4_layer_step_plan(one, 1, 0, info) == ESHAPE
     assert cdll.mlora_w4_layer_step_plan(one, 0, 8, info) == EINVAL
     assert cdll.mlora_w4_layer_step_plan(one, 1, 8, None) == EINVAL

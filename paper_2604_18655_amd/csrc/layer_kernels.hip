@@ -1137,7 +1137,10 @@ __device__ __forceinline__ void base_unit(const LayerArgs &a, const ProjArgs &P,
 // up to four tiles at a time.  What bounds a block is the trips to memory behind one another: a quarter of
 // 256 inputs is one trip (two batches in registers), where a wave that worked through a K chunk of a tile by
 // itself needed four (t of 14336 inputs, 64 rows, 32 adapters of rank 64: 34 -> 21 us after the start of
-// the launch, the whole call 46 -> 33 us).  DEPTH = batches in registers: four where 256 are there.
+// the launch, the whole call 46 -> 33 us).  In a K chunk of one or two batches a quarter would be a batch with one or two
+// k-steps in it, and every wave would stage every tile: there one or two waves share a tile (128 x 4991 at 276 rows,
+// rank 128, 19.6 -> 16.9 us; 41 drawn calls of 128 inputs 0.94 of the time, 64 of 256 inputs 0.99).  DEPTH = batches
+// in registers: four where 256 are there (whose kernels have no registers for that second form).
 struct ShrinkLds {
     static constexpr int SB = 4;                            // k-steps per batch
     static constexpr int ROW = SB * 64 + 16;                // bytes of a staged row; +16: rows 4 banks apart
@@ -1147,42 +1150,43 @@ struct ShrinkLds {
     alignas(16) f32x4 red[4][4][64];                        // a wave's share of four tiles
 };
 
-template <bool A8, int DEPTH>
-__device__ __forceinline__ void shrink_block(const LayerArgs &a, const ProjArgs &P, int pi, int local, ShrinkLds &lds)
+// The tiles of one block: share, share + shares, ... of its chunk of rows, four at a time.  PARTS waves share the
+// inputs of a tile (a balanced split of the block's k-steps), the others have tiles of their own.
+template <bool A8, int DEPTH, int PARTS>
+__device__ __forceinline__ void shrink_tiles(const LayerArgs &a, const ProjArgs &P, ShrinkLds &lds, int m_base, int share, int shares,
+                                             int jb, int kc, int blk_beg, int blk_cnt)
 {
     using L = ShrinkLds;
     constexpr int SB = L::SB;
+    constexpr int STEP = 4 / PARTS;                         // a wave's tiles of the four: my_slot, my_slot + STEP, ...
     RowTiles &g = lds.g;
-    const int jblocks = P.r16 / 16;
-    const int shares = shrink_tile_shares(a.M_plan, P.n_adapters, a.shrink_tiles);
-    const int kc = local % P.kch;
-    const int jb = (local / P.kch) % jblocks;
-    const int share = (local / (P.kch * jblocks)) % shares;
-    const int chunk = local / (P.kch * jblocks * shares);
-    const int m_base = chunk * SHRINK_CHUNK_ROWS;
-
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, lq = lane >> 4;
-    if (wave == 0) cut_row_tiles(a.row_adapter + m_base, min(SHRINK_CHUNK_ROWS, a.M - m_base), P.n_adapters, g);
-    __syncthreads();
-
-    // k-steps of this block's K chunk, then of this wave (balanced splits; a K chunk has at least four)
-    const int nks = P.K / KSTEP;
-    const int q = nks / P.kch, r = nks % P.kch;
-    const int blk_beg = kc * q + min(kc, r), blk_cnt = q + (kc < r ? 1 : 0);
-    const int wq = blk_cnt / 4, wr = blk_cnt % 4;
-    const int my_beg = blk_beg + wave * wq + min(wave, wr), my_cnt = wq + (wave < wr ? 1 : 0);
+    const int part = wave % PARTS, my_slot = wave / PARTS;
+    const int wq = blk_cnt / PARTS, wr = blk_cnt % PARTS;
+    const int my_beg = blk_beg + part * wq + min(part, wr), my_cnt = wq + (part < wr ? 1 : 0);
+    const int batches = (my_cnt + SB - 1) / SB;
     unsigned char *la = lds.a[wave], *lx = lds.x[wave];
     const u32x4 zero = {0u, 0u, 0u, 0u};
     const int n_tiles = g.n_tiles;
-    const int batches = (my_cnt + SB - 1) / SB;
+    // the sums of tile t, lane (rank column l16, quarter lq) with tile rows 4*lq + e
+    auto store_tile = [&](int t, const f32x4 &v) {
+        const int first = g.first[t], rows_here = (int)g.first[t + 1] - first;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = 4 * lq + e;
+            if (i < rows_here) {
+                const int m = m_base + g.perm[first + i];
+                store_shared(P.t_part + ((size_t)kc * a.M + m) * P.r16 + jb * 16 + l16, v[e]);
+            }
+        }
+    };
 
-    // the block's tiles are share, share + shares, ..., four at a time
     for (int t0 = share; t0 < n_tiles; t0 += 4 * shares) {
         const int n_here = min(4, (n_tiles - t0 + shares - 1) / shares);
         // what is requested next: tile and first k-step.  Instruction i covers staged rows 4*i + lane/16
         // (rows of x; rank rows of A), 16 bytes per lane (lane%16 of 16).
-        int rq_tile = 0, rq_s0 = 0;
+        int rq_tile = my_slot, rq_s0 = 0;
         const uint16_t *xsrc[4], *asrc[4];
         bool x_ok[4], a_ok[4];
         u32x4 xv[DEPTH][4], av[DEPTH][4];
@@ -1220,11 +1224,11 @@ __device__ __forceinline__ void shrink_block(const LayerArgs &a, const ProjArgs 
             rq_s0 += SB;
             if (rq_s0 >= my_cnt) {
                 rq_s0 = 0;
-                ++rq_tile;
+                rq_tile += STEP;
             }
         };
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        int tile = 0, batch = 0;
+        int tile = my_slot, batch = 0;
         auto consume = [&](int set) {
             // (wave-private buffers: the wave's own LDS accesses are ordered, no barrier)
 #pragma unroll
@@ -1239,15 +1243,16 @@ __device__ __forceinline__ void shrink_block(const LayerArgs &a, const ProjArgs 
                 acc = mfma16(xa, ab, acc);
             }
             if (++batch == batches) {
-                lds.red[wave][tile][lane] = acc;
+                if constexpr (PARTS == 1) store_tile(t0 + tile * shares, acc);
+                else                      lds.red[part][tile][lane] = acc;
                 acc = f32x4{0.f, 0.f, 0.f, 0.f};
                 batch = 0;
-                ++tile;
+                tile += STEP;
             }
         };
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) request(d);
-        const int items = n_here * batches;
+        const int items = (n_here - my_slot + STEP - 1) / STEP * batches;
         for (int i = 0; i < items; i += DEPTH) {
 #pragma unroll
             for (int d = 0; d < DEPTH; ++d) {
@@ -1257,25 +1262,41 @@ __device__ __forceinline__ void shrink_block(const LayerArgs &a, const ProjArgs 
                 }
             }
         }
+        if constexpr (PARTS == 1) continue;
         __syncthreads();
         if (wave < n_here) {
-            const int t = t0 + wave * shares;
-            const int first = g.first[t], rows_here = (int)g.first[t + 1] - first;
             f32x4 v = lds.red[0][wave][lane];
 #pragma unroll
-            for (int w = 1; w < 4; ++w) v += lds.red[w][wave][lane];
-            // lane (rank column l16, quarter lq) holds tile rows 4*lq + e
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int i = 4 * lq + e;
-                if (i < rows_here) {
-                    const int m = m_base + g.perm[first + i];
-                    store_shared(P.t_part + ((size_t)kc * a.M + m) * P.r16 + jb * 16 + l16, v[e]);
-                }
-            }
+            for (int w = 1; w < PARTS; ++w) v += lds.red[w][wave][lane];
+            store_tile(t0 + wave * shares, v);
         }
         if (t0 + 4 * shares < n_tiles) __syncthreads();     // (the next tiles' sums go to the same place)
     }
+}
+
+template <bool A8, int DEPTH>
+__device__ __forceinline__ void shrink_block(const LayerArgs &a, const ProjArgs &P, int pi, int local, ShrinkLds &lds)
+{
+    constexpr int SB = ShrinkLds::SB;
+    RowTiles &g = lds.g;
+    const int jblocks = P.r16 / 16;
+    const int shares = shrink_tile_shares(a.M_plan, P.n_adapters, a.shrink_tiles);
+    const int kc = local % P.kch;
+    const int jb = (local / P.kch) % jblocks;
+    const int share = (local / (P.kch * jblocks)) % shares;
+    const int chunk = local / (P.kch * jblocks * shares);
+    const int m_base = chunk * SHRINK_CHUNK_ROWS;
+
+    if (threadIdx.x < 64) cut_row_tiles(a.row_adapter + m_base, min(SHRINK_CHUNK_ROWS, a.M - m_base), P.n_adapters, g);
+    __syncthreads();
+
+    // k-steps of this block's K chunk (balanced split; a K chunk has at least four)
+    const int nks = P.K / KSTEP;
+    const int q = nks / P.kch, r = nks % P.kch;
+    const int blk_beg = kc * q + min(kc, r), blk_cnt = q + (kc < r ? 1 : 0);
+    if (DEPTH == 2 && blk_cnt <= SB)          shrink_tiles<A8, DEPTH, 1>(a, P, lds, m_base, share, shares, jb, kc, blk_beg, blk_cnt);
+    else if (DEPTH == 2 && blk_cnt <= 2 * SB) shrink_tiles<A8, DEPTH, 2>(a, P, lds, m_base, share, shares, jb, kc, blk_beg, blk_cnt);
+    else                                      shrink_tiles<A8, DEPTH, 4>(a, P, lds, m_base, share, shares, jb, kc, blk_beg, blk_cnt);
     signal_done(a.ctrl + shrink_ctr(pi, 0), P.ctr_copies);
 }
 

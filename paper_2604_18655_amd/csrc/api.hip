@@ -244,18 +244,24 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
     const int shrink_chunks = (M + SHRINK_CHUNK_ROWS - 1) / SHRINK_CHUNK_ROWS;
     // most row tiles of a grouped shrink block (see SHRINK_ALL_LIVE_BLOCKS)
     int shrink_tiles = wide && block_rows == 32 ? 8 : 16;
-    for (int tiles = 1; lora_on && Mc > 16 && tiles <= 4; tiles *= 4) {
-        long long live = 0;
+    if (lora_on && Mc > 16) {
+        long long base = 0;
+        int longest = 0;                       // of the inputs with adapters
         for (int i = 0; i < count; ++i) {
-            const mlora_w4_proj &p = projs[i];
-            live += (long long)((tiles_n(p.N) + tiles_per_block(wide) - 1) / tiles_per_block(wide)) * row_blocks * ksplit_of(p, wide, lb);
-            if (p.n_adapters > 0)
-                live += (long long)shrink_chunks * shrink_tile_shares(M, p.n_adapters, tiles) * (r16_of(p) / 16) * kch_of(p, M, wide);
+            base += (long long)((tiles_n(projs[i].N) + tiles_per_block(wide) - 1) / tiles_per_block(wide)) * row_blocks * ksplit_of(projs[i], wide, lb);
+            if (projs[i].n_adapters > 0) longest = std::max(longest, (int)projs[i].K);
         }
-        if (live <= SHRINK_ALL_LIVE_BLOCKS) {
-            shrink_tiles = tiles;
-            break;
-        }
+        auto shrink_blocks = [&](int tiles) {
+            long long n = 0;
+            for (int i = 0; i < count; ++i)
+                if (projs[i].n_adapters > 0)
+                    n += (long long)shrink_chunks * shrink_tile_shares(M, projs[i].n_adapters, tiles) * (r16_of(projs[i]) / 16) * kch_of(projs[i], M, wide);
+            return n;
+        };
+        const bool whole_tiles = wide && block_rows == 32 && longest <= SUPER_K;    // a tile per wave
+        if (!whole_tiles && base + shrink_blocks(1) <= SHRINK_ALL_LIVE_BLOCKS) shrink_tiles = 1;
+        else if (base + shrink_blocks(4) <= SHRINK_ALL_LIVE_BLOCKS) shrink_tiles = 4;
+        else if (wide && shrink_blocks(4) <= SHRINK_FEW_BLOCKS) shrink_tiles = 4;
     }
     bool shared = false;                       // anything handed from block to block?
     size_t part_lines = 0, data_bytes = 0, bound_lines = 0, data_bound = 0;

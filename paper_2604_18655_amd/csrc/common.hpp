@@ -222,11 +222,17 @@ __device__ inline f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
 // bound of the tiles of a chunk of `rows` rows (at most 64): a tile per 16 rows plus one per
 // segment, at most a tile per row.  The chunk's tiles are shared out over blocks of up to 8 (wide blocks of 32
 // rows) or 16 (the others, which have two places per compute unit: 16 layers at 512 rows 1313 us against 1342
-// with 8, a layer at 32 rows in tile blocks 25 against 29).  Where all blocks of the launch, idle ones
-// included, find a place at once, the finishing blocks wait for t, and a block gets one tile, or up to 4 if that
-// is too many blocks (4096 x 14336 at 64 rows, 32 adapters of rank 64: 41.5 us with 16 tiles, 35.4 with 4;
-// 14336 x 4096 49.5 and 32.5; 8192 x 2048 at 64 rows, 8 adapters of rank 16, 40 with 16, 22.7 with 4, 19.4 with
-// 1).  Host (grid size) and device (block index -> chunk, share) use the same figures.
+// with 8, a layer at 32 rows in tile blocks 25 against 29) where a launch has many of them.  Fewer tiles are a shorter
+// chain ahead of every block that finishes outputs, more are fewer blocks, idle ones included, whose signals queue up at
+// the same counters.  One tile per block where all blocks of the launch find a place at once with it
+// (SHRINK_ALL_LIVE_BLOCKS; 8192 x 2048 at 64 rows, 8 adapters of rank 16, 40 us with 16, 22.7 with 4, 19.4 with
+// 1), unless every wave has tiles of its own (128 inputs: 100 drawn calls at 17 to 700 rows 0.98 of the time with 4);
+// else 4 where they do with 4 (4096 x 14336 at 64 rows, 32 adapters of rank 64: 41.5 us with 16 tiles, 35.4 with 4; 14336
+// x 4096 49.5 and 32.5), or, in wide blocks, where 4 make at most 300 shrink blocks (SHRINK_FEW_BLOCKS; 4352 x
+// 5466 at 441 rows, 10 adapters of rank 32, 80 us with 8, 49 with 4, 4480 x 12672 at 320 rows 97 and 65; 280 drawn calls of
+// 3000 to 14336 outputs at 150 to 1024 rows 0.97 of the time, 8 of them more than 3 % longer, by 17 % at most; 320
+// to 480 such blocks: as many calls lose as gain, 3328 x 3563 at 593 rows 52 -> 61).
+// Host (grid size) and device (block index -> chunk, share) use the same figures.
 constexpr int SHRINK_CHUNK_ROWS = 64;
 __host__ __device__ inline int max_row_tiles(int rows, int n_adapters)
 {
@@ -234,7 +240,7 @@ __host__ __device__ inline int max_row_tiles(int rows, int n_adapters)
     const int bound = rows / 16 + segs;
     return bound < rows ? bound : rows;
 }
-constexpr int SHRINK_ALL_LIVE_BLOCKS = 500;
+constexpr int SHRINK_ALL_LIVE_BLOCKS = 500, SHRINK_FEW_BLOCKS = 300;
 __host__ __device__ inline int shrink_tile_shares(int M, int n_adapters, int tiles_per_block)
 {
     const int tiles = max_row_tiles(M < SHRINK_CHUNK_ROWS ? M : SHRINK_CHUNK_ROWS, n_adapters);

@@ -356,20 +356,20 @@ struct StreamRegs {
 // lane's offset).  A request past the wave's range (ss >= n_ss) becomes one 16-byte read of the
 // first chunk by all lanes: every load stays unconditional, so the waits the compiler derives
 // stay exact, and the useless ones cost next to nothing.
-template <int SPG>
-__device__ __forceinline__ void stream_request(StreamRegs &r, const u32x4 *wp0, const uint2 *sp0, int ss, int n_ss, int lane)
+// gs = scale groups of a super-step, at most MAX_GS; what is left of the registers takes the last one.
+template <int MAX_GS>
+__device__ __forceinline__ void stream_request(StreamRegs &r, const u32x4 *wp0, const uint2 *sp0, int ss, int n_ss, int lane, int gs)
 {
-    constexpr int GS = 4 / SPG;                                // scale groups per super-step
     const bool in = ss < n_ss;
     const u32x4 *wn = wp0 + (in ? (size_t)ss * 256 + lane : 0);
-    const uint2 *sn = sp0 + (in ? (size_t)ss * GS * 16 + (lane & 15) : 0);
+    const uint2 *sn = sp0 + (in ? (size_t)ss * gs * 16 + (lane & 15) : 0);
 #pragma unroll
     for (int u = 0; u < 4; ++u) r.w[u] = __builtin_nontemporal_load(wn + (in ? u * 64 : 0));
 #pragma unroll
-    for (int g = 0; g < GS; ++g) {
+    for (int g = 0; g < MAX_GS; ++g) {
         // (the scales' type is HIP's struct, which the builtin does not take: read as two words)
         const unsigned long long v = __builtin_nontemporal_load(
-            reinterpret_cast<const unsigned long long *>(sn + (in ? g * 16 : 0)));
+            reinterpret_cast<const unsigned long long *>(sn + (in ? min(g, gs - 1) * 16 : 0)));
         r.sc[g] = make_uint2((unsigned)v, (unsigned)(v >> 32));
     }
 }
@@ -413,6 +413,7 @@ __device__ __forceinline__ void stream_loop(f32x4 (&acc)[4], bool full, StreamRe
                                             const unsigned *poll_s, const unsigned *poll_p,
                                             unsigned &seen_s, unsigned &seen_p)
 {
+    constexpr int GS = 4 / SPG;                                // scale groups per super-step
     const unsigned *dummy = reinterpret_cast<const unsigned *>(wp0);
 #pragma nounroll
     for (int ss = 0; ss < n_ss; ss += 2) {
@@ -420,9 +421,9 @@ __device__ __forceinline__ void stream_loop(f32x4 (&acc)[4], bool full, StreamRe
         seen_s = __hip_atomic_load(last ? poll_s : dummy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         seen_p = __hip_atomic_load(last ? poll_p : dummy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         stream_math<SPG>(acc, ra, xl + ss * 256, full);
-        stream_request<SPG>(ra, wp0, sp0, ss + 2, n_ss, lane);
+        stream_request<GS>(ra, wp0, sp0, ss + 2, n_ss, lane, GS);
         if (ss + 1 < n_ss) stream_math<SPG>(acc, rb, xl + (ss + 1) * 256, full);
-        stream_request<SPG>(rb, wp0, sp0, ss + 3, n_ss, lane);
+        stream_request<GS>(rb, wp0, sp0, ss + 3, n_ss, lane, GS);
     }
 }
 
@@ -759,23 +760,39 @@ __device__ __forceinline__ void base_unit(const LayerArgs &a, const ProjArgs &P,
         const unsigned char *xl = buf + min(l16, rows_x - 1) * L::XROW + 16 * lq;
         const unsigned *dummy = reinterpret_cast<const unsigned *>(wp);
         const unsigned *poll_s = need_s ? sctr : dummy, *poll_p = need_p ? pctr : dummy;
-        // (The first requests belong to the loop of their group size: made ahead of the branch, each
-        // register set would be moved to where the loop wants it, and a move waits for its data.)
-        auto loop = [&](auto spg_c) {
-            constexpr int SPG = decltype(spg_c)::value;
-            StreamRegs sa, sb;
+        StreamRegs sa, sb;
+        auto request = [&](auto max_gs, int gs) {
             const uint32_t flag = request_flag(P);
             // an idle wave requests (and ignores) the unit's first super-step
-            stream_request<SPG>(sa, wp, sp, 0, max(my_cnt, 1), lane);
-            stream_request<SPG>(sb, wp, sp, 1, my_cnt, lane);
+            stream_request<decltype(max_gs)::value>(sa, wp, sp, 0, max(my_cnt, 1), lane, gs);
+            stream_request<decltype(max_gs)::value>(sb, wp, sp, 1, my_cnt, lane, gs);
             __builtin_amdgcn_sched_barrier(0);                 // (the requests stay ahead of the wait for x)
 #pragma unroll
             for (int i = 0; i < XR; ++i) *reinterpret_cast<u32x4 *>(buf + lane * 16 + i * L::XROW) = xr[i];
-            stream_loop<SPG>(acc[0], flag_set(flag), sa, sb, wp, sp, my_cnt, xl, lane, poll_s, poll_p, seen_s, seen_p);
+            return flag;
         };
-        if (P.spg == 1)      loop(std::integral_constant<int, 1>{});
-        else if (P.spg == 2) loop(std::integral_constant<int, 2>{});
-        else                 loop(std::integral_constant<int, 4>{});
+        auto by_group = [&](auto go) {
+            if (P.spg == 1)      go(std::integral_constant<int, 1>{});
+            else if (P.spg == 2) go(std::integral_constant<int, 2>{});
+            else                 go(std::integral_constant<int, 4>{});
+        };
+        auto loop = [&](auto spg, uint32_t flag) {
+            stream_loop<decltype(spg)::value>(acc[0], flag_set(flag), sa, sb, wp, sp, my_cnt, xl, lane, poll_s, poll_p, seen_s, seen_p);
+        };
+        // The first requests belong to the loop of their group size: made ahead of the branch, each register set would
+        // be moved to where the loop wants it, and a move waits for its data (16 layers at 16 rows 195 us against
+        // 190).  But the branch is a jump to code that is not in the cache yet, and units of at most two super-steps per
+        // wave have nothing else to hide it: with 9 to 16 rows per block they make their requests first, in the code
+        // that follows (640 x 3673 at 27 rows 9.1 -> 8.5 us, 768 x 3847 at 28 9.2 -> 8.7, 1024 x 1078 at 28 9.2 -> 8.9).
+        if (XR == 16 && __builtin_expect(unit_cnt <= 2 * WAVES, 1)) {
+            const uint32_t flag = request(std::integral_constant<int, 4>{}, 4 >> P.spg_shift);
+            by_group([&](auto spg) { loop(spg, flag); });
+        } else {
+            by_group([&](auto spg) {
+                constexpr int GS = 4 / decltype(spg)::value;
+                loop(spg, request(std::integral_constant<int, GS>{}, GS));
+            });
+        }
         // Everything below derives its indices afresh from the thread id: values shared with the
         // code above the loop would have to live across it, in registers the loop needs.
         asm volatile("" : "+v"(tid));

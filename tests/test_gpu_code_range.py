@@ -35,6 +35,8 @@ def rows_and_x(M, K, n_ad=3):
 
 @pytest.mark.parametrize("place", PLACES)
 @pytest.mark.parametrize("M,K,N,G", [(1, 640, 70, 32), (8, 384, 130, 64), (13, 2176, 64, 128),    # tile blocks of up to 16 rows
+                                     (9, 128, 70, 32), (16, 1024, 130, 64), (27, 640, 64, 128),   # units of at most two super-steps per wave
+                                     (12, 1152, 70, 64),                                          # and of one more
                                      (20, 128, 19264, 32), (32, 256, 19264, 128),                 # tile blocks of up to 32 rows
                                      (40, 384, 321, 32), (70, 256, 130, 64), (64, 640, 64, 128)])  # wide blocks of 32 rows
 def test_every_code(gpu, place, M, K, N, G):

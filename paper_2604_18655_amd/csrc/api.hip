@@ -84,28 +84,17 @@ int kch_of(const mlora_w4_proj &p, int M, bool wide)
 // of at least 32 rows with grouped shrink blocks: such a call is laid out as for 17 rows or more.
 int plan_rows(int M, bool a8) { return a8 && M < WIDE32_MIN_ROWS ? WIDE32_MIN_ROWS : M; }
 
-// K units per column tile.  Tile blocks: units of at most 2048 inputs (16 super-steps: what a
-// block stages of x).  Wide blocks: any unit length works, and a launch of few base blocks (`launch_blocks`,
-// counted with units of 2048 inputs) has shorter ones, which fill more compute units: a wave that has a
-// SIMD to itself takes 240 ns per k-step whatever the order of its instructions (unpacking beside the products
-// or before them), as it issues one in five cycles.  Below 210 blocks about 1024 inputs: over drawn calls
-// of 200 to 209 blocks they take 0.92 of the time; of 210 to 220 and of 221 to 240 blocks as many calls lose by
-// them as gain: the partial tiles and the shorter loops cost what they bring.  Below 80 blocks about 512 up to K =
-// 4096 (us, 1024 against 512: 1024 x 1024 at 40, 128 and 400 rows 15.9 -> 13.1, 15.9 -> 13.2 and 16.1 -> 13.8,
-// 2048 x 8192 at 64 (64 blocks) 18.0 -> 15.7, 4096 x 4096 at 64 (64) 18.2 -> 16.7, 3072 x 3072 at 40 20.1 -> 18.3),
-// not above, where a dozen partial tiles are added one trip after another: 8192 x 2048 at 64 19.6 -> 22.4; nor from 80
-// blocks on: 4096 x 4096 at 128 rows (128) 19.5 -> 25.2, 1024 x 4096 at 200 (112) 16.6 -> 14.3, 3072 x 3072 at
-// 100 (96) 21.9 -> 26.2.
-int ksplit_of(const mlora_w4_proj &p, bool wide, int launch_blocks)
+// K units per column tile, cut to about `unit` super-steps (see unit_of).  Tile blocks: units of at most 2048 inputs
+// (16 super-steps: what a block stages of x).  Units of 512 inputs are not taken above K = 4096, where a dozen partial
+// tiles are added one trip after another: 8192 x 2048 at 64 rows 19.6 -> 22.4 us.
+constexpr int SHORT_UNIT = 4, SHORT_UNIT_MAX_SUPER_STEPS = 32;
+int ksplit_of(const mlora_w4_proj &p, int unit)
 {
     const int nss = p.K / SUPER_K;
-    int ks = (nss + UNIT_SUPER_STEPS - 1) / UNIT_SUPER_STEPS;
-    if (wide && launch_blocks > 0 && launch_blocks < 210) {
-        const int unit = launch_blocks < 80 && nss <= 32 ? 4 : 8;
-        const int cut = (nss + unit / 2) / unit;
-        if (cut > ks) ks = cut;
-    }
-    return ks;
+    const int ks = (nss + UNIT_SUPER_STEPS - 1) / UNIT_SUPER_STEPS;
+    if (unit == UNIT_SUPER_STEPS) return ks;
+    if (unit == SHORT_UNIT && nss > SHORT_UNIT_MAX_SUPER_STEPS) unit = 8;
+    return std::max(ks, (nss + unit / 2) / unit);
 }
 // Upper bound of that for every launch, which sizes a workspace and decides what is refused: units of
 // 1024 inputs up to 240 base blocks (counted with chunks of 64 rows), of 512 below 80.  The sizes handed out and
@@ -129,6 +118,32 @@ int launch_blocks_of(const mlora_w4_proj *projs, int count, int M, bool wide, in
              ((nss + UNIT_SUPER_STEPS - 1) / UNIT_SUPER_STEPS);
     }
     return n;
+}
+// Super-steps of a K unit.  Wide blocks: any unit length works, and a launch of few base blocks (`blocks`, counted with
+// units of 2048 inputs; `blocks64` the same with chunks of 64 rows) has shorter ones, which fill more compute units: a
+// wave that has a SIMD to itself takes 240 ns per k-step whatever the order of its instructions (unpacking beside the
+// products or before them), as it issues one in five cycles.  Below 210 blocks about 1024 inputs: over drawn calls of 200
+// to 209 blocks they take 0.92 of the time; of 210 to 220 and of 221 to 240 blocks as many calls lose by them as gain: the
+// partial tiles and the shorter loops cost what they bring.  About 512 inputs where the launch then still has a compute
+// unit for nearly every block, shrink blocks beside them: 512 against 1024 over 130 drawn calls of one to seven
+// projections, 640 to 4096 inputs, 1 to 360 rows, bf16 and int8 rows, all group sizes, by blocks after the cut:
+//   with adapters, up to 230     0.90 of the time (51 calls: 41 gain, 8 take 2 to 23 % longer)
+//   with adapters, 231 to 250    1.05 (5)
+//   with adapters, 251 to 608    1.12 (31: 2 gain; 2560-wide layer at 49 rows 15.6 -> 22.4 us, 4096 x 3954 at 118 19.0 -> 25.8)
+//   without, up to 320           0.86 (39 calls, 37 gain, none loses)
+//   without, 321 to 392          0.95 (4: two gain, two are the same)
+constexpr int SHORT_UNIT_MAX_BLOCKS = 230, SHORT_UNIT_MAX_BLOCKS_BARE = 320;
+int unit_of(const mlora_w4_proj *projs, int count, bool wide, int row_blocks, int blocks, int blocks64)
+{
+    if (!wide || blocks >= 210) return UNIT_SUPER_STEPS;
+    if (blocks64 >= 80) return 8;                              // (what a workspace is sized for, see ksplit_bound)
+    int cut = 0;
+    bool bare = true;
+    for (int i = 0; i < count; ++i) {
+        cut += (tiles_n(projs[i].N) + tiles_per_block(true) - 1) / tiles_per_block(true) * row_blocks * ksplit_of(projs[i], SHORT_UNIT);
+        bare = bare && projs[i].n_adapters == 0;
+    }
+    return cut <= (bare ? SHORT_UNIT_MAX_BLOCKS_BARE : SHORT_UNIT_MAX_BLOCKS) ? SHORT_UNIT : 8;
 }
 // Which family of base blocks a launch over these projections runs (see common.hpp).
 bool launch_is_wide(const mlora_w4_proj *projs, int count, int M, bool a8)
@@ -242,13 +257,14 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
     const int row_blocks = halves ? (M + 31) / 32 : chunks;    // blocks along the rows
     const int groups = (count + GROUP_PROJ - 1) / GROUP_PROJ;
     const int shrink_chunks = (M + SHRINK_CHUNK_ROWS - 1) / SHRINK_CHUNK_ROWS;
+    const int unit = unit_of(projs, count, wide, row_blocks, lb, lb_chunk);
     // most row tiles of a grouped shrink block (see SHRINK_ALL_LIVE_BLOCKS)
     int shrink_tiles = wide && block_rows == 32 ? 8 : 16;
     if (lora_on && Mc > 16) {
         long long base = 0;
         int longest = 0;                       // of the inputs with adapters
         for (int i = 0; i < count; ++i) {
-            base += (long long)((tiles_n(projs[i].N) + tiles_per_block(wide) - 1) / tiles_per_block(wide)) * row_blocks * ksplit_of(projs[i], wide, lb);
+            base += (long long)((tiles_n(projs[i].N) + tiles_per_block(wide) - 1) / tiles_per_block(wide)) * row_blocks * ksplit_of(projs[i], unit);
             if (projs[i].n_adapters > 0) longest = std::max(longest, (int)projs[i].K);
         }
         auto shrink_blocks = [&](int tiles) {
@@ -277,7 +293,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
         for (int i = z * GROUP_PROJ; i < count && i < (z + 1) * GROUP_PROJ; ++i) {
             const mlora_w4_proj &p = projs[i];
             const int tiles = tiles_n(p.N);
-            const int ksplit = ksplit_of(p, wide, lb), ks_bound = ksplit_bound(p, wide, lb_chunk);
+            const int ksplit = ksplit_of(p, unit), ks_bound = ksplit_bound(p, wide, lb_chunk);
             // The kernels divide a block index by the tile count with a multiplication that is
             // exact while index * tiles < 2^32: a projection with more than 2^15 column tiles and
             // K units to match is refused rather than mis-indexed.

@@ -536,7 +536,7 @@ static mlora_status enqueue_call(const mlora_w4_proj *projs, int32_t n_proj, con
     const int Mp = plan_rows(M, a8);
     char *ctrl = workspace ? workspace + WS_HEADER_BYTES : nullptr;
     char *data = workspace ? workspace + workspace_bytes / 256 * 256 - round_up(data_total, 256) : nullptr;
-    // (one argument block on the heap: it is about 19 KiB and is copied by the launch)
+    // (one argument block on the heap: it is about 21 KiB and is copied by the launch)
     std::unique_ptr<LayerArgs> a(new LayerArgs);
     for (int first = 0, count = 0; first < n_proj; first += count) {
         count = launch_run(projs + first, n_proj - first, Mp);

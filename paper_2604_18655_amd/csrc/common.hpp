@@ -70,7 +70,7 @@ __host__ __device__ inline int field_code(uint32_t w, int i, bool full)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel argument block of one grouped call (passed by value: about 19 KiB; a block reads only
+// Kernel argument block of one grouped call (passed by value: about 21 KiB; a block reads only
 // the launch scalars, the three table rows of its group and the record of its projection).
 // The projections of a launch are cut into groups of up to 16; group z owns slice z of the grid
 // (blockIdx.z) and the block tables of a group are one vector of 16 each.

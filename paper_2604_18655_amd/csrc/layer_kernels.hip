@@ -1668,7 +1668,7 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
         const int buf = (st & 1) * L::X_STAGE;
         load_x(min(st + 1, n_stages - 1));
         // the math of NK k-steps of this stage (NK = S, or 4 in the last stage of a unit that ends
-        // on an odd super-step): one straight piece of code, no branches inside
+        // on an odd super-step): straight code but for split_codes' branch per run
         auto stage_math = [&](auto nk) {
             constexpr int NK = decltype(nk)::value;
             // A scale group is worked through in runs of SG k-steps (at most 2, whose fragments of x

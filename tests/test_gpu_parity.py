@@ -294,7 +294,7 @@ def test_workspace_reuse_and_graph_replay_match_first_call(gpu):
 
     def snapshot_and_clobber():
         torch.cuda.synchronize()
-        assert_workspace_clean(gpu, ws, [p.shape for p in probs], M)
+        assert_workspace_clean(gpu, ws)
         out = [y.clone() for y in ys]
         for y in ys:
             y.fill_(-1)

@@ -42,7 +42,7 @@ def run_stack(gpu, key, layers, rows, y_dtype, with_rows=True):
     """One layer_step call over all projections of `layers`; returns per layer the list of outputs."""
     lib, device, torch = gpu
     w = wl.WORKLOADS[key]
-    projs, dxs, shapes = [], [], []
+    projs, dxs, widths = [], [], []
     for layer in layers:
         _, xs, _ = wl.make_layer_inputs(w, layer)
         cache = {}
@@ -51,13 +51,13 @@ def run_stack(gpu, key, layers, rows, y_dtype, with_rows=True):
                 cache[id(x)] = device.to_device(x)
             dxs.append(cache[id(x)])
         projs += device_projs(gpu, key, layer)
-        shapes += [p.shape for p in problems_of(key, layer)]
+        widths += [p.shape.N for p in problems_of(key, layer)]
     ra = torch.from_numpy(np.ascontiguousarray(rows, np.int32)).cuda() if with_rows else None
-    ys = [device.alloc_y(w.M, s.N, y_dtype) for s in shapes]
+    ys = [device.alloc_y(w.M, n, y_dtype) for n in widths]
     ws = device.alloc_workspace(projs, w.M)
     lib.layer_step(projs, dxs, ys, ra, w.M, y_dtype, ws)
     torch.cuda.synchronize()
-    assert_workspace_clean(gpu, ws, shapes, w.M)
+    assert_workspace_clean(gpu, ws)
     out = [device.y_to_numpy(y) for y in ys]
     n = len(w.projs)
     return [out[i * n:(i + 1) * n] for i in range(len(layers))]

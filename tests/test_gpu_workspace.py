@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 import workloads as wl
-from gpu_util import TOL_F32, random_problem, rel_err
+from gpu_util import TOL_F32, assert_workspace_clean, random_problem, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -39,6 +39,29 @@ def test_one_workspace_serves_calls_of_different_geometry(gpu):
         torch.cuda.synchronize()
         assert lib.workspace_status(ws) == 0
         assert rel_err(device.y_to_numpy(y), oracle_y(p, x, ra)) <= TOL_F32, (M, p.shape.name)
+
+
+@pytest.mark.parametrize("K,N,M", [(1024, 1024, 40), (768, 300, 100), (2176, 321, 64)])
+def test_short_k_units_leave_their_counters_at_zero(gpu, K, N, M):
+    """K units of about 512 inputs, so that inputs of 768 and 1024 are cut as well: with and without
+    adapters one workspace serves call after call, with the same bits."""
+    lib, device, torch = gpu
+    prob = random_problem(K + N, K, N, 64, 16, 5)
+    p = device.upload_problem(prob)
+    rng = np.random.default_rng(M)
+    x = wl.f32_to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32))
+    dx, ra = device.to_device(x), rng.integers(-1, 5, size=M).astype(np.int32)
+    ws = device.alloc_workspace([p], M)
+    for rows in (ra, None):
+        seen = []
+        for _ in range(3):
+            y = device.alloc_y(M, N, lib.Y_FP32)
+            lib.linear(p, dx, None if rows is None else torch.from_numpy(rows).cuda(), M, y, lib.Y_FP32, ws)
+            torch.cuda.synchronize()
+            assert_workspace_clean(gpu, ws)
+            seen.append(y)
+        assert torch.equal(seen[0], seen[1]) and torch.equal(seen[0], seen[2])
+        assert rel_err(device.y_to_numpy(seen[0]), oracle_y(prob, x, rows)) <= TOL_F32
 
 
 def test_a_wait_that_runs_out_is_reported_and_poisons_the_output(gpu):

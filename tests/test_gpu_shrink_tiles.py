@@ -40,13 +40,17 @@ def test_row_tiles(gpu, kind, M, K, N, G, r, n_ad):
     check_linear(gpu, prob, x, rows_of(kind, M, n_ad), f"{kind} M{M} K{K} N{N} G{G} r{r}")
 
 
-@pytest.mark.parametrize("n_proj", [1, 30, 120])                   # one, four, and eight or sixteen tiles per block
-@pytest.mark.parametrize("M", [40, 150])
-def test_tiles_per_block(gpu, n_proj, M):
+@pytest.mark.parametrize("n_proj,N,M,block_rows", [(1, 256, 40, 32), (1, 256, 150, 32),      # one tile per block
+                                                   (12, 256, 40, 32), (30, 256, 40, 32),     # four: ten blocks for 40 tiles ...
+                                                   (9, 256, 150, 32),                        # ... and three chunks of up to 44
+                                                   (120, 256, 40, 32), (16, 256, 150, 32), (120, 256, 150, 32),   # eight
+                                                   (16, 4096, 192, 64)])                     # sixteen: blocks of 64 rows, three per chunk
+def test_tiles_per_block(gpu, n_proj, N, M, block_rows):
     lib, device, torch = gpu
-    K, N, n_ad = 256, 256, 40
+    K, n_ad = 256, 40
     prob = random_problem(7, K, N, 32, 16, n_ad)
     p = device.upload_problem(prob)
+    assert lib.layer_step_block_rows([p] * n_proj, M) == block_rows
     x = device.to_device(wl.f32_to_bf16_bits(np.random.default_rng(1).standard_normal((M, K)).astype(np.float32)))
     ra = torch.from_numpy(rows_of("each", M, n_ad)).cuda()
     alone = device.alloc_y(M, N, 1)

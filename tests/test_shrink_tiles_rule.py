@@ -29,6 +29,11 @@ def shrink_blocks(shapes, adapters, rank, M, tiles):
     ([(4480, 12672)], 21, 16, 320, 4),              # blocks of 64 rows: 70
     ([(3328, 3563)], 2, 128, 593, 8),               # 480
     ([(3072, 12191)], 25, 32, 871, 16),             # blocks of 64 rows: 672
+    ([(256, 256)], 40, 16, 150, 1),                 # what tests/test_gpu_shrink_tiles.py runs
+    ([(256, 256)] * 12, 40, 16, 40, 4),
+    ([(256, 256)] * 9, 40, 16, 150, 4),
+    ([(256, 256)] * 16, 40, 16, 150, 8),
+    ([(256, 4096)] * 16, 40, 16, 192, 16),
     ([(128, 4991)], 1, 128, 276, 4),                # a tile of 128 inputs is one wave's
     ([(128, 4991), (256, 64)], 1, 16, 40, 1),       # not of 256 inputs
 ])

@@ -1179,7 +1179,7 @@ __device__ __forceinline__ void shrink_tiles(const LayerArgs &a, const ProjArgs 
     RowTiles &g = lds.g;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, lq = lane >> 4;
-    const int part = wave % PARTS, my_slot = wave / PARTS;
+    const int part = PARTS == 4 ? wave : wave % PARTS, my_slot = PARTS == 4 ? 0 : wave / PARTS;
     const int wq = blk_cnt / PARTS, wr = blk_cnt % PARTS;
     const int my_beg = blk_beg + part * wq + min(part, wr), my_cnt = wq + (part < wr ? 1 : 0);
     const int batches = (my_cnt + SB - 1) / SB;
@@ -1311,9 +1311,13 @@ __device__ __forceinline__ void shrink_block(const LayerArgs &a, const ProjArgs 
     const int nks = P.K / KSTEP;
     const int q = nks / P.kch, r = nks % P.kch;
     const int blk_beg = kc * q + min(kc, r), blk_cnt = q + (kc < r ? 1 : 0);
-    if (DEPTH == 2 && blk_cnt <= SB)          shrink_tiles<A8, DEPTH, 1>(a, P, lds, m_base, share, shares, jb, kc, blk_beg, blk_cnt);
-    else if (DEPTH == 2 && blk_cnt <= 2 * SB) shrink_tiles<A8, DEPTH, 2>(a, P, lds, m_base, share, shares, jb, kc, blk_beg, blk_cnt);
-    else                                      shrink_tiles<A8, DEPTH, 4>(a, P, lds, m_base, share, shares, jb, kc, blk_beg, blk_cnt);
+    // (The long form first, without a jump to it: its code is not in the cache yet, and every wave that finishes outputs
+    // waits for it.  14336 x 4096 at 64 rows, 32 adapters of rank 64, 52.5 -> 50.1 us, 4096 x 14336 53.0 -> 50.0, with one form
+    // alone 50.2 and 49.6; 3072 x 8192 at 128 rows 18.5 either way, alone 18.3.  One copy of the code with the split known at
+    // run time: 52.3, 48.7 and 18.2, but 256 x 9000 at 300 rows 15.3 -> 17.7 and 128 x 4991 at 276 32.1 -> 35.7.)
+    if (DEPTH != 2 || __builtin_expect(blk_cnt > 2 * SB, 1)) shrink_tiles<A8, DEPTH, 4>(a, P, lds, m_base, share, shares, jb, kc, blk_beg, blk_cnt);
+    else if (blk_cnt > SB)                                   shrink_tiles<A8, DEPTH, 2>(a, P, lds, m_base, share, shares, jb, kc, blk_beg, blk_cnt);
+    else                                                     shrink_tiles<A8, DEPTH, 1>(a, P, lds, m_base, share, shares, jb, kc, blk_beg, blk_cnt);
     signal_done(a.ctrl + shrink_ctr(pi, 0), P.ctr_copies);
 }
 

@@ -143,9 +143,26 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else int(t.data_ptr())
 
 
+_torch_c = None
+
+
 def _stream() -> int:
-    import torch
-    return int(torch.cuda.current_stream().cuda_stream)
+    """torch's current stream on the current device, without the Python object around it: 2.9 us of a
+    call's 8.9 us of host time, where its kernel takes 6.0 (256 x 256 at 8 rows)."""
+    global _torch_c
+    if _torch_c is None:
+        import torch
+        torch.cuda.current_stream()                      # initialises the device, or says why it cannot
+        _torch_c = torch._C
+    return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice())
+
+
+def _forget_device() -> None:
+    global _torch_c
+    _torch_c = None
+
+
+os.register_at_fork(after_in_child=_forget_device)       # (torch refuses a device that the parent has initialised)
 
 
 class Proj:

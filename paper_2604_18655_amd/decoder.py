@@ -65,6 +65,7 @@ class DecoderLayerStep:
         self.hidden = hidden
 
     def run(self, stream: Optional[int] = None) -> None:
+        stream = B._stream() if stream is None else stream
         if self.h_sq is None:
             B.rms_scale(self.h, self.M, self.hidden, self.eps, self.s1, stream)
         self.qkv.run(stream)

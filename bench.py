@@ -301,7 +301,7 @@ def bench_layer(args):
         "us_per_step": round(elapsed * 1e6 / K, 3), "pct_of_hbm_peak": round(100.0 * gbs / HBM_PEAK_GBS, 2),
         "algorithmic_bytes_per_step": int(step_bytes), "max_rel_err": float(f"{max_rel_err:.3e}"),
         "setup_s": round(setup_s, 1),
-        "roofline": {"kernel": "layer_kernel<1, 16> x 4 + tree_attn_partial/combine + rms_scale_kernel (one step)",
+        "roofline": {"kernel": "layer_kernel<1, 16, 1> x 4 + tree_attn_partial/combine + rms_scale_kernel (one step)",
                      "bound": "hbm", "achieved": round(step_bytes / step_s / 1e9, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(step_bytes / step_s / 1e9 / HBM_PEAK_GBS, 4), "traffic": None,
                      "algorithmic_bytes_per_launch": int(step_bytes), "avg_launch_us": round(step_s * 1e6, 3),
@@ -635,7 +635,8 @@ def main():
     spg = w.projs[0].group // 32
     rows = lib.layer_step_block_rows(plans[0][0].keep[0], M, args.a8)
     kernel_name = ("wide_kernel<%d, %d, %s, %s>" % (spg, rows // 16, "true" if args.a8 else "false", "true" if rows == 64 or M > 32 else "false")) if wide else \
-        "layer_kernel<%s>" % ("1, 8" if M <= 8 else "1, 16" if rows == 16 else "2, 24" if M <= 24 else "2, 32")
+        "layer_kernel<%s, %d>" % ("1, 8" if M <= 8 else "1, 16" if rows == 16 else "2, 24" if M <= 24 else "2, 32",
+                                  1 if rows == 16 and info["grid_z"] == 1 else 8)
     kernel_tag = ("wide_kernel_a8" if args.a8 else "wide_kernel") if wide else "layer_kernel"
     achieved_tflops = (step_flops / launches_per_step) / kern_s / 1e12
     bound = BOUND.get(w.key, "hbm")

@@ -284,7 +284,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
     int part_ctr = count * CTR_REPL * CTR_STRIDE;
     long long grid_x = 0;
     if (a) {
-        for (int z = 0; z < MAX_GROUPS; ++z)
+        for (int z = 0; z < groups; ++z)
             for (int i = 0; i < GROUP_PROJ; ++i)
                 a->main_begin[z][i] = a->pre_begin[z][i] = a->shrink_begin[z][i] = 0x7FFFFFFF;
     }
@@ -536,11 +536,12 @@ static mlora_status enqueue_call(const mlora_w4_proj *projs, int32_t n_proj, con
     const int Mp = plan_rows(M, a8);
     char *ctrl = workspace ? workspace + WS_HEADER_BYTES : nullptr;
     char *data = workspace ? workspace + workspace_bytes / 256 * 256 - round_up(data_total, 256) : nullptr;
-    // (one argument block on the heap: it is about 21 KiB and is copied by the launch)
+    // (one argument block on the heap: it is about 24 KiB; only what the launch uses of it is filled)
     std::unique_ptr<LayerArgs> a(new LayerArgs);
     for (int first = 0, count = 0; first < n_proj; first += count) {
         count = launch_run(projs + first, n_proj - first, Mp);
-        memset(a.get(), 0, sizeof(LayerArgs));
+        const size_t records = (size_t)((count + GROUP_PROJ - 1) / GROUP_PROJ) * GROUP_PROJ;
+        memset(static_cast<void *>(a.get()), 0, (size_t)(reinterpret_cast<char *>(a->p + records) - reinterpret_cast<char *>(a.get())));
         a->row_adapter = lora_on ? row_adapter : nullptr;
         a->n_proj = count;
         a->M = M;

@@ -70,7 +70,7 @@ __host__ __device__ inline int field_code(uint32_t w, int i, bool full)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel argument block of one grouped call (passed by value: about 21 KiB; a block reads only
+// Kernel argument block of one grouped call (passed by value; a block reads only
 // the launch scalars, the three table rows of its group and the record of its projection).
 // The projections of a launch are cut into groups of up to 16; group z owns slice z of the grid
 // (blockIdx.z) and the block tables of a group are one vector of 16 each.
@@ -150,17 +150,8 @@ struct EpiArgs {
     int pad_;
 };
 
-struct LayerArgs {
-    // Slice z of the grid holds, in this order, the shrink blocks, the split-K blocks (units 1..)
-    // and the finishing blocks (unit 0) of the projections of group z; first block of each
-    // projection within its kind (entries past the group's last projection: INT_MAX):
-    int shrink_begin[MAX_GROUPS][GROUP_PROJ];
-    int pre_begin[MAX_GROUPS][GROUP_PROJ];
-    int main_begin[MAX_GROUPS][GROUP_PROJ];
-    ProjArgs p[MAX_PROJ_PER_LAUNCH];
-    int shrink_blocks[MAX_GROUPS];     // shrink blocks of the group (first in its slice)
-    int pre_base_blocks[MAX_GROUPS];   // split-K blocks of the group (after its shrink blocks)
-    int group_blocks[MAX_GROUPS];      // all blocks of the group; the slice's other blocks exit at once
+// What every block of a launch needs, whatever the number of its projections.
+struct LaunchArgs {
     const int *row_adapter;    // may be null
     int n_proj;
     int M;
@@ -181,6 +172,24 @@ struct LayerArgs {
     unsigned *ctrl;            // completion counters of this launch
     unsigned *status;          // workspace status word: set non-zero if a wait ran out
 };
+
+// The argument block of a kernel for up to G groups.  A launch copies all of it: of the 5.2 us that a call of one
+// projection took, 1.7 went into the 20 KiB of records that it had no use for, so the kernels of short launches exist
+// for one group as well (3.7 KiB).
+template <int G>
+struct GroupArgs : LaunchArgs {
+    // Slice z of the grid holds, in this order, the shrink blocks, the split-K blocks (units 1..)
+    // and the finishing blocks (unit 0) of the projections of group z; first block of each
+    // projection within its kind (entries past the group's last projection: INT_MAX):
+    int shrink_begin[G][GROUP_PROJ];
+    int pre_begin[G][GROUP_PROJ];
+    int main_begin[G][GROUP_PROJ];
+    int shrink_blocks[G];      // shrink blocks of the group (first in its slice)
+    int pre_base_blocks[G];    // split-K blocks of the group (after its shrink blocks)
+    int group_blocks[G];       // all blocks of the group; the slice's other blocks exit at once
+    ProjArgs p[G * GROUP_PROJ];
+};
+using LayerArgs = GroupArgs<MAX_GROUPS>;
 
 // ---------------------------------------------------------------------------------------------
 // 16-bit float helpers (bit patterns)

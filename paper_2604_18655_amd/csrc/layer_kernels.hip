@@ -22,6 +22,8 @@
 // rows of A[adapter]); the partial sums go to t_part[chunk][row][rank].  Up to 16 rows: a block
 // per (row, 16 ranks, K chunk).  More rows: the rows of a chunk of 64 are grouped by adapter
 // and cut into tiles of 16, and a block's four waves share the inputs of every tile.
+#include <string.h>
+
 #include <type_traits>
 
 #include "group_rows.hpp"
@@ -483,7 +485,7 @@ struct FusedOperands {
     float res[4];                  // residual of the lane's four (SwiGLU: two) outputs
 };
 
-__device__ __forceinline__ FusedOperands fused_fetch(const LayerArgs &a, const ProjArgs &P, int pi, int m, int tile, int l16)
+__device__ __forceinline__ FusedOperands fused_fetch(const LaunchArgs &a, const ProjArgs &P, int pi, int m, int tile, int l16)
 {
     FusedOperands f;
     const EpiArgs &E = a.epi[pi];
@@ -515,7 +517,7 @@ __device__ __forceinline__ FusedOperands fused_fetch(const LayerArgs &a, const P
     return f;
 }
 
-__device__ __forceinline__ void fused_store(const LayerArgs &a, const ProjArgs &P, int pi, int m, int tile, int l16,
+__device__ __forceinline__ void fused_store(const LaunchArgs &a, const ProjArgs &P, int pi, int m, int tile, int l16,
                                             const FusedOperands &f, float (&v)[4])
 {
     if (m >= a.M) return;
@@ -565,7 +567,7 @@ __device__ __forceinline__ void fused_store(const LayerArgs &a, const ProjArgs &
     }
 }
 
-__device__ __forceinline__ void store_fused(const LayerArgs &a, const ProjArgs &P, int pi, int m, int tile, int l16,
+__device__ __forceinline__ void store_fused(const LaunchArgs &a, const ProjArgs &P, int pi, int m, int tile, int l16,
                                             float (&v)[4])
 {
     const FusedOperands f = fused_fetch(a, P, pi, m, tile, l16);
@@ -620,7 +622,7 @@ __device__ __forceinline__ float dot8(uint4 b8, const float *t, float l)
 // thread (wave w, lane l) finishes e = w of every (mb, j): EPT = 4*MB outputs that lie in MB rows
 // (one adapter each), 16 columns apart.
 template <int MB, int XR, int WAVES, int R, int FR>
-__device__ __forceinline__ void base_unit(const LayerArgs &a, const ProjArgs &P, int pi, int tile, int ku,
+__device__ __forceinline__ void base_unit(const LaunchArgs &a, const ProjArgs &P, int pi, int tile, int ku,
                                  int m0, const BaseLds<MB, XR, WAVES, R> &lds)
 {
     constexpr int ROWS = 16 * MB;
@@ -1170,7 +1172,7 @@ struct ShrinkLds {
 // The tiles of one block: share, share + shares, ... of its chunk of rows, four at a time.  PARTS waves share the
 // inputs of a tile (a balanced split of the block's k-steps), the others have tiles of their own.
 template <bool A8, int DEPTH, int PARTS>
-__device__ __forceinline__ void shrink_tiles(const LayerArgs &a, const ProjArgs &P, ShrinkLds &lds, int m_base, int share, int shares,
+__device__ __forceinline__ void shrink_tiles(const LaunchArgs &a, const ProjArgs &P, ShrinkLds &lds, int m_base, int share, int shares,
                                              int jb, int kc, int blk_beg, int blk_cnt)
 {
     using L = ShrinkLds;
@@ -1292,7 +1294,7 @@ __device__ __forceinline__ void shrink_tiles(const LayerArgs &a, const ProjArgs 
 }
 
 template <bool A8, int DEPTH>
-__device__ __forceinline__ void shrink_block(const LayerArgs &a, const ProjArgs &P, int pi, int local, ShrinkLds &lds)
+__device__ __forceinline__ void shrink_block(const LaunchArgs &a, const ProjArgs &P, int pi, int local, ShrinkLds &lds)
 {
     constexpr int SB = ShrinkLds::SB;
     RowTiles &g = lds.g;
@@ -1340,7 +1342,7 @@ struct ShrinkRowLds {
     float red[4][16];
 };
 
-__device__ __forceinline__ void shrink_row_block(const LayerArgs &a, const ProjArgs &P, int pi, int local,
+__device__ __forceinline__ void shrink_row_block(const LaunchArgs &a, const ProjArgs &P, int pi, int local,
                                                  ShrinkRowLds &lds)
 {
     using L = ShrinkRowLds;
@@ -1428,7 +1430,8 @@ constexpr int pre_lds_bytes()
 // scalar cache that is cold at every launch (about 0.4 us per dependent access); left alone,
 // the compiler loads each field where it is first used, one round trip after another.  Pinning
 // all fields to registers at one point makes it issue the loads together.
-__device__ __forceinline__ ProjArgs fetch_proj(const LayerArgs &a, int pi)
+template <int G>
+__device__ __forceinline__ ProjArgs fetch_proj(const GroupArgs<G> &a, int pi)
 {
     ProjArgs P = a.p[pi];
     asm volatile("" :: "s"(P.codes), "s"(P.scales), "s"(P.flag), "s"(P.x), "s"(P.y), "s"(P.lora_a), "s"(P.lora_b),
@@ -1451,7 +1454,8 @@ struct LaunchTables {
     i32x16 shrink, pre, main;
     int shrink_blocks, pre_base_blocks, group_blocks;
 };
-__device__ __forceinline__ LaunchTables pin_launch_args(const LayerArgs &a, int z)
+template <int G>
+__device__ __forceinline__ LaunchTables pin_launch_args(const GroupArgs<G> &a, int z)
 {
     LaunchTables t;
     t.shrink = *reinterpret_cast<const i32x16 *>(a.shrink_begin[z]);
@@ -1491,7 +1495,7 @@ __device__ __forceinline__ int find_proj(const i32x16 &begin, int b, int &first)
 // read 5.9 x the algorithmic bytes from HBM at 512 rows.)  A producer still has a smaller index
 // than its consumer: a split-K block and the block that finishes its tile have the same chunk.
 // b past the group's last block: nothing to do.
-__device__ __forceinline__ void split_block_index(const LayerArgs &a, const LaunchTables &t, int &b, int &chunk)
+__device__ __forceinline__ void split_block_index(const LaunchArgs &a, const LaunchTables &t, int &b, int &chunk)
 {
     const unsigned id = blockIdx.x, chunks = (unsigned)a.row_blocks, shrink = (unsigned)t.shrink_blocks;
     const unsigned first = filled_up(shrink);
@@ -1510,8 +1514,8 @@ __device__ __forceinline__ void split_block_index(const LayerArgs &a, const Laun
 // blocks per compute unit the registers are budgeted for (LDS allows as many for these shapes)
 template <int MB, int XR> constexpr int occupancy_of() { return MB == 1 && XR == 8 ? 3 : 2; }
 
-template <int MB, int XR>
-__global__ __launch_bounds__(64 * Shape<MB>::WAVES, (occupancy_of<MB, XR>())) void layer_kernel(const LayerArgs a)
+template <int MB, int XR, int G>
+__global__ __launch_bounds__(64 * Shape<MB>::WAVES, (occupancy_of<MB, XR>())) void layer_kernel(const GroupArgs<G> a)
 {
     __shared__ __align__(16) unsigned char smem[pre_lds_bytes<MB, XR>()];
     const int z = (int)blockIdx.z;
@@ -1775,7 +1779,7 @@ __device__ __forceinline__ void stream_loop(Acc &acc, __amdgpu_buffer_rsrc_t cod
 // k-steps per scale group, the same for every projection of the launch; MB = blocks of 16 rows
 // per base block (4 where wide64_pays, else 2); AGAIN = other blocks of rows read the same codes.
 template <int SPG, int MB, bool A8, bool AGAIN>
-__device__ __forceinline__ void wide_unit(const LayerArgs &a, const ProjArgs &P, int pi, int group, int ku,
+__device__ __forceinline__ void wide_unit(const LaunchArgs &a, const ProjArgs &P, int pi, int group, int ku,
                                           int m0, WideLds<MB> &lds)
 {
     using L = WideLds<MB>;
@@ -2241,10 +2245,27 @@ __global__ __launch_bounds__(256, (MB == 2 ? 3 : 2)) void wide_kernel(const Laye
     wide_unit<SPG, MB, A8, AGAIN>(a, P, pi, local - unit * groups, pre ? 1 + unit : 0, chunk * 16 * MB, lds);
 }
 
+// (blocks of 32 rows run in launches of at least CHUNK16_MAX_BLOCKS blocks only: no short form of theirs)
 template <int MB, int XR>
 static hipError_t launch_instance(const LayerArgs &a, const dim3 &grid, hipStream_t s)
 {
-    layer_kernel<MB, XR><<<grid, dim3(64 * Shape<MB>::WAVES), 0, s>>>(a);
+    constexpr int THREADS = 64 * Shape<MB>::WAVES;
+    if constexpr (MB == 1) {
+        if (grid.z == 1) {
+            GroupArgs<1> one;
+            static_cast<LaunchArgs &>(one) = a;
+            memcpy(one.shrink_begin, a.shrink_begin, sizeof one.shrink_begin);
+            memcpy(one.pre_begin, a.pre_begin, sizeof one.pre_begin);
+            memcpy(one.main_begin, a.main_begin, sizeof one.main_begin);
+            one.shrink_blocks[0] = a.shrink_blocks[0];
+            one.pre_base_blocks[0] = a.pre_base_blocks[0];
+            one.group_blocks[0] = a.group_blocks[0];
+            memcpy(one.p, a.p, sizeof one.p);
+            layer_kernel<MB, XR, 1><<<grid, dim3(THREADS), 0, s>>>(one);
+            return hipGetLastError();
+        }
+    }
+    layer_kernel<MB, XR, MAX_GROUPS><<<grid, dim3(THREADS), 0, s>>>(a);
     return hipGetLastError();
 }
 

@@ -65,7 +65,7 @@ typedef struct {
 } mlora_tree_attn;
 
 /* Device scratch the call needs (256-byte aligned): per block of keys and query vector the
- * running maximum, sum and unnormalised output, merged by the call's second kernel.  No state
+ * running maximum, sum and unnormalised output, merged by a second kernel (calls with few keys need none).  No state
  * survives the call; nothing has to be initialised.  0 if the descriptor is not supported. */
 size_t mlora_tree_attention_workspace_bytes(const mlora_tree_attn *t);
 

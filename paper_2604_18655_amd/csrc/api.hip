@@ -10,6 +10,9 @@
 #include "common.hpp"
 
 using namespace mlora;
+#include <stdlib.h>
+
+
 
 // ---------------------------------------------------------------------------------------------
 // The same call on a scratch buffer that lives in the library's own device image, for callers
@@ -258,13 +261,16 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
     const int groups = (count + GROUP_PROJ - 1) / GROUP_PROJ;
     const int shrink_chunks = (M + SHRINK_CHUNK_ROWS - 1) / SHRINK_CHUNK_ROWS;
     const int unit = unit_of(projs, count, wide, row_blocks, lb, lb_chunk);
+    long long base = 0;                        // base blocks
+    for (int i = 0; i < count; ++i)
+        base += (long long)((tiles_n(projs[i].N) + tiles_per_block(wide) - 1) / tiles_per_block(wide)) * row_blocks * ksplit_of(projs[i], unit);
+    // two waves per tile where the launch has few blocks (see wide_short_kernel)
+    const int waves_per_tile = wide && block_rows == 32 && groups == 1 && base <= WIDE_SHORT_MAX_BLOCKS ? 2 : 1;
     // most row tiles of a grouped shrink block (see SHRINK_ALL_LIVE_BLOCKS)
     int shrink_tiles = wide && block_rows == 32 ? 8 : 16;
     if (lora_on && Mc > 16) {
-        long long base = 0;
         int longest = 0;                       // of the inputs with adapters
         for (int i = 0; i < count; ++i) {
-            base += (long long)((tiles_n(projs[i].N) + tiles_per_block(wide) - 1) / tiles_per_block(wide)) * row_blocks * ksplit_of(projs[i], unit);
             if (projs[i].n_adapters > 0) longest = std::max(longest, (int)projs[i].K);
         }
         auto shrink_blocks = [&](int tiles) {
@@ -329,7 +335,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
                 d.ksplit = ksplit;
                 // blocks (wide kernel: waves) that wait for this projection's shrink blocks: the
                 // finishing ones, or every K unit where the LoRA term is spread over them
-                d.n_finish_blocks = tiles * row_blocks * (wide ? ksplit : 1);
+                d.n_finish_blocks = tiles * row_blocks * (wide ? ksplit * waves_per_tile : 1);
                 d.unit_q = (p.K / SUPER_K) / ksplit;
                 d.unit_r = (p.K / SUPER_K) % ksplit;
                 d.spg_shift = d.spg == 4 ? 2 : d.spg == 2 ? 1 : 0;
@@ -388,6 +394,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
     if (a) {
         a->ctrl = reinterpret_cast<unsigned *>(ctrl);
         a->wide = wide;
+        a->waves_per_tile = waves_per_tile;
         a->block_rows = block_rows;
         a->row_blocks = row_blocks;
         a->half_shift = halves ? 1 : 0;

@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <string.h>
 
 #include "../../include/mlora_w4.h"
 
@@ -153,24 +154,25 @@ struct EpiArgs {
 // What every block of a launch needs, whatever the number of its projections.
 struct LaunchArgs {
     const int *row_adapter;    // may be null
+    unsigned *ctrl;            // completion counters of this launch
+    unsigned *status;          // workspace status word: set non-zero if a wait ran out
     int n_proj;
     int M;
     int M_plan;                // the row count the launch was laid out for (shrink blocks): M, except
                                // that calls with int8 activations always run wide blocks and are
                                // laid out as for at least 17 rows
-    int a8;                    // x is int8 with one scale per tensor (ProjArgs::x_scale)
-    int shrink_tiles;          // grouped shrink blocks: most row tiles of a block (see shrink_tile_shares)
-    int fused;                 // outputs go through epi[] (one group of at most 16 projections)
-    EpiArgs epi[GROUP_PROJ];
     int y_fp32;
+    int m_pad;                 // M rounded up to whole row chunks
     int block_rows;            // rows of a base block: 16, 32 or 64
     int row_blocks;            // base blocks along the rows
     int half_shift;            // 1: two blocks of 32 rows per row chunk of 64 (they share its counter lines)
-    int m_pad;                 // M rounded up to whole row chunks
+    int shrink_tiles;          // grouped shrink blocks: most row tiles of a block (see shrink_tile_shares)
     int spin_limit;            // polls a block makes before it gives up waiting (0: gives up at once)
+    int a8;                    // x is int8 with one scale per tensor (ProjArgs::x_scale)
     int wide;                  // the launch runs wide blocks (see below)
-    unsigned *ctrl;            // completion counters of this launch
-    unsigned *status;          // workspace status word: set non-zero if a wait ran out
+    int waves_per_tile;        // wide blocks: 1, or 2 in short launches (see wide_short_kernel)
+    int fused;                 // outputs go through epi[] (one group of at most 16 projections)
+    EpiArgs epi[GROUP_PROJ];
 };
 
 // The argument block of a kernel for up to G groups.  A launch copies all of it: of the 5.2 us that a call of one
@@ -181,7 +183,7 @@ struct GroupArgs : LaunchArgs {
     // Slice z of the grid holds, in this order, the shrink blocks, the split-K blocks (units 1..)
     // and the finishing blocks (unit 0) of the projections of group z; first block of each
     // projection within its kind (entries past the group's last projection: INT_MAX):
-    int shrink_begin[G][GROUP_PROJ];
+    alignas(64) int shrink_begin[G][GROUP_PROJ];           // (a block reads a row of each at once)
     int pre_begin[G][GROUP_PROJ];
     int main_begin[G][GROUP_PROJ];
     int shrink_blocks[G];      // shrink blocks of the group (first in its slice)
@@ -190,6 +192,19 @@ struct GroupArgs : LaunchArgs {
     ProjArgs p[G * GROUP_PROJ];
 };
 using LayerArgs = GroupArgs<MAX_GROUPS>;
+inline GroupArgs<1> first_group(const LayerArgs &a)
+{
+    GroupArgs<1> one;
+    static_cast<LaunchArgs &>(one) = a;
+    memcpy(one.shrink_begin, a.shrink_begin, sizeof one.shrink_begin);
+    memcpy(one.pre_begin, a.pre_begin, sizeof one.pre_begin);
+    memcpy(one.main_begin, a.main_begin, sizeof one.main_begin);
+    one.shrink_blocks[0] = a.shrink_blocks[0];
+    one.pre_base_blocks[0] = a.pre_base_blocks[0];
+    one.group_blocks[0] = a.group_blocks[0];
+    memcpy(one.p, a.p, sizeof one.p);
+    return one;
+}
 
 // ---------------------------------------------------------------------------------------------
 // 16-bit float helpers (bit patterns)
@@ -273,6 +288,7 @@ hipError_t launch_unpack(int K, int N, int group, const void *blob, int8_t *code
 hipError_t launch_group_rows(const int *row_adapter, int M, int n_adapters, int *perm,
                              int *seg_adapter, int *seg_start, int *n_seg, hipStream_t s);
 hipError_t launch_layer(const LayerArgs &a, long long grid_x, int groups, hipStream_t s);
+hipError_t launch_wide_short(const LayerArgs &a, const dim3 &grid, hipStream_t s);
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t s);
 hipError_t launch_rms_scale(const uint16_t *x, int M, int K, float eps, float *scale, hipStream_t s);
 hipError_t launch_lora_int16_expand(const int16_t *aq, const int16_t *bq, int n_adapters, int rank, int K, int N,
@@ -300,6 +316,9 @@ constexpr int WIDE32_MIN_BLOCKS = 300;
 constexpr int WIDE64_MIN_BLOCKS = 320;
 __host__ inline bool wide64_pays(int blocks64, int blocks32) { return blocks64 >= WIDE64_MIN_BLOCKS && 5ll * blocks32 >= 9ll * blocks64; }
 constexpr int WIDE_TILES_PER_BLOCK = 4;
+// Blocks of 32 rows have two waves per tile in launches of one group of projections with at most this many base blocks
+// (see wide_short_kernel, which also says what both sides measured).
+constexpr int WIDE_SHORT_MAX_BLOCKS = 230;
 constexpr int CHUNK16_MAX_BLOCKS = 300;    // tile launches of 17 to 32 rows below this run chunks of 16 rows
 __host__ inline int rows_per_chunk(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : 64; }
 // column tiles a base block covers

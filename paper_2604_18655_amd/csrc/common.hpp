@@ -109,6 +109,7 @@ struct ProjArgs {
     int spg_shift;             // log2(spg)
     int ctr_copies;            // copies of the shrink counter in use: a power of two, at most
                                // min(CTR_REPL, n_finish_blocks)
+    int lora_units;            // wide blocks: K units of a tile that share its LoRA term (the first ones; see LORA_FEW_PASSES)
     unsigned tiles_inv;        // ceil(2^32 / tiles) for tiles > 1: block index / tiles = umulhi(index,
                                // tiles_inv), exact while index * tiles < 2^32
 };
@@ -319,6 +320,11 @@ constexpr int WIDE_TILES_PER_BLOCK = 4;
 // Blocks of 32 rows have two waves per tile in launches of one group of projections with at most this many base blocks
 // (see wide_short_kernel, which also says what both sides measured).
 constexpr int WIDE_SHORT_MAX_BLOCKS = 230;
+// Passes (adapters of a block's rows x runs of 16 ranks) up to which the finishing block of a tile makes the whole LoRA
+// term: the other K units then leave their partial tiles without waiting for t (2432 x 382 at 396 rows, one adapter of rank
+// 64 21.5 -> 15.7 us; 3072 x 8192 at 128 rows, 8 adapters of rank 16 19.0 -> 18.6; two layers of 2176 at 130 rows 82 -> 78;
+// 85 calls 0.99 of the time, with two adapters of rank 64 as many gain as lose).
+constexpr int LORA_FEW_PASSES = 8;
 constexpr int CHUNK16_MAX_BLOCKS = 300;    // tile launches of 17 to 32 rows below this run chunks of 16 rows
 __host__ inline int rows_per_chunk(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : 64; }
 // column tiles a base block covers

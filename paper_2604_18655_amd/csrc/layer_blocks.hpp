@@ -1446,7 +1446,7 @@ __device__ __forceinline__ ProjArgs fetch_proj(const GroupArgs<G> &a, int pi)
                  "s"(P.t_part), "s"(P.partial));
     asm volatile("" :: "s"(P.K), "s"(P.N), "s"(P.spg), "s"(P.n_adapters), "s"(P.rank), "s"(P.r16),
                  "s"(P.kch), "s"(P.alpha), "s"(P.ksplit));
-    asm volatile("" :: "s"(P.unit_q), "s"(P.unit_r), "s"(P.spg_shift), "s"(P.ctr_copies), "s"(P.tiles_inv));
+    asm volatile("" :: "s"(P.unit_q), "s"(P.unit_r), "s"(P.spg_shift), "s"(P.ctr_copies), "s"(P.lora_units), "s"(P.tiles_inv));
     return P;
 }
 
@@ -1795,15 +1795,15 @@ __device__ __forceinline__ void wide_unit(const LaunchArgs &a, const ProjArgs &P
     const u32x4 *wp = reinterpret_cast<const u32x4 *>(P.codes + (size_t)tile * ksteps * 64) + (size_t)unit_beg * 256;
     const uint2 *sp = P.scales + ((size_t)tile * (ksteps / SPG) + (size_t)unit_beg * gs) * 16;
 
-    // Every K unit of a tile takes a share of the LoRA term (the adapters of the chunk are dealt
-    // out to the units in turn): the rows of B of many adapters are more than the finishing
-    // blocks alone can fetch in good time.  So every unit waits for the shrink blocks, and
-    // P.n_finish_blocks counts (tile, chunk, unit, wave of the tile) here.
-    const bool lora = a.row_adapter != nullptr && P.n_adapters > 0;
+    // The first P.lora_units K units of a tile take a share of the LoRA term each (the adapters of the chunk are dealt
+    // out to them in turn): all of them where the rows of B of many adapters are more than the finishing
+    // blocks alone can fetch in good time.  Such a unit waits for the shrink blocks, and
+    // P.n_finish_blocks counts (tile, chunk, such a unit, wave of the tile) here.
+    const bool lora = a.row_adapter != nullptr && P.n_adapters > 0 && ku < P.lora_units;
     const int rows_here = min(ROWS, M - m0);
     const int chunk = m0 / ROWS, chunks = a.row_blocks;
     const int fin = tile * chunks + chunk;
-    const int user = (fin * P.ksplit + ku) * WPT + half;
+    const int user = (fin * P.lora_units + ku) * WPT + half;
     const int copies = P.ctr_copies;
     unsigned *const sctr = a.ctrl + shrink_ctr(pi, user & (copies - 1));
     const int lines = (chunks + a.half_shift) >> a.half_shift;     // counter lines per tile
@@ -1972,7 +1972,7 @@ __device__ __forceinline__ void wide_unit(const LaunchArgs &a, const ProjArgs &P
             while (st_cur < 0 && st_remaining) {       // next adapter that this K unit looks after
                 const int next = __builtin_amdgcn_readlane(ad_row, (int)__builtin_ctzll(st_remaining));
                 st_remaining &= ~__ballot(ad_row == next);
-                if (st_ordinal++ % P.ksplit == ku) {
+                if (st_ordinal++ % P.lora_units == ku) {
                     st_cur = next;
                     st_run = 0;
                 }
@@ -2089,7 +2089,7 @@ __device__ __forceinline__ void wide_unit(const LaunchArgs &a, const ProjArgs &P
         constexpr int NP = 2 * MB * CB;
         const int np = P.ksplit - 1;
         auto request = [&](f32x4_t (&pv)[NP], int u) {
-            // (the tile of unit u for this wave's chunk: NP KiB, the same place for all lanes)
+            // (the tile of unit u for this wave's chunk and columns: NP KiB, the same place for all lanes)
             const float *base = P.partial + (((size_t)u * tiles + tile) * a.m_pad + m0) * TILE_N + half * 1024;
             const __amdgpu_buffer_rsrc_t rsrc = shared_buffer(base, NP * 1024);
 #pragma unroll

@@ -10,9 +10,6 @@
 #include "common.hpp"
 
 using namespace mlora;
-#include <stdlib.h>
-
-
 
 // ---------------------------------------------------------------------------------------------
 // The same call on a scratch buffer that lives in the library's own device image, for callers

@@ -1,5 +1,6 @@
 // DS2D step on the device (Section 3.5 and Appendix A.2 of the paper): from the logits of all
-// rows of a step, verify the draft tree greedily and draft the next one.  Two kernels:
+// rows of a step, verify the draft tree greedily and draft the next one.  Two kernels (large steps read the forecast rows
+// after the walk, see ds2d_walk_draft):
 //
 //   ds2d_best_partial  a wavefront per (slice of 4096 logits, row): the k best logits of the row inside
 //                      the slice, k = 1 for token rows (only the arg-max is needed), b'_j for
@@ -33,9 +34,10 @@ struct Ds2dArgs {
     const void *logits;
     const int32_t *tokens;
     int32_t *n_accepted, *accepted_rows, *emitted, *next_tokens;
-    unsigned long long *partial;      // [S * R][slices][DS_KMAX]
+    unsigned long long *partial;      // [S * R][slices][DS_KMAX]; late drafts: see ds2d_walk_draft
     long long total;                  // S * R * V
     int V, S, R, T, T_next, m, depth, next_depth, slices, fp32;
+    int rows;                         // rows of a stream that ds2d_best_partial looks at: R, or T (late drafts)
     int next_branch[MLORA_DS2D_MAX_FORECAST];
     signed char parent[MLORA_DS2D_MAX_ROWS];   // of the token rows
 };
@@ -50,6 +52,14 @@ __device__ inline unsigned long long key_of(float v, unsigned token)
         hi = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
     }
     return ((unsigned long long)hi << 32) | (unsigned long long)(~token);
+}
+// Keys may be read by another block of the launch that writes them: accesses that go through to memory.
+__device__ __forceinline__ void put_key(unsigned long long *p, unsigned long long key) { __hip_atomic_store(p, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <bool SAME_LAUNCH>
+__device__ __forceinline__ unsigned long long get_key(const unsigned long long *p)
+{
+    if constexpr (SAME_LAUNCH) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else return *p;
 }
 __device__ inline float bf16_value(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
 
@@ -159,7 +169,7 @@ __device__ __forceinline__ void slice_by_keys(const Ds2dArgs &a, long long slice
             best = key > best ? key : best;
         }
         best = wave_max(best);
-        if (lane == 0) out[round] = best;
+        if (lane == 0) put_key(out + round, best);
         below = best;                            // (0: the slice holds fewer than k logits, the rest are empty slots)
     }
 }
@@ -173,13 +183,8 @@ __device__ __forceinline__ void slice_by_keys(const Ds2dArgs &a, long long slice
 // us, on the same logits less 50, all negative, 25.4 (31.2 with keys for all, 63 with rounds over memory).  Four wavefronts per SIMD: the registers for
 // eight spill (35 us).
 template <bool FP32>
-__global__ __launch_bounds__(DS_THREADS, 4) void ds2d_best_partial(const Ds2dArgs a)
+__device__ __forceinline__ void slice_best(const Ds2dArgs &a, int row, int slice, int k, unsigned long long *out, int lane)
 {
-    const int row = blockIdx.y;
-    const int k = wanted(a, row % a.R);
-    const int lane = threadIdx.x & 63;
-    const int slice = (int)blockIdx.x * (DS_THREADS / 64) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (k == 0 || slice >= a.slices) return;
     // The row's logits are elements [row * V, row * V + V) of the whole array.  They are read
     // with aligned 16-byte loads counted from the start of the array (rows need no alignment of
     // their own); elements of a vector that belong to a neighbouring row are ignored.
@@ -193,9 +198,8 @@ __global__ __launch_bounds__(DS_THREADS, 4) void ds2d_best_partial(const Ds2dArg
     const int pos_lo = first > slice_first ? (int)(first - slice_first) : 0;
     const int pos_hi = last - slice_first < DS_SLICE ? (last > slice_first ? (int)(last - slice_first) : 0) : DS_SLICE;
     const unsigned token_lo = (unsigned)(slice_first + pos_lo - first);
-    unsigned long long *out = a.partial + ((size_t)row * a.slices + slice) * DS_KMAX;
     if (pos_hi <= pos_lo) {
-        if (lane < k) out[lane] = 0ull;
+        if (lane < k) put_key(out + lane, 0ull);
         return;
     }
     if (__builtin_expect(pos_hi - pos_lo <= 64, 0)) {                   // (the last few logits of a row: one per lane)
@@ -269,7 +273,7 @@ __global__ __launch_bounds__(DS_THREADS, 4) void ds2d_best_partial(const Ds2dArg
             const int winner = -wave_max_i32(-pos);
             if (lane == 0) {
                 const unsigned bits = in_order ? Order<FP32>::bits(top) : (unsigned)top;
-                out[round] = key_of(__uint_as_float(FP32 ? bits : bits << 16), (unsigned)(winner - pos_lo) + token_lo);
+                put_key(out + round, key_of(__uint_as_float(FP32 ? bits : bits << 16), (unsigned)(winner - pos_lo) + token_lo));
             }
             if (round + 1 < k) {                                        // the winner's lane: its next best
                 const int rest = rest_max(v, base, top, winner);
@@ -291,6 +295,20 @@ __global__ __launch_bounds__(DS_THREADS, 4) void ds2d_best_partial(const Ds2dArg
     for (int u = 0; u < VPT; ++u) q[u] = ordered<FP32>(q[u]);
     if (take(std::true_type{})) return;
     slice_by_keys<FP32>(a, slice_first, pos_lo, pos_hi, token_lo, k, out, lane);
+}
+
+template <bool FP32>
+__global__ __launch_bounds__(DS_THREADS, 4) void ds2d_best_partial(const Ds2dArgs a)
+{
+    const int stream = (int)blockIdx.y / a.rows, r = (int)blockIdx.y - stream * a.rows, row = stream * a.R + r;
+    const int k = wanted(a, r);
+    const int lane = threadIdx.x & 63;
+    const int slice = (int)blockIdx.x * (DS_THREADS / 64) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (k == 0 || slice >= a.slices) return;
+    unsigned long long *out = a.partial + ((size_t)row * a.slices + slice) * DS_KMAX;
+    // (late drafts: the count of the stream's blocks in the next launch starts from zero)
+    if (a.rows != a.R && r == 0 && slice == 0 && lane == 0) put_key(out + 1, 0ull);
+    slice_best<FP32>(a, row, slice, k, out, lane);
 }
 
 // One block per stream: a chain of latencies, kept short.  Sixteen lanes reduce a token row's slices
@@ -317,16 +335,18 @@ __device__ __forceinline__ unsigned long long row16_max(unsigned long long v)
     step(std::integral_constant<int, 1>{});
     return v;
 }
-__global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a)
+struct VerifyLds {
+    unsigned long long best_key[MLORA_DS2D_MAX_ROWS];
+    unsigned long long pool[DS_POOL];
+    int walk_end, walk_token;
+    int cand[MLORA_DS2D_MAX_FORECAST][DS_KMAX];
+    int lists[MLORA_DS2D_MAX_FORECAST][DS_KMAX];           // slices whose best is among the b' best of all
+};
+// The walk down stream s's tree: lds.walk_end and walk_token, and (`write`) the accepted rows and tokens.
+__device__ __forceinline__ void walk_tree(const Ds2dArgs &a, int s, VerifyLds &lds, bool write)
 {
-    __shared__ unsigned long long best_key[MLORA_DS2D_MAX_ROWS];
-    __shared__ unsigned long long pool[DS_POOL];
-    __shared__ int walk_end, walk_token;
-    __shared__ int cand[MLORA_DS2D_MAX_FORECAST][DS_KMAX];
-    __shared__ int lists[MLORA_DS2D_MAX_FORECAST][DS_KMAX];    // slices whose best is among the b' best of all
-    const int s = blockIdx.x, tid = threadIdx.x;
+    const int tid = threadIdx.x;
     const unsigned long long *base = a.partial + (size_t)s * a.R * a.slices * DS_KMAX;
-
     const int my_tok = tid < a.T ? a.tokens[(size_t)s * a.T + tid] : 0;
     const int my_parent = tid < a.T ? a.parent[tid] : -1;
     // arg-max of every token row: the best of the first keys of its slices, four loads in flight per lane
@@ -341,7 +361,7 @@ __global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a
             for (int u = 0; u < 4; ++u) best = v[u] > best ? v[u] : best;
         }
         best = row16_max(best);
-        if ((tid & 15) == 0) best_key[r] = best;
+        if ((tid & 15) == 0) lds.best_key[r] = best;
     }
     __syncthreads();
 
@@ -349,38 +369,47 @@ __global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a
     if (tid < 64) {
         int32_t *rows = a.accepted_rows + (size_t)s * (a.m + 1);
         int32_t *out = a.emitted + (size_t)s * (a.m + 1);
-        const int target = tid < a.T ? (int)(~(unsigned)(best_key[tid] & 0xFFFFFFFFull)) : 0;
+        const int target = tid < a.T ? (int)(~(unsigned)(lds.best_key[tid] & 0xFFFFFFFFull)) : 0;
         int cur = 0, n = 0, my_row = tid == 0 ? 0 : -1, my_out = -1;          // lane i holds entry i of both lists
         while (true) {
             const int want = __builtin_amdgcn_readlane(target, cur);
             if (tid == n) my_out = want;
             const unsigned long long kids = n < a.depth ? __ballot(my_parent == cur && tid < a.T && my_tok == want) : 0ull;
             if (!kids) {
-                if (tid == 0) walk_token = want;
+                if (tid == 0) lds.walk_token = want;
                 break;
             }
             cur = (int)__builtin_ctzll(kids);
             ++n;
             if (tid == n) my_row = cur;
         }
-        if (tid <= a.m) {
+        if (write && tid <= a.m) {
             rows[tid] = my_row;
             out[tid] = my_out;
         }
         if (tid == 0) {
-            a.n_accepted[s] = n;
-            walk_end = cur;
+            if (write) a.n_accepted[s] = n;
+            lds.walk_end = cur;
         }
     }
     __syncthreads();
-    const int cur = walk_end;
+}
+
+// The next tree of stream s from the lists of level i's candidates in row first_row + i of the stream.
+template <bool SAME_LAUNCH>
+__device__ __forceinline__ void draft_tree(const Ds2dArgs &a, int s, VerifyLds &lds, int first_row)
+{
+    const int tid = threadIdx.x, cur = lds.walk_end;
+    unsigned long long *const pool = lds.pool;
+    auto &cand = lds.cand;
+    auto &lists = lds.lists;
     int32_t *nt = a.next_tokens + (size_t)s * a.T_next;
-    if (tid == 0) nt[0] = walk_token;
+    if (tid == 0) nt[0] = lds.walk_token;
 
     // Level i of the next tree: the b'_i best of forecast embedding i of the node `cur`, by rank: a
     // candidate with r better ones is number r (keys differ).  Common case: the candidates of all levels
     // fit the pool and are requested at once, candidate t % 16 of slices t / 16, t / 16 + 16, ... by thread t.
-    const unsigned long long *rows_of_cur = base + (size_t)(a.T + cur * a.m) * a.slices * DS_KMAX;
+    const unsigned long long *rows_of_cur = a.partial + (size_t)(s * a.R + first_row) * a.slices * DS_KMAX;
     const int r16 = tid & 15, s16 = tid >> 4;
     int total = 0, most = 0;
     for (int i = 0; i < a.next_depth; ++i) {
@@ -394,7 +423,7 @@ __global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a
             const int b = a.next_branch[i];
             const unsigned long long *p = rows_of_cur + (size_t)i * a.slices * DS_KMAX;
             if (r16 < b)
-                for (int c = s16; c < a.slices; c += 16) pool[at + c * b + r16] = p[(size_t)c * DS_KMAX + r16];
+                for (int c = s16; c < a.slices; c += 16) pool[at + c * b + r16] = get_key<SAME_LAUNCH>(p + (size_t)c * DS_KMAX + r16);
             at += a.slices * b;
         }
         __syncthreads();
@@ -453,7 +482,7 @@ __global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a
             for (int c0 = 0; c0 < a.slices;) {
                 const int n_new = min(a.slices - c0, DS_POOL - kept), n = kept + n_new;
                 __syncthreads();
-                for (int c = tid; c < n_new; c += DS_THREADS) pool[kept + c] = p[(size_t)(c0 + c) * DS_KMAX];
+                for (int c = tid; c < n_new; c += DS_THREADS) pool[kept + c] = get_key<SAME_LAUNCH>(p + (size_t)(c0 + c) * DS_KMAX);
                 __syncthreads();
                 constexpr int OWN = DS_POOL / DS_THREADS;
                 unsigned long long own[OWN];
@@ -486,7 +515,7 @@ __global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a
             if (tid < b * b) {
                 const unsigned long long head = pool[tid / b];
                 const int slice = (int)(((unsigned)(first % epv) + ~(unsigned)(head & 0xFFFFFFFFull)) / DS_SLICE);
-                if (head) key = p[(size_t)slice * DS_KMAX + tid % b];
+                if (head) key = get_key<SAME_LAUNCH>(p + (size_t)slice * DS_KMAX + tid % b);
             }
             __syncthreads();
             if (tid < b * b) pool[tid] = key;
@@ -504,6 +533,42 @@ __global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a
         for (int q = tid; q < width; q += DS_THREADS) nt[offset + q] = cand[i][q % b];
         offset += width;
     }
+}
+
+__global__ __launch_bounds__(DS_THREADS) void ds2d_verify_draft(const Ds2dArgs a)
+{
+    __shared__ VerifyLds lds;
+    walk_tree(a, blockIdx.x, lds, true);
+    draft_tree<false>(a, blockIdx.x, lds, a.T + lds.walk_end * a.m);
+}
+
+// Late drafts: of a stream's forecast rows the step needs those of the node where the walk ends, so where reading the
+// others takes longer than walking first, ds2d_best_partial looks at the token rows only and this kernel follows.
+// Every block makes the walk for itself (T * slices keys, a trip to memory that runs beside nothing else), takes four
+// slices of one forecast row, and the last block of a stream, by a count that the launch before has set to zero, drafts.
+// The lists of level i lie where those of node 0's row would.  8 streams of 30 rows over 128256 bf16 logits, of which 24.6
+// of 61.5 MB are read: 21.8 -> 17.0 us a step.
+template <bool FP32>
+__global__ __launch_bounds__(DS_THREADS, 4) void ds2d_walk_draft(const Ds2dArgs a)
+{
+    __shared__ VerifyLds lds;
+    __shared__ bool last;
+    const int s = (int)blockIdx.y / a.next_depth, level = (int)blockIdx.y - s * a.next_depth, lane = threadIdx.x & 63;
+    walk_tree(a, s, lds, blockIdx.x == 0 && level == 0);
+    const int slice = (int)blockIdx.x * (DS_THREADS / 64) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    unsigned long long *const lists = a.partial + (size_t)(s * a.R + a.T + level) * a.slices * DS_KMAX;
+    if (slice < a.slices) slice_best<FP32>(a, s * a.R + a.T + lds.walk_end * a.m + level, slice, a.next_branch[level], lists + (size_t)slice * DS_KMAX, lane);
+    // (the keys, then the count: see put_key; all of a wave's stores are acknowledged before the block meets)
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0)
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned *const count = reinterpret_cast<unsigned *>(a.partial + (size_t)s * a.R * a.slices * DS_KMAX + 1);
+        last = atomicAdd(count, 1u) + 1u == gridDim.x * (unsigned)a.next_depth;
+    }
+    __syncthreads();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    if (last) draft_tree<true>(a, s, lds, a.T);
 }
 
 }  // namespace mlora
@@ -547,6 +612,16 @@ int slices_of(const mlora_ds2d &d)
     const long long vectors = (long long)d.vocab / epv + 2;             // a row may straddle two more
     const long long per_block = DS_SLICE / epv;
     return (int)((vectors + per_block - 1) / per_block);
+}
+
+// Whether the forecast rows wait for the walk (see ds2d_walk_draft): where that spares more than LATE_BYTES of logits
+// (42 drawn steps both ways, us by MB spared: 8 13.3 -> 14.8, 15 14.1 -> 15.1, 21 15.2 -> 15.5 and 26.0 -> 22.0, 28 16.3 ->
+// 15.4, 37 21.8 -> 17.0, 47 21.7 -> 16.0; a few kB 8.9 -> 11.9).
+constexpr long long LATE_BYTES = 22000000;
+bool late_drafts(const Ds2dArgs &a)
+{
+    const long long row = (long long)a.V * (a.fp32 ? 4 : 2);
+    return (long long)a.S * (a.T - 1) * a.next_depth * row > LATE_BYTES;
 }
 
 mlora_status check(const mlora_ds2d *d, int &T, int &R, int &T_next)
@@ -646,9 +721,17 @@ mlora_status mlora_ds2d_step(const mlora_ds2d *d, const void *logits, const int3
     for (int r = 0; r < MLORA_DS2D_MAX_ROWS; ++r) a.parent[r] = r < T ? (signed char)par[r] : (signed char)-1;
 
     hipStream_t s = (hipStream_t)stream;
-    if (a.fp32) hipLaunchKernelGGL(ds2d_best_partial<true>, dim3((a.slices + 3) / 4, d->n_streams * R), dim3(DS_THREADS), 0, s, a);
-    else hipLaunchKernelGGL(ds2d_best_partial<false>, dim3((a.slices + 3) / 4, d->n_streams * R), dim3(DS_THREADS), 0, s, a);
-    hipLaunchKernelGGL(ds2d_verify_draft, dim3(d->n_streams), dim3(DS_THREADS), 0, s, a);
+    const bool late = late_drafts(a);
+    a.rows = late ? T : R;
+    const dim3 grid((a.slices + 3) / 4, d->n_streams * a.rows), late_grid((a.slices + 3) / 4, d->n_streams * (late ? a.next_depth : 1));
+    auto by_type = [&](auto fp32) {
+        constexpr bool FP32 = decltype(fp32)::value;
+        ds2d_best_partial<FP32><<<grid, dim3(DS_THREADS), 0, s>>>(a);
+        if (late) ds2d_walk_draft<FP32><<<late_grid, dim3(DS_THREADS), 0, s>>>(a);
+        else      ds2d_verify_draft<<<dim3(d->n_streams), dim3(DS_THREADS), 0, s>>>(a);
+    };
+    if (a.fp32) by_type(std::true_type{});
+    else        by_type(std::false_type{});
     return hipGetLastError() == hipSuccess ? MLORA_OK : MLORA_EHIP;
 }
 

@@ -279,6 +279,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
         };
         const bool whole_tiles = wide && block_rows == 32 && longest <= SUPER_K;    // a tile per wave
         if (!whole_tiles && base + shrink_blocks(1) <= SHRINK_ALL_LIVE_BLOCKS) shrink_tiles = 1;
+        else if (wide && longest >= SHRINK_LONG_INPUTS && base + shrink_blocks(2) <= (waves_per_tile == 2 ? SHRINK_ALL_LIVE_BLOCKS : SHRINK_TWO_LIVE_BLOCKS)) shrink_tiles = 2;
         else if (base + shrink_blocks(4) <= SHRINK_ALL_LIVE_BLOCKS) shrink_tiles = 4;
         else if (wide && shrink_blocks(4) <= SHRINK_FEW_BLOCKS) shrink_tiles = 4;
     }

@@ -253,7 +253,10 @@ __device__ inline f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
 // (SHRINK_ALL_LIVE_BLOCKS; 8192 x 2048 at 64 rows, 8 adapters of rank 16, 40 us with 16, 22.7 with 4, 19.4 with
 // 1), unless every wave has tiles of its own (128 inputs: 100 drawn calls at 17 to 700 rows 0.98 of the time with 4);
 // else 4 where they do with 4 (4096 x 14336 at 64 rows, 32 adapters of rank 64: 41.5 us with 16 tiles, 35.4 with 4; 14336
-// x 4096 49.5 and 32.5), or, in wide blocks, where 4 make at most 300 shrink blocks (SHRINK_FEW_BLOCKS; 4352 x
+// x 4096 49.5 and 32.5; two in wide blocks where inputs are long, so that a tile is several trips to memory, and the launch
+// stays within the places with them, 500 of eight waves, 640 of four: 2688 x 1103 at 251 rows, 4 adapters of rank 128
+// 23.2 -> 18.7, three layers of 2048 at 126 rows 81 -> 76; 53 drawn calls 0.985 of the time; with 640 of eight waves 4096 x
+// 14336 as above 31.3 -> 32.0), or, in wide blocks, where 4 make at most 300 shrink blocks (SHRINK_FEW_BLOCKS; 4352 x
 // 5466 at 441 rows, 10 adapters of rank 32, 80 us with 8, 49 with 4, 4480 x 12672 at 320 rows 97 and 65; 280 drawn calls of
 // 3000 to 14336 outputs at 150 to 1024 rows 0.97 of the time, 8 of them more than 3 % longer, by 17 % at most; 320
 // to 480 such blocks: as many calls lose as gain, 3328 x 3563 at 593 rows 52 -> 61).
@@ -265,7 +268,7 @@ __host__ __device__ inline int max_row_tiles(int rows, int n_adapters)
     const int bound = rows / 16 + segs;
     return bound < rows ? bound : rows;
 }
-constexpr int SHRINK_ALL_LIVE_BLOCKS = 500, SHRINK_FEW_BLOCKS = 300;
+constexpr int SHRINK_ALL_LIVE_BLOCKS = 500, SHRINK_TWO_LIVE_BLOCKS = 640, SHRINK_FEW_BLOCKS = 300, SHRINK_LONG_INPUTS = 1024;
 __host__ __device__ inline int shrink_tile_shares(int M, int n_adapters, int tiles_per_block)
 {
     const int tiles = max_row_tiles(M < SHRINK_CHUNK_ROWS ? M : SHRINK_CHUNK_ROWS, n_adapters);

@@ -333,7 +333,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
                 d.ksplit = ksplit;
                 // blocks (wide kernel: waves) that wait for this projection's shrink blocks: the
                 // finishing ones, or every K unit where the LoRA term is spread over them
-                d.lora_units = std::min(p.n_adapters, block_rows) * (r16_of(p) / 16) <= LORA_FEW_PASSES ? 1 : ksplit;
+                d.lora_units = base <= LORA_FEW_BLOCKS && std::min(p.n_adapters, block_rows) * (r16_of(p) / 16) <= LORA_FEW_PASSES ? 1 : ksplit;
                 d.n_finish_blocks = tiles * row_blocks * (wide ? d.lora_units * waves_per_tile : 1);
                 d.unit_q = (p.K / SUPER_K) / ksplit;
                 d.unit_r = (p.K / SUPER_K) % ksplit;

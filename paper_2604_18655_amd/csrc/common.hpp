@@ -324,10 +324,12 @@ constexpr int WIDE_TILES_PER_BLOCK = 4;
 // (see wide_short_kernel, which also says what both sides measured).
 constexpr int WIDE_SHORT_MAX_BLOCKS = 230;
 // Passes (adapters of a block's rows x runs of 16 ranks) up to which the finishing block of a tile makes the whole LoRA
-// term: the other K units then leave their partial tiles without waiting for t (2432 x 382 at 396 rows, one adapter of rank
+// term in launches of at most LORA_FEW_BLOCKS base blocks, one per compute unit: the other K units then leave their partial
+// tiles without waiting for t (with more blocks they wait beside others' work, and the share they take is worth more:
+// two layers of 1536 with int8 rows at 56 rows, 280 blocks, 24.0 -> 24.3 us; 2432 x 382 at 396 rows, one adapter of rank
 // 64 21.5 -> 15.7 us; 3072 x 8192 at 128 rows, 8 adapters of rank 16 19.0 -> 18.6; two layers of 2176 at 130 rows 82 -> 78;
 // 85 calls 0.99 of the time, with two adapters of rank 64 as many gain as lose).
-constexpr int LORA_FEW_PASSES = 8;
+constexpr int LORA_FEW_PASSES = 8, LORA_FEW_BLOCKS = 256;
 constexpr int CHUNK16_MAX_BLOCKS = 300;    // tile launches of 17 to 32 rows below this run chunks of 16 rows
 __host__ inline int rows_per_chunk(int M) { return M <= 16 ? 16 : M <= 32 ? 32 : 64; }
 // column tiles a base block covers

@@ -242,24 +242,29 @@ __device__ inline f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
 }
 
-// The grouped shrink step (more than 16 rows) works on chunks of 64 rows: the rows of a chunk are
-// grouped by adapter (one wave, no sort) and every segment is cut into tiles of 16 rows.  Upper
-// bound of the tiles of a chunk of `rows` rows (at most 64): a tile per 16 rows plus one per
-// segment, at most a tile per row.  The chunk's tiles are shared out over blocks of up to 8 (wide blocks of 32
-// rows) or 16 (the others, which have two places per compute unit: 16 layers at 512 rows 1313 us against 1342
-// with 8, a layer at 32 rows in tile blocks 25 against 29) where a launch has many of them.  Fewer tiles are a shorter
-// chain ahead of every block that finishes outputs, more are fewer blocks, idle ones included, whose signals queue up at
-// the same counters.  One tile per block where all blocks of the launch find a place at once with it
-// (SHRINK_ALL_LIVE_BLOCKS; 8192 x 2048 at 64 rows, 8 adapters of rank 16, 40 us with 16, 22.7 with 4, 19.4 with
-// 1), unless every wave has tiles of its own (128 inputs: 100 drawn calls at 17 to 700 rows 0.98 of the time with 4);
-// else 4 where they do with 4 (4096 x 14336 at 64 rows, 32 adapters of rank 64: 41.5 us with 16 tiles, 35.4 with 4; 14336
-// x 4096 49.5 and 32.5; two in wide blocks where inputs are long, so that a tile is several trips to memory, and the launch
-// stays within the places with them, 500 of eight waves, 640 of four: 2688 x 1103 at 251 rows, 4 adapters of rank 128
-// 23.2 -> 18.7, three layers of 2048 at 126 rows 81 -> 76; 53 drawn calls 0.985 of the time; with 640 of eight waves 4096 x
-// 14336 as above 31.3 -> 32.0), or, in wide blocks, where 4 make at most 300 shrink blocks (SHRINK_FEW_BLOCKS; 4352 x
-// 5466 at 441 rows, 10 adapters of rank 32, 80 us with 8, 49 with 4, 4480 x 12672 at 320 rows 97 and 65; 280 drawn calls of
-// 3000 to 14336 outputs at 150 to 1024 rows 0.97 of the time, 8 of them more than 3 % longer, by 17 % at most; 320
-// to 480 such blocks: as many calls lose as gain, 3328 x 3563 at 593 rows 52 -> 61).
+// The grouped shrink step (more than 16 rows) works on chunks of 64 rows: the rows of a chunk are grouped by adapter
+// (one wave, no sort) and every segment is cut into tiles of 16 rows.  Upper bound of the tiles of a chunk of `rows`
+// rows (at most 64): a tile per 16 rows plus one per segment, at most a tile per row.  The chunk's tiles are shared
+// out over blocks of up to 8 (wide blocks of 32 rows) or 16 (the others, which have two places per compute unit: 16
+// layers at 512 rows 1313 us against 1342 with 8, a layer at 32 rows in tile blocks 25 against 29) where a launch
+// has many of them.  Fewer tiles are a shorter chain ahead of every block that finishes outputs, more are fewer
+// blocks, idle ones included, whose signals queue up at the same counters.  One tile per block where all blocks of
+// the launch find a place at once with it (SHRINK_ALL_LIVE_BLOCKS; 8192 x 2048 at 64 rows, 8 adapters of rank 16, 40
+// us with 16, 22.7 with 4, 19.4 with 1), unless every wave has tiles of its own (128 inputs: 100 drawn calls at 17
+// to 700 rows 0.98 of the time with 4); else 4 where they do with 4 (4096 x 14336 at 64 rows, 32 adapters of rank
+// 64: 41.5 us with 16 tiles, 35.4 with 4; 14336 x 4096 49.5 and 32.5; two in wide blocks where inputs are long, so
+// that a tile is several trips to memory, and the launch stays within 640 blocks with them: three layers of 2048 at
+// 126 rows 81 -> 76; blocks of eight waves share a CU's matrix and memory pipes with fewer others and stand in each
+// other's way sooner: one tile where that makes up to 160 shrink blocks and 300 in all, two from 2048 inputs where
+// that makes up to 260 and 500 in all; one tile at 24 to 150 shrink blocks 1.03 to 1.2 times as fast as four, four
+// at 176 and more 1.0 to 1.3 times as fast as one: 1152 x 4261 at 65 rows, 7 adapters of rank 128, 18.6 and 14.6 us,
+// 3456 x 865 at 72, 5 of rank 64, 20.1 and with two tiles 17.3; two at 470, 1152 x 2453 at 450 rows, 32.8, four
+// 23.2; two at 456, 2688 x 1103 at 251 rows, 4 of rank 128, 21.1, four 28.1; 10112 x 537 at 84 rows, all on one of
+// 30 adapters of rank 24, 22.1 with two (272 blocks, most idle), 17.5 with four), or, in wide blocks, where 4 make
+// at most 300 shrink blocks (SHRINK_FEW_BLOCKS; 4352 x 5466 at 441 rows, 10 adapters of rank 32, 80 us with 8, 49
+// with 4, 4480 x 12672 at 320 rows 97 and 65; 280 drawn calls of 3000 to 14336 outputs at 150 to 1024 rows 0.97 of
+// the time, 8 of them more than 3 % longer, by 17 % at most; 320 to 480 such blocks: as many calls lose as gain,
+// 3328 x 3563 at 593 rows 52 -> 61).
 // Host (grid size) and device (block index -> chunk, share) use the same figures.
 constexpr int SHRINK_CHUNK_ROWS = 64;
 __host__ __device__ inline int max_row_tiles(int rows, int n_adapters)
@@ -268,7 +273,9 @@ __host__ __device__ inline int max_row_tiles(int rows, int n_adapters)
     const int bound = rows / 16 + segs;
     return bound < rows ? bound : rows;
 }
-constexpr int SHRINK_ALL_LIVE_BLOCKS = 500, SHRINK_TWO_LIVE_BLOCKS = 640, SHRINK_FEW_BLOCKS = 300, SHRINK_LONG_INPUTS = 1024;
+constexpr int SHRINK_ALL_LIVE_BLOCKS = 500, SHRINK_TWO_LIVE_BLOCKS = 640;
+constexpr int SHRINK_ALL_SHORT_BLOCKS = 300, SHRINK_ONE_SHORT_BLOCKS = 160, SHRINK_TWO_SHORT_BLOCKS = 260;
+constexpr int SHRINK_FEW_BLOCKS = 300, SHRINK_LONG_INPUTS = 1024;
 __host__ __device__ inline int shrink_tile_shares(int M, int n_adapters, int tiles_per_block)
 {
     const int tiles = max_row_tiles(M < SHRINK_CHUNK_ROWS ? M : SHRINK_CHUNK_ROWS, n_adapters);

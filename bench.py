@@ -301,7 +301,7 @@ def bench_layer(args):
         "us_per_step": round(elapsed * 1e6 / K, 3), "pct_of_hbm_peak": round(100.0 * gbs / HBM_PEAK_GBS, 2),
         "algorithmic_bytes_per_step": int(step_bytes), "max_rel_err": float(f"{max_rel_err:.3e}"),
         "setup_s": round(setup_s, 1),
-        "roofline": {"kernel": "layer_kernel<1, 16, 1> x 4 + tree_attn_partial/combine + rms_scale_kernel (one step)",
+        "roofline": {"kernel": "layer_kernel<1, 16, 1> x 4 + tree_attn/combine + rms_scale_kernel (one step)",
                      "bound": "hbm", "achieved": round(step_bytes / step_s / 1e9, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(step_bytes / step_s / 1e9 / HBM_PEAK_GBS, 4), "traffic": None,
                      "algorithmic_bytes_per_launch": int(step_bytes), "avg_launch_us": round(step_s * 1e6, 3),
@@ -406,7 +406,7 @@ def bench_attention(args):
         "us_per_step": round(elapsed * 1e6 / K, 3), "us_per_call": round(elapsed * 1e6 / K / layers, 3),
         "pct_of_hbm_peak": round(100.0 * gbs / HBM_PEAK_GBS, 2), "algorithmic_bytes_per_step": step_bytes,
         "max_rel_err": float(f"{max_rel_err:.3e}"), "setup_s": round(setup_s, 1),
-        "roofline": {"kernel": "tree_attn_partial<64> + tree_attn_combine<64> (one call)", "bound": "hbm",
+        "roofline": {"kernel": "tree_attn<64, 1, 8, true> + tree_attn_combine<64> (one call)", "bound": "hbm",
                      "achieved": round(call_bytes / call_s / 1e9, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(call_bytes / call_s / 1e9 / HBM_PEAK_GBS, 4), "traffic": None,
                      "algorithmic_bytes_per_launch": int(call_bytes), "avg_launch_us": round(call_s * 1e6, 3),
@@ -634,10 +634,14 @@ def main():
     wide = info["wide"]
     spg = w.projs[0].group // 32
     rows = lib.layer_step_block_rows(plans[0][0].keep[0], M, args.a8)
-    kernel_name = ("wide_kernel<%d, %d, %s, %s>" % (spg, rows // 16, "true" if args.a8 else "false", "true" if rows == 64 or M > 32 else "false")) if wide else \
+    # two waves per tile in launches of one group with at most 230 base blocks of 32 rows (rounded up to whole XCDs here)
+    bare = [lib.Proj(p.K, p.N, p.group, None) for p in plans[0][0].keep[0]]
+    short = wide and rows == 32 and info["grid_z"] == 1 and lib.layer_step_plan(bare, M)["grid_x"] <= 232
+    kernel_name = "wide_short_kernel<%d, %s>" % (spg, "true" if args.a8 else "false") if short else \
+        ("wide_kernel<%d, %d, %s, %s>" % (spg, rows // 16, "true" if args.a8 else "false", "true" if rows == 64 or M > 32 else "false")) if wide else \
         "layer_kernel<%s, %d>" % ("1, 8" if M <= 8 else "1, 16" if rows == 16 else "2, 24" if M <= 24 else "2, 32",
                                   1 if rows == 16 and info["grid_z"] == 1 else 8)
-    kernel_tag = ("wide_kernel_a8" if args.a8 else "wide_kernel") if wide else "layer_kernel"
+    kernel_tag = "wide_short_kernel" if short else ("wide_kernel_a8" if args.a8 else "wide_kernel") if wide else "layer_kernel"
     achieved_tflops = (step_flops / launches_per_step) / kern_s / 1e12
     bound = BOUND.get(w.key, "hbm")
     traffic, traffic_src = measured_traffic(kernel_tag, w.key) if not (args.per_layer_calls or args.lora_int16) else (None, None)

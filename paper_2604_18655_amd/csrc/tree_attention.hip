@@ -309,7 +309,7 @@ __global__ __launch_bounds__(64 * W, (D == 64 && QT == 1 ? 4 : 2)) void tree_att
             if (f == 0) a.part_ml[at] = make_float2(top, den);
             *reinterpret_cast<f32x4 *>(a.part_out + at * D + f) = num;
         } else {
-            num *= 1.0f / den;                                 // (a row always sees itself: den > 0)
+            num /= den;                                        // (a row always sees itself: den > 0)
             if (a.out_fp32) *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.out) + vec * D + f) = num;
             else *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(a.out) + vec * D + f) = make_uint2(pack_bf16(num[0], num[1]), pack_bf16(num[2], num[3]));
         }
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(256) void tree_attn_combine(const AttnArgs a)
         }
         run_top = top;
     }
-    num *= 1.0f / den;
+    num /= den;
     const size_t at = (size_t)vec * D + f;
     if (a.out_fp32) *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.out) + at) = num;
     else *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(a.out) + at) = make_uint2(pack_bf16(num[0], num[1]), pack_bf16(num[2], num[3]));

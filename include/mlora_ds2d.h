@@ -71,6 +71,10 @@ typedef struct mlora_ds2d {
  * descriptor.  Contents need no initialisation and carry nothing from call to call. */
 size_t mlora_ds2d_workspace_bytes(const mlora_ds2d *d);
 
+/* How such a step reads the forecast rows: 1 = after the walk, those of the node where it ends only; 0 = all of them
+ * beside the token rows (or a bad descriptor).  The outputs are the same. */
+int32_t mlora_ds2d_late_drafts(const mlora_ds2d *d);
+
 /* One step for all streams.  R = rows of this step's tree, T = its tokens, T' = tokens of the
  * next step's tree (mlora_ds2d_rows).
  *   logits      [S * R][V]   in  bf16 or fp32: row s * R + r is row r of stream s

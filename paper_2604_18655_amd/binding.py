@@ -20,7 +20,8 @@ exported_symbols = (
     "mlora_tree_attention_workspace_bytes", "mlora_tree_attention",
     "mlora_w4a8_workspace_bytes", "mlora_w4a8_layer_step",
     "mlora_w4_layer_step_fused", "mlora_rms_scale", "mlora_lora_int16_expand",
-    "mlora_ds2d_rows", "mlora_ds2d_layout", "mlora_ds2d_workspace_bytes", "mlora_ds2d_step",
+    "mlora_ds2d_rows", "mlora_ds2d_layout", "mlora_ds2d_workspace_bytes", "mlora_ds2d_late_drafts",
+    "mlora_ds2d_step",
 )
 
 
@@ -120,6 +121,8 @@ def load_library():
         lib.mlora_ds2d_layout.argtypes = [ip, i32, i32, ip, C.POINTER(C.c_uint8), ip]
         lib.mlora_ds2d_workspace_bytes.restype = sz
         lib.mlora_ds2d_workspace_bytes.argtypes = [dp]
+        lib.mlora_ds2d_late_drafts.restype = i32
+        lib.mlora_ds2d_late_drafts.argtypes = [dp]
         lib.mlora_ds2d_step.restype = C.c_int
         lib.mlora_ds2d_step.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         lib.mlora_w4_workspace_status.restype = C.c_int
@@ -447,6 +450,10 @@ class Ds2dStep:
 
     def workspace_bytes(self) -> int:
         return int(load_library().mlora_ds2d_workspace_bytes(C.byref(self.struct)))
+
+    def late_drafts(self) -> bool:
+        """Whether the step reads the forecast rows after the walk (see mlora_ds2d_late_drafts)."""
+        return bool(load_library().mlora_ds2d_late_drafts(C.byref(self.struct)))
 
     def run(self, logits, tokens, n_accepted, accepted_rows, emitted, next_tokens, workspace,
             stream: Optional[int] = None) -> None:

@@ -616,12 +616,19 @@ int slices_of(const mlora_ds2d &d)
 
 // Whether the forecast rows wait for the walk (see ds2d_walk_draft): where that spares more than LATE_BYTES of logits
 // (42 drawn steps both ways, us by MB spared: 8 13.3 -> 14.8, 15 14.1 -> 15.1, 21 15.2 -> 15.5 and 26.0 -> 22.0, 28 16.3 ->
-// 15.4, 37 21.8 -> 17.0, 47 21.7 -> 16.0; a few kB 8.9 -> 11.9).
+// 15.4, 37 21.8 -> 17.0, 47 21.7 -> 16.0; a few kB 8.9 -> 11.9) and the walk that every block makes for itself is not too
+// long: its keys lie in lines of their own, so the blocks' walks grow with the square of the vocabulary while what is spared
+// grows with the vocabulary.  At most LATE_WALK times the bytes spared (1 to 8 streams, trees of 2 to 10 tokens, up to 20
+// million logits a row, time of the late form against the other by that ratio: up to 3.3 0.55 to 1.04, 3.8 to 4.8 0.88 to
+// 1.03, 5.7 to 6.4 0.96 to 1.09, 6.9 to 9.6 1.01 to 1.21, above that 1.01 to 2.6; with rows of 128256 bf16 logits it is 0.14).
 constexpr long long LATE_BYTES = 22000000;
-bool late_drafts(const Ds2dArgs &a)
+constexpr double LATE_WALK = 3.5;
+bool late_drafts(const mlora_ds2d &d, int T)
 {
-    const long long row = (long long)a.V * (a.fp32 ? 4 : 2);
-    return (long long)a.S * (a.T - 1) * a.next_depth * row > LATE_BYTES;
+    const long long row = (long long)d.vocab * (d.logits_dtype == MLORA_Y_FP32 ? 4 : 2), slices = slices_of(d);
+    const long long spared = (T - 1) * row;                             // of a stream and level
+    const double walk = (double)((slices + 3) / 4) * (double)(T * slices * DS_KMAX * (long long)sizeof(unsigned long long));
+    return (long long)d.n_streams * d.next_depth * spared > LATE_BYTES && walk <= LATE_WALK * (double)spared;
 }
 
 mlora_status check(const mlora_ds2d *d, int &T, int &R, int &T_next)
@@ -684,6 +691,12 @@ size_t mlora_ds2d_workspace_bytes(const mlora_ds2d *d)
     return (size_t)d->n_streams * R * slices_of(*d) * DS_KMAX * sizeof(unsigned long long);
 }
 
+int32_t mlora_ds2d_late_drafts(const mlora_ds2d *d)
+{
+    int T, R, T_next;
+    return check(d, T, R, T_next) == MLORA_OK && late_drafts(*d, T) ? 1 : 0;
+}
+
 mlora_status mlora_ds2d_step(const mlora_ds2d *d, const void *logits, const int32_t *tokens,
                              int32_t *n_accepted, int32_t *accepted_rows, int32_t *emitted,
                              int32_t *next_tokens, void *workspace, size_t workspace_bytes,
@@ -721,7 +734,7 @@ mlora_status mlora_ds2d_step(const mlora_ds2d *d, const void *logits, const int3
     for (int r = 0; r < MLORA_DS2D_MAX_ROWS; ++r) a.parent[r] = r < T ? (signed char)par[r] : (signed char)-1;
 
     hipStream_t s = (hipStream_t)stream;
-    const bool late = late_drafts(a);
+    const bool late = late_drafts(*d, T);
     a.rows = late ? T : R;
     const dim3 grid((a.slices + 3) / 4, d->n_streams * a.rows), late_grid((a.slices + 3) / 4, d->n_streams * (late ? a.next_depth : 1));
     auto by_type = [&](auto fp32) {

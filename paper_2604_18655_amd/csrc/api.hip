@@ -283,7 +283,8 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
                               (!short_launch || shrink_blocks(1) <= SHRINK_ONE_SHORT_BLOCKS);
         const bool two_fit = short_launch ? longest >= 2 * SHRINK_LONG_INPUTS && shrink_blocks(2) <= SHRINK_TWO_SHORT_BLOCKS &&
                                                 base + shrink_blocks(2) <= SHRINK_ALL_LIVE_BLOCKS
-                                          : longest >= SHRINK_LONG_INPUTS && base + shrink_blocks(2) <= SHRINK_TWO_LIVE_BLOCKS;
+                                          : block_rows == 32 && longest >= SHRINK_LONG_INPUTS && shrink_blocks(2) <= SHRINK_TWO_BLOCKS &&
+                                                base + shrink_blocks(2) <= SHRINK_TWO_LIVE_BLOCKS;
         if (!whole_tiles && one_fits) shrink_tiles = 1;
         else if (wide && two_fit) shrink_tiles = 2;
         else if (base + shrink_blocks(4) <= SHRINK_ALL_LIVE_BLOCKS) shrink_tiles = 4;

@@ -252,9 +252,11 @@ __device__ inline f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
 // the launch find a place at once with it (SHRINK_ALL_LIVE_BLOCKS; 8192 x 2048 at 64 rows, 8 adapters of rank 16, 40
 // us with 16, 22.7 with 4, 19.4 with 1), unless every wave has tiles of its own (128 inputs: 100 drawn calls at 17
 // to 700 rows 0.98 of the time with 4); else 4 where they do with 4 (4096 x 14336 at 64 rows, 32 adapters of rank
-// 64: 41.5 us with 16 tiles, 35.4 with 4; 14336 x 4096 49.5 and 32.5; two in wide blocks where inputs are long, so
-// that a tile is several trips to memory, and the launch stays within 640 blocks with them: three layers of 2048 at
-// 126 rows 81 -> 76; blocks of eight waves share a CU's matrix and memory pipes with fewer others and stand in each
+// 64: 41.5 us with 16 tiles, 35.4 with 4; 14336 x 4096 49.5 and 32.5; two in wide blocks of 32 rows where inputs are long,
+// so that a tile is several trips to memory, that makes up to 192 shrink blocks and the launch stays within 640 blocks: 68
+// drawn calls 0.987 of the time with four, 5632 x 1700 at 466 rows, 11 adapters of rank 16, 33.3 -> 29.1, 8576 x 1840 at 309
+// rows 29.5 -> 27.0, the worst 1.06; with more than 192 such blocks 19 calls 1.04, 12928 x 4198 at 56 rows, 23 of rank
+// 64, 27.6 -> 31.2; blocks of 64 rows, 22 calls: 1.02, 4480 x 5658 at 302 rows, 19 of rank 24, 42.0 -> 46.4; blocks of eight waves share a CU's matrix and memory pipes with fewer others and stand in each
 // other's way sooner: one tile where that makes up to 160 shrink blocks and 300 in all, two from 2048 inputs where
 // that makes up to 260 and 500 in all; one tile at 24 to 150 shrink blocks 1.03 to 1.2 times as fast as four, four
 // at 176 and more 1.0 to 1.3 times as fast as one: 1152 x 4261 at 65 rows, 7 adapters of rank 128, 18.6 and 14.6 us,
@@ -273,7 +275,7 @@ __host__ __device__ inline int max_row_tiles(int rows, int n_adapters)
     const int bound = rows / 16 + segs;
     return bound < rows ? bound : rows;
 }
-constexpr int SHRINK_ALL_LIVE_BLOCKS = 500, SHRINK_TWO_LIVE_BLOCKS = 640;
+constexpr int SHRINK_ALL_LIVE_BLOCKS = 500, SHRINK_TWO_LIVE_BLOCKS = 640, SHRINK_TWO_BLOCKS = 192;
 constexpr int SHRINK_ALL_SHORT_BLOCKS = 300, SHRINK_ONE_SHORT_BLOCKS = 160, SHRINK_TWO_SHORT_BLOCKS = 260;
 constexpr int SHRINK_FEW_BLOCKS = 300, SHRINK_LONG_INPUTS = 1024;
 __host__ __device__ inline int shrink_tile_shares(int M, int n_adapters, int tiles_per_block)

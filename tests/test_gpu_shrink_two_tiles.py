@@ -16,6 +16,8 @@ CASES = [                                 # inputs, outputs, group, rank, adapte
     (4480, 470, 64, 32, 5, 268, 2),
     (640, 1399, 64, 64, 2, 354, 1),
     (2432, 9000, 64, 64, 4, 130, 2),      # four waves
+    (12928, 4198, 64, 64, 23, 56, 4),     # four waves: two tiles would make 312
+    (4480, 5658, 64, 24, 19, 302, 4),     # blocks of 64 rows
 ]
 
 

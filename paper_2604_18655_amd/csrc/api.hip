@@ -281,7 +281,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
         const bool short_launch = waves_per_tile == 2;
         const bool one_fits = base + shrink_blocks(1) <= (short_launch ? SHRINK_ALL_SHORT_BLOCKS : SHRINK_ALL_LIVE_BLOCKS) &&
                               (!short_launch || shrink_blocks(1) <= SHRINK_ONE_SHORT_BLOCKS);
-        const bool two_fit = short_launch ? longest >= 2 * SHRINK_LONG_INPUTS && shrink_blocks(2) <= SHRINK_TWO_SHORT_BLOCKS &&
+        const bool two_fit = short_launch ? longest >= (count > 1 ? 1 : 2) * SHRINK_LONG_INPUTS && shrink_blocks(2) <= SHRINK_TWO_SHORT_BLOCKS &&
                                                 base + shrink_blocks(2) <= SHRINK_ALL_LIVE_BLOCKS
                                           : block_rows == 32 && longest >= SHRINK_LONG_INPUTS && shrink_blocks(2) <= SHRINK_TWO_BLOCKS &&
                                                 base + shrink_blocks(2) <= SHRINK_TWO_LIVE_BLOCKS;

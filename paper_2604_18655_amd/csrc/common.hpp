@@ -257,7 +257,9 @@ __device__ inline f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
 // drawn calls 0.987 of the time with four, 5632 x 1700 at 466 rows, 11 adapters of rank 16, 33.3 -> 29.1, 8576 x 1840 at 309
 // rows 29.5 -> 27.0, the worst 1.06; with more than 192 such blocks 19 calls 1.04, 12928 x 4198 at 56 rows, 23 of rank
 // 64, 27.6 -> 31.2; blocks of 64 rows, 22 calls: 1.02, 4480 x 5658 at 302 rows, 19 of rank 24, 42.0 -> 46.4; blocks of eight waves share a CU's matrix and memory pipes with fewer others and stand in each
-// other's way sooner: one tile where that makes up to 160 shrink blocks and 300 in all, two from 2048 inputs where
+// other's way sooner: one tile where that makes up to 160 shrink blocks and 300 in all, two from 2048 inputs (in calls of several
+// projections, whose shrink blocks signal to counters of their own, from 1024: 12 drawn calls 0.95 of the time with four,
+// the worst 1.03, a layer of 512 wide at 177 rows, 11 adapters of rank 16, 16.6 -> 14.5) where
 // that makes up to 260 and 500 in all; one tile at 24 to 150 shrink blocks 1.03 to 1.2 times as fast as four, four
 // at 176 and more 1.0 to 1.3 times as fast as one: 1152 x 4261 at 65 rows, 7 adapters of rank 128, 18.6 and 14.6 us,
 // 3456 x 865 at 72, 5 of rank 64, 20.1 and with two tiles 17.3; two at 470, 1152 x 2453 at 450 rows, 32.8, four

@@ -34,3 +34,42 @@ def test_outputs(gpu, K, N, G, rank, adapters, M, tiles):
     x = wl.f32_to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32))
     rows = rng.integers(-1, adapters, size=M).astype(np.int32)
     check_linear(gpu, random_problem(K + N, K, N, G, rank, adapters), x, rows, f"K{K} N{N} r{rank} a{adapters} M{M}")
+
+
+def layer(h, kv, f):
+    return [(h, h), (h, kv), (h, kv), (h, h), (h, f), (h, f), (f, h)]
+
+
+LAYERS = [                                # projections, group, rank, adapters, rows, row tiles per block (all in blocks of eight waves)
+    (layer(512, 256, 1536), 128, 16, 11, 177, 2),
+    (layer(768, 384, 1536) * 2, 32, 32, 8, 37, 2),
+    (layer(768, 256, 2048), 32, 32, 8, 235, 4),         # two tiles would make 384
+    (layer(512, 256, 896), 32, 32, 3, 188, 4),          # no input of 1024
+    (layer(512, 192, 1920), 32, 8, 4, 117, 1),
+]
+
+
+@pytest.mark.parametrize("shapes,G,rank,adapters,M,tiles", LAYERS)
+def test_grid_of_several_projections(shapes, G, rank, adapters, M, tiles):
+    more = grid_x(shapes, adapters, rank, M) - grid_x(shapes, 0, rank, M)
+    assert more == shrink_blocks(shapes, adapters, rank, M, tiles)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shapes,G,rank,adapters,M,tiles", LAYERS)
+def test_outputs_of_several_projections(gpu, shapes, G, rank, adapters, M, tiles):
+    """As each projection by itself, up to the order of fp32 sums (2e-4 of the largest output, far above it)."""
+    lib, device, torch = gpu
+    rng = np.random.default_rng(M)
+    ra = torch.from_numpy(rng.integers(-1, adapters, size=M).astype(np.int32)).cuda()
+    projs, xs, ys, alone = [], [], [], []
+    for i, (K, N) in enumerate(shapes):
+        projs.append(device.upload_problem(random_problem(i, K, N, G, rank, adapters)))
+        xs.append(device.to_device(wl.f32_to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32))))
+        ys.append(device.alloc_y(M, N, lib.Y_FP32))
+        alone.append(device.alloc_y(M, N, lib.Y_FP32))
+        lib.linear(projs[i], xs[i], ra, M, alone[i], lib.Y_FP32, device.alloc_workspace([projs[i]], M))
+    lib.layer_step(projs, xs, ys, ra, M, lib.Y_FP32, device.alloc_workspace(projs, M))
+    torch.cuda.synchronize()
+    for y, one in zip(ys, alone):
+        assert float((y - one).abs().max()) <= 2e-4 * float(one.abs().max())

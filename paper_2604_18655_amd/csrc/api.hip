@@ -287,6 +287,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
                                                 base + shrink_blocks(2) <= SHRINK_TWO_LIVE_BLOCKS;
         if (!whole_tiles && one_fits) shrink_tiles = 1;
         else if (wide && two_fit) shrink_tiles = 2;
+        else if (whole_tiles && short_launch) shrink_tiles = base + shrink_blocks(4) <= SHRINK_WHOLE_SHORT_BLOCKS ? 4 : 8;
         else if (base + shrink_blocks(4) <= SHRINK_ALL_LIVE_BLOCKS) shrink_tiles = 4;
         else if (wide && shrink_blocks(4) <= SHRINK_FEW_BLOCKS) shrink_tiles = 4;
     }

@@ -245,30 +245,37 @@ __device__ inline f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
 // The grouped shrink step (more than 16 rows) works on chunks of 64 rows: the rows of a chunk are grouped by adapter
 // (one wave, no sort) and every segment is cut into tiles of 16 rows.  Upper bound of the tiles of a chunk of `rows`
 // rows (at most 64): a tile per 16 rows plus one per segment, at most a tile per row.  The chunk's tiles are shared
-// out over blocks of up to 8 (wide blocks of 32 rows) or 16 (the others, which have two places per compute unit: 16
-// layers at 512 rows 1313 us against 1342 with 8, a layer at 32 rows in tile blocks 25 against 29) where a launch
-// has many of them.  Fewer tiles are a shorter chain ahead of every block that finishes outputs, more are fewer
-// blocks, idle ones included, whose signals queue up at the same counters.  One tile per block where all blocks of
-// the launch find a place at once with it (SHRINK_ALL_LIVE_BLOCKS; 8192 x 2048 at 64 rows, 8 adapters of rank 16, 40
-// us with 16, 22.7 with 4, 19.4 with 1), unless every wave has tiles of its own (128 inputs: 100 drawn calls at 17
-// to 700 rows 0.98 of the time with 4); else 4 where they do with 4 (4096 x 14336 at 64 rows, 32 adapters of rank
-// 64: 41.5 us with 16 tiles, 35.4 with 4; 14336 x 4096 49.5 and 32.5; two in wide blocks of 32 rows where inputs are long,
-// so that a tile is several trips to memory, that makes up to 192 shrink blocks and the launch stays within 640 blocks: 68
-// drawn calls 0.987 of the time with four, 5632 x 1700 at 466 rows, 11 adapters of rank 16, 33.3 -> 29.1, 8576 x 1840 at 309
-// rows 29.5 -> 27.0, the worst 1.06; with more than 192 such blocks 19 calls 1.04, 12928 x 4198 at 56 rows, 23 of rank
-// 64, 27.6 -> 31.2; blocks of 64 rows, 22 calls: 1.02, 4480 x 5658 at 302 rows, 19 of rank 24, 42.0 -> 46.4; blocks of eight waves share a CU's matrix and memory pipes with fewer others and stand in each
-// other's way sooner: one tile where that makes up to 160 shrink blocks and 300 in all, two from 2048 inputs (in calls of several
-// projections, whose shrink blocks signal to counters of their own, from 1024: 12 drawn calls 0.95 of the time with four,
-// the worst 1.03, a layer of 512 wide at 177 rows, 11 adapters of rank 16, 16.6 -> 14.5) where
-// that makes up to 260 and 500 in all; one tile at 24 to 150 shrink blocks 1.03 to 1.2 times as fast as four, four
-// at 176 and more 1.0 to 1.3 times as fast as one: 1152 x 4261 at 65 rows, 7 adapters of rank 128, 18.6 and 14.6 us,
-// 3456 x 865 at 72, 5 of rank 64, 20.1 and with two tiles 17.3; two at 470, 1152 x 2453 at 450 rows, 32.8, four
-// 23.2; two at 456, 2688 x 1103 at 251 rows, 4 of rank 128, 21.1, four 28.1; 10112 x 537 at 84 rows, all on one of
-// 30 adapters of rank 24, 22.1 with two (272 blocks, most idle), 17.5 with four), or, in wide blocks, where 4 make
-// at most 300 shrink blocks (SHRINK_FEW_BLOCKS; 4352 x 5466 at 441 rows, 10 adapters of rank 32, 80 us with 8, 49
-// with 4, 4480 x 12672 at 320 rows 97 and 65; 280 drawn calls of 3000 to 14336 outputs at 150 to 1024 rows 0.97 of
-// the time, 8 of them more than 3 % longer, by 17 % at most; 320 to 480 such blocks: as many calls lose as gain,
-// 3328 x 3563 at 593 rows 52 -> 61).
+// out over blocks.  Fewer tiles per block are a shorter chain ahead of every block that finishes outputs; more are fewer
+// blocks, idle ones included, whose signals queue up at the same counters.  The most tiles of a block, the first
+// line that holds (S(t) = shrink blocks of the launch with t tiles each, B = its base blocks; us of calls both ways):
+//
+//   blocks of four waves
+//    1  B + S(1) <= 500, all find a place at once, and a wave has no tiles of its own (128 inputs: 100 drawn calls at 17 to
+//       700 rows 0.98 of the time with 4): 8192 x 2048 at 64 rows, 8 adapters of rank 16, 16 tiles 40, 4 22.7, 1 19.4
+//    2  wide blocks of 32 rows, inputs from 1024 (a tile is several trips to memory), S(2) <= 192, B + S(2) <= 640: 68 drawn
+//       calls 0.987 of the time with 4, 5632 x 1700 at 466 rows, 11 adapters of rank 16, 33.3 -> 29.1, the worst 1.06.
+//       S(2) above 192: 19 calls 1.04, 12928 x 4198 at 56 rows, 23 of rank 64, 27.6 -> 31.2; blocks of 64 rows: 22 calls 1.02,
+//       4480 x 5658 at 302 rows, 19 of rank 24, 42.0 -> 46.4
+//    4  B + S(4) <= 500: 4096 x 14336 at 64 rows, 32 adapters of rank 64, 16 tiles 41.5, 4 35.4; 14336 x 4096 49.5 and 32.5
+//    4  wide blocks, S(4) <= 300: 4352 x 5466 at 441 rows, 10 adapters of rank 32, 8 tiles 80, 4 49; 280 drawn calls of 3000
+//       to 14336 outputs at 150 to 1024 rows 0.97 of the time, 8 of them more than 3 % longer, by 17 % at most; S(4) from 320
+//       to 480: as many calls lose as gain, 3328 x 3563 at 593 rows 52 -> 61
+//    8  wide blocks of 32 rows
+//   16  the others, which have two places per compute unit (16 layers at 512 rows 1313, 1342 with 8; a layer at 32 rows
+//       in tile blocks 25, 29 with 8)
+//
+//   blocks of eight waves (short launches: they share a compute unit's pipes with fewer others and stand in each other's way sooner)
+//    1  B + S(1) <= 300, S(1) <= 160, no tiles of a wave's own: at 24 to 150 shrink blocks 1.03 to 1.2 times as fast as 4, from
+//       176 on 4 are 1.0 to 1.3 times as fast: 1152 x 4261 at 65 rows, 7 adapters of rank 128, 18.6 and 14.6
+//    2  inputs from 2048, S(2) <= 260, B + S(2) <= 500: 2688 x 1103 at 251 rows, 4 of rank 128, 21.1, 4 tiles
+//       28.1; shorter inputs, 1152 x 2453 at 450 rows 32.8, 4 tiles 23.2; lost: 10112 x 537 at 84 rows, all on one of 30
+//       adapters of rank 24 (most blocks idle), 22.1, 4 tiles 17.5
+//    2  the same in calls of several projections from 1024 inputs (their blocks signal to counters of their own): 12
+//       drawn calls 0.95 of the time with 4, the worst 1.03, a layer of 512 wide at 177 rows, 11 of rank 16, 16.6 -> 14.5
+//    4  a wave with tiles of its own, B + S(4) <= 280; above, 8: 6 calls 0.88 of the time with 4, 128 x 4442 at 341 rows, 2
+//       of rank 128, 18.9 -> 16.6 (between 150 and 280 as many gain as lose, below 150 4 are 1.03 times as fast)
+//    4  B + S(4) <= 500, or S(4) <= 300
+//    8  the others
 // Host (grid size) and device (block index -> chunk, share) use the same figures.
 constexpr int SHRINK_CHUNK_ROWS = 64;
 __host__ __device__ inline int max_row_tiles(int rows, int n_adapters)
@@ -279,6 +286,7 @@ __host__ __device__ inline int max_row_tiles(int rows, int n_adapters)
 }
 constexpr int SHRINK_ALL_LIVE_BLOCKS = 500, SHRINK_TWO_LIVE_BLOCKS = 640, SHRINK_TWO_BLOCKS = 192;
 constexpr int SHRINK_ALL_SHORT_BLOCKS = 300, SHRINK_ONE_SHORT_BLOCKS = 160, SHRINK_TWO_SHORT_BLOCKS = 260;
+constexpr int SHRINK_WHOLE_SHORT_BLOCKS = 280;
 constexpr int SHRINK_FEW_BLOCKS = 300, SHRINK_LONG_INPUTS = 1024;
 __host__ __device__ inline int shrink_tile_shares(int M, int n_adapters, int tiles_per_block)
 {

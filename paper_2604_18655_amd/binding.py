@@ -149,6 +149,20 @@ def _ptr(t) -> Optional[int]:
 _torch_c = None
 
 
+class _PublicStream:
+    """The two calls of _stream() by torch's public ones, for a torch without the private pair."""
+
+    @staticmethod
+    def _cuda_getDevice() -> int:
+        import torch
+        return torch.cuda.current_device()
+
+    @staticmethod
+    def _cuda_getCurrentRawStream(device: int) -> int:
+        import torch
+        return int(torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream() -> int:
     """torch's current stream on the current device, without the Python object around it: 2.9 us of a
     call's 8.9 us of host time, where its kernel takes 6.0 (256 x 256 at 8 rows)."""
@@ -156,7 +170,8 @@ def _stream() -> int:
     if _torch_c is None:
         import torch
         torch.cuda.current_stream()                      # initialises the device, or says why it cannot
-        _torch_c = torch._C
+        both = hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice")
+        _torch_c = torch._C if both else _PublicStream
     return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice())
 
 

@@ -69,6 +69,11 @@ typedef struct {
  * survives the call; nothing has to be initialised.  0 if the descriptor is not supported. */
 size_t mlora_tree_attention_workspace_bytes(const mlora_tree_attn *t);
 
+/* How such a call would be run, for reading profiles; host only, nothing is launched.  info (HOST memory, 3 int32):
+ * [0] tiles of 16 query vectors a block takes (1 or 2), [1] waves of a block (4 or 8), [2] blocks that share the keys of
+ * a query tile (above 1 a second kernel merges their results).  MLORA_EINVAL if info is null, else as mlora_tree_attention. */
+mlora_status mlora_tree_attention_plan(const mlora_tree_attn *t, int32_t *info);
+
 /*   q    bf16 [S * R][n_q_heads][head_dim]
  *   out  [S * R][n_q_heads][head_dim], bf16 (out_dtype = MLORA_Y_BF16, round to nearest even) or fp32 */
 mlora_status mlora_tree_attention(const mlora_tree_attn *t, const void *q, void *out, int32_t out_dtype,

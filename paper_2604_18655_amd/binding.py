@@ -17,7 +17,7 @@ exported_symbols = (
     "mlora_group_rows", "mlora_w4_workspace_bytes", "mlora_w4_linear", "mlora_w4_layer_step",
     "mlora_w4_workspace_init", "mlora_w4_workspace_status", "mlora_w4_debug_spin_limit",
     "mlora_w4_layer_step_static", "mlora_w4_layer_step_plan", "mlora_w4_layer_step_block_rows",
-    "mlora_tree_attention_workspace_bytes", "mlora_tree_attention",
+    "mlora_tree_attention_workspace_bytes", "mlora_tree_attention_plan", "mlora_tree_attention",
     "mlora_w4a8_workspace_bytes", "mlora_w4a8_layer_step",
     "mlora_w4_layer_step_fused", "mlora_rms_scale", "mlora_lora_int16_expand",
     "mlora_ds2d_rows", "mlora_ds2d_layout", "mlora_ds2d_workspace_bytes", "mlora_ds2d_late_drafts",
@@ -98,6 +98,8 @@ def load_library():
         tp = C.POINTER(_TreeAttnStruct)
         lib.mlora_tree_attention_workspace_bytes.restype = sz
         lib.mlora_tree_attention_workspace_bytes.argtypes = [tp]
+        lib.mlora_tree_attention_plan.restype = C.c_int
+        lib.mlora_tree_attention_plan.argtypes = [tp, C.POINTER(i32)]
         lib.mlora_tree_attention.restype = C.c_int
         lib.mlora_tree_attention.argtypes = [tp, vp, vp, i32, vp, sz, vp]
         lib.mlora_w4a8_workspace_bytes.restype = sz
@@ -422,6 +424,12 @@ class TreeAttention:
 
     def workspace_bytes(self) -> int:
         return int(load_library().mlora_tree_attention_workspace_bytes(C.byref(self.struct)))
+
+    def plan(self) -> dict:
+        """How the library would run the call (see mlora_tree_attention_plan)."""
+        info = (C.c_int32 * 3)()
+        _check(load_library().mlora_tree_attention_plan(C.byref(self.struct), info), "mlora_tree_attention_plan")
+        return {"tiles": info[0], "waves": info[1], "splits": info[2]}
 
     def run(self, q, out, out_dtype: int, workspace, stream: Optional[int] = None) -> None:
         n = 0 if workspace is None else workspace.numel() * workspace.element_size()

@@ -449,6 +449,18 @@ size_t mlora_tree_attention_workspace_bytes(const mlora_tree_attn *t)
     return workspace_floats(*t) * sizeof(float) + 256;
 }
 
+mlora_status mlora_tree_attention_plan(const mlora_tree_attn *t, int32_t *info)
+{
+    if (!info) return MLORA_EINVAL;
+    const mlora_status st = check(t);
+    if (st != MLORA_OK) return st;
+    const Plan p = plan_of(*t);
+    info[0] = p.tiles;
+    info[1] = p.waves;
+    info[2] = p.splits;
+    return MLORA_OK;
+}
+
 mlora_status mlora_tree_attention(const mlora_tree_attn *t, const void *q, void *out, int32_t out_dtype,
                                   void *workspace, size_t workspace_bytes, void *stream)
 {

@@ -1,7 +1,6 @@
-"""Masked tree attention around the sizes where its kernels change: chunks of 64 keys (their masks as
-bits, pairs of keys per thread), one and two chunks on their way at the start, up to 4, up to 10
-and more partial results per row in the merging kernel, scores of very different size.  Same
-bars as test_gpu_tree_attention."""
+"""Masked tree attention at the edges of its chunks of 32 keys (segments that end with a chunk, one key before and one
+after it, empty and full streams side by side) in one launch and with shared keys, and scores of very different
+size.  Same bars as test_gpu_tree_attention."""
 import numpy as np
 import pytest
 

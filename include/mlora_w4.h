@@ -142,6 +142,10 @@ mlora_status mlora_w4_layer_step_plan(const mlora_w4_proj *projs, int32_t n_proj
  * mlora_w4a8_layer_step), 0 for what the library refuses.  Host only, nothing is launched. */
 int32_t mlora_w4_layer_step_block_rows(const mlora_w4_proj *projs, int32_t n_proj, int32_t M, int32_t int8_rows);
 
+/* Waves that share a column tile in the first launch of such a call: 2 in short launches of blocks of four column tiles
+ * and 32 rows ("wide_short_kernel", eight waves a block), else 1; 0 for what the library refuses.  Host only. */
+int32_t mlora_w4_layer_step_waves_per_tile(const mlora_w4_proj *projs, int32_t n_proj, int32_t M, int32_t int8_rows);
+
 /* Zero-fill a workspace (a small kernel on `stream`; no memset node, so it can be captured). */
 mlora_status mlora_w4_workspace_init(void *workspace, size_t workspace_bytes, void *stream);
 

@@ -17,6 +17,7 @@ exported_symbols = (
     "mlora_group_rows", "mlora_w4_workspace_bytes", "mlora_w4_linear", "mlora_w4_layer_step",
     "mlora_w4_workspace_init", "mlora_w4_workspace_status", "mlora_w4_debug_spin_limit",
     "mlora_w4_layer_step_static", "mlora_w4_layer_step_plan", "mlora_w4_layer_step_block_rows",
+    "mlora_w4_layer_step_waves_per_tile",
     "mlora_tree_attention_workspace_bytes", "mlora_tree_attention_plan", "mlora_tree_attention",
     "mlora_w4a8_workspace_bytes", "mlora_w4a8_layer_step",
     "mlora_w4_layer_step_fused", "mlora_rms_scale", "mlora_lora_int16_expand",
@@ -268,6 +269,11 @@ def layer_step_plan(projs: Sequence[Proj], M: int) -> dict:
 def layer_step_block_rows(projs: Sequence[Proj], M: int, int8_rows: bool = False) -> int:
     """Rows per base block of such a call's first launch (see mlora_w4_layer_step_block_rows)."""
     return load_library().mlora_w4_layer_step_block_rows(_proj_array(projs), len(projs), M, int(int8_rows))
+
+
+def layer_step_waves_per_tile(projs: Sequence[Proj], M: int, int8_rows: bool = False) -> int:
+    """Waves that share a column tile in such a call's first launch (see mlora_w4_layer_step_waves_per_tile)."""
+    return load_library().mlora_w4_layer_step_waves_per_tile(_proj_array(projs), len(projs), M, int(int8_rows))
 
 
 def linear(proj: Proj, x, row_adapter, M: int, y, y_dtype: int = Y_BF16, workspace=None) -> None:

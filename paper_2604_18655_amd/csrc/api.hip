@@ -231,7 +231,7 @@ struct LaunchNeed {
     size_t ctrl_bytes, data_bytes;     // of this launch
     size_t ctrl_bound, data_bound;     // what a workspace is sized for (never less)
     long long grid_x;
-    int groups, rpc, block_rows;
+    int groups, rpc, block_rows, waves_per_tile;
 };
 
 static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *xs, void *const *ys,
@@ -398,6 +398,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
     need.groups = groups;
     need.rpc = rpc;
     need.block_rows = block_rows;
+    need.waves_per_tile = waves_per_tile;
     if (a) {
         a->ctrl = reinterpret_cast<unsigned *>(ctrl);
         a->wide = wide;
@@ -478,16 +479,27 @@ mlora_status mlora_w4_layer_step_plan(const mlora_w4_proj *projs, int32_t n_proj
     return MLORA_OK;
 }
 
+// the plan of a call's first launch, for the two queries below
+static bool first_launch(const mlora_w4_proj *projs, int32_t n_proj, int32_t M, bool int8_rows, LaunchNeed &need)
+{
+    if (!projs || n_proj <= 0 || M <= 0 || M > MLORA_MAX_ROWS) return false;
+    for (int i = 0; i < n_proj; ++i)
+        if (check_weight_shape(projs[i].K, projs[i].N, projs[i].group) != MLORA_OK) return false;
+    const int Mp = plan_rows(M, int8_rows);
+    const int count = launch_run(projs, n_proj, Mp);
+    return plan_launch(projs, nullptr, nullptr, count, Mp, int8_rows, true, need, nullptr, nullptr, nullptr) == MLORA_OK;
+}
+
 int32_t mlora_w4_layer_step_block_rows(const mlora_w4_proj *projs, int32_t n_proj, int32_t M, int32_t int8_rows)
 {
-    if (!projs || n_proj <= 0 || M <= 0 || M > MLORA_MAX_ROWS) return 0;
-    for (int i = 0; i < n_proj; ++i)
-        if (check_weight_shape(projs[i].K, projs[i].N, projs[i].group) != MLORA_OK) return 0;
-    const int Mp = plan_rows(M, int8_rows != 0);
     LaunchNeed need;
-    const int count = launch_run(projs, n_proj, Mp);
-    if (plan_launch(projs, nullptr, nullptr, count, Mp, int8_rows != 0, true, need, nullptr, nullptr, nullptr) != MLORA_OK) return 0;
-    return need.block_rows;
+    return first_launch(projs, n_proj, M, int8_rows != 0, need) ? need.block_rows : 0;
+}
+
+int32_t mlora_w4_layer_step_waves_per_tile(const mlora_w4_proj *projs, int32_t n_proj, int32_t M, int32_t int8_rows)
+{
+    LaunchNeed need;
+    return first_launch(projs, n_proj, M, int8_rows != 0, need) ? need.waves_per_tile : 0;
 }
 
 mlora_status mlora_w4_workspace_init(void *workspace, size_t workspace_bytes, void *stream)

@@ -634,9 +634,7 @@ def main():
     wide = info["wide"]
     spg = w.projs[0].group // 32
     rows = lib.layer_step_block_rows(plans[0][0].keep[0], M, args.a8)
-    # two waves per tile in launches of one group with at most 230 base blocks of 32 rows (rounded up to whole XCDs here)
-    bare = [lib.Proj(p.K, p.N, p.group, None) for p in plans[0][0].keep[0]]
-    short = wide and rows == 32 and info["grid_z"] == 1 and lib.layer_step_plan(bare, M)["grid_x"] <= 232
+    short = lib.layer_step_waves_per_tile(plans[0][0].keep[0], M, args.a8) == 2
     kernel_name = "wide_short_kernel<%d, %s>" % (spg, "true" if args.a8 else "false") if short else \
         ("wide_kernel<%d, %d, %s, %s>" % (spg, rows // 16, "true" if args.a8 else "false", "true" if rows == 64 or M > 32 else "false")) if wide else \
         "layer_kernel<%s, %d>" % ("1, 8" if M <= 8 else "1, 16" if rows == 16 else "2, 24" if M <= 24 else "2, 32",

@@ -129,7 +129,8 @@ size_t mlora_w4_workspace_bytes(const mlora_w4_proj *projs, int32_t n_proj, int3
 /* How a call over these projections and M rows would be run, for reading profiles; host only,
  * nothing is launched.  info (HOST memory, 5 int32): [0] kernel launches of the call (one per
  * 128 projections; from 17 rows on also a new one where the group size changes),
- * [1] 1 if the first launch runs blocks of four column tiles ("wide_kernel"), 0 if blocks of
+ * [1] 1 if the first launch runs blocks of four column tiles ("wide_kernel"; in short launches
+ * "wide_short_kernel", see mlora_w4_layer_step_waves_per_tile), 0 if blocks of
  * one column tile ("layer_kernel"), [2] rows per row chunk (16, 32 or 64; a short launch of 17
  * to 32 rows runs as two chunks of 16; a chunk of 64 rows is worked through by a block of 64 or two
  * of 32, see mlora_w4_layer_step_block_rows), [3] and [4] the first launch's grid: blocks along x

@@ -277,7 +277,7 @@ static mlora_status plan_launch(const mlora_w4_proj *projs, const void *const *x
                     n += (long long)shrink_chunks * shrink_tile_shares(M, projs[i].n_adapters, tiles) * (r16_of(projs[i]) / 16) * kch_of(projs[i], M, wide);
             return n;
         };
-        const bool whole_tiles = wide && block_rows == 32 && longest <= SUPER_K;    // a tile per wave
+        const bool whole_tiles = wide && block_rows == 32 && longest <= SUPER_K;    // a tile is one wave's (two of eight waves)
         const bool short_launch = waves_per_tile == 2;
         const bool one_fits = base + shrink_blocks(1) <= (short_launch ? SHRINK_ALL_SHORT_BLOCKS : SHRINK_ALL_LIVE_BLOCKS) &&
                               (!short_launch || shrink_blocks(1) <= SHRINK_ONE_SHORT_BLOCKS);

@@ -101,7 +101,9 @@ struct ProjArgs {
     float x_scale;             // int8 activations: the per-tensor scale of x (1 otherwise)
     int ksplit;                // K units per tile; unit 0 finishes the tile, the others run ahead
     int n_shrink_blocks;       // shrink blocks of this projection (each bumps its counter once)
-    int n_finish_blocks;       // finishing blocks of this projection (tiles x row chunks)
+    int n_finish_blocks;       // who waits for this projection's shrink blocks: tile blocks, the finishing blocks (tiles x
+                               // blocks of rows); wide blocks, the waves that make a LoRA term (tiles x blocks of rows x
+                               // lora_units x waves per tile)
     int part_ctr;              // index of this projection's first split-K counter line in ctrl
     // Derived on the host so that no block starts with integer divisions (each one costs some 30
     // cold instructions, and they sat in front of the first memory request of every block):
@@ -120,8 +122,9 @@ struct ProjArgs {
 // line queue up behind each other in one memory channel, and since a wave's loads return in
 // order that stalls their weight streams too.
 //   shrink_ctr(p, r)      + 0: shrink blocks of projection p that have finished (copy r)
-//                         + 1: finishing blocks that have used copy r (the last one resets both)
-//   part_ctr + (tile * chunks + chunk) * CTR_STRIDE: split-K units of that tile that have finished
+//                         + 1: those of n_finish_blocks that have used copy r (the last one resets both)
+//   part_ctr + (tile * chunks + chunk) * CTR_STRIDE: split-K units of that tile that have finished; two blocks of 32 rows in a
+//                           chunk of 64 have a word each, CTR_STRIDE / 2 apart, two waves of a tile CTR_STRIDE / 4 apart
 constexpr int CTR_REPL = 16;
 constexpr int CTR_STRIDE = 32;                 // uint32 per counter line
 __host__ __device__ inline int shrink_ctr(int p, int r) { return (p * CTR_REPL + r) * CTR_STRIDE; }
@@ -250,8 +253,8 @@ __device__ inline f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
 // line that holds (S(t) = shrink blocks of the launch with t tiles each, B = its base blocks; us of calls both ways):
 //
 //   blocks of four waves
-//    1  B + S(1) <= 500, all find a place at once, and a wave has no tiles of its own (128 inputs: 100 drawn calls at 17 to
-//       700 rows 0.98 of the time with 4): 8192 x 2048 at 64 rows, 8 adapters of rank 16, 16 tiles 40, 4 22.7, 1 19.4
+//    1  B + S(1) <= 500, all find a place at once, in wide blocks of 32 rows for inputs above 128 (with 128 a tile is one wave's:
+//       100 drawn calls at 17 to 700 rows 0.98 of the time with 4): 8192 x 2048 at 64 rows, 8 adapters of rank 16, 16 tiles 40, 4 22.7, 1 19.4
 //    2  wide blocks of 32 rows, inputs from 1024 (a tile is several trips to memory), S(2) <= 192, B + S(2) <= 640: 68 drawn
 //       calls 0.987 of the time with 4, 5632 x 1700 at 466 rows, 11 adapters of rank 16, 33.3 -> 29.1, the worst 1.06.
 //       S(2) above 192: 19 calls 1.04, 12928 x 4198 at 56 rows, 23 of rank 64, 27.6 -> 31.2; blocks of 64 rows: 22 calls 1.02,
@@ -264,15 +267,15 @@ __device__ inline f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
 //   16  the others, which have two places per compute unit (16 layers at 512 rows 1313, 1342 with 8; a layer at 32 rows
 //       in tile blocks 25, 29 with 8)
 //
-//   blocks of eight waves (short launches: they share a compute unit's pipes with fewer others and stand in each other's way sooner)
-//    1  B + S(1) <= 300, S(1) <= 160, no tiles of a wave's own: at 24 to 150 shrink blocks 1.03 to 1.2 times as fast as 4, from
+//   blocks of eight waves (short launches: fewer of them share a compute unit's pipes, and they stand in each other's way sooner)
+//    1  B + S(1) <= 300, S(1) <= 160, inputs above 128: at 24 to 150 shrink blocks 1.03 to 1.2 times as fast as 4, from
 //       176 on 4 are 1.0 to 1.3 times as fast: 1152 x 4261 at 65 rows, 7 adapters of rank 128, 18.6 and 14.6
 //    2  inputs from 2048, S(2) <= 260, B + S(2) <= 500: 2688 x 1103 at 251 rows, 4 of rank 128, 21.1, 4 tiles
 //       28.1; shorter inputs, 1152 x 2453 at 450 rows 32.8, 4 tiles 23.2; lost: 10112 x 537 at 84 rows, all on one of 30
 //       adapters of rank 24 (most blocks idle), 22.1, 4 tiles 17.5
 //    2  the same in calls of several projections from 1024 inputs (their blocks signal to counters of their own): 12
 //       drawn calls 0.95 of the time with 4, the worst 1.03, a layer of 512 wide at 177 rows, 11 of rank 16, 16.6 -> 14.5
-//    4  a wave with tiles of its own, B + S(4) <= 280; above, 8: 6 calls 0.88 of the time with 4, 128 x 4442 at 341 rows, 2
+//    4  128 inputs (a tile is two waves'), B + S(4) <= 280; above, 8: 6 calls 0.88 of the time with 4, 128 x 4442 at 341 rows, 2
 //       of rank 128, 18.9 -> 16.6 (between 150 and 280 as many gain as lose, below 150 4 are 1.03 times as fast)
 //    4  B + S(4) <= 500, or S(4) <= 300
 //    8  the others

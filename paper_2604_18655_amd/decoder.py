@@ -4,7 +4,7 @@ projections' output stages:
 
     s1 = rms_scale(h)                                   mlora_rms_scale (first layer of a stack only)
     q, k, v = fused(h; row scale s1; RoPE on q and k)   mlora_w4_layer_step_fused, one launch
-    attn = tree_attention(q, cache, k, v)               mlora_tree_attention, two launches
+    attn = tree_attention(q, cache, k, v)               mlora_tree_attention, one or two launches
     h2 = fused(attn; + residual h; leaves the sums     o projection
          of squares of the rows of h2, per column tile)
     act = fused(h2; row scale from those sums; SwiGLU)  gate and up as one projection

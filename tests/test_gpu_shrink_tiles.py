@@ -26,9 +26,9 @@ def rows_of(kind, M, n_ad):
 @pytest.mark.parametrize("kind", ["one", "each", "seventeen", "absent"])
 @pytest.mark.parametrize("M,K,N,G,r,n_ad", [(17, 128, 19264, 32, 8, 3),        # tile blocks; one k-step per wave
                                             (32, 640, 19264, 64, 40, 32),      # 512 inputs per K chunk, 5 k-steps each
-                                            (33, 128, 70, 32, 16, 33),         # wide blocks; one tile per block, a wave of its own for each
+                                            (33, 128, 70, 32, 16, 33),         # wide blocks; 128 inputs: two of the eight waves share a tile
                                             (190, 128, 200, 64, 24, 17),       # several tiles of one batch
-                                            (150, 256, 130, 64, 24, 9),        # two batches: two waves per tile
+                                            (150, 256, 130, 64, 24, 9),        # 256 inputs: four of the eight waves share a tile
                                             (300, 256, 4000, 128, 8, 3),
                                             (64, 2176, 321, 128, 24, 64),      # 17 super-steps: units of 512 inputs
                                             (65, 4224, 64, 32, 8, 5),          # two chunks, the second of one row

@@ -18,7 +18,7 @@ CASES = [                                 # inputs, outputs, group, rank, adapte
     (2432, 9000, 64, 64, 4, 130, 2),      # four waves
     (12928, 4198, 64, 64, 23, 56, 4),     # four waves: two tiles would make 312
     (4480, 5658, 64, 24, 19, 302, 4),     # blocks of 64 rows
-    (128, 4442, 128, 128, 2, 341, 8),     # a tile of 128 inputs per wave: 198 base blocks, four tiles would make 96 more
+    (128, 4442, 128, 128, 2, 341, 8),     # 128 inputs, eight waves: 198 base blocks, four tiles would make 96 more
     (128, 3779, 128, 64, 2, 299, 4),
 ]
 
